@@ -33,8 +33,6 @@ struct KvGeom {
 void launch_pack_weight(const h16_t *src, int64_t ld, int k0, int c0, int K, int N, h16_t *dst,
                         int dst_tile0, int dst_tile_stride, int dst_n_tiles, int rope_d, hipStream_t s);
 void launch_accumulate_f32(float *dst, const float *src, int64_t n, hipStream_t s);
-// decode row map: row i -> (seq i, pos lens[i])
-void launch_decode_rowmap(const int32_t *lens, int32_t *row_seq, int32_t *row_pos, int b, hipStream_t s);
 void launch_advance_lens(int32_t *lens, int b, hipStream_t s);
 
 // plain streaming kernels of known size (HBM calibration for the benchmarks and profiler counters)
@@ -120,15 +118,33 @@ void launch_embed_rows(const void *table, int64_t row_bytes, int vocab, const in
 void launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 
 
-// ---- fp32 path (kernels_f32.hip): plain layouts, vector ALU -----------------------------------
-void f32_launch_rmsnorm(const float *in, const float *g, float *out, int T, int H, float eps, hipStream_t s);
-void f32_launch_gemm(const float *X, const float *W, float *out, int T, int K, int N, hipStream_t s);
+// ---- fp32 path (kernels_f32.hip): plain row-major layouts, fp32 matrix instructions -------------------------------
+// One projection out = f(x) . w.  F32_PLAIN: out[T][cols] = the product; F32_RESID: resid + product -> resid_out, or, with
+// resid_out == NULL (the stage's last projection), the product -> out and resid -> out_resid (may be NULL); F32_SWIGLU:
+// w holds `cols` gate columns, then `cols` up columns, out = silu(gate) * up.  Rows of `out`, `resid`, ... are `cols` wide.
+enum { F32_PLAIN = 0, F32_RESID = 1, F32_SWIGLU = 2 };
+struct F32Proj {
+    const float *x, *x2;       // [T][K]; x2 (may be NULL, only with F32_PLAIN, g and T <= 32) is added to x
+    const float *g;            // RMSNorm gain [K]: x is normalised first; NULL = as it is
+    const float *w;            // [Kp][N], rows K .. Kp - 1 zero
+    int T, K, Kp, N, cols;     // K a multiple of 4, Kp of 32, cols of 16
+    float eps;
+    float *out;
+    const float *resid;
+    float *resid_out, *out_resid;
+    int32_t *lens;             // not NULL (T <= 32 only): lens[0 .. T) += 1 once every earlier launch is through
+};
+// n_buf [T][K] (normalised rows) and part (partial sums of a split contraction, may be NULL) are needed for T > 32 only
+void f32_launch_proj(int mode, const F32Proj &p, float *n_buf, float *part, size_t part_floats, hipStream_t s);
 void f32_launch_rope_append(const float *qkv, int T, int hq_l, int hkv_l, int d, int smax, RowMap rm,
                             const float *cos_tab, const float *sin_tab, float *q_out, float *kc, float *vc,
                             hipStream_t s);
-void f32_launch_attn(const float *q, const float *kc, const float *vc, int T, int hq_l, int hkv_l, int d,
-                     int smax, RowMap rm, float *o, hipStream_t s);
-void f32_launch_swiglu(const float *ab, float *u, int T, int F_l, hipStream_t s);
+// causal attention of packed new rows whose keys and values are in the cache already; items as in launch_attn_prefill
+void f32_launch_attn_prefill(const float *q, float *kc, float *vc, int hq_l, int hkv_l, int d, int smax, const int32_t *pos0,
+                             const int32_t *cu_rows, const int32_t *items, int n_items, float *o, hipStream_t s);
+// one new row per sequence at pos[seq]: rotary embedding and cache append of the raw projection qkv, then the attention
+void f32_launch_attn_decode(const float *qkv, float *kc, float *vc, int b, int hq_l, int hkv_l, int d, int smax, const int32_t *pos,
+                            const float *cos_tab, const float *sin_tab, float *o, hipStream_t s);
 void f32_launch_kv_copy(float *kc, float *vc, float *k, float *v, int hkv_l, int d, int smax, int seq,
                         int pos0, int n, int to_cache, hipStream_t s);
 

@@ -1,7 +1,21 @@
-// fp32 stage path: plain row-major layouts and vector-ALU kernels.  It exists for the small
-// full-precision configuration (tight 1e-4 parity, identical greedy tokens); the whole model sits in
-// cache there, so these kernels are written for clarity and exact fp32 accumulation, not for a roofline.
+// fp32 stage path: plain row-major layouts, every product on the fp32 matrix instructions (each multiply-add is an fp32
+// fused multiply-add, so operands, products and sums keep full precision).
+//   * up to 32 rows: f32_stream_kernel -- a block streams the weights of 16 or 32 output columns over the whole
+//     contraction and finishes them in registers (norm, residual, SwiGLU): five launches per layer in a decode step;
+//   * more rows: f32_tile_kernel -- 64 x 128 tiles through LDS, the contraction split where the tiles leave CUs idle;
+//   * attention: f32_attn_kernel -- 16 query columns (rows of one head, or the heads of one kv group) against the cache.
+// Weight rows are padded with zeros to a multiple of 32 and matrix widths to a multiple of 16 (stage.hip), so no loop here
+// has a ragged end in either direction.
+#include <algorithm>
+
 #include "kernels.h"
+
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ floatx4 f32_mfma16(float a, float b, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ floatx16 f32_mfma32(float a, float b, floatx16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ float f32_silu_mul(float a, float b) { return a / (1.0f + expf(-a)) * b; }
 
 __global__ __launch_bounds__(256) void f32_rmsnorm_kernel(const float *__restrict__ in, const float *__restrict__ g,
                                                          float *__restrict__ out, int H, float eps) {
@@ -18,52 +32,370 @@ void f32_launch_rmsnorm(const float *in, const float *g, float *out, int T, int 
     hipLaunchKernelGGL(f32_rmsnorm_kernel, dim3(T), dim3(256), 0, s, in, g, out, H, eps);
 }
 
-// out[T][N] = X[T][K] . W[K][N]; 64 x 64 block tile, 16-deep k steps through LDS, 4 x 4 per thread.
-__global__ __launch_bounds__(256) void f32_gemm_kernel(const float *__restrict__ X, const float *__restrict__ W,
-                                                      float *__restrict__ out, int T, int K, int N) {
-    __shared__ float sX[16][64 + 1];
-    __shared__ float sW[16][64 + 1];
-    const int bt = blockIdx.y * 64, bn = blockIdx.x * 64;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        for (int e = threadIdx.x; e < 16 * 64; e += 256) {
-            const int kk = e & 15, r = e >> 4;          // X: consecutive threads walk k (contiguous)
-            const int t = bt + r, k = k0 + kk;
-            sX[kk][r] = (t < T && k < K) ? X[(size_t)t * K + k] : 0.f;
-            const int c = e & 63, kw = e >> 6;          // W: consecutive threads walk n (contiguous)
-            const int n = bn + c, k2 = k0 + kw;
-            sW[kw][c] = (n < N && k2 < K) ? W[(size_t)k2 * N + n] : 0.f;
-        }
-        __syncthreads();
+// -------------------------------------------------------------------------------------------------
+// T <= 32 rows.  A block of 8 waves owns 16 V output columns (for SwiGLU: 16 V gate columns and the 16 V up columns that
+// belong to them) over the whole contraction; the waves interleave over chunks of 16 weight rows and are summed through
+// LDS in wave order.  v_mfma_f32_16x16x4_f32: operand A = 16 columns x 4 weight rows, B = 16 token rows x 4.  Which column
+// is which row of A, and which weight row which k-slot, is free as long as A and B (and the epilogue) agree:
+//   * lane l loads V neighbouring columns V (l % 16) .. of weight row 16 c + 4 (l / 16) + x in one request (four rows of
+//     64 V bytes), one register of it per MFMA: column n0 + V i + j is row i of MFMA j;
+//   * the lane's token row contributes x[t][16 c + 4 (l / 16) + 0 .. 3] in one 16-byte request, one value per x.
+// 32 MFMA cycles per 256 bytes of weights and wave leave the kernel bound by memory up to two token tiles, and by latency
+// (launch, one round trip, the reduction) on small matrices; the ring of four chunks covers a contraction of 512 at once.
+// RMSNorm costs nothing extra: the block reads every element of its rows anyway, so it sums their squares on the way,
+// multiplies by the gain at the operand and by 1 / rms after the contraction.
+// V = 2 (128-byte pieces) where that leaves 128 blocks or more, else V = 1: twice the blocks.
+// Measured, tiny stage (hidden 512, TP2): a projection of one row 55 -> 4 us (before: a vector-ALU tile kernel, 12 .. 22
+// blocks walking the contraction 16 rows at a time), a decode step of two layers with its head 28 -> 12 launches, prefill of
+// 32 rows and eight such steps 5030 -> 615 us.
+// -------------------------------------------------------------------------------------------------
+template <int MODE, int NB, int V, bool NORM, bool ADD>
+__global__ __launch_bounds__(512) void f32_stream_kernel(F32Proj p) {
+    constexpr int W = 8, U = 4, NM = MODE == F32_SWIGLU ? 2 : 1;
+    static_assert(NM * V * NB <= 4, "32 KB of LDS for the sums over the waves");
+    typedef float vec __attribute__((ext_vector_type(V == 1 ? 2 : V)));       // V = 1 uses element 0
+    __shared__ floatx4 red[W][NM * V * NB][64];
+    __shared__ float s_ss[W][NB * 16];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    const int n0 = blockIdx.x * 16 * V;
+    const int col = min(n0 + V * i, p.cols - V);           // columns past the last one re-read it and are not stored
+    const int chunks = p.Kp >> 4;
+    const bool finisher = wave < NB;
+
+    // the finishing wave of token tile `wave` asks for the residual now, so that it does not wait for it at the end
+    floatx4 res[V];
+    if (MODE == F32_RESID && finisher) {
 #pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = sX[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = sW[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
+        for (int q = 0; q < V; ++q)
+            res[q] = *reinterpret_cast<const floatx4 *>(p.resid + (size_t)min(i + 16 * wave, p.T - 1) * p.N + min(n0 + 4 * V * g + 4 * q, p.cols - 4));
     }
+    const float *xr[NB], *x2r[NB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int t = bt + ty * 4 + i;
-        if (t >= T) continue;
+    for (int b = 0; b < NB; ++b) {
+        const size_t row = (size_t)min(i + 16 * b, p.T - 1) * p.K;
+        xr[b] = p.x + row;
+        x2r[b] = ADD ? p.x2 + row : nullptr;
+    }
+    vec wv[U][NM][4];
+    floatx4 xv[U][NB], x2v[U][ADD ? NB : 1], gv[U];
+    auto request = [&](int u, int c) {
+        const int k = 16 * c + 4 * g, kx = min(k, p.K - 4);          // K is a multiple of 4; weight rows K .. Kp - 1 are zero
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = bn + tx * 4 + j;
-            if (n < N) out[(size_t)t * N + n] = acc[i][j];
+        for (int b = 0; b < NB; ++b) {
+            xv[u][b] = *reinterpret_cast<const floatx4 *>(xr[b] + kx);
+            if (ADD) x2v[u][b] = *reinterpret_cast<const floatx4 *>(x2r[b] + kx);
+        }
+        if (NORM) gv[u] = *reinterpret_cast<const floatx4 *>(p.g + kx);
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const float *src = p.w + (size_t)(k + x) * p.N + (m ? p.cols : 0) + col;
+                if constexpr (V == 1) wv[u][m][x][0] = *src;
+                else wv[u][m][x] = *reinterpret_cast<const vec *>(src);
+            }
+    };
+    floatx4 acc[NM][V][NB];
+    float ss[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        ss[b] = 0.f;
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int j = 0; j < V; ++j) acc[m][j][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto contract = [&](int u, int c) {
+        const bool in = 16 * c + 4 * g < p.K;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            floatx4 x = xv[u][b];
+            if (ADD) x += x2v[u][b];
+            if (!in) x = floatx4{0.f, 0.f, 0.f, 0.f};
+            if (NORM) {
+                ss[b] += x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
+                x *= gv[u];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int m = 0; m < NM; ++m)
+#pragma unroll
+                    for (int j = 0; j < V; ++j) acc[m][j][b] = f32_mfma16(wv[u][m][q][j], x[q], acc[m][j][b]);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) request(u, min(wave + u * W, chunks - 1));
+    for (int c0 = wave; c0 < chunks; c0 += U * W)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + u * W;
+            if (c < chunks) {                                        // uniform over the wave
+                contract(u, c);
+                request(u, min(c + U * W, chunks - 1));
+            }
+        }
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+        for (int j = 0; j < V; ++j)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) red[wave][(m * V + j) * NB + b][lane] = acc[m][j][b];
+    if (NORM) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            ss[b] += __shfl_xor(ss[b], 16, 64);
+            ss[b] += __shfl_xor(ss[b], 32, 64);
+            if (g == 0) s_ss[wave][b * 16 + i] = ss[b];
+        }
+    }
+    __syncthreads();
+    // every attention of the call has read the lengths: the step that was asked to advance them does so here
+    if (p.lens != nullptr && blockIdx.x == 0 && (int)threadIdx.x < p.T) p.lens[threadIdx.x] += 1;
+    if (!finisher) return;
+    const int b = wave, t = i + 16 * b;
+    floatx4 v[NM][V];
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            v[m][j] = red[0][(m * V + j) * NB + b][lane];
+#pragma unroll
+            for (int w = 1; w < W; ++w) v[m][j] += red[w][(m * V + j) * NB + b][lane];
+        }
+    if (NORM) {
+        float tot = s_ss[0][t];
+#pragma unroll
+        for (int w = 1; w < W; ++w) tot += s_ss[w][t];
+        const float r = 1.0f / sqrtf(tot / (float)p.K + p.eps);
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int j = 0; j < V; ++j) v[m][j] *= r;
+    }
+    if (t >= p.T) return;
+    // lane: columns n0 + 4 V g .. + 4 V - 1, column 4 q + r of them in register (4 q + r) / V of v[(4 q + r) % V]
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+        const int n = n0 + 4 * V * g + 4 * q;
+        if (n >= p.cols) continue;
+        floatx4 o;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float a = v[0][(4 * q + r) % V][(4 * q + r) / V];
+            o[r] = MODE == F32_SWIGLU ? f32_silu_mul(a, v[NM - 1][(4 * q + r) % V][(4 * q + r) / V]) : a;
+        }
+        if (MODE == F32_RESID && p.resid_out == nullptr) {           // the stage's last projection: partial and residual apart
+            *reinterpret_cast<floatx4 *>(p.out + (size_t)t * p.cols + n) = o;
+            if (p.out_resid) *reinterpret_cast<floatx4 *>(p.out_resid + (size_t)t * p.cols + n) = res[q];
+        } else if (MODE == F32_RESID) {
+            *reinterpret_cast<floatx4 *>(p.resid_out + (size_t)t * p.cols + n) = res[q] + o;
+        } else {
+            *reinterpret_cast<floatx4 *>(p.out + (size_t)t * p.cols + n) = o;
         }
     }
 }
-void f32_launch_gemm(const float *X, const float *W, float *out, int T, int K, int N, hipStream_t s) {
-    if (T <= 0 || N <= 0) return;
-    hipLaunchKernelGGL(f32_gemm_kernel, dim3((N + 63) / 64, (T + 63) / 64), dim3(256), 0, s, X, W, out, T, K, N);
+
+// What leaves a tile or the sum of the splits: four consecutive columns n .. n + 3 of row t (for SwiGLU: a = gate, b = up)
+template <int MODE>
+__device__ __forceinline__ void f32_finish4(const F32Proj &p, int t, int n, floatx4 a, floatx4 b) {
+    const size_t o = (size_t)t * p.cols + n;
+    if (MODE == F32_SWIGLU) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[r] = f32_silu_mul(a[r], b[r]);
+        *reinterpret_cast<floatx4 *>(p.out + o) = a;
+    } else if (MODE == F32_RESID) {
+        const floatx4 h = *reinterpret_cast<const floatx4 *>(p.resid + o);
+        if (p.resid_out) {
+            *reinterpret_cast<floatx4 *>(p.resid_out + o) = h + a;
+        } else {
+            *reinterpret_cast<floatx4 *>(p.out + o) = a;
+            if (p.out_resid) *reinterpret_cast<floatx4 *>(p.out_resid + o) = h;
+        }
+    } else {
+        *reinterpret_cast<floatx4 *>(p.out + o) = a;
+    }
+}
+
+// -------------------------------------------------------------------------------------------------
+// T > 32 rows: 64 rows x 128 columns (SwiGLU: 64 gate columns and their 64 up columns) per block of 4 waves, a wave 32 rows
+// x 64 columns as two 32x32 results of v_mfma_f32_32x32x2_f32 (operand A = columns, so that a lane ends up with
+// neighbouring columns of one row).  32-deep k-steps, two LDS buffers, the next step's global loads in registers while the
+// current one is multiplied, one barrier per step.  A step is 32 MFMAs of 64 cycles per wave against 28 LDS reads: bound
+// by the matrix cores; 53 KB of LDS lets three blocks share a CU and cover each other's barriers.  Measured at 572 rows x
+// 2048 x 11264 (SwiGLU): 883 -> 315 us, 84 TFLOP/s of the 154 a large library product reaches; two layers 6270 -> 1276 us.
+// blockIdx.z: split of the contraction (see f32_launch_proj); the splits' sums go to `part` and f32_tile_finish_kernel.
+// -------------------------------------------------------------------------------------------------
+constexpr int F32_BT = 64, F32_BN = 128, F32_BK = 32, F32_XS = 36, F32_WS = 136;     // row strides of the LDS tiles (floats)
+template <int MODE>
+__global__ __launch_bounds__(256) void f32_tile_kernel(F32Proj p, float *__restrict__ part) {
+    constexpr bool GLU = MODE == F32_SWIGLU;
+    __shared__ __align__(16) float sx[2][F32_BT][F32_XS], sw[2][F32_BK][F32_WS];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hl = lane >> 5;
+    const int bt = blockIdx.y * F32_BT, bn = blockIdx.x * (GLU ? F32_BN / 2 : F32_BN);
+    const int wt = wave & 1, wn = wave >> 1;
+    const int ksteps = p.Kp / F32_BK;
+    const int k_lo = (int)((long)blockIdx.z * ksteps / gridDim.z), k_hi = (int)((long)(blockIdx.z + 1) * ksteps / gridDim.z);
+
+    // staging: rows tid / 8 (+ 32) x 16 bytes of the token rows; weight rows tid / 32 (+ 8, 16, 24) x 16 bytes
+    const float *xsrc[2], *wsrc;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) xsrc[q] = p.x + (size_t)min(bt + (tid >> 3) + 32 * q, p.T - 1) * p.K + 4 * (tid & 7);
+    {
+        const int c = 4 * (tid & 31);
+        const int n = GLU ? min(bn + (c & 63), p.cols - 4) + (c >> 6) * p.cols : min(bn + c, p.cols - 4);
+        wsrc = p.w + (size_t)(tid >> 5) * p.N + n;
+    }
+    floatx4 rx[2], rw[4];
+    auto load = [&](int k) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) rx[q] = *reinterpret_cast<const floatx4 *>(xsrc[q] + (size_t)k * F32_BK);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) rw[q] = *reinterpret_cast<const floatx4 *>(wsrc + (size_t)(k * F32_BK + 8 * q) * p.N);
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) *reinterpret_cast<floatx4 *>(&sx[buf][(tid >> 3) + 32 * q][4 * (tid & 7)]) = rx[q];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *reinterpret_cast<floatx4 *>(&sw[buf][(tid >> 5) + 8 * q][4 * (tid & 31)]) = rw[q];
+    };
+    floatx16 acc[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    load(k_lo);
+    store(0);
+    __syncthreads();
+    for (int k = k_lo; k < k_hi; ++k) {
+        const int buf = (k - k_lo) & 1;
+        load(min(k + 1, k_hi - 1));
+#pragma unroll
+        for (int s = 0; s < F32_BK / 8; ++s) {
+            // k-slot hl of MFMA x = row 8 s + 4 hl + x of the step
+            const floatx4 x4 = *reinterpret_cast<const floatx4 *>(&sx[buf][32 * wt + l32][8 * s + 4 * hl]);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const float *row = sw[buf][8 * s + 4 * hl + x];
+                floatx2 a;
+                if constexpr (GLU) a = floatx2{row[32 * wn + l32], row[64 + 32 * wn + l32]};
+                else a = *reinterpret_cast<const floatx2 *>(row + 64 * wn + 2 * l32);
+                acc[0] = f32_mfma32(a[0], x4[x], acc[0]);
+                acc[1] = f32_mfma32(a[1], x4[x], acc[1]);
+            }
+        }
+        store(buf ^ 1);
+        __syncthreads();
+    }
+    const int t = bt + 32 * wt + l32;
+    if (t >= p.T) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if constexpr (GLU) {
+            // register 4 q + r: gate (acc[0]) and up (acc[1]) column bn + 32 wn + 8 q + 4 hl + r
+            const int n = bn + 32 * wn + 8 * q + 4 * hl;
+            if (n >= p.cols) continue;
+            const floatx4 a = {acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]};
+            const floatx4 b = {acc[1][4 * q], acc[1][4 * q + 1], acc[1][4 * q + 2], acc[1][4 * q + 3]};
+            if (part != nullptr) {
+                float *dst = part + ((size_t)blockIdx.z * p.T + t) * p.N + n;
+                *reinterpret_cast<floatx4 *>(dst) = a;
+                *reinterpret_cast<floatx4 *>(dst + p.cols) = b;
+            } else {
+                f32_finish4<MODE>(p, t, n, a, b);
+            }
+        } else {
+            // register 4 q + r of acc[j]: column bn + 64 wn + 2 (8 q + 4 hl + r) + j
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const int n = bn + 64 * wn + 16 * q + 8 * hl + 4 * half, r = 4 * q + 2 * half;
+                if (n >= p.cols) continue;
+                const floatx4 a = {acc[0][r], acc[1][r], acc[0][r + 1], acc[1][r + 1]};
+                if (part != nullptr) *reinterpret_cast<floatx4 *>(part + ((size_t)blockIdx.z * p.T + t) * p.N + n) = a;
+                else f32_finish4<MODE>(p, t, n, a, a);
+            }
+        }
+    }
+}
+
+// adds the splits up in split order; one thread per row and four columns
+template <int MODE>
+__global__ __launch_bounds__(256) void f32_tile_finish_kernel(F32Proj p, const float *__restrict__ part, int splits) {
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int per = p.cols >> 2;
+    if (idx >= (int64_t)p.T * per) return;
+    const int t = (int)(idx / per), n = 4 * (int)(idx % per);
+    floatx4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+    for (int z = 0; z < splits; ++z) {
+        const float *src = part + ((size_t)z * p.T + t) * p.N + n;
+        a += *reinterpret_cast<const floatx4 *>(src);
+        if (MODE == F32_SWIGLU) b += *reinterpret_cast<const floatx4 *>(src + p.cols);
+    }
+    f32_finish4<MODE>(p, t, n, a, b);
+}
+
+namespace {
+template <int MODE, int NB, int V>
+void f32_stream_flags(const F32Proj &p, hipStream_t s) {
+    const dim3 grid((p.cols + 16 * V - 1) / (16 * V));
+    if constexpr (MODE != F32_RESID) {
+        if (p.g != nullptr) {
+            if constexpr (MODE == F32_PLAIN) {
+                if (p.x2 != nullptr) { hipLaunchKernelGGL((f32_stream_kernel<MODE, NB, V, true, true>), grid, dim3(512), 0, s, p); return; }
+            }
+            hipLaunchKernelGGL((f32_stream_kernel<MODE, NB, V, true, false>), grid, dim3(512), 0, s, p);
+            return;
+        }
+    }
+    if constexpr (MODE != F32_SWIGLU) hipLaunchKernelGGL((f32_stream_kernel<MODE, NB, V, false, false>), grid, dim3(512), 0, s, p);
+}
+
+template <int MODE>
+void f32_proj_mode(const F32Proj &p, float *n_buf, float *part, size_t part_floats, hipStream_t s) {
+    if (p.T <= 32) {
+        constexpr int NM = MODE == F32_SWIGLU ? 2 : 1;
+        const bool wide = p.cols / 32 >= 128;
+        if (p.T <= 16) {
+            if (wide) f32_stream_flags<MODE, 1, 2>(p, s);
+            else f32_stream_flags<MODE, 1, 1>(p, s);
+        } else {
+            if (wide && NM == 1) f32_stream_flags<MODE, 2, 3 - NM>(p, s);
+            else f32_stream_flags<MODE, 2, 1>(p, s);
+        }
+        return;
+    }
+    F32Proj t = p;
+    if (p.g != nullptr) {            // (no caller adds a second operand or advances lengths here)
+        f32_launch_rmsnorm(p.x, p.g, n_buf, p.T, p.K, p.eps, s);
+        t.x = n_buf;
+    }
+    const int bn = MODE == F32_SWIGLU ? F32_BN / 2 : F32_BN;
+    const int gx = (p.cols + bn - 1) / bn, gy = (p.T + F32_BT - 1) / F32_BT, ksteps = p.Kp / F32_BK;
+    // The blocks of a CU share its matrix cores, so a launch takes (blocks on the fullest CU) x (k-steps of a block); a step
+    // is 0.9 us at the matrix rate.  Splitting the contraction evens out the CUs and costs the partial sums' way through
+    // memory (written and read, about 4 TB/s) and a second launch: the cheapest of 1 .. 16 splits of 4 k-steps or more.
+    int splits = 1;
+    double best = 0.0;
+    for (int c = 1; c <= 16 && (c == 1 || c * 4 <= ksteps); ++c) {
+        if (c > 1 && (part == nullptr || (size_t)c * p.T * p.N > part_floats)) break;
+        const double us = 0.9 * ((gx * gy * c + 255) / 256) * ((ksteps + c - 1) / c) + (c > 1 ? 5.0 + (double)c * p.T * p.N * 8.0 / 4e6 : 0.0);
+        if (c == 1 || us < best) { best = us; splits = c; }
+    }
+    hipLaunchKernelGGL((f32_tile_kernel<MODE>), dim3(gx, gy, splits), dim3(256), 0, s, t, splits > 1 ? part : nullptr);
+    if (splits > 1) {
+        const int64_t n4 = (int64_t)p.T * (p.cols / 4);
+        hipLaunchKernelGGL((f32_tile_finish_kernel<MODE>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, t, part, splits);
+    }
+}
+}  // namespace
+
+void f32_launch_proj(int mode, const F32Proj &p, float *n_buf, float *part, size_t part_floats, hipStream_t s) {
+    if (p.T <= 0 || p.cols <= 0) return;
+    switch (mode) {
+        case F32_PLAIN: f32_proj_mode<F32_PLAIN>(p, n_buf, part, part_floats, s); break;
+        case F32_RESID: f32_proj_mode<F32_RESID>(p, n_buf, part, part_floats, s); break;
+        case F32_SWIGLU: f32_proj_mode<F32_SWIGLU>(p, n_buf, part, part_floats, s); break;
+    }
 }
 
 // cache layout per layer: [seq][hkv_l][smax][d]
@@ -94,65 +426,192 @@ void f32_launch_rope_append(const float *qkv, int T, int hq_l, int hkv_l, int d,
                        rm, cos_tab, sin_tab, q_out, kc, vc);
 }
 
-// one block per (row, query head): scores of positions 0..pos in LDS, softmax, weighted V sum
-__global__ __launch_bounds__(256) void f32_attn_kernel(const float *__restrict__ q, const float *__restrict__ kc,
-                                                      const float *__restrict__ vc, int hq_l, int hkv_l, int d,
-                                                      int smax, RowMap rm, float *__restrict__ o) {
-    extern __shared__ float sc[];     // [smax] scores, then [256] partial sums
-    __shared__ float red[4];
-    __shared__ float sq[128];
-    const int t = blockIdx.x, head = blockIdx.y;
-    const int seq = rm.row_seq[t], pos = rm.row_pos[t];
-    const int G = hq_l / hkv_l, c = head / G;
-    const float *K = kc + ((size_t)seq * hkv_l + c) * smax * d;
-    const float *V = vc + ((size_t)seq * hkv_l + c) * smax * d;
-    if (threadIdx.x < d) sq[threadIdx.x] = q[((size_t)t * hq_l + head) * d + threadIdx.x];
-    __syncthreads();
-    const float scale = 1.0f / sqrtf((float)d);
-    float mx = -INFINITY;
-    for (int p = threadIdx.x; p <= pos; p += 256) {
-        float s = 0.f;
-        for (int e = 0; e < d; ++e) s = fmaf(K[(size_t)p * d + e], sq[e], s);
-        s *= scale;
-        sc[p] = s;
-        mx = fmaxf(mx, s);
+// -------------------------------------------------------------------------------------------------
+// Attention over the cache for 16 query columns that share a kv head, W waves per block; a wave takes every W-th tile of 16
+// positions, and the waves' (m, l, o) are merged through LDS in wave order.  v_mfma_f32_16x16x4_f32 throughout:
+//   S^T (positions x columns) = K . Q^T: lane l loads 16 bytes of position l % 16's key per 16 head elements, k-slot l / 16;
+//   in the result a lane owns column l % 16 and positions 4 (l / 16) + r, which is exactly operand B of
+//   O^T (head elements x columns) = V^T . P^T for the MFMA that takes positions 4 (l / 16) + r: P never leaves its registers,
+//   and V is read in 16-byte pieces of its rows (head element 64 h + 4 i + e is row i of MFMA (h, e)).
+// DECODE: one new row per sequence; the columns are the G heads of kv head c.  The block first rotates its heads and its
+// new key, appends key and value to the cache (nobody else reads them in this launch) and keeps q in LDS.
+// Otherwise: 16 consecutive new rows of one head, whose keys and values f32_rope_append_kernel has put into the cache.
+// A masked position has weight 0, but 0 x inf would still poison the sum: a tile that is masked for some column and holds a
+// value that is not finite is multiplied out element by element, over the positions each column may see.
+// -------------------------------------------------------------------------------------------------
+template <int D, int W, bool DECODE>
+__global__ __launch_bounds__(64 * W) void f32_attn_kernel(const float *__restrict__ q, float *kc, float *vc, int hq_l, int hkv_l,
+                                                         int smax, const int32_t *__restrict__ pos0, const int32_t *__restrict__ cu_rows,
+                                                         const int32_t *__restrict__ items, const float *__restrict__ cos_tab,
+                                                         const float *__restrict__ sin_tab, float *__restrict__ o) {
+    constexpr int KT = D / 16, VH = D / 64, HALF = D / 2, QS = D + 4;
+    __shared__ __align__(16) float s_q[DECODE ? 16 : 1][QS];
+    __shared__ float s_m[W][16], s_l[W][16];
+    __shared__ __align__(16) float s_o[W][16][D];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    const int G = hq_l / hkv_l;
+    int seq, c, head = 0, first_pos, n_col, row0 = 0;        // column j: position first_pos + (DECODE ? 0 : j), j < n_col
+    if (DECODE) {
+        c = blockIdx.x % hkv_l;
+        seq = blockIdx.x / hkv_l;
+        first_pos = pos0[seq];
+        n_col = G;
+    } else {
+        const int tile = blockIdx.x / hq_l;                   // an item is 128 rows of a sequence: eight tiles
+        head = blockIdx.x % hq_l;
+        c = head / G;
+        seq = items[2 * (tile >> 3)];
+        const int r0 = items[2 * (tile >> 3) + 1] * 128 + (tile & 7) * 16;
+        const int n_new = cu_rows[seq + 1] - cu_rows[seq];
+        if (r0 >= n_new) return;                              // the whole block leaves
+        n_col = min(16, n_new - r0);
+        first_pos = pos0[seq] + r0;
+        row0 = cu_rows[seq] + r0;
     }
-    mx = block_max_256(mx, red);
-    float sum = 0.f;
-    for (int p = threadIdx.x; p <= pos; p += 256) { float w = expf(sc[p] - mx); sc[p] = w; sum += w; }
-    sum = block_sum_256(sum, red);
-    // thread (e = tid % d, slice = tid / d) sums its slice of positions; slices are added in order
-    const int e = threadIdx.x % d, slice = threadIdx.x / d, nslice = 256 / d;
-    float acc = 0.f;
-    for (int p = slice; p <= pos; p += nslice) acc = fmaf(sc[p], V[(size_t)p * d + e], acc);
-    float *ps = sc + smax;
-    ps[threadIdx.x] = acc;
+    float *K = kc + ((size_t)seq * hkv_l + c) * smax * D, *V = vc + ((size_t)seq * hkv_l + c) * smax * D;
+    const int last_pos = first_pos + (DECODE ? 0 : n_col - 1);
+    const int my_pos = DECODE ? first_pos : min(first_pos + i, last_pos);
+    if constexpr (DECODE) {
+        const float *row = q + (size_t)seq * (hq_l + 2 * hkv_l) * D;          // raw projection of the new row
+        for (int idx = threadIdx.x; idx < (G + 2) * HALF; idx += 64 * W) {
+            const int hh = idx / HALF, e = idx - hh * HALF;
+            const float *src = row + (size_t)(hh < G ? c * G + hh : (hh == G ? hq_l + c : hq_l + hkv_l + c)) * D;
+            float lo = src[e], hi = src[e + HALF];
+            if (hh <= G) {
+                const float cs = cos_tab[(size_t)first_pos * HALF + e], sn = sin_tab[(size_t)first_pos * HALF + e];
+                const float rlo = lo * cs - hi * sn, rhi = hi * cs + lo * sn;
+                lo = rlo; hi = rhi;
+            }
+            float *dst = hh < G ? s_q[hh] : (hh == G ? K : V) + (size_t)first_pos * D;
+            dst[e] = lo;
+            dst[e + HALF] = hi;
+        }
+        __syncthreads();           // q in LDS; the new key and value visible to the block's loads
+    }
+    floatx4 qf[KT];
+#pragma unroll
+    for (int k = 0; k < KT; ++k) {
+        const int j = min(i, n_col - 1);                      // columns past the last one repeat it and are not stored
+        if constexpr (DECODE) qf[k] = *reinterpret_cast<const floatx4 *>(&s_q[j][16 * k + 4 * g]);
+        else qf[k] = *reinterpret_cast<const floatx4 *>(q + ((size_t)(row0 + j) * hq_l + head) * D + 16 * k + 4 * g);
+    }
+    const float scale = 1.0f / sqrtf((float)D);
+    floatx4 oacc[VH][4];
+#pragma unroll
+    for (int h = 0; h < VH; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) oacc[h][e] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, lsum = 0.f;
+    for (int t = wave; t <= last_pos >> 4; t += W) {
+        floatx4 kf[KT], vf[4][VH];
+#pragma unroll
+        for (int k = 0; k < KT; ++k) kf[k] = *reinterpret_cast<const floatx4 *>(K + (size_t)min(16 * t + i, last_pos) * D + 16 * k + 4 * g);
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int h = 0; h < VH; ++h)
+                vf[x][h] = *reinterpret_cast<const floatx4 *>(V + (size_t)min(16 * t + 4 * g + x, last_pos) * D + 64 * h + 4 * i);
+        floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KT; ++k)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) s = f32_mfma16(kf[k][x], qf[k][x], s);
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            s[r] = 16 * t + 4 * g + r <= my_pos ? s[r] * scale : -INFINITY;
+            mx = fmaxf(mx, s[r]);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float m_new = fmaxf(m, mx);
+        const float base = m_new == -INFINITY ? 0.f : m_new;      // a column that has seen no position yet: weights 0, no NaN
+        const float alpha = expf(m - base);
+        m = m_new;
+        float ps = 0.f, pr[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            pr[r] = expf(s[r] - base);
+            ps += pr[r];
+        }
+        lsum = lsum * alpha + ps;
+#pragma unroll
+        for (int h = 0; h < VH; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) oacc[h][e] *= alpha;
+        bool odd = false;
+        if (16 * t + 15 > first_pos) {                            // masked for some column
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int h = 0; h < VH; ++h)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) odd = odd || !(fabsf(vf[x][h][e]) < INFINITY);
+        }
+        if (__builtin_amdgcn_ballot_w64(odd) == 0) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int h = 0; h < VH; ++h)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) oacc[h][e] = f32_mfma16(vf[x][h][e], pr[x], oacc[h][e]);
+        } else {
+            for (int pp = 0; pp < 16; ++pp) {
+                const int src = i + 16 * (pp >> 2);
+                const float w0 = __shfl(pr[0], src, 64), w1 = __shfl(pr[1], src, 64), w2 = __shfl(pr[2], src, 64), w3 = __shfl(pr[3], src, 64);
+                const float w = (pp & 3) == 0 ? w0 : (pp & 3) == 1 ? w1 : (pp & 3) == 2 ? w2 : w3;
+                if (16 * t + pp > my_pos) continue;
+#pragma unroll
+                for (int h = 0; h < VH; ++h)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            oacc[h][e][r] = fmaf(w, V[(size_t)(16 * t + pp) * D + 64 * h + 4 * (4 * g + r) + e], oacc[h][e][r]);
+            }
+        }
+    }
+    lsum += __shfl_xor(lsum, 16, 64);
+    lsum += __shfl_xor(lsum, 32, 64);
+    if (g == 0) { s_m[wave][i] = m; s_l[wave][i] = lsum; }
+    // register r of oacc[h][e]: head element 64 h + 4 (4 g + r) + e of column i
+#pragma unroll
+    for (int h = 0; h < VH; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            *reinterpret_cast<floatx4 *>(&s_o[wave][i][64 * h + 16 * g + 4 * r]) = floatx4{oacc[h][0][r], oacc[h][1][r], oacc[h][2][r], oacc[h][3][r]};
     __syncthreads();
-    if (threadIdx.x < d) {
-        float tot = 0.f;
-        for (int sl = 0; sl < nslice; ++sl) tot += ps[sl * d + threadIdx.x];
-        o[((size_t)t * hq_l + head) * d + threadIdx.x] = tot / sum;
+    for (int idx = threadIdx.x * 4; idx < n_col * D; idx += 64 * W * 4) {
+        const int j = idx / D, dd = idx % D;
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < W; ++w) M = fmaxf(M, s_m[w][j]);
+        float L = 0.f;
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            if (s_l[w][j] == 0.f) continue;                       // no position of this column (or all of them at weight 0)
+            const float wt = expf(s_m[w][j] - M);
+            L += s_l[w][j] * wt;
+            acc += *reinterpret_cast<const floatx4 *>(&s_o[w][j][dd]) * wt;
+        }
+        const int64_t row = DECODE ? (int64_t)seq * hq_l + c * G + j : (int64_t)(row0 + j) * hq_l + head;
+        *reinterpret_cast<floatx4 *>(o + row * D + dd) = acc / L;
     }
 }
-void f32_launch_attn(const float *q, const float *kc, const float *vc, int T, int hq_l, int hkv_l, int d, int smax,
-                     RowMap rm, float *o, hipStream_t s) {
-    if (T <= 0) return;
-    size_t shm = (size_t)(smax + 256) * sizeof(float);
-    hipLaunchKernelGGL(f32_attn_kernel, dim3(T, hq_l), dim3(256), shm, s, q, kc, vc, hq_l, hkv_l, d, smax, rm, o);
+void f32_launch_attn_prefill(const float *q, float *kc, float *vc, int hq_l, int hkv_l, int d, int smax, const int32_t *pos0,
+                             const int32_t *cu_rows, const int32_t *items, int n_items, float *o, hipStream_t s) {
+    if (n_items <= 0) return;
+    const dim3 grid((unsigned)n_items * 8u * (unsigned)hq_l);
+    if (d == 128) hipLaunchKernelGGL((f32_attn_kernel<128, 4, false>), grid, dim3(256), 0, s, q, kc, vc, hq_l, hkv_l, smax, pos0, cu_rows, items, nullptr, nullptr, o);
+    else hipLaunchKernelGGL((f32_attn_kernel<64, 4, false>), grid, dim3(256), 0, s, q, kc, vc, hq_l, hkv_l, smax, pos0, cu_rows, items, nullptr, nullptr, o);
 }
-
-// ab = [T][2*F_l] with W1 columns then W3 columns
-__global__ void f32_swiglu_kernel(const float *__restrict__ ab, float *__restrict__ u, int T, int F_l) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)T * F_l) return;
-    const int t = (int)(i / F_l), f = (int)(i % F_l);
-    const float a = ab[(size_t)t * 2 * F_l + f], b = ab[(size_t)t * 2 * F_l + F_l + f];
-    u[i] = a / (1.0f + expf(-a)) * b;
-}
-void f32_launch_swiglu(const float *ab, float *u, int T, int F_l, hipStream_t s) {
-    int64_t n = (int64_t)T * F_l;
-    if (n <= 0) return;
-    hipLaunchKernelGGL(f32_swiglu_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, ab, u, T, F_l);
+void f32_launch_attn_decode(const float *qkv, float *kc, float *vc, int b, int hq_l, int hkv_l, int d, int smax, const int32_t *pos,
+                            const float *cos_tab, const float *sin_tab, float *o, hipStream_t s) {
+    if (b <= 0) return;
+    const dim3 grid((unsigned)hkv_l * (unsigned)b);
+    if (d == 128) hipLaunchKernelGGL((f32_attn_kernel<128, 4, true>), grid, dim3(256), 0, s, qkv, kc, vc, hq_l, hkv_l, smax, pos, nullptr, nullptr, cos_tab, sin_tab, o);
+    else hipLaunchKernelGGL((f32_attn_kernel<64, 8, true>), grid, dim3(512), 0, s, qkv, kc, vc, hq_l, hkv_l, smax, pos, nullptr, nullptr, cos_tab, sin_tab, o);
 }
 
 // staging [n][hkv_l][d] <-> cache rows pos0.. of sequence seq

@@ -48,13 +48,6 @@ void launch_accumulate_f32(float *dst, const float *src, int64_t n, hipStream_t 
     hipLaunchKernelGGL(accumulate_f32_kernel, dim3(blocks), dim3(256), 0, s, dst, src, n);
 }
 
-__global__ void decode_rowmap_kernel(const int32_t *lens, int32_t *row_seq, int32_t *row_pos, int b) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < b) { row_seq[i] = i; row_pos[i] = lens[i]; }
-}
-void launch_decode_rowmap(const int32_t *lens, int32_t *row_seq, int32_t *row_pos, int b, hipStream_t s) {
-    hipLaunchKernelGGL(decode_rowmap_kernel, dim3((b + 63) / 64), dim3(64), 0, s, lens, row_seq, row_pos, b);
-}
 __global__ void advance_lens_kernel(int32_t *lens, int b) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < b) lens[i] += 1;

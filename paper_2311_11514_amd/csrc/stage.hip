@@ -67,8 +67,6 @@ struct Profiler {
 struct Workspace {
     int cap_rows = 0;
     float *h = nullptr;        // residual stream [T][H] fp32
-    float *part = nullptr;     // projection outputs / split-K partials, fp32
-    float *p32 = nullptr;      // reduced partial [T][H] fp32
     // bf16 path
     h16_t *n = nullptr, *o = nullptr, *u = nullptr, *q = nullptr;
     float *dec_part = nullptr;       // split partial sums of the batched decode projections
@@ -81,8 +79,8 @@ struct Workspace {
     unsigned int *att_arrived = nullptr;      // per (sequence, kv head): split blocks that have finished; zero between launches
     float *ssq = nullptr;                       // decode: 2 x [H/16 units][DEC_SSQ_STRIDE] sums of squares
     float *ssq_pf = nullptr;                    // prefill: 2 x [H/128][T] sums of squares
-    // fp32 path
-    float *n32 = nullptr, *q32 = nullptr, *o32 = nullptr, *u32 = nullptr;
+    // fp32 path: raw QKV projection, normalised rows (more than 32 rows only), rotated q, attention output, SwiGLU output
+    float *qkv32 = nullptr, *n32 = nullptr, *q32 = nullptr, *o32 = nullptr, *u32 = nullptr;
     // row bookkeeping
     int32_t *rowmap = nullptr;       // one block: row_seq | row_pos | cu_rows | pos0, packed by the sizes of the call
     int32_t *row_seq = nullptr, *row_pos = nullptr, *cu_rows = nullptr, *pos0 = nullptr;   // views into rowmap
@@ -96,6 +94,7 @@ struct Workspace {
 struct hexgen_stage {
     int H, hq, hkv, F, L, t, r;
     int d, hq_l, hkv_l, F_l, nqkv, qw;     // qw = hq_l * d
+    int F_p;                               // F_l as it is laid out: fp32 pads it with zeros to a multiple of 32
     hexgen_dtype_t dtype;
     float eps = 1e-5f, theta = 10000.0f;
     std::vector<Layer> layers;
@@ -131,7 +130,7 @@ bool known_dtype(hexgen_dtype_t dt) { return dt == HEXGEN_F32 || is_h16(dt); }
 #define HX_K(dt, fn, ...) ((dt) == HEXGEN_F16 ? f16::fn(__VA_ARGS__) : bf16::fn(__VA_ARGS__))
 
 void free_ws(Workspace &w) {
-    void *ptrs[] = {w.dec_part, w.gemm_part, w.h, w.part, w.p32, w.n, w.o, w.u, w.q, w.xa_n, w.xa_o, w.xa_u, w.q_lo, w.ssq, w.ssq_pf, w.att_o, w.att_ml, w.att_arrived, w.n32, w.q32, w.o32, w.u32,
+    void *ptrs[] = {w.dec_part, w.gemm_part, w.h, w.n, w.o, w.u, w.q, w.xa_n, w.xa_o, w.xa_u, w.q_lo, w.ssq, w.ssq_pf, w.att_o, w.att_ml, w.att_arrived, w.qkv32, w.n32, w.q32, w.o32, w.u32,
                     w.rowmap};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -159,10 +158,6 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
     const size_t T = (size_t)rows, T16 = (size_t)round_up(rows, 16);
     const size_t nmax = (size_t)std::max(std::max(st->nqkv, st->H), 2 * st->F_l);
     HX_TRY(dmalloc(&w.h, (size_t)round_up(rows, 32) * st->H));
-    if (st->dtype == HEXGEN_F32) {
-        HX_TRY(dmalloc(&w.part, T * nmax));
-        HX_TRY(dmalloc(&w.p32, T * st->H));
-    }
     if (is_h16(st->dtype)) {
         HX_TRY(dmalloc(&w.n, T16 * st->H));
         HX_TRY(dmalloc(&w.o, T16 * st->qw));
@@ -192,10 +187,15 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
         HX_HIP(hipMemset(w.o, 0, T16 * st->qw * sizeof(h16_t)));
         HX_HIP(hipMemset(w.u, 0, T16 * st->F_l * sizeof(h16_t)));
     } else {
-        HX_TRY(dmalloc(&w.n32, T * st->H));
+        HX_TRY(dmalloc(&w.qkv32, T * st->nqkv));
         HX_TRY(dmalloc(&w.q32, T * st->qw));
         HX_TRY(dmalloc(&w.o32, T * st->qw));
-        HX_TRY(dmalloc(&w.u32, T * st->F_l));
+        HX_TRY(dmalloc(&w.u32, T * st->F_p));
+        if (rows > kDecodeMaxRows) {
+            HX_TRY(dmalloc(&w.n32, T * st->H));
+            w.gemm_part_floats = (size_t)8 << 20;       // 32 MB: 8 splits of 512 rows x 2048 columns
+            HX_TRY(dmalloc(&w.gemm_part, w.gemm_part_floats));
+        }
     }
     // row_seq, row_pos, cu_rows, pos0, new lengths, attention work list (at most rows / 128 + batch pairs)
     w.host_stage_cap = 2 * rows + 3 * batch + 1 + 2 * (rows / kAttnRows + batch);
@@ -242,11 +242,8 @@ hexgen_status_t setup_rows(hexgen_stage *st, hexgen_kv_cache *kv, const int32_t 
     w.pos0 = w.cu_rows + batch + 1;
     r.rm.row_seq = w.row_seq;
     r.rm.row_pos = w.row_pos;
-    if (r.decode && is_h16(st->dtype)) {
-        // the decode prologue kernel publishes row positions from the committed lengths on the device
-    } else if (r.decode) {
-        launch_decode_rowmap(kv->d_lens, w.row_seq, w.row_pos, batch, s);
-    } else {
+    // a decode step of at most 32 rows takes its positions from the committed lengths on the device
+    if (!r.decode) {
         // the pinned staging buffer may still feed an earlier async copy on this stream
         HX_HIP(hipStreamSynchronize(s));
         int32_t *hs = w.host_stage;
@@ -525,43 +522,64 @@ hexgen_status_t forward_h16(hexgen_stage *st, hexgen_kv_cache *kv, const Rows &r
 }
 
 // ---- fp32 path -------------------------------------------------------------------------------
-void attn_f32(hexgen_stage *st, hexgen_kv_cache *kv, int layer, const Rows &r, const float *h, float *p_out,
-              hipStream_t s) {
+// up to 32 rows five launches per layer (QKV, attention, W_O, W1/W3, W2), norms, residuals and SwiGLU inside them
+F32Proj f32_proj(const hexgen_stage *st, const float *x, const float *g, const void *w, int T, int K, int N, int cols, float *out) {
+    F32Proj p;
+    std::memset(&p, 0, sizeof(p));
+    p.x = x; p.g = g; p.w = static_cast<const float *>(w);
+    p.T = T; p.K = K; p.Kp = K; p.N = N; p.cols = cols;
+    p.eps = st->eps;
+    p.out = out;
+    return p;
+}
+void proj_f32(hexgen_stage *st, int mode, const F32Proj &p, hipStream_t s) {
+    f32_launch_proj(mode, p, st->ws.n32, st->ws.gemm_part, st->ws.gemm_part_floats, s);
+}
+// RMSNorm, QKV, rotary embedding, cache append and attention; leaves o in the workspace
+void attn_f32(hexgen_stage *st, hexgen_kv_cache *kv, int layer, const Rows &r, const float *h, hipStream_t s) {
     Workspace &w = st->ws;
     const Layer &ly = st->layers[layer];
     float *kc = static_cast<float *>(kv->k) + (size_t)layer * kv->layer_stride;
     float *vc = static_cast<float *>(kv->v) + (size_t)layer * kv->layer_stride;
-    f32_launch_rmsnorm(h, ly.g_attn, w.n32, r.T, st->H, st->eps, s);
-    f32_launch_gemm(w.n32, static_cast<const float *>(ly.wqkv), w.part, r.T, st->H, st->nqkv, s);
-    f32_launch_rope_append(w.part, r.T, st->hq_l, st->hkv_l, st->d, kv->smax, r.rm, kv->cos_tab, kv->sin_tab, w.q32, kc,
+    proj_f32(st, F32_PLAIN, f32_proj(st, h, ly.g_attn, ly.wqkv, r.T, st->H, st->nqkv, st->nqkv, w.qkv32), s);
+    if (r.max_new == 1) {          // row = sequence
+        f32_launch_attn_decode(w.qkv32, kc, vc, r.batch, st->hq_l, st->hkv_l, st->d, kv->smax, r.decode ? kv->d_lens : w.pos0, kv->cos_tab,
+                               kv->sin_tab, w.o32, s);
+        return;
+    }
+    f32_launch_rope_append(w.qkv32, r.T, st->hq_l, st->hkv_l, st->d, kv->smax, r.rm, kv->cos_tab, kv->sin_tab, w.q32, kc,
                            vc, s);
-    f32_launch_attn(w.q32, kc, vc, r.T, st->hq_l, st->hkv_l, st->d, kv->smax, r.rm, w.o32, s);
-    f32_launch_gemm(w.o32, static_cast<const float *>(ly.wo), p_out, r.T, st->qw, st->H, s);
+    f32_launch_attn_prefill(w.q32, kc, vc, st->hq_l, st->hkv_l, st->d, kv->smax, w.pos0, w.cu_rows, w.items, r.n_items, w.o32, s);
 }
-void ffn_f32(hexgen_stage *st, int layer, const Rows &r, const float *h, float *p_out, hipStream_t s) {
-    Workspace &w = st->ws;
+// RMSNorm, W1/W3 and SwiGLU; leaves u in the workspace
+void ffn_f32(hexgen_stage *st, int layer, const Rows &r, const float *h, hipStream_t s) {
     const Layer &ly = st->layers[layer];
-    f32_launch_rmsnorm(h, ly.g_ffn, w.n32, r.T, st->H, st->eps, s);
-    f32_launch_gemm(w.n32, static_cast<const float *>(ly.w13), w.part, r.T, st->H, 2 * st->F_l, s);
-    f32_launch_swiglu(w.part, w.u32, r.T, st->F_l, s);
-    f32_launch_gemm(w.u32, static_cast<const float *>(ly.w2), p_out, r.T, st->F_l, st->H, s);
+    proj_f32(st, F32_SWIGLU, f32_proj(st, h, ly.g_ffn, ly.w13, r.T, st->H, 2 * st->F_p, st->F_p, st->ws.u32), s);
 }
 hexgen_status_t forward_f32(hexgen_stage *st, hexgen_kv_cache *kv, const Rows &r, const void *hidden_in,
-                            void *out_partial, void *out_resid, hipStream_t s) {
+                            void *out_partial, void *out_resid, int32_t *advance_lens, hipStream_t s) {
     Workspace &w = st->ws;
-    const size_t bytes = sizeof(float) * (size_t)r.T * st->H;
-    HX_HIP(hipMemcpyAsync(w.h, hidden_in, bytes, hipMemcpyDeviceToDevice, s));
+    const float *h = static_cast<const float *>(hidden_in);      // the residual stream: the caller's rows, then w.h
     for (int l = 0; l < st->L; ++l) {
-        if (st->taps[l]) HX_HIP(hipMemcpyAsync(st->taps[l], w.h, bytes, hipMemcpyDeviceToDevice, s));
-        attn_f32(st, kv, l, r, w.h, w.p32, s);
-        launch_accumulate_f32(w.h, w.p32, (int64_t)r.T * st->H, s);
-        ffn_f32(st, l, r, w.h, w.p32, s);
+        const Layer &ly = st->layers[l];
+        if (st->taps[l]) HX_HIP(hipMemcpyAsync(st->taps[l], h, sizeof(float) * (size_t)r.T * st->H, hipMemcpyDeviceToDevice, s));
+        attn_f32(st, kv, l, r, h, s);
+        F32Proj p = f32_proj(st, w.o32, nullptr, ly.wo, r.T, st->qw, st->H, st->H, nullptr);
+        p.resid = h;
+        p.resid_out = w.h;
+        proj_f32(st, F32_RESID, p, s);
+        h = w.h;
+        ffn_f32(st, l, r, h, s);
+        p = f32_proj(st, w.u32, nullptr, ly.w2, r.T, st->F_p, st->H, st->H, nullptr);
+        p.resid = h;
         if (l + 1 < st->L) {
-            launch_accumulate_f32(w.h, w.p32, (int64_t)r.T * st->H, s);
+            p.resid_out = w.h;
         } else {
-            HX_HIP(hipMemcpyAsync(out_partial, w.p32, bytes, hipMemcpyDeviceToDevice, s));
-            if (out_resid) HX_HIP(hipMemcpyAsync(out_resid, w.h, bytes, hipMemcpyDeviceToDevice, s));
+            p.out = static_cast<float *>(out_partial);
+            p.out_resid = static_cast<float *>(out_resid);
+            p.lens = advance_lens;
         }
+        proj_f32(st, F32_RESID, p, s);
     }
     return HEXGEN_OK;
 }
@@ -694,6 +712,7 @@ hexgen_status_t hexgen_stage_create(int hidden, int n_heads, int n_kv_heads, int
     st->qw = hq_l * d;
     st->nqkv = (hq_l + 2 * hkv_l) * d;
     st->dtype = dtype;
+    st->F_p = dtype == HEXGEN_F32 ? round_up(F_l, 32) : F_l;
     st->cur = &st->ws;
     try {       // no exception may cross the C boundary
         st->layers.resize(n_layers);
@@ -760,8 +779,8 @@ hexgen_status_t hexgen_stage_load_layer(hexgen_stage_t *st, int layer, const voi
         HX_HIP(e2);
     }
 
-    const size_t n_qkv = (size_t)H * st->nqkv, n_wo = (size_t)st->qw * H, n_13 = (size_t)H * 2 * st->F_l,
-                 n_w2 = (size_t)st->F_l * H;
+    const size_t n_qkv = (size_t)H * st->nqkv, n_wo = (size_t)st->qw * H, n_13 = (size_t)H * 2 * st->F_p,
+                 n_w2 = (size_t)st->F_p * H;
     HX_HIP(hipMalloc(&ly.wqkv, n_qkv * es));
     HX_HIP(hipMalloc(&ly.wo, n_wo * es));
     HX_HIP(hipMalloc(&ly.w13, n_13 * es));
@@ -772,7 +791,11 @@ hexgen_status_t hexgen_stage_load_layer(hexgen_stage_t *st, int layer, const voi
         return static_cast<const char *>(base) + (row * ld + col) * es;
     };
     if (st->dtype == HEXGEN_F32) {
-        // plain layouts: wqkv [H][q | k | v], w13 [H][w1 | w3]; row shards are contiguous
+        // plain layouts: wqkv [H][q | k | v], w13 [H][w1 | w3]; row shards are contiguous; the padding of F is zero
+        if (st->F_p != st->F_l) {
+            HX_HIP(hipMemset(ly.w13, 0, n_13 * es));
+            HX_HIP(hipMemset(ly.w2, 0, n_w2 * es));
+        }
         char *qkv = static_cast<char *>(ly.wqkv);
         HX_HIP(hipMemcpy2D(qkv, cbytes(st->nqkv), src_at(wq, 0, q0, qcols), cbytes(qcols), cbytes(st->qw), H,
                            hipMemcpyDefault));
@@ -781,12 +804,13 @@ hexgen_status_t hexgen_stage_load_layer(hexgen_stage_t *st, int layer, const voi
         HX_HIP(hipMemcpy2D(qkv + cbytes(st->qw + kw), cbytes(st->nqkv), src_at(wv, 0, k0, kcols), cbytes(kcols),
                            cbytes(kw), H, hipMemcpyDefault));
         char *w13 = static_cast<char *>(ly.w13);
-        HX_HIP(hipMemcpy2D(w13, cbytes(2 * st->F_l), src_at(w1, 0, f0, st->F), cbytes(st->F), cbytes(st->F_l), H,
+        HX_HIP(hipMemcpy2D(w13, cbytes(2 * st->F_p), src_at(w1, 0, f0, st->F), cbytes(st->F), cbytes(st->F_l), H,
                            hipMemcpyDefault));
-        HX_HIP(hipMemcpy2D(w13 + cbytes(st->F_l), cbytes(2 * st->F_l), src_at(w3, 0, f0, st->F), cbytes(st->F),
+        HX_HIP(hipMemcpy2D(w13 + cbytes(st->F_p), cbytes(2 * st->F_p), src_at(w3, 0, f0, st->F), cbytes(st->F),
                            cbytes(st->F_l), H, hipMemcpyDefault));
         HX_HIP(hipMemcpy(ly.wo, src_at(wo, q0, 0, H), n_wo * es, hipMemcpyDefault));
-        HX_HIP(hipMemcpy(ly.w2, src_at(w2, f0, 0, H), n_w2 * es, hipMemcpyDefault));
+        HX_HIP(hipMemcpy(ly.w2, src_at(w2, f0, 0, H), (size_t)st->F_l * H * es, hipMemcpyDefault));
+        HX_HIP(hipDeviceSynchronize());
     } else {
         // stage each shard in a dense device buffer, then repack it into MFMA fragment order
         const size_t tmp_elems = std::max(std::max((size_t)H * st->qw, (size_t)H * st->F_l), n_wo);
@@ -820,14 +844,14 @@ hexgen_status_t hexgen_stage_load_layer(hexgen_stage_t *st, int layer, const voi
         if (rc != HEXGEN_OK) { (void)hipGetLastError(); free_layer(ly); return rc; }
     }
     ly.loaded = true;
-    st->weight_bytes += (int64_t)es * (int64_t)(n_qkv + n_wo + n_13 + n_w2);
+    st->weight_bytes += (int64_t)es * ((int64_t)H * st->nqkv + (int64_t)st->qw * H + 3LL * H * st->F_l);
     return HEXGEN_OK;
 }
 
 // ---- KV cache ------------------------------------------------------------------------------------
 hexgen_status_t hexgen_kv_cache_create(hexgen_stage_t *st, int max_batch, int max_seq, hexgen_kv_cache_t **out) {
     if (!st || !out || max_batch <= 0 || max_seq <= 0) return HEXGEN_ERR_INVALID_ARG;
-    if (st->dtype == HEXGEN_F32 && max_seq > 8192) return HEXGEN_ERR_CAPACITY;   // fp32 attention keeps scores in LDS
+    if (st->dtype == HEXGEN_F32 && max_seq > 8192) return HEXGEN_ERR_CAPACITY;
     hexgen_kv_cache *kv = new (std::nothrow) hexgen_kv_cache();
     if (!kv) return HEXGEN_ERR_OOM;
     kv->st = st;
@@ -996,7 +1020,7 @@ hexgen_status_t hexgen_stage_prefill(hexgen_stage_t *st, hexgen_kv_cache_t *kv, 
     HX_TRY(setup_rows(st, kv, seq_lens, batch, false, s, &r));      // a prefill always takes the GEMM path
     st->prof.mark(PROF_CALL, s);
     if (is_h16(st->dtype)) HX_TRY(forward_h16(st, kv, r, hidden_in, out_partial, out_resid, s));
-    else HX_TRY(forward_f32(st, kv, r, hidden_in, out_partial, out_resid, s));
+    else HX_TRY(forward_f32(st, kv, r, hidden_in, out_partial, out_resid, nullptr, s));
     st->prof.mark(PROF_CALL, s);
     for (int i = 0; i < batch; ++i) kv->lens[i] = seq_lens[i];
     kv->batch = batch;
@@ -1020,9 +1044,9 @@ hexgen_status_t hexgen_stage_decode(hexgen_stage_t *st, hexgen_kv_cache_t *kv, i
     HX_TRY(setup_rows(st, kv, nullptr, kv->batch, true, s, &r));
     st->prof.mark(PROF_CALL, s);
     if (is_h16(st->dtype)) HX_TRY(forward_h16(st, kv, r, hidden_in, out_partial, out_resid, s));
-    else HX_TRY(forward_f32(st, kv, r, hidden_in, out_partial, out_resid, s));
+    else HX_TRY(forward_f32(st, kv, r, hidden_in, out_partial, out_resid, r.decode ? kv->d_lens : nullptr, s));
     if (r.decode && is_h16(st->dtype)) st->last_decode_rows = r.T;
-    if (!r.decode || !is_h16(st->dtype)) launch_advance_lens(kv->d_lens, kv->batch, s);   // else: the prologue did
+    if (!r.decode) launch_advance_lens(kv->d_lens, kv->batch, s);   // else: the prologue (fp32: the last projection) did
     st->prof.mark(PROF_CALL, s);
     for (int i = 0; i < kv->batch; ++i) kv->lens[i] += 1;
     kv->steps += 1;
@@ -1095,8 +1119,11 @@ hexgen_status_t hexgen_stage_run_sublayer(hexgen_stage_t *st, hexgen_kv_cache_t 
             sublayer_prefill_h16(st, kv, layer, which, r, h, p, s);
         }
     } else {
-        if (which == 0) attn_f32(st, kv, layer, r, h, p, s);
-        else ffn_f32(st, layer, r, h, p, s);
+        const Layer &ly = st->layers[layer];
+        if (which == 0) attn_f32(st, kv, layer, r, h, s);
+        else ffn_f32(st, layer, r, h, s);
+        if (which == 0) proj_f32(st, F32_PLAIN, f32_proj(st, st->ws.o32, nullptr, ly.wo, r.T, st->qw, st->H, st->H, p), s);
+        else proj_f32(st, F32_PLAIN, f32_proj(st, st->ws.u32, nullptr, ly.w2, r.T, st->F_p, st->H, st->H, p), s);
     }
     return HEXGEN_OK;
 }
@@ -1191,12 +1218,11 @@ struct hexgen_head {
     hexgen_dtype_t dtype = HEXGEN_BF16;
     float eps = 1e-5f;
     bool loaded = false;
-    void *w = nullptr;            // bf16: fragment tiles, k-tile-major [H/32][Vpad/16][64][8]; f32: [H][Vl]
+    void *w = nullptr;            // bf16: fragment tiles, k-tile-major [H/32][Vpad/16][64][8]; f32: [H][Vpad], H padded with zero rows to 32
     float *g = nullptr;           // final norm gain, fp32 [H]
     // workspace for one chunk of up to kDecodeMaxRows rows
     h16_t *xa = nullptr;         // bf16: (x * g) as compact hi/lo operand
     float *ssq = nullptr;         // bf16: sums of squares per 16 columns
-    float *x32 = nullptr, *n32 = nullptr;      // f32: x = a + b, normalised rows
     float *logits = nullptr;      // [rows][Vpad]
     float *scratch = nullptr;     // split partial sums of the batched projection
     size_t scratch_floats = 0;
@@ -1204,7 +1230,7 @@ struct hexgen_head {
 
 namespace {
 void free_head(hexgen_head *hd) {
-    void *ptrs[] = {hd->w, hd->g, hd->xa, hd->ssq, hd->x32, hd->n32, hd->logits, hd->scratch};
+    void *ptrs[] = {hd->w, hd->g, hd->xa, hd->ssq, hd->logits, hd->scratch};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -1232,9 +1258,6 @@ hexgen_status_t hexgen_head_create(int hidden, int vocab, int tp_degree, int tp_
         if (rc == HEXGEN_OK) rc = dmalloc(&hd->ssq, (size_t)(hidden / 16) * DEC_SSQ_STRIDE);
         hd->scratch_floats = rows * ((size_t)512 * 128 + 2 * (size_t)hd->Vpad);
         if (rc == HEXGEN_OK) rc = dmalloc(&hd->scratch, hd->scratch_floats);
-    } else if (rc == HEXGEN_OK) {
-        rc = dmalloc(&hd->x32, rows * hidden);
-        if (rc == HEXGEN_OK) rc = dmalloc(&hd->n32, rows * hidden);
     }
     if (rc != HEXGEN_OK) { free_head(hd); delete hd; (void)hipGetLastError(); return rc == HEXGEN_ERR_DEVICE ? HEXGEN_ERR_OOM : rc; }
     *out = hd;
@@ -1257,9 +1280,12 @@ hexgen_status_t hexgen_head_load(hexgen_head_t *hd, const void *g_final, const v
     hd->loaded = false;
     if (hd->dtype == HEXGEN_F32) {
         HX_HIP(hipMemcpy(hd->g, g_final, sizeof(float) * H, hipMemcpyDefault));
-        HX_HIP(hipMalloc(&hd->w, (size_t)H * hd->Vl * es));
-        HX_HIP(hipMemcpy2D(hd->w, (size_t)hd->Vl * es, static_cast<const char *>(w_lm) + (size_t)c0 * es, (size_t)hd->V * es,
+        const size_t bytes = (size_t)round_up(H, 32) * hd->Vpad * es;
+        HX_HIP(hipMalloc(&hd->w, bytes));
+        HX_HIP(hipMemset(hd->w, 0, bytes));
+        HX_HIP(hipMemcpy2D(hd->w, (size_t)hd->Vpad * es, static_cast<const char *>(w_lm) + (size_t)c0 * es, (size_t)hd->V * es,
                            (size_t)hd->Vl * es, H, hipMemcpyDefault));
+        HX_HIP(hipDeviceSynchronize());
     } else {
         // gain -> fp32; the rank's columns -> a dense zero-padded device matrix -> MFMA fragment tiles
         h16_t *tmp = nullptr;
@@ -1293,7 +1319,6 @@ hexgen_status_t hexgen_head_greedy(hexgen_head_t *hd, const void *hidden_a, cons
         const int n = std::min(kDecodeMaxRows, n_rows - r0);
         const char *a = static_cast<const char *>(hidden_a) + (size_t)r0 * H * es;
         const char *b = hidden_b ? static_cast<const char *>(hidden_b) + (size_t)r0 * H * es : nullptr;
-        int64_t ld = hd->Vpad;
         if (is_h16(hd->dtype)) {
             // same kernels as a decode projection: prologue (x = a + b, x * g as hi/lo operand, sums of squares),
             // weight-streaming projection with 1 / rms applied after the contraction, fp32 logits
@@ -1308,13 +1333,18 @@ hexgen_status_t hexgen_head_greedy(hexgen_head_t *hd, const void *hidden_a, cons
             e.raw_out = hd->logits;
             HX_K(hd->dtype, launch_decode_proj, static_cast<const h16_t *>(hd->w), hd->xa, hd->Vpad, H, n, e, hd->scratch, hd->scratch_floats, s);
         } else {
-            HX_HIP(hipMemcpyAsync(hd->x32, a, (size_t)n * H * es, hipMemcpyDeviceToDevice, s));
-            if (b) launch_accumulate_f32(hd->x32, reinterpret_cast<const float *>(b), (int64_t)n * H, s);
-            f32_launch_rmsnorm(hd->x32, hd->g, hd->n32, n, H, hd->eps, s);
-            f32_launch_gemm(hd->n32, static_cast<const float *>(hd->w), hd->logits, n, H, hd->Vl, s);
-            ld = hd->Vl;
+            F32Proj p;
+            std::memset(&p, 0, sizeof(p));
+            p.x = reinterpret_cast<const float *>(a);
+            p.x2 = reinterpret_cast<const float *>(b);
+            p.g = hd->g;
+            p.w = static_cast<const float *>(hd->w);
+            p.T = n; p.K = H; p.Kp = round_up(H, 32); p.N = hd->Vpad; p.cols = hd->Vpad;
+            p.eps = hd->eps;
+            p.out = hd->logits;
+            f32_launch_proj(F32_PLAIN, p, nullptr, nullptr, 0, s);
         }
-        launch_row_argmax(hd->logits, ld, hd->Vl, n, hd->r * hd->Vl, token_out + r0, logit_out ? logit_out + r0 : nullptr, s);
+        launch_row_argmax(hd->logits, hd->Vpad, hd->Vl, n, hd->r * hd->Vl, token_out + r0, logit_out ? logit_out + r0 : nullptr, s);
     }
     HX_HIP(hipGetLastError());
     return HEXGEN_OK;
