@@ -196,7 +196,7 @@ class Bench:
 
 def hbm_roofline(cfg, b, k):
     achieved = k["bytes_per_launch"] / (k["avg_launch_us"] * 1e-6) / 1e9
-    name = ("decode_splitk_kernel<2> (W1/W3 projection, 17..32 rows; its finishing kernel with the SwiGLU epilogue "
+    name = ("decode_splitk_kernel<4> (W1/W3 projection, 17..32 rows; its finishing kernel with the SwiGLU epilogue "
             "follows)" if b > 16 else
             "decode_splitk_kernel<1> (W1/W3 projection, 3..16 rows; finishing kernel follows)" if b > 2 else
             "decode_proj_kernel<1,2,8,4,SWIGLU> (W1/W3 projection + SwiGLU epilogue)")

@@ -33,11 +33,23 @@ typedef __attribute__((__vector_size__(8 * sizeof(hx_elem)))) hx_elem h16x8;
 
 #define HX_WAVE 64
 
-// Decode activations (at most 32 token rows) use a compact token-major layout instead: per token and
-// k-tile one 128-byte line holding the 32 hi values then the 32 lo values of the hi + lo bf16 split.
-// A decode projection then touches one cache line per (token, k-tile) instead of eight.
-__host__ __device__ inline size_t dec_act_offset(int token, int k, int k_tiles, int plane) {
-    return (((size_t)token * k_tiles + (k >> 5)) * 2 + plane) * 32 + (k & 31);
+// Decode activations are hi + lo pairs (split_h16), laid out by the number of rows T of the call:
+//   T <= 2: compact token-major, per token and k-tile one 128-byte line holding the 32 hi values then the 32 lo values; a
+//           projection touches one cache line per (token, k-tile) where a 16-token tile would cost it eight;
+//   T >= 3: fragment tiles per k-tile, each one 1 KB request of an MFMA's second operand: for up to 8 rows ONE tile with
+//           the hi parts as token columns 0 .. 7 and the lo parts as columns 8 .. 15 (the two halves of the result are
+//           added at the end), beyond that a hi and a lo tile per 16 rows.  Columns of rows that do not exist are never
+//           written; what they multiply out to is never stored.
+// Returns the element offset of (token, k) in plane 0 (hi) or 1 (lo); k .. k + 3 are contiguous for k % 4 == 0.
+__host__ __device__ inline int dec_act_tiles(int T) { return T <= 8 ? 1 : 2 * ((T + 15) >> 4); }
+__host__ __device__ inline size_t dec_act_elems(int T, int K) {
+    return T <= 2 ? (size_t)2 * T * K : (size_t)dec_act_tiles(T) * 16 * K;
+}
+__host__ __device__ inline size_t dec_act_offset(int token, int k, int k_tiles, int plane, int T) {
+    if (T <= 2) return (((size_t)token * k_tiles + (k >> 5)) * 2 + plane) * 32 + (k & 31);
+    const int g = (k & 31) >> 3;
+    const int tile = T <= 8 ? 0 : 2 * (token >> 4) + plane, col = T <= 8 ? token + 8 * plane : token & 15;
+    return (((size_t)(k >> 5) * dec_act_tiles(T) + tile) * 64 + col + 16 * g) * 8 + (k & 7);
 }
 
 // Prefill keeps its fp32 residual stream in the order the 32x32 MFMA result leaves the registers: blocks of

@@ -45,11 +45,12 @@ void launch_mfma_probe(int variant, float *sink, int iters, int blocks, hipStrea
 
 // ---- decode projections with fused epilogues (kernels_bf16_decode.hip) ---------------------------
 enum { DEC_RAW = 0, DEC_QKV = 1, DEC_RESID = 2, DEC_SWIGLU = 3 };
-#define DEC_SSQ_STRIDE 32      // tokens per unit row of the sum-of-squares scratch
+#define DEC_SCRATCH_RSTD 64    // floats at the end of the split projections' scratch: the rows' 1 / rms
 struct DecodeEpi {
     int mode;                  // DEC_*
-    // RMSNorm statistics of the rows feeding this projection: sums of squares per (16-column unit,
-    // token); NULL when the input is not a normalised residual stream (W_O, W2)
+    // RMSNorm statistics of the rows feeding this projection: sums of squares per token and 16-column unit,
+    // [token][units] (a wave adds a token's up from contiguous loads); NULL when the input is not a normalised
+    // residual stream (W_O, W2)
     const float *ssq_in;
     int ssq_units, norm_dim;
     float eps;
@@ -63,12 +64,12 @@ struct DecodeEpi {
     // RESID
     float *h;                  // residual stream [T][N] fp32, updated in place
     const float *g_next;       // gain of the next RMSNorm
-    h16_t *hg;                // (h * g_next) as compact hi/lo decode operand (dec_act_offset)
-    float *ssq_out;
+    h16_t *hg;                // (h * g_next) as hi/lo decode operand (dec_act_offset)
+    float *ssq_out;            // [token][N / 16]
     int last_layer;            // 1: write out_partial / out_resid (bf16 [T][N]) instead of updating h
     h16_t *out_partial, *out_resid;
     // SWIGLU
-    h16_t *u;                 // compact hi/lo decode operand [T][F_l]
+    h16_t *u;                 // hi/lo decode operand [T][F_l]
     int F_l;
 };
 // What the decode attention needs to finish a QKV projection whose contraction was split over blocks: it adds up the

@@ -272,9 +272,9 @@ __global__ __launch_bounds__(512) void attn_decode_block_kernel(const h16_t *__r
         if (PF) {
             *reinterpret_cast<uint2 *>(o_act + frag_offset(sq, (c * G + hh) * D + dd, k_tiles)) = ph;
         } else {
-            const size_t off = dec_act_offset(sq, (c * G + hh) * D + dd, k_tiles, 0);
-            *reinterpret_cast<uint2 *>(o_act + off) = ph;
-            *reinterpret_cast<uint2 *>(o_act + off + 32) = pl;
+            const int T = gridDim.y;
+            *reinterpret_cast<uint2 *>(o_act + dec_act_offset(sq, (c * G + hh) * D + dd, k_tiles, 0, T)) = ph;
+            *reinterpret_cast<uint2 *>(o_act + dec_act_offset(sq, (c * G + hh) * D + dd, k_tiles, 1, T)) = pl;
         }
     }
 }
@@ -422,9 +422,8 @@ __global__ __launch_bounds__(512) void attn_decode_split_kernel(const h16_t *__r
             uint2 ph, pl;
             split_pack2(o[0] * inv, o[1] * inv, ph.x, pl.x);
             split_pack2(o[2] * inv, o[3] * inv, ph.y, pl.y);
-            const size_t off = dec_act_offset(sq, (c * G + hh) * D + dd, (hq_l * D) >> 5, 0);
-            *reinterpret_cast<uint2 *>(o_act + off) = ph;
-            *reinterpret_cast<uint2 *>(o_act + off + 32) = pl;
+            *reinterpret_cast<uint2 *>(o_act + dec_act_offset(sq, (c * G + hh) * D + dd, (hq_l * D) >> 5, 0, gridDim.z)) = ph;
+            *reinterpret_cast<uint2 *>(o_act + dec_act_offset(sq, (c * G + hh) * D + dd, (hq_l * D) >> 5, 1, gridDim.z)) = pl;
             continue;
         }
         float *po = part_o + e * D + dd;
@@ -462,9 +461,8 @@ __global__ __launch_bounds__(512) void attn_decode_split_kernel(const h16_t *__r
         uint2 ph, pl;
         split_pack2(o[0] * inv, o[1] * inv, ph.x, pl.x);
         split_pack2(o[2] * inv, o[3] * inv, ph.y, pl.y);
-        const size_t off = dec_act_offset(sq, (c * G + hh) * D + dd, (hq_l * D) >> 5, 0);
-        *reinterpret_cast<uint2 *>(o_act + off) = ph;
-        *reinterpret_cast<uint2 *>(o_act + off + 32) = pl;
+        *reinterpret_cast<uint2 *>(o_act + dec_act_offset(sq, (c * G + hh) * D + dd, (hq_l * D) >> 5, 0, gridDim.z)) = ph;
+        *reinterpret_cast<uint2 *>(o_act + dec_act_offset(sq, (c * G + hh) * D + dd, (hq_l * D) >> 5, 1, gridDim.z)) = pl;
     }
 }
 

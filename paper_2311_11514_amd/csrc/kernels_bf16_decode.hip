@@ -1,8 +1,8 @@
-// Decode projections (T <= 32 token rows): weight-streaming skinny GEMMs on the matrix cores with the
-// whole sub-layer glue fused into their tails.  Two forms: decode_proj_kernel (one or two rows, small or short
-// matrices: one kernel, complete dot products per block, no scratch buffers, no atomics) and, further down,
-// decode_splitk_kernel + decode_finish_kernel (3 to 32 rows: operand shared through LDS, contraction split over
-// blocks); launch_decode_proj chooses.
+// Decode projections (up to 64 token rows): weight-streaming skinny GEMMs on the matrix cores with the
+// whole sub-layer glue fused into their tails.  Two forms: decode_proj_kernel (one or two rows, and up to 32 where the
+// operand is small: one kernel, complete dot products per block, no scratch buffers, no atomics) and, further down,
+// decode_splitk_kernel + decode_finish_kernel (operand shared through LDS, contraction split over blocks);
+// decode_single_kernel chooses.
 //
 // Main loop of decode_proj_kernel.  Each wave streams 1 KB weight tiles with one 128-bit load per lane (fully coalesced,
 // non-temporal) and feeds them to v_mfma_f32_16x16x32_bf16 against a 16-token activation tile: 16 MFMA
@@ -14,8 +14,7 @@
 // consecutive features):
 //   QKV    : x rstd of the input rows, RoPE, q -> hi/lo rows, k / v -> KV cache.  The QKV weight tiles are
 //            packed so that a tile holds 8 rotary pairs (features i and i + d/2), which lie 32 lanes apart.
-//   RESID  : h += partial; (h * gain of the next norm) -> hi/lo operand of the next projection (compact
-//            token-major layout, see dec_act_offset);
+//   RESID  : h += partial; (h * gain of the next norm) -> hi/lo operand of the next projection (dec_act_offset);
 //            per-unit sum of squares of the new h, from which the next kernel derives rstd
 //   SWIGLU : x rstd, silu(gate) * up -> hi/lo operand of the W2 projection (gate / up tiles interleaved)
 //   RAW    : x rstd (if the input is a normalised stream), plain fp32 partial (validation surface)
@@ -35,7 +34,7 @@ __device__ inline void rstd_row(const DecodeEpi &e, int t, int lane, float *s_rs
     float r = 1.0f;
     if (e.ssq_in) {
         float ss = 0.f;
-        for (int i = lane; i < e.ssq_units; i += 64) ss += e.ssq_in[i * DEC_SSQ_STRIDE + t];
+        for (int i = lane; i < e.ssq_units; i += 64) ss += e.ssq_in[(size_t)t * e.ssq_units + i];
         ss = wave_sum(ss);
         r = 1.0f / sqrtf(ss / (float)e.norm_dim + e.eps);
     }
@@ -51,13 +50,13 @@ __device__ inline void load_rstd(const DecodeEpi &e, int T, int wave, int lane, 
 constexpr int RSTD_REGS = 8;
 __device__ inline void rstd_request(const DecodeEpi &e, int t, int lane, float (&sv)[RSTD_REGS]) {
 #pragma unroll
-    for (int j = 0; j < RSTD_REGS; ++j) sv[j] = e.ssq_in[min(lane + 64 * j, e.ssq_units - 1) * DEC_SSQ_STRIDE + t];
+    for (int j = 0; j < RSTD_REGS; ++j) sv[j] = e.ssq_in[(size_t)t * e.ssq_units + min(lane + 64 * j, e.ssq_units - 1)];
 }
 __device__ inline void rstd_finish(const DecodeEpi &e, int t, int lane, const float (&sv)[RSTD_REGS], float *s_rstd) {
     float ss = 0.f;
 #pragma unroll
     for (int j = 0; j < RSTD_REGS; ++j) ss += lane + 64 * j < e.ssq_units ? sv[j] : 0.f;      // lane's units ascending
-    for (int i = lane + 64 * RSTD_REGS; i < e.ssq_units; i += 64) ss += e.ssq_in[i * DEC_SSQ_STRIDE + t];
+    for (int i = lane + 64 * RSTD_REGS; i < e.ssq_units; i += 64) ss += e.ssq_in[(size_t)t * e.ssq_units + i];
     ss = wave_sum(ss);
     if (lane == 0) s_rstd[t] = 1.0f / sqrtf(ss / (float)e.norm_dim + e.eps);
 }
@@ -69,14 +68,13 @@ __device__ inline void store_split4(const float x[4], h16_t *hi, h16_t *lo, size
     *reinterpret_cast<uint2 *>(hi + off) = o;
     *reinterpret_cast<uint2 *>(lo + off) = ol;
 }
-// 4 consecutive features k..k+3 of one token into a compact decode operand (hi and lo planes)
-__device__ inline void store_act4(const float x[4], h16_t *xa, int token, int k, int k_tiles) {
-    const size_t off = dec_act_offset(token, k, k_tiles, 0);
+// 4 consecutive features k..k+3 of one of T tokens into a decode operand (hi and lo parts)
+__device__ inline void store_act4(const float x[4], h16_t *xa, int token, int k, int k_tiles, int T) {
     uint2 o, ol;
     split_pack2(x[0], x[1], o.x, ol.x);
     split_pack2(x[2], x[3], o.y, ol.y);
-    *reinterpret_cast<uint2 *>(xa + off) = o;
-    *reinterpret_cast<uint2 *>(xa + off + 32) = ol;
+    *reinterpret_cast<uint2 *>(xa + dec_act_offset(token, k, k_tiles, 0, T)) = o;
+    *reinterpret_cast<uint2 *>(xa + dec_act_offset(token, k, k_tiles, 1, T)) = ol;
 }
 
 // What the register epilogue reads from memory, requested long before it is used (the finishing wave asks for it at
@@ -149,14 +147,14 @@ __device__ inline void decode_epilogue(const floatx4 (&v)[UT], int unit, int b, 
                 *reinterpret_cast<floatx4 *>(e.h + (size_t)token * N + n0) = hn;
                 const floatx4 g4 = pre.b;
                 const float x[4] = {hn[0] * g4[0], hn[1] * g4[1], hn[2] * g4[2], hn[3] * g4[3]};
-                store_act4(x, e.hg, token, n0, N >> 5);
+                store_act4(x, e.hg, token, n0, N >> 5, T);
                 ss = hn[0] * hn[0] + hn[1] * hn[1] + hn[2] * hn[2] + hn[3] * hn[3];
             }
         }
         if (!e.last_layer) {
             ss += __shfl_xor(ss, 16, 64);
             ss += __shfl_xor(ss, 32, 64);
-            if (g == 0 && valid) e.ssq_out[unit * DEC_SSQ_STRIDE + token] = ss;
+            if (g == 0 && valid) e.ssq_out[(size_t)token * (N >> 4) + unit] = ss;
         }
     } else if (MODE == DEC_SWIGLU) {
         // unit = one gate tile (v[0]) and the matching up tile (v[1]): 16 features of u
@@ -168,7 +166,7 @@ __device__ inline void decode_epilogue(const floatx4 (&v)[UT], int unit, int b, 
                 const float aa = v[0][j] * r;
                 uu[j] = aa / (1.0f + __expf(-aa)) * (v[UT - 1][j] * r);
             }
-            store_act4(uu, e.u, token, f0, e.F_l >> 5);
+            store_act4(uu, e.u, token, f0, e.F_l >> 5, T);
         }
     } else {   // DEC_QKV
         const int d = e.kg.d, half = d >> 1, tiles_per_head = d >> 4;
@@ -213,12 +211,16 @@ __device__ inline void decode_epilogue(const floatx4 (&v)[UT], int unit, int b, 
 
 constexpr int kXldsMaxBytes = 64 * 1024;      // activation operand staged in LDS up to this size
 
-// XLDS: the whole activation operand (T <= 2 rows) is staged once per block in LDS, so the main loop
+// NP = 0: one or two rows, compact operand.  XLDS: the whole operand is staged once per block in LDS, so the main loop
 // issues nothing but weight loads; otherwise each lane fetches its 16-byte pieces per k-tile (L2 hits).
-template <int NB, int UT, int WAVES, int UNROLL, int MODE, bool XLDS, int XR>
+// NP = 1, 2, 4: 3 to 8, 16, 32 rows, NP operand tiles per k-tile (dec_act_offset), each one contiguous 1 KB request.
+template <int NP, int UT, int WAVES, int UNROLL, int MODE, bool XLDS, int XR>
 __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__restrict__ Wp,
                                                                 const h16_t *__restrict__ Xa, int N, int k_tiles,
                                                                 int T, DecodeEpi e) {
+    constexpr int NB = NP <= 2 ? 1 : NP / 2;       // 16-token result tiles
+    constexpr int NX = NP == 0 ? 2 : NP;           // operand pieces per k-tile
+    static_assert(!XLDS || NP == 0, "only the compact operand is staged");
     __shared__ floatx4 red[WAVES][UT * NB][64];
     __shared__ float s_rstd[32];
     extern __shared__ h16x8 xs[];          // XLDS: copy of Xa, [token][k_tile][plane][lane group]
@@ -236,15 +238,11 @@ __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__
     for (int u = 0; u < UT; ++u)
         wp[u] = reinterpret_cast<const h16x8 *>(Wp) + (size_t)(unit * UT + u) * 64 + lane;
     const size_t kstride = (size_t)(N >> 4) * 64;          // k-tile-major weights: one k-tile of all features
-    // operand B of lane (token j, group g) for k-tile kt: hi at x[b][kt * 8], lo at x[b][kt * 8 + 4]
-    const h16x8 *xg[NB];
-    bool xv[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int token = (lane & 15) + 16 * b;
-        xv[b] = token < T;
-        xg[b] = (XLDS ? xs : reinterpret_cast<const h16x8 *>(Xa)) + (size_t)(xv[b] ? token : 0) * k_tiles * 8 + (lane >> 4);
-    }
+    // operand B.  Compact: lane (token j, group g) takes hi at xg[kt * 8] and lo at xg[kt * 8 + 4]; tiles: slot `lane` of tile
+    // kt * NP + piece
+    const bool xv = NP > 0 || (lane & 15) < T;
+    const h16x8 *xg = NP > 0 ? reinterpret_cast<const h16x8 *>(Xa) + lane
+                             : (XLDS ? xs : reinterpret_cast<const h16x8 *>(Xa)) + (size_t)(xv ? lane & 15 : 0) * k_tiles * 8 + (lane >> 4);
     const h16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
     // Wave w owns k-tiles w, w + WAVES, ...; it holds a ring of UNROLL of them per feature tile in registers.  The
     // first ring round is requested before anything else, so the weights are already on their way while the block
@@ -264,20 +262,21 @@ __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__
         for (int j = 0; j < XR; ++j)
             xr[j] = reinterpret_cast<const h16x8 *>(Xa)[min((int)threadIdx.x + j * WAVES * 64, n16 - 1)];
     }
-    float sv[RSTD_REGS];
-    const bool rstd_wave = MODE != DEC_RESID && wave < T && e.ssq_in != nullptr;       // wave t derives rstd of row t
+    float sv[RSTD_REGS], sv2[NP >= 2 ? RSTD_REGS : 1];
+    const bool rstd_wave = MODE != DEC_RESID && wave < T && e.ssq_in != nullptr;       // wave t derives rstd of row t (and t + WAVES)
+    const bool rstd_wave2 = NP >= 2 && rstd_wave && wave + WAVES < T;
     if (rstd_wave) rstd_request(e, wave, lane, sv);
+    if constexpr (NP >= 2) {
+        if (rstd_wave2) rstd_request(e, wave + WAVES, lane, sv2);
+    }
     // ring slot = the weight tiles of one k-tile and, when the operand is not staged in LDS, its hi / lo pieces too
     // (requested together, so that no wait for an operand piece ever drains the weight requests behind it)
-    h16x8 a[UNROLL][UT], xq[XLDS ? 1 : UNROLL][NB][2];
+    h16x8 a[UNROLL][UT], xq[XLDS ? 1 : UNROLL][NX];
     auto request = [&](int i, int kt) {
         if (!XLDS) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                // unconditional (see above): lanes past the last row re-read row 0 and feed output columns nobody stores
-                xq[i][b][0] = xg[b][kt * 8];
-                xq[i][b][1] = xg[b][kt * 8 + 4];
-            }
+            // unconditional (see above): lanes past the last row re-read row 0 and feed output columns nobody stores
+            for (int q = 0; q < NX; ++q) xq[i][q] = NP > 0 ? xg[((size_t)kt * NX + q) * 64] : xg[kt * 8 + 4 * q];
         }
 #pragma unroll
         for (int u = 0; u < UT; ++u) a[i][u] = __builtin_nontemporal_load(wp[u] + (size_t)kt * kstride);
@@ -293,28 +292,25 @@ __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__
         }
     }
     if (rstd_wave) rstd_finish(e, wave, lane, sv, s_rstd);
+    if constexpr (NP >= 2) {
+        if (rstd_wave2) rstd_finish(e, wave + WAVES, lane, sv2, s_rstd);
+    }
     if (MODE != DEC_RESID)
-        for (int t = rstd_wave ? wave + WAVES : wave; t < T; t += WAVES) rstd_row(e, t, lane, s_rstd);
+        for (int t = wave + (rstd_wave2 ? 2 * WAVES : rstd_wave ? WAVES : 0); t < T; t += WAVES) rstd_row(e, t, lane, s_rstd);
     if (XLDS) __syncthreads();       // (s_rstd is read behind the barrier of the reduction below)
 
-    // the k-tile held by ring slot i against the operand
+    // the k-tile held by ring slot i against the operand: lo, then hi (NP = 1: both in one tile)
     auto contract = [&](int i, int kt) {
+        h16x8 x[NX];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            h16x8 x, y;
-            if (XLDS) {
-                x = xv[b] ? xg[b][kt * 8] : zero;
-                y = xv[b] ? xg[b][kt * 8 + 4] : zero;
-            } else {
-                x = xq[i][b][0];
-                y = xq[i][b][1];
-            }
+        for (int q = 0; q < NX; ++q) x[q] = XLDS ? (xv ? xg[kt * 8 + 4 * q] : zero) : xq[i][q];
 #pragma unroll
-            for (int u = 0; u < UT; ++u) {
-                acc[u][b] = hx_mfma16(a[i][u], y, acc[u][b]);
-                acc[u][b] = hx_mfma16(a[i][u], x, acc[u][b]);
+        for (int u = 0; u < UT; ++u)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                if (NX > 1) acc[u][b] = hx_mfma16(a[i][u], x[NX > 1 ? 2 * b + 1 : 0], acc[u][b]);
+                acc[u][b] = hx_mfma16(a[i][u], x[2 * b], acc[u][b]);
             }
-        }
     };
     // steady state: slot i is consumed and at once refilled with the tile one ring round ahead, so UNROLL - 1
     // requests per feature tile stay in flight all the time
@@ -365,69 +361,68 @@ __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__
         v[u] = red[0][u * NB + b][lane];
 #pragma unroll
         for (int w = 1; w < WAVES; ++w) v[u] += red[w][u * NB + b][lane];
+        if (NP == 1) {          // token columns 8 .. 15 hold the lo parts of tokens 0 .. 7
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[u][r] += __shfl_xor(v[u][r], 8, 64);
+        }
     }
     decode_epilogue<MODE, UT>(v, unit, b, lane, N, T, e, s_rstd, pre);
 }
 
 // -------------------------------------------------------------------------------------------------
-// Batched decode (3 <= T <= 32 rows).  With more than a couple of rows the activation operand outweighs the
-// weights a block streams (32 rows of hi + lo pairs are 4 KB per k-tile against 1 KB of weights per 16 features),
-// and fetching it per wave from L2 in 64-byte pieces leaves the kernel at a quarter of the HBM rate.  Here the
+// Batched decode (3 <= T <= 64 rows).  With more than a couple of rows the activation operand outweighs the
+// weights a block streams (32 rows of hi + lo pairs are 4 KB per k-tile against 1 KB of weights per 16 features).  Here the
 // eight waves of a block own eight neighbouring feature tiles and walk the SAME k-tiles, so the block stages each
-// 8-k-tile chunk of the operand once in LDS (global -> registers -> LDS, double-buffered) and all waves read it
-// from there; a k-tile's weights for the block are one contiguous 8 KB run.  To still fill the chip the
+// chunk of k-tiles of the operand once in LDS (global -> registers -> LDS, double-buffered, whole 1 KB fragment tiles) and all
+// waves read it from there; a k-tile's weights for the block are one contiguous 8 KB run.  To still fill the chip the
 // contraction is split over blockIdx.y; the fp32 partial sums go to a scratch buffer [split][token][feature] and
 // decode_finish_kernel adds them in split order (bit-reproducible) and runs the same register epilogue as the
-// single-kernel path.
+// single-kernel path.  Bound by HBM up to 32 rows (W1/W3 of the full-width 70B layer: 939 MB in 157 us), beyond by the LDS
+// reads: a wave reads NP KB for every KB of weights.  Chunks of 4 k-tiles instead of 8 beyond 32 rows keep two blocks on a
+// CU, one covering the other's barriers: full-width layer at 33 / 48 rows 377 / 386 -> 353 / 365 us.
 // -------------------------------------------------------------------------------------------------
-constexpr int SK_CH = 8;                       // k-tiles per chunk: 1 KB of one token's compact operand
-constexpr int SK_TOK_STRIDE = 1024 + 16;       // LDS bytes per token and chunk; the pad spreads tokens over the banks
+// k-tiles per chunk: 16 .. 64 KB of operand in the two LDS buffers, so that two blocks fit a CU at any number of rows
+constexpr int sk_chunk(int np) { return np <= 4 ? 8 : 4; }
 
-template <int NB>
+// NP: operand tiles per k-tile (dec_act_tiles), 1 .. 8 for 3 .. 64 rows
+template <int NP>
 __global__ __launch_bounds__(512) void decode_splitk_kernel(const h16_t *__restrict__ Wp, const h16_t *__restrict__ Xa,
                                                            int n_tiles, int k_tiles, int T,
                                                            float *__restrict__ part, const float *__restrict__ ssq_in,
                                                            int ssq_units, int norm_dim, float eps,
                                                            float *__restrict__ rstd_out) {
-    constexpr int TOK = 16 * NB, LPW = TOK / 8;        // token rows staged per chunk; rows copied per wave
-    constexpr int BUF = TOK * SK_TOK_STRIDE;
-    extern __shared__ unsigned char sk_lds[];          // [2][TOK][SK_TOK_STRIDE]
+    constexpr int NB = NP == 1 ? 1 : NP / 2, CH = sk_chunk(NP);
+    constexpr int XT = CH * NP / 8;                    // operand tiles of a chunk each wave copies
+    extern __shared__ h16x8 sk_lds[];                  // [2][CH][NP][64]
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
     const int tile = blockIdx.x * 8 + wave;
     const bool tile_ok = tile < n_tiles;
     // the chunks of the contraction are dealt out evenly over the splits (blockIdx.y)
-    const int chunks = (k_tiles + SK_CH - 1) / SK_CH;
-    const int kt0 = (int)((long)blockIdx.y * chunks / gridDim.y) * SK_CH;
-    const int kt1 = min(k_tiles, (int)((long)(blockIdx.y + 1) * chunks / gridDim.y) * SK_CH);
-    const int n_chunks = (kt1 - kt0 + SK_CH - 1) / SK_CH;
+    const int chunks = (k_tiles + CH - 1) / CH;
+    const int kt0 = (int)((long)blockIdx.y * chunks / gridDim.y) * CH;
+    const int kt1 = min(k_tiles, (int)((long)(blockIdx.y + 1) * chunks / gridDim.y) * CH);
+    const int n_chunks = (kt1 - kt0 + CH - 1) / CH;
     const int N = n_tiles * 16;
 
-    // chunk c of the operand rows this wave copies: lane l carries bytes 16 l .. 16 l + 15 of the row's 1 KB
-    const h16x8 *xsrc[LPW];
+    // a chunk's operand tiles are contiguous; this wave copies tiles wave, wave + 8, ... (past the end: the last one, unused)
+    auto load_x = [&](int c, h16x8(&x)[XT]) {
 #pragma unroll
-    for (int i = 0; i < LPW; ++i)
-        xsrc[i] = reinterpret_cast<const h16x8 *>(Xa) + (size_t)min(wave + 8 * i, T - 1) * k_tiles * 8 + lane;
-    auto load_x = [&](int c, h16x8(&x)[LPW]) {
-        const int kc = kt0 + c * SK_CH;
-        const bool ok = c < n_chunks && kc + (lane >> 3) < kt1;         // 8 lanes per k-tile line
-#pragma unroll
-        for (int i = 0; i < LPW; ++i)
-            if (ok) x[i] = xsrc[i][(size_t)kc * 8];
+        for (int i = 0; i < XT; ++i)
+            x[i] = reinterpret_cast<const h16x8 *>(Xa)[(size_t)min((kt0 + c * CH) * NP + wave + 8 * i, k_tiles * NP - 1) * 64 + lane];
     };
-    auto store_x = [&](int c, const h16x8(&x)[LPW]) {
-        unsigned char *buf = sk_lds + (c & 1) * BUF;
+    auto store_x = [&](int c, const h16x8(&x)[XT]) {
+        h16x8 *buf = sk_lds + ((c & 1) * CH * NP + wave) * 64 + lane;
 #pragma unroll
-        for (int i = 0; i < LPW; ++i)
-            *reinterpret_cast<h16x8 *>(buf + (wave + 8 * i) * SK_TOK_STRIDE + lane * 16) = x[i];
+        for (int i = 0; i < XT; ++i) buf[i * 8 * 64] = x[i];
     };
     // this wave's weight tile for the k-tiles of chunk c
     const h16x8 *wsrc = reinterpret_cast<const h16x8 *>(Wp) + (size_t)min(tile, n_tiles - 1) * 64 + lane;
     const size_t kstride = (size_t)n_tiles * 64;
     const h16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-    auto load_w = [&](int c, h16x8(&w)[SK_CH]) {
-        const int kc = kt0 + c * SK_CH;
+    auto load_w = [&](int c, h16x8(&w)[CH]) {
+        const int kc = kt0 + c * CH;
 #pragma unroll
-        for (int i = 0; i < SK_CH; ++i)
+        for (int i = 0; i < CH; ++i)
             w[i] = (c < n_chunks && kc + i < kt1) ? __builtin_nontemporal_load(wsrc + (size_t)(kc + i) * kstride) : zero;
     };
 
@@ -439,15 +434,14 @@ __global__ __launch_bounds__(512) void decode_splitk_kernel(const h16_t *__restr
     float sv[RSTD_REGS];
     if (rstd_mine && ssq_in != nullptr) {
 #pragma unroll
-        for (int q = 0; q < RSTD_REGS; ++q) sv[q] = ssq_in[min(lane + 64 * q, ssq_units - 1) * DEC_SSQ_STRIDE + rstd_row];
+        for (int q = 0; q < RSTD_REGS; ++q) sv[q] = ssq_in[(size_t)rstd_row * ssq_units + min(lane + 64 * q, ssq_units - 1)];
     }
 
-    floatx4 acc[NB];
+    // the hi and the lo products are summed apart and added at the end: half as many roundings per sum
+    floatx4 acc[NB], acl[NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = floatx4{0.f, 0.f, 0.f, 0.f};
-    h16x8 xr[LPW], wc[SK_CH], wn[SK_CH];
-#pragma unroll
-    for (int i = 0; i < LPW; ++i) xr[i] = zero;
+    for (int b = 0; b < NB; ++b) acc[b] = acl[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+    h16x8 xr[XT], wc[CH], wn[CH];
     load_x(0, xr);
     load_w(0, wc);
     store_x(0, xr);
@@ -460,23 +454,20 @@ __global__ __launch_bounds__(512) void decode_splitk_kernel(const h16_t *__restr
         store_x(c + 1, xr);
         load_x(c + 2, xr);
         load_w(c + 1, wn);
-        const unsigned char *buf = sk_lds + (c & 1) * BUF;
-        const int nk = min(SK_CH, kt1 - (kt0 + c * SK_CH));
+        const h16x8 *buf = sk_lds + (c & 1) * CH * NP * 64 + lane;
+        const int nk = min(CH, kt1 - (kt0 + c * CH));
 #pragma unroll
-        for (int i = 0; i < SK_CH; ++i) {
+        for (int i = 0; i < CH; ++i) {
             if (i < nk) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const unsigned char *row = buf + (j + 16 * b) * SK_TOK_STRIDE + i * 128 + g * 16;
-                    const h16x8 x = *reinterpret_cast<const h16x8 *>(row);
-                    const h16x8 y = *reinterpret_cast<const h16x8 *>(row + 64);
-                    acc[b] = hx_mfma16(wc[i], y, acc[b]);
-                    acc[b] = hx_mfma16(wc[i], x, acc[b]);
+                    if (NP > 1) acl[b] = hx_mfma16(wc[i], buf[(i * NP + 2 * b + 1) * 64], acl[b]);
+                    acc[b] = hx_mfma16(wc[i], buf[(i * NP + 2 * b) * 64], acc[b]);
                 }
             }
         }
 #pragma unroll
-        for (int i = 0; i < SK_CH; ++i) wc[i] = wn[i];
+        for (int i = 0; i < CH; ++i) wc[i] = wn[i];
     }
     if (rstd_mine) {
         float r = 1.0f;
@@ -484,7 +475,7 @@ __global__ __launch_bounds__(512) void decode_splitk_kernel(const h16_t *__restr
             float ss = 0.f;
 #pragma unroll
             for (int q = 0; q < RSTD_REGS; ++q) ss += lane + 64 * q < ssq_units ? sv[q] : 0.f;
-            for (int i = lane + 64 * RSTD_REGS; i < ssq_units; i += 64) ss += ssq_in[i * DEC_SSQ_STRIDE + rstd_row];
+            for (int i = lane + 64 * RSTD_REGS; i < ssq_units; i += 64) ss += ssq_in[(size_t)rstd_row * ssq_units + i];
             ss = wave_sum(ss);
             r = 1.0f / sqrtf(ss / (float)norm_dim + eps);
         }
@@ -495,13 +486,19 @@ __global__ __launch_bounds__(512) void decode_splitk_kernel(const h16_t *__restr
             float r = 1.0f;
             if (ssq_in != nullptr) {
                 float ss = 0.f;
-                for (int i = lane; i < ssq_units; i += 64) ss += ssq_in[i * DEC_SSQ_STRIDE + row];
+                for (int i = lane; i < ssq_units; i += 64) ss += ssq_in[(size_t)row * ssq_units + i];
                 ss = wave_sum(ss);
                 r = 1.0f / sqrtf(ss / (float)norm_dim + eps);
             }
             if (lane == 0) rstd_out[row] = r;
         }
     if (!tile_ok) return;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] += acl[b];
+    if (NP == 1) {          // token columns 8 .. 15 hold the lo parts of tokens 0 .. 7
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[0][r] += __shfl_xor(acc[0][r], 8, 64);
+    }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int token = j + 16 * b;
@@ -538,10 +535,10 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(const float *__restr
 
 namespace {
 
-template <int NB, int UT, int UNR, int MODE, bool XLDS, int XR>
+template <int NP, int UT, int UNR, int MODE, bool XLDS, int XR>
 void launch_one(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, const DecodeEpi &e, hipStream_t s) {
     constexpr int WAVES = 8;
-    auto kern = decode_proj_kernel<NB, UT, WAVES, UNR, MODE, XLDS, XR>;
+    auto kern = decode_proj_kernel<NP, UT, WAVES, UNR, MODE, XLDS, XR>;
     size_t dyn = 0;
     if (XLDS) {
         dyn = (size_t)T * k_tiles * 8 * sizeof(h16x8);
@@ -558,36 +555,46 @@ void launch_one(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, con
 template <int UT, int MODE>
 void launch_mode(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, const DecodeEpi &e, hipStream_t s) {
     const size_t xbytes = (size_t)T * k_tiles * 8 * sizeof(h16x8);
-    // staged operand: XR 16-byte pieces per thread (512 threads), 4 up to 32 KB, 8 up to 64 KB
-    // With one or two rows each wave of the residual projections (W_O, W2) and of W1/W3 fetches its operand pieces
-    // through its request ring instead of the block staging the operand in LDS behind a barrier (measured: W_O
-    // 17.9 -> 16.6 us and W2 44.0 -> 43.4 at one row, W1/W3 81.0 -> 77.9 at two rows and unchanged at one).  The
-    // QKV projection keeps the staged operand: through the ring it loses 3.5 us.
-    if ((MODE == DEC_RESID || MODE == DEC_SWIGLU) && T <= 2) {
-        // (a contraction of at most 32 k-tiles gives a wave 4 of them: a ring of 4 requests nothing it does not use)
-        if constexpr (UT == 1) {
-            if (k_tiles <= 32) { launch_one<1, 1, 4, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s); return; }
-        }
-        launch_one<1, UT, 8 / UT, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);
-        return;
-    }
-    if (T <= 2 && xbytes <= (size_t)kXldsMaxBytes / 2) launch_one<1, UT, 8 / UT, MODE, true, 4>(Wp, Xa, N, k_tiles, T, e, s);
-    else if (T <= 2 && xbytes <= (size_t)kXldsMaxBytes) launch_one<1, UT, 8 / UT, MODE, true, 8>(Wp, Xa, N, k_tiles, T, e, s);
-    else if (T <= 16) launch_one<1, UT, 8 / UT, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);
-    else launch_one<2, UT, 8 / UT, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);
+    // a contraction of at most 32 k-tiles gives a wave 4 of them: a ring of 4 requests nothing it does not use
+    const bool short_k = UT == 1 && MODE == DEC_RESID && k_tiles <= 32;
+#define HX_ONE(NP)                                                                                              \
+    do {                                                                                                        \
+        if (short_k) launch_one<NP, UT, 4, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);                        \
+        else launch_one<NP, UT, 8 / UT, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);                           \
+    } while (0)
+    if (T > 16) HX_ONE(4);
+    else if (T > 8) HX_ONE(2);
+    else if (T > 2) HX_ONE(1);
+    // One or two rows.  With W_O, W2 and W1/W3 each wave fetches its operand pieces through its request ring instead of the
+    // block staging the operand in LDS behind a barrier (measured: W_O 17.9 -> 16.6 us and W2 44.0 -> 43.4 at one row, W1/W3
+    // 81.0 -> 77.9 at two rows and unchanged at one).  The QKV projection keeps the staged operand -- XR 16-byte pieces per
+    // thread (512 threads), 4 up to 32 KB, 8 up to 64 KB: through the ring it loses 3.5 us.
+    else if (MODE == DEC_RESID || MODE == DEC_SWIGLU || xbytes > (size_t)kXldsMaxBytes) HX_ONE(0);
+    else if (xbytes <= (size_t)kXldsMaxBytes / 2) launch_one<0, UT, 8 / UT, MODE, true, 4>(Wp, Xa, N, k_tiles, T, e, s);
+    else launch_one<0, UT, 8 / UT, MODE, true, 8>(Wp, Xa, N, k_tiles, T, e, s);
+#undef HX_ONE
 }
 }  // namespace
 
 namespace {
+template <int NP>
+void launch_splitk_main(dim3 grid, const h16_t *Wp, const h16_t *Xa, int n_tiles, int k_tiles, int T, float *part, const DecodeEpi &e,
+                        float *rstd, hipStream_t s) {
+    const size_t lds = (size_t)2 * sk_chunk(NP) * NP * 64 * sizeof(h16x8);
+    hipLaunchKernelGGL(decode_splitk_kernel<NP>, grid, dim3(512), lds, s, Wp, Xa, n_tiles, k_tiles, T, part, e.ssq_in, e.ssq_units,
+                       e.norm_dim, e.eps, rstd);
+}
+
 template <int MODE, int UT>
 void launch_splitk(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, const DecodeEpi &e, float *scratch,
                    size_t scratch_floats, hipStream_t s, hipEvent_t mid, QkvTail *tail = nullptr) {
-    const int n_tiles = N / 16, groups = (n_tiles + 7) / 8;
-    // Two blocks fit a CU (registers), 512 on the chip.  The number of splits (at most 8, or 16 for a matrix of fewer than 64
-    // feature groups: the finishing kernel walks them one after the other; partials within the scratch) minimises rounds of blocks x chunks per block, the time
-    // of the launch in units of one chunk per block; on a tie the fewer splits (less partial-sum traffic) win.
-    const int chunks = (k_tiles + SK_CH - 1) / SK_CH;
-    const size_t part_floats = scratch_floats - 32;      // the last 32 floats of the scratch carry the rows' rstd
+    const int n_tiles = N / 16, groups = (n_tiles + 7) / 8, np = dec_act_tiles(T);
+    // Two blocks fit a CU (registers, 64 KB of LDS), 512 on the chip.  The number of splits (at most 8, or 16 for a matrix of
+    // fewer than 64 feature groups: the finishing kernel walks them one after the other; partials within the scratch)
+    // minimises rounds of blocks x chunks per block, the time of the launch in units of one chunk per block; on a tie the
+    // fewer splits (less partial-sum traffic) win.
+    const int chunks = (k_tiles + sk_chunk(np) - 1) / sk_chunk(np);
+    const size_t part_floats = scratch_floats - DEC_SCRATCH_RSTD;      // the tail of the scratch carries the rows' rstd
     float *rstd = scratch + part_floats;
     int splits = 1;
     long best = -1;
@@ -597,21 +604,13 @@ void launch_splitk(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, 
         const long cost = (long)((groups * c + 511) / 512) * ((chunks + c - 1) / c) * 16 + c;
         if (best < 0 || cost < best) { best = cost; splits = c; }
     }
-    const int nb = T > 16 ? 2 : 1;
-    const size_t lds = (size_t)2 * 16 * nb * SK_TOK_STRIDE;
     const dim3 grid(groups, splits);
-    if (nb == 2) {
-        static bool raised = false;           // 65 KB: above the default limit
-        if (!raised) {
-            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(decode_splitk_kernel<2>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            raised = true;
-        }
-        hipLaunchKernelGGL(decode_splitk_kernel<2>, grid, dim3(512), lds, s, Wp, Xa, n_tiles, k_tiles, T, scratch, e.ssq_in,
-                           e.ssq_units, e.norm_dim, e.eps, rstd);
-    } else {
-        hipLaunchKernelGGL(decode_splitk_kernel<1>, grid, dim3(512), lds, s, Wp, Xa, n_tiles, k_tiles, T, scratch, e.ssq_in,
-                           e.ssq_units, e.norm_dim, e.eps, rstd);
+    switch (np) {
+        case 1: launch_splitk_main<1>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
+        case 2: launch_splitk_main<2>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
+        case 4: launch_splitk_main<4>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
+        case 6: launch_splitk_main<6>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
+        default: launch_splitk_main<8>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
     }
     if (mid) (void)hipEventRecord(mid, s);
     if (tail != nullptr) {          // the consumer finishes the projection (QKV -> decode attention)
@@ -624,32 +623,37 @@ void launch_splitk(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, 
 }
 }  // namespace
 
+namespace {
+// two feature tiles per block (2 KB of weights per wave and k-tile) stream a few percent faster than one
+bool raw_pairs(int N) { return (N / 16) % 2 == 0 && N / 32 >= 512; }
+
+// One kernel with complete dot products per block, or a contraction split over blocks and a finishing pass?  One or two
+// rows: always one kernel.  More: the single kernel saves the partial sums and the second launch (4 .. 5 us), and pays with
+// the operand, which every block reads for itself from L2 where the split kernel's eight feature tiles share it through LDS:
+// blocks x k-tiles x operand tiles x 1 KB.  Measured (single minus split, us per projection, against those bytes):
+//   W1/W3   8 rows:  58 MB -2.9 (TP8 of the 70B shape), 92 -6.4 (4096-wide layer), 117 -2.2 (TP4), 235 +2.4 (TP2), 470 +9.5
+//          16 rows:  46 -2.9 (2048-wide), 117 -1.3 (TP8), 235 +3.0 (TP4)
+//   W2      8 rows:  23 -4.1 (2048-wide), 59 -2.0 (TP8), 117 0.0 (TP4), 235 +1.7    16 rows: 46 -3.3, 117 -0.9, 185 +1.4, 235 +3.7
+//   W_O     8 rows:  17 -3.5, 33 -2.3, 134 -0.8    16 rows: 34 -2.8, 134 -0.2, 268 +3.8    32 rows: 67 -3.2, 134 -2.7, 268 +2.0
+// The line is 128 MiB.  The QKV projection has no finishing launch to save (the attention sums its partials):
+//           8 rows:  42 -0.9 (TP4), 50 -0.6, 84 +3.5 (TP2)    16 rows: 25 -1.0, 84 +1.5
+// 56 MiB, and at least 128 blocks (TP8 has 80: +0.9 .. +4.7).
+bool decode_single_kernel(int mode, int N, int k_tiles, int T) {
+    if (T <= 2) return true;
+    if (T > 32) return false;
+    if (k_tiles < 8) return true;              // not one chunk of the split kernel
+    const int units = N / 16 / (mode == DEC_SWIGLU || (mode == DEC_RAW && raw_pairs(N)) ? 2 : 1);
+    const size_t operand = (size_t)units * k_tiles * dec_act_tiles(T) << 10;
+    if (mode == DEC_QKV) return units >= 128 && operand <= (size_t)56 << 20;
+    return operand <= (size_t)128 << 20;
+}
+}  // namespace
+
 void launch_decode_proj(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, const DecodeEpi &e, float *scratch,
                         size_t scratch_floats, hipStream_t s, hipEvent_t mid) {
     const int k_tiles = K / 32;
-    // one or two rows: one kernel, complete dot products per block; more: shared operand, split contraction
-    // A small matrix (launch-bound) with a handful of rows is better off without the second kernel: each block then
-    // fetches the rows' operand pieces itself (an L2 read of T x K x 4 bytes per block, which is what limits this to
-    // few rows, fewer when the contraction is long), and needs enough k-tiles per wave to fill its request ring.
-    const bool small = (size_t)N * K * sizeof(h16_t) <= ((size_t)72 << 20) && k_tiles >= 64 && T <= (K <= 4096 ? 8 : 4);
-    // A residual projection with a short contraction (W_O of a narrow shard: 1024 or 2048 long) is one kernel as well:
-    // a block holds complete dot products after 4 (8) k-tiles per wave, its ring sized to exactly that, and what the
-    // split path adds -- partial sums, a second launch -- costs more than the rows' operand pieces fetched per block.
-    // Measured on 70B shards, W_O per layer: TP8 (32 k-tiles) 3 / 8 / 16 / 17 / 32 rows 11.3 / 12.0 / 12.3 / 12.9 / 13.0 ->
-    // 8.1 / 8.5 / 9.7 / 10.8 / 12.8 us; TP4 (64 k-tiles) 9 / 16 rows 15.3 / 15.9 -> 12.6 / 14.4, but 32 rows 17.7 -> 21.8.
-    const bool short_k = e.mode == DEC_RESID && T > 2 && !small && k_tiles >= 8 &&
-                         ((k_tiles <= 32 && T <= 32) || (k_tiles <= 64 && T <= 16));
-    if (short_k) {
-        if (k_tiles <= 32) {
-            if (T <= 16) launch_one<1, 1, 4, DEC_RESID, false, 1>(Wp, Xa, N, k_tiles, T, e, s);
-            else launch_one<2, 1, 4, DEC_RESID, false, 1>(Wp, Xa, N, k_tiles, T, e, s);
-        } else {
-            launch_one<1, 1, 8, DEC_RESID, false, 1>(Wp, Xa, N, k_tiles, T, e, s);
-        }
-        if (mid) (void)hipEventRecord(mid, s);
-        return;
-    }
-    if (T > 2 && !small && scratch != nullptr && scratch_floats >= (size_t)T * N + 32 && k_tiles >= SK_CH) {
+    const bool single = decode_single_kernel(e.mode, N, k_tiles, T);
+    if (!single && scratch != nullptr && scratch_floats >= (size_t)T * N + DEC_SCRATCH_RSTD) {
         switch (e.mode) {
             case DEC_RAW: launch_splitk<DEC_RAW, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
             case DEC_QKV: launch_splitk<DEC_QKV, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
@@ -660,8 +664,7 @@ void launch_decode_proj(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, c
     }
     switch (e.mode) {
         case DEC_RAW:
-            // two feature tiles per block (2 KB of weights per wave and k-tile) stream a few percent faster than one
-            if ((N / 16) % 2 == 0 && N / 32 >= 512) launch_mode<2, DEC_RAW>(Wp, Xa, N, k_tiles, T, e, s);
+            if (raw_pairs(N)) launch_mode<2, DEC_RAW>(Wp, Xa, N, k_tiles, T, e, s);
             else launch_mode<1, DEC_RAW>(Wp, Xa, N, k_tiles, T, e, s);
             break;
         case DEC_QKV: launch_mode<1, DEC_QKV>(Wp, Xa, N, k_tiles, T, e, s); break;
@@ -675,11 +678,8 @@ void launch_decode_qkv(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, co
                        size_t scratch_floats, QkvTail *tail, hipStream_t s) {
     *tail = QkvTail{nullptr, 0, T, N, nullptr, e.cos_tab, e.sin_tab};
     const int k_tiles = K / 32;
-    // the same choice between the single-kernel and the split path as launch_decode_proj makes
-    // (a matrix of fewer than 128 feature tiles would run the single kernel on that many blocks: TP8's 80 tiles with
-    // 3 / 4 rows took 14.8 / 15.0 us against 10.0 / 10.4 split, 2.5 us per layer after the attention's longer start)
-    const bool small = (size_t)N * K * sizeof(h16_t) <= ((size_t)72 << 20) && k_tiles >= 64 && T <= (K <= 4096 ? 8 : 4) && N / 16 >= 128;
-    if (e.mode == DEC_QKV && T > 2 && !small && scratch != nullptr && scratch_floats >= (size_t)T * N + 32 && k_tiles >= SK_CH)
+    if (e.mode == DEC_QKV && !decode_single_kernel(e.mode, N, k_tiles, T) && scratch != nullptr &&
+        scratch_floats >= (size_t)T * N + DEC_SCRATCH_RSTD)
         launch_splitk<DEC_QKV, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, nullptr, tail);
     else
         launch_decode_proj(Wp, Xa, N, K, T, e, scratch, scratch_floats, s, nullptr);
@@ -733,13 +733,13 @@ __global__ __launch_bounds__(512) void decode_prologue_kernel(const void *__rest
             if (h_out) *reinterpret_cast<floatx4 *>(h_out + (size_t)t * H + col) = floatx4{x[0], x[1], x[2], x[3]};
             const floatx4 g4 = *reinterpret_cast<const floatx4 *>(g + col);
             const float y[4] = {x[0] * g4[0], x[1] * g4[1], x[2] * g4[2], x[3] * g4[3]};
-            store_act4(y, hg, t, col, H >> 5);
+            store_act4(y, hg, t, col, H >> 5, T);
             ss = x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
         }
         // the 4 quads of one 16-column unit are 4 consecutive lanes
         ss += __shfl_xor(ss, 1, 64);
         ss += __shfl_xor(ss, 2, 64);
-        if ((quad & 3) == 0 && col < H) ssq_out[(col >> 4) * DEC_SSQ_STRIDE + t] = ss;
+        if ((quad & 3) == 0 && col < H) ssq_out[(size_t)t * (H >> 4) + (col >> 4)] = ss;
     }
 }
 

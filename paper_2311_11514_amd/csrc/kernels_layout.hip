@@ -110,13 +110,14 @@ void launch_stream_read(const void *src, float *sink, int64_t bytes, int blocks,
 
 // ---- the model's ends: greedy argmax over a row of logits, embedding row gather --------------------------------
 // One block of 1024 threads per row.  Each thread scans a strided slice (four entries per load when the row pitch
-// allows it, several loads in flight) keeping (value, lowest index); the block reduces in LDS with the same rule, so
-// the result is the first maximum of the row, as numpy / torch argmax define it.
+// allows it, eight loads in flight: a 32000-entry row is one round trip) keeping (value, lowest index); waves and then the
+// block reduce with the same rule, so the result is the first maximum of the row, as numpy / torch argmax define it.
+// Latency-bound: the reduction across lanes takes two barriers where a tree in LDS took eleven.
 template <bool VEC4>
 __global__ __launch_bounds__(1024) void row_argmax_kernel(const float *__restrict__ logits, int64_t ld, int valid, int id0,
                                                          int32_t *__restrict__ token_out, float *__restrict__ logit_out) {
-    __shared__ float sv[1024];
-    __shared__ int si[1024];
+    __shared__ float sv[16];
+    __shared__ int si[16];
     const float *row = logits + (int64_t)blockIdx.x * ld;
     float bv = -INFINITY;
     int bi = 0x7fffffff;
@@ -125,7 +126,7 @@ __global__ __launch_bounds__(1024) void row_argmax_kernel(const float *__restric
     };
     if (VEC4) {
         const int n4 = (valid + 3) >> 2;          // the pitch is a multiple of 4: the last quad stays inside the row
-#pragma unroll 4
+#pragma unroll 8
         for (int q = threadIdx.x; q < n4; q += 1024) {
             const floatx4 v = *reinterpret_cast<const floatx4 *>(row + 4 * q);
             take(v[0], 4 * q); take(v[1], 4 * q + 1); take(v[2], 4 * q + 2); take(v[3], 4 * q + 3);
@@ -134,20 +135,23 @@ __global__ __launch_bounds__(1024) void row_argmax_kernel(const float *__restric
 #pragma unroll 4
         for (int i = threadIdx.x; i < valid; i += 1024) take(row[i], i);
     }
-    sv[threadIdx.x] = bv;
-    si[threadIdx.x] = bi;
-    __syncthreads();
-    for (int o = 512; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            const float v = sv[threadIdx.x + o];
-            const int i = si[threadIdx.x + o];
-            if (v > sv[threadIdx.x] || (v == sv[threadIdx.x] && i < si[threadIdx.x])) { sv[threadIdx.x] = v; si[threadIdx.x] = i; }
+    auto reduce = [&](int lanes) {
+        for (int o = lanes >> 1; o > 0; o >>= 1) {
+            const float v = __shfl_xor(bv, o, 64);
+            const int i = __shfl_xor(bi, o, 64);
+            if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
         }
-        __syncthreads();
-    }
+    };
+    reduce(64);
+    if ((threadIdx.x & 63) == 0) { sv[threadIdx.x >> 6] = bv; si[threadIdx.x >> 6] = bi; }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    bv = sv[threadIdx.x & 15];
+    bi = si[threadIdx.x & 15];
+    reduce(16);
     if (threadIdx.x == 0) {
-        token_out[blockIdx.x] = id0 + (si[0] == 0x7fffffff ? 0 : si[0]);
-        if (logit_out) logit_out[blockIdx.x] = sv[0];
+        token_out[blockIdx.x] = id0 + (bi == 0x7fffffff ? 0 : bi);
+        if (logit_out) logit_out[blockIdx.x] = bv;
     }
 }
 void launch_row_argmax(const float *logits, int64_t ld, int valid, int n, int id0, int32_t *token_out, float *logit_out,

@@ -31,7 +31,13 @@
 
 namespace {
 
-constexpr int kDecodeMaxRows = 32;      // rows handled by the weight-streaming decode kernels
+// Rows of a decode step on the weight-streaming decode kernels; beyond, the prefill projections.  Measured per layer of
+// 70B shards at context 600, prefill path against decode path: TP8 33 / 48 / 64 rows 108 / 109 / 110 -> 92 / 98 / 112 us, TP4
+// 140 / 144 / 147 -> 128 / 136 / 156, TP2 211 / 217 / 223 -> 199 / 209 / 242, full width 375 / 380 / 391 -> 353 / 365 / 421.
+constexpr int kDecodeMaxRows = 48;
+constexpr int kHeadRows = 64;           // rows of one pass over the LM head's weights: a second pass costs more than 64 rows in one
+constexpr int kStaticMaxRows = 32;      // rows of a decode call on the static scratch
+constexpr int kF32StreamRows = 32;      // fp32: rows of the streaming projections
 constexpr int kAttnRows = 128;            // new rows per block of the prefill attention (4 waves x 32)
 constexpr int kMaxAttnSplit = 32;         // blocks per (sequence, kv head) the workspace has partials for
 constexpr int kStaticAttnSplit = 8;       // what pick_attn_split chooses at most, and what the static scratch is laid out for
@@ -73,11 +79,11 @@ struct Workspace {
     size_t dec_part_floats = 0;
     float *gemm_part = nullptr;      // fp32 partial tiles of a split prefill contraction (short prompts)
     size_t gemm_part_floats = 0;
-    h16_t *xa_n = nullptr, *xa_o = nullptr, *xa_u = nullptr;   // decode operands, compact hi/lo layout [32][K][2]
+    h16_t *xa_n = nullptr, *xa_o = nullptr, *xa_u = nullptr;   // decode operands, hi / lo (dec_act_offset)
     h16_t *q_lo = nullptr;
     float *att_o = nullptr, *att_ml = nullptr;
     unsigned int *att_arrived = nullptr;      // per (sequence, kv head): split blocks that have finished; zero between launches
-    float *ssq = nullptr;                       // decode: 2 x [H/16 units][DEC_SSQ_STRIDE] sums of squares
+    float *ssq = nullptr;                       // decode: 2 x [kDecodeMaxRows][H/16 units] sums of squares
     float *ssq_pf = nullptr;                    // prefill: 2 x [H/128][T] sums of squares
     // fp32 path: raw QKV projection, normalised rows (more than 32 rows only), rotated q, attention output, SwiGLU output
     float *qkv32 = nullptr, *n32 = nullptr, *q32 = nullptr, *o32 = nullptr, *u32 = nullptr;
@@ -164,9 +170,9 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
         HX_TRY(dmalloc(&w.u, T16 * st->F_l));
         HX_TRY(dmalloc(&w.q, T16 * st->qw));
         const size_t drows = (size_t)std::min(rows, kDecodeMaxRows);
-        HX_TRY(dmalloc(&w.xa_n, 2 * drows * st->H));
-        HX_TRY(dmalloc(&w.xa_o, 2 * drows * st->qw));
-        HX_TRY(dmalloc(&w.xa_u, 2 * drows * st->F_l));
+        HX_TRY(dmalloc(&w.xa_n, dec_act_elems((int)drows, st->H)));
+        HX_TRY(dmalloc(&w.xa_o, dec_act_elems((int)drows, st->qw)));
+        HX_TRY(dmalloc(&w.xa_u, dec_act_elems((int)drows, st->F_l)));
         HX_TRY(dmalloc(&w.q_lo, drows * st->qw));
         if (drows > 2) {      // splits x features stays near 512 x 128 (see launch_splitk), plus one unsplit matrix
             w.dec_part_floats = drows * ((size_t)512 * 128 + 2 * nmax);
@@ -178,7 +184,7 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
         HX_TRY(dmalloc(&w.att_ml, drows * st->hq_l * kMaxAttnSplit * 2));
         HX_TRY(dmalloc(&w.att_arrived, drows * st->hkv_l));
         HX_HIP(hipMemset(w.att_arrived, 0, drows * st->hkv_l * sizeof(unsigned int)));
-        const size_t ssq_n = 2 * (size_t)(st->H / 16) * DEC_SSQ_STRIDE;
+        const size_t ssq_n = 2 * (size_t)(st->H / 16) * kDecodeMaxRows;
         HX_TRY(dmalloc(&w.ssq, ssq_n));
         HX_TRY(dmalloc(&w.ssq_pf, 2 * (size_t)(st->H / GEMM_SSQ_COLS + 1) * T));
         HX_HIP(hipMemset(w.ssq, 0, ssq_n * sizeof(float)));
@@ -191,7 +197,7 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
         HX_TRY(dmalloc(&w.q32, T * st->qw));
         HX_TRY(dmalloc(&w.o32, T * st->qw));
         HX_TRY(dmalloc(&w.u32, T * st->F_p));
-        if (rows > kDecodeMaxRows) {
+        if (rows > kF32StreamRows) {
             HX_TRY(dmalloc(&w.n32, T * st->H));
             w.gemm_part_floats = (size_t)8 << 20;       // 32 MB: 8 splits of 512 rows x 2048 columns
             HX_TRY(dmalloc(&w.gemm_part, w.gemm_part_floats));
@@ -233,7 +239,7 @@ hexgen_status_t setup_rows(hexgen_stage *st, hexgen_kv_cache *kv, const int32_t 
     }
     if (total > 0x3fffffff) return HEXGEN_ERR_CAPACITY;
     r.T = (int)total;
-    r.decode = allow_decode && r.max_new == 1 && r.T <= kDecodeMaxRows;
+    r.decode = allow_decode && r.max_new == 1 && r.T <= (is_h16(st->dtype) ? kDecodeMaxRows : kF32StreamRows);
     HX_TRY(ensure_workspace(st, r.T, batch));
     Workspace &w = st->ws;
     w.row_seq = w.rowmap;
@@ -242,7 +248,7 @@ hexgen_status_t setup_rows(hexgen_stage *st, hexgen_kv_cache *kv, const int32_t 
     w.pos0 = w.cu_rows + batch + 1;
     r.rm.row_seq = w.row_seq;
     r.rm.row_pos = w.row_pos;
-    // a decode step of at most 32 rows takes its positions from the committed lengths on the device
+    // a decode step on the decode kernels takes its positions from the committed lengths on the device
     if (!r.decode) {
         // the pinned staging buffer may still feed an earlier async copy on this stream
         HX_HIP(hipStreamSynchronize(s));
@@ -388,7 +394,7 @@ void sublayer_prefill_h16(hexgen_stage *st, hexgen_kv_cache *kv, int layer, int 
     }
 }
 
-// ---- bf16 decode flow (T <= 32 rows): five kernels per layer, everything else fused into their tails ----
+// ---- bf16 decode flow (up to kDecodeMaxRows rows): five kernels per layer, everything else fused into their tails ----
 int g_attn_split_forced = 0;      // measurement and test hook (hexgen_set_attn_split); 0 = choose
 
 int pick_attn_split(const hexgen_stage *st, const hexgen_kv_cache *kv, int batch) {
@@ -468,7 +474,7 @@ void attn_decode_h16(hexgen_stage *st, hexgen_kv_cache *kv, int layer, const Row
 hexgen_status_t forward_decode_h16(hexgen_stage *st, hexgen_kv_cache *kv, const Rows &r, const void *hidden_in,
                                     void *out_partial, void *out_resid, hipStream_t s) {
     Workspace &w = *st->cur;
-    float *ssq_a = w.ssq, *ssq_f = w.ssq + (size_t)(st->H / 16) * DEC_SSQ_STRIDE;
+    float *ssq_a = w.ssq, *ssq_f = w.ssq + (size_t)(st->H / 16) * kDecodeMaxRows;
     HX_K(st->dtype, launch_decode_prologue, hidden_in, nullptr, 1, w.h, st->layers[0].g_attn, w.xa_n, ssq_a, r.T, st->H, kv->d_lens,
                            w.row_pos, 1, s);
     for (int l = 0; l < st->L; ++l) {
@@ -653,9 +659,9 @@ size_t carve_decode_workspace(const hexgen_stage *st, int rows, unsigned char *b
     Workspace v;
     v.cap_rows = rows;
     v.h = static_cast<float *>(take(T * st->H * sizeof(float)));
-    v.xa_n = static_cast<h16_t *>(take(2 * T * st->H * sizeof(h16_t)));
-    v.xa_o = static_cast<h16_t *>(take(2 * T * st->qw * sizeof(h16_t)));
-    v.xa_u = static_cast<h16_t *>(take(2 * T * st->F_l * sizeof(h16_t)));
+    v.xa_n = static_cast<h16_t *>(take(dec_act_elems(rows, st->H) * sizeof(h16_t)));
+    v.xa_o = static_cast<h16_t *>(take(dec_act_elems(rows, st->qw) * sizeof(h16_t)));
+    v.xa_u = static_cast<h16_t *>(take(dec_act_elems(rows, st->F_l) * sizeof(h16_t)));
     v.q = static_cast<h16_t *>(take(T * st->qw * sizeof(h16_t)));
     v.q_lo = static_cast<h16_t *>(take(T * st->qw * sizeof(h16_t)));
     if (rows > 2) {
@@ -665,7 +671,7 @@ size_t carve_decode_workspace(const hexgen_stage *st, int rows, unsigned char *b
     v.att_o = static_cast<float *>(take(T * st->hq_l * kStaticAttnSplit * st->d * sizeof(float)));
     v.att_ml = static_cast<float *>(take(T * st->hq_l * kStaticAttnSplit * 2 * sizeof(float)));
     v.att_arrived = static_cast<unsigned int *>(take(T * st->hkv_l * sizeof(unsigned int)));
-    v.ssq = static_cast<float *>(take(2 * (size_t)(st->H / 16) * DEC_SSQ_STRIDE * sizeof(float)));
+    v.ssq = static_cast<float *>(take(2 * (size_t)(st->H / 16) * kDecodeMaxRows * sizeof(float)));
     v.row_pos = static_cast<int32_t *>(take(T * sizeof(int32_t)));
     if (w) *w = v;
     return off;
@@ -1061,7 +1067,7 @@ hexgen_status_t hexgen_stage_decode_static(hexgen_stage_t *st, hexgen_kv_cache_t
     if (!kv->prefilled || kv->batch <= 0 || step != kv->steps) return HEXGEN_ERR_STATE;
     HX_TRY(check_rope(st, kv));
     const int batch = kv->batch;
-    if (batch > kDecodeMaxRows) return HEXGEN_ERR_CAPACITY;
+    if (batch > kStaticMaxRows) return HEXGEN_ERR_CAPACITY;
     for (int i = 0; i < batch; ++i)
         if ((long)kv->lens[i] + 1 > kv->max_seq) return HEXGEN_ERR_CAPACITY;
     if (carve_decode_workspace(st, batch, nullptr, nullptr) > kStaticScratchBytes) return HEXGEN_ERR_CAPACITY;
@@ -1073,7 +1079,7 @@ hexgen_status_t hexgen_stage_decode_static(hexgen_stage_t *st, hexgen_kv_cache_t
     // what must start at zero: the arrival counters of the split attention and the sums of squares (a fill kernel,
     // not a memset node, so that the call can be captured into a graph)
     launch_fill_zero(view.att_arrived, (size_t)batch * st->hkv_l * sizeof(unsigned int), s);
-    launch_fill_zero(view.ssq, 2 * (size_t)(st->H / 16) * DEC_SSQ_STRIDE * sizeof(float), s);
+    launch_fill_zero(view.ssq, 2 * (size_t)(st->H / 16) * kDecodeMaxRows * sizeof(float), s);
     Rows r;
     r.T = batch;
     r.batch = batch;
@@ -1176,7 +1182,7 @@ hexgen_status_t hexgen_stage_time_w13_decode(hexgen_stage_t *st, int reps, doubl
     const unsigned saved = st->prof.mask;
     st->prof.mask = 0;
     DecodeEpi e = epi_base(st, DEC_SWIGLU);
-    e.ssq_in = w.ssq + (size_t)(st->H / 16) * DEC_SSQ_STRIDE;
+    e.ssq_in = w.ssq + (size_t)(st->H / 16) * kDecodeMaxRows;
     e.u = w.xa_u;
     e.F_l = st->F_l;
     HX_HIP(hipEventRecord(e0, s));
@@ -1220,8 +1226,8 @@ struct hexgen_head {
     bool loaded = false;
     void *w = nullptr;            // bf16: fragment tiles, k-tile-major [H/32][Vpad/16][64][8]; f32: [H][Vpad], H padded with zero rows to 32
     float *g = nullptr;           // final norm gain, fp32 [H]
-    // workspace for one chunk of up to kDecodeMaxRows rows
-    h16_t *xa = nullptr;         // bf16: (x * g) as compact hi/lo operand
+    // workspace for one chunk of rows (head_chunk_rows)
+    h16_t *xa = nullptr;         // bf16: (x * g) as hi/lo operand
     float *ssq = nullptr;         // bf16: sums of squares per 16 columns
     float *logits = nullptr;      // [rows][Vpad]
     float *scratch = nullptr;     // split partial sums of the batched projection
@@ -1229,6 +1235,8 @@ struct hexgen_head {
 };
 
 namespace {
+// rows of one pass over the head's weights: what the projections of either type take at a time
+int head_chunk_rows(const hexgen_head *hd) { return is_h16(hd->dtype) ? kHeadRows : kF32StreamRows; }
 void free_head(hexgen_head *hd) {
     void *ptrs[] = {hd->w, hd->g, hd->xa, hd->ssq, hd->logits, hd->scratch};
     for (void *p : ptrs)
@@ -1250,12 +1258,12 @@ hexgen_status_t hexgen_head_create(int hidden, int vocab, int tp_degree, int tp_
     hd->H = hidden; hd->V = vocab; hd->t = tp_degree; hd->r = tp_rank; hd->dtype = dtype; hd->eps = rms_eps;
     hd->Vl = vocab / tp_degree;
     hd->Vpad = round_up(hd->Vl, 16);
-    const size_t rows = kDecodeMaxRows;
+    const size_t rows = (size_t)head_chunk_rows(hd);
     hexgen_status_t rc = dmalloc(&hd->g, (size_t)hidden);
     if (rc == HEXGEN_OK) rc = dmalloc(&hd->logits, rows * hd->Vpad);
     if (rc == HEXGEN_OK && is_h16(dtype)) {
-        rc = dmalloc(&hd->xa, 2 * rows * hidden);
-        if (rc == HEXGEN_OK) rc = dmalloc(&hd->ssq, (size_t)(hidden / 16) * DEC_SSQ_STRIDE);
+        rc = dmalloc(&hd->xa, dec_act_elems((int)rows, hidden));
+        if (rc == HEXGEN_OK) rc = dmalloc(&hd->ssq, (size_t)(hidden / 16) * rows);
         hd->scratch_floats = rows * ((size_t)512 * 128 + 2 * (size_t)hd->Vpad);
         if (rc == HEXGEN_OK) rc = dmalloc(&hd->scratch, hd->scratch_floats);
     }
@@ -1315,8 +1323,9 @@ hexgen_status_t hexgen_head_greedy(hexgen_head_t *hd, const void *hidden_a, cons
     hipStream_t s = static_cast<hipStream_t>(stream);
     const size_t es = esize(hd->dtype);
     const int H = hd->H;
-    for (int r0 = 0; r0 < n_rows; r0 += kDecodeMaxRows) {
-        const int n = std::min(kDecodeMaxRows, n_rows - r0);
+    const int chunk = head_chunk_rows(hd);
+    for (int r0 = 0; r0 < n_rows; r0 += chunk) {
+        const int n = std::min(chunk, n_rows - r0);
         const char *a = static_cast<const char *>(hidden_a) + (size_t)r0 * H * es;
         const char *b = hidden_b ? static_cast<const char *>(hidden_b) + (size_t)r0 * H * es : nullptr;
         if (is_h16(hd->dtype)) {

@@ -1,0 +1,65 @@
+"""The forms of the decode projections at the row counts where they change: operand tiles of 8 (hi and lo in one tile), 16,
+32, 48 and 64 rows, the single kernel against the split one with its finishing pass (a layer whose W1/W3 and W2 lie just
+beyond the line between them at three rows: 2052 feature tiles, 513 k-tiles), the prefill kernels beyond 48 rows, and the LM
+head's passes of 64 rows.  Gate: the suite's per-type tolerance; the hi + lo operands keep decode steps well below it."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import stage_oracle as so
+from tests.helpers import TOL, check, gpu_decode, gpu_prefill, make_gpu_stage, make_oracle
+from workloads import StageConfig, generate
+
+pytestmark = pytest.mark.gpu
+
+WIDE = StageConfig("wide", "bf16", 4096, 32, 8, 16416, 1, 1, (0,), batch=1, seed=801)
+NARROW = StageConfig("narrow", "f16", 512, 8, 2, 1472, 2, 2, (1,), batch=1, seed=802)      # W_O: 8 k-tiles, W2: 23
+_sides = {}
+
+
+def _side(cfg):
+    if cfg.name not in _sides:
+        w = [generate.layer_weights(cfg, l) for l in range(cfg.n_layers)]
+        _sides[cfg.name] = make_oracle(cfg, cfg.tp_ranks[0], w), make_gpu_stage(cfg, cfg.tp_ranks[0], w)
+    return _sides[cfg.name]
+
+
+@pytest.mark.parametrize("cfg,rows", [(WIDE, t) for t in (3, 8, 9, 17, 32, 33, 48, 49)] + [(NARROW, t) for t in (3, 9, 16, 31, 33, 47, 48, 49)],
+                         ids=lambda v: getattr(v, "name", v))
+def test_decode_step(cfg, rows):
+    print(cfg.name, rows, flush=True)
+    ora, st = _side(cfg)
+    lens = [1 + (i * 7) % 5 for i in range(rows)]
+    X = generate.hidden_rows(cfg, sum(lens))
+    oc = ora.new_cache(rows)
+    kv = st.kv_cache_create(rows, 16)
+    ora.prefill(oc, X, lens)
+    gpu_prefill(st, kv, cfg, X, lens)
+    for i in range(rows):                       # the steps start from the very rows the GPU holds
+        for l in range(cfg.n_layers):
+            k, v = kv.read(l, i, 0, lens[i])
+            oc.fill(l, i, k, v)
+    for k in range(2):
+        x = generate.hidden_rows(cfg, rows, stream_id=1 + k)
+        p_ref, h_ref = ora.decode(oc, x)
+        p, h = gpu_decode(st, kv, cfg, k, x)
+        check(f"{rows} rows step {k} resid", h, h_ref, TOL[cfg.dtype])
+        check(f"{rows} rows step {k} partial", p, p_ref, TOL[cfg.dtype])
+
+
+@pytest.mark.parametrize("hidden,vocab,rows", [(128, 1000, 40), (1024, 4104, 33), (1024, 4104, 48), (1024, 4104, 49), (1024, 4104, 64), (1024, 4104, 65)])
+def test_head_rows(hidden, vocab, rows):
+    import paper_2311_11514_amd as hx
+    cfg = StageConfig("headrows", "bf16", hidden, 8, 8, 64, 1, 1, (0,), batch=1, seed=803, vocab=vocab)
+    hw = generate.head_weights(cfg)
+    hd = hx.Head(hidden, vocab, 1, 0, "bf16", cfg.rms_eps)
+    hd.load(hw["g_final"].cuda(), hw["w_lm"].cuda())
+    a, b = (generate.hidden_rows(cfg, rows, stream_id=s).to(torch.bfloat16) for s in (3, 4))
+    tok, val = hd.greedy(a.cuda(), b.cuda())
+    torch.cuda.synchronize()
+    logits = so.rmsnorm(a.double().numpy() + b.double().numpy(), hw["g_final"].double().numpy(), cfg.rms_eps) @ hw["w_lm"].double().numpy()
+    top = np.sort(logits, axis=1)
+    # the operands carry 16 mantissa bits: a logit is off by about 2^-17 of the row's scale
+    assert np.max(np.abs(val.cpu().numpy() - top[:, -1]) / np.abs(top[:, -1])) < 2e-4
+    clear = top[:, -1] - top[:, -2] > 1e-3 * np.abs(top[:, -1])
+    assert clear.mean() > 0.8 and np.array_equal(tok.cpu().numpy()[clear], np.argmax(logits, axis=1)[clear])
