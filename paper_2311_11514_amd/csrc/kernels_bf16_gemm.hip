@@ -45,10 +45,10 @@ namespace HX_NS {
 // (q % 2) * 8 + 4 (l / 32) .. + 3.  Rotary pairs (tile rows r, r + 8) and gate / up pairs (tiles 2m, 2m + 1)
 // therefore sit in the same lane, in quads q and q ^ 1 respectively q and q + 2: no cross-lane traffic.
 // acc_of(i, j): the wave's result tile (i, j) of its FM x FT tiles of block (bm, bt), wave (wm, wt), each asked for once
-// (the two-phase loop converts its 16 x 16 results tile by tile on demand); rstd_s: 1 / rms of the block's token columns.
-template <int FM, int FT, int WM, int WT, int MODE, typename AccF>
+// (the two-phase loop converts its 16 x 16 results tile by tile on demand); rstd_of(t): 1 / rms of the block's token column t.
+template <int FM, int FT, int WM, int WT, int MODE, typename AccF, typename RstdF>
 __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int wm, int wt, int lane, int N,
-                                              int n_tiles, int T, const GemmEpi &e, const float *rstd_s,
+                                              int n_tiles, int T, const GemmEpi &e, RstdF rstd_of,
                                               float *ssq_lds = nullptr) {
     constexpr int TA = 2 * FM * WM, TB = 2 * FT * WT, NTOK = TB * 16;
     const int hl = lane >> 5;
@@ -157,7 +157,7 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
         const int tl = (wt * FT + j) * 32 + (lane & 31);       // token column inside the block tile
         const int token = bt * NTOK + tl;
         const bool tv = token < T;
-        const float r = e.ssq_in != nullptr ? rstd_s[tl] : 1.0f;
+        const float r = e.ssq_in != nullptr ? rstd_of(tl) : 1.0f;
         int seq = 0, pos = 0;
         if (MODE == DEC_QKV && tv) { seq = e.rm.row_seq[token]; pos = e.rm.row_pos[token]; }
 #pragma unroll
@@ -236,6 +236,25 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
     }
 }
 
+// Partial sums of a split contraction: [split][32-feature block][32-token block][quad][lane][4], a 4 KB piece per result
+// tile in the order it sits in the registers (1 KB per store), whatever kernel and tile shape wrote it; blocks that hold
+// nothing but padding are not stored.  nb feature blocks from the launch's first one, tb token blocks.
+struct PartGeom {
+    int nb, tb;
+};
+__host__ __device__ inline PartGeom part_geom(int n_tiles, int t_tiles, int nb32_first, int nb32_count) {
+    const int all = (n_tiles + 1) / 2 - nb32_first;
+    return PartGeom{all < nb32_count ? all : nb32_count, (t_tiles + 1) / 2};
+}
+__host__ __device__ inline size_t part_offset(const PartGeom &g, int split, int nb, int tb) {
+    return (((size_t)split * g.nb + nb) * g.tb + tb) * 1024;
+}
+__device__ __forceinline__ void part_store(float *dst, const floatx16 &c, int lane) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<floatx4 *>(dst + q * 256 + lane * 4) = floatx4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+}
+
 // Linear tile id -> (feature block bm, token block bt).  Ids are dealt out patch by patch: a patch is pm_h feature
 // blocks x pt_w token blocks (lower / narrower at the edges), patches run along the token blocks first, and inside a
 // patch the feature block varies fastest.  pm_h = 1, pt_w = t_blocks is the plain row-major order.
@@ -281,8 +300,8 @@ __global__ __launch_bounds__(64 * WM * WT) void gemm_mfma_kernel(const h16_t *__
     constexpr int STAGE = (TA + TB) * 64;            // h16x8 elements per stage
     constexpr int NTOK = TB * 16;                    // token columns of the block tile
     static_assert(TA % NW == 0 && TB % NW == 0, "operand tiles must divide evenly over the waves");
-    extern __shared__ h16x8 smem[];                 // [S][TA + TB][64], then NTOK floats
-    float *rstd_s = reinterpret_cast<float *>(smem + (size_t)S * STAGE);
+    extern __shared__ h16x8 smem[];                 // [S][TA + TB][64], then NT floats
+    float *ssq_s = reinterpret_cast<float *>(smem + (size_t)S * STAGE);
     // XCD-aware remap of the linear block id
     const int total = n_blocks * t_blocks;
     int id = blockIdx.x;
@@ -301,6 +320,33 @@ __global__ __launch_bounds__(64 * WM * WT) void gemm_mfma_kernel(const h16_t *__
     // fp32 result tiles in `part`; gemm_finish_kernel adds the splits up and runs the epilogue
     const int k0 = (int)((long)blockIdx.y * k_tiles / gridDim.y);
     const int k_len = (int)((long)(blockIdx.y + 1) * k_tiles / gridDim.y) - k0;
+
+    // The sums of squares of the block's token columns from the producer's partials, once per block while the pipeline fills:
+    // NT / NTOK threads per token, each with its share of the partials in one round of requests (one thread per token
+    // and 16 at a time was four round trips, about 3 us of a block's start); 1 / rms follows in the epilogue.
+    constexpr int SSP = NT / NTOK;
+    static_assert(SSP >= 1 && NT % NTOK == 0, "whole threads per token");
+    auto sum_squares = [&]() {
+        if (MODE == DEC_RESID || e.ssq_in == nullptr || part != nullptr) return;
+        const int groups = e.norm_dim / GEMM_SSQ_COLS, tok = (int)threadIdx.x % NTOK, token = min(bt * NTOK + tok, T - 1);
+        float ss = 0.f;
+#pragma unroll 32
+        for (int gI = threadIdx.x / NTOK; gI < groups; gI += SSP) ss += e.ssq_in[(size_t)gI * T + token];
+        ssq_s[threadIdx.x] = ss;
+    };
+    auto rstd_of = [&](int tl) {
+        float ss = ssq_s[tl];
+#pragma unroll
+        for (int w = 1; w < SSP; ++w) ss += ssq_s[w * NTOK + tl];
+        return 1.0f / sqrtf(ss / (float)e.norm_dim + e.eps);
+    };
+
+    // result tile (i, j) of this wave to the partial sums of this split
+    const PartGeom pg = part_geom(n_tiles, t_tiles, nb0 * FM * WM, n_blocks * FM * WM);
+    auto store_part = [&](int i, int j, const floatx16 &c) {
+        const int nb = (bm - nb0) * FM * WM + wm * FM + i, tb = (bt * WT + wt) * FT + j;
+        if (nb < pg.nb && tb < pg.tb) part_store(part + part_offset(pg, blockIdx.y, nb, tb), c, lane);
+    };
 
     floatx16 acc[FM][FT];
 #pragma unroll
@@ -361,18 +407,7 @@ __global__ __launch_bounds__(64 * WM * WT) void gemm_mfma_kernel(const h16_t *__
         for (int p2 = 0; p2 < S - 1; ++p2)
 #pragma unroll
             for (int x = 0; x < LPT; ++x) issue_one(p2, x);
-        if (MODE != DEC_RESID && e.ssq_in != nullptr && part == nullptr) {
-            const int groups = e.norm_dim / GEMM_SSQ_COLS;
-            for (int t = tid; t < NTOK; t += NT) {
-                const int token = bt * NTOK + t;
-                float ss = 0.f;
-                if (token < T) {
-#pragma unroll 16
-                    for (int gI = 0; gI < groups; ++gI) ss += e.ssq_in[(size_t)gI * T + token];
-                }
-                rstd_s[t] = 1.0f / sqrtf(ss / (float)e.norm_dim + e.eps);
-            }
-        }
+        sum_squares();
         HX_WAIT_VM((S - 2) * LPT);                 // stage 0 has landed (this wave's share of it)
         HX_LDS_BARRIER();                          // ... and everybody's
         if (grp == 1) asm volatile("s_barrier" ::: "memory");       // half a step behind waves 0..3 from here on
@@ -439,19 +474,13 @@ __global__ __launch_bounds__(64 * WM * WT) void gemm_mfma_kernel(const h16_t *__
             return c;
         };
         if (part != nullptr) {
-            float *dst = part + ((((size_t)blockIdx.y * total + id) * NW + wave) * (FM * FT)) * 1024 + lane * 4;
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
-                for (int j = 0; j < FT; ++j) {
-                    const floatx16 c = acc_of(i, j);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *reinterpret_cast<floatx4 *>(dst + (i * FT + j) * 1024 + q * 256) = floatx4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
-                }
+                for (int j = 0; j < FT; ++j) store_part(i, j, acc_of(i, j));
             return;
         }
-        gemm_epilogue<FM, FT, WM, WT, MODE>(acc_of, bm, bt, wm, wt, lane, N, n_tiles, T, e, rstd_s);
+        gemm_epilogue<FM, FT, WM, WT, MODE>(acc_of, bm, bt, wm, wt, lane, N, n_tiles, T, e, rstd_of);
         return;
     }
     constexpr int H1 = (LPT + 1) / 2, H2 = LPT / 2;  // loads issued behind / in front of the barrier
@@ -468,20 +497,7 @@ __global__ __launch_bounds__(64 * WM * WT) void gemm_mfma_kernel(const h16_t *__
         for (int x = 0; x < LPT; ++x) issue_one(p, x);
 #pragma unroll
     for (int x = 0; x < H1; ++x) issue_one(S - 2, x);
-    // 1 / rms of the block's token columns from the producer's partial sums of squares, once per block (the
-    // values are the youngest loads in flight: the compiler's wait for them also covers the stages above)
-    if (MODE != DEC_RESID && e.ssq_in != nullptr && part == nullptr) {
-        const int groups = e.norm_dim / GEMM_SSQ_COLS;
-        for (int t = tid; t < NTOK; t += NT) {
-            const int token = bt * NTOK + t;
-            float ss = 0.f;
-            if (token < T) {
-#pragma unroll 16
-                for (int gI = 0; gI < groups; ++gI) ss += e.ssq_in[(size_t)gI * T + token];
-            }
-            rstd_s[t] = 1.0f / sqrtf(ss / (float)e.norm_dim + e.eps);
-        }
-    }
+    sum_squares();
     h16x8 fa0[FM], fb0[FT], fa1[FM], fb1[FT];
     // x-th operand fetch of a half step: the FT token operands first, then the FM feature operands
     auto fetch_one = [&](h16x8(&fa)[FM], h16x8(&fb)[FT], int kt, int kh, int x) {
@@ -540,75 +556,85 @@ __global__ __launch_bounds__(64 * WM * WT) void gemm_mfma_kernel(const h16_t *__
     }
     HX_WAIT_VM(0);
     if (part != nullptr) {
-        // result tiles as they sit in the registers: per tile 4 quads x 64 lanes x 4 floats, 1 KB per store
-        float *dst = part + ((((size_t)blockIdx.y * total + id) * NW + wave) * (FM * FT)) * 1024 + lane * 4;
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < FT; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<floatx4 *>(dst + (i * FT + j) * 1024 + q * 256) =
-                        floatx4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+            for (int j = 0; j < FT; ++j) store_part(i, j, acc[i][j]);
         return;
     }
-    gemm_epilogue<FM, FT, WM, WT, MODE>([&](int i, int j) { return acc[i][j]; }, bm, bt, wm, wt, lane, N, n_tiles, T, e, rstd_s);
+    gemm_epilogue<FM, FT, WM, WT, MODE>([&](int i, int j) { return acc[i][j]; }, bm, bt, wm, wt, lane, N, n_tiles, T, e, rstd_of);
 }
 
-// Second pass of a split contraction: block `id` (the same tile and wave layout as gemm_mfma_kernel) adds its result
-// tiles up over the splits, in split order, and runs the epilogue.  parts > 1 (a power of two that divides the waves;
-// only where the epilogue needs nothing from another wave): a tile is finished by `parts` blocks, each with a
-// contiguous share of the waves -- a split launch has few tiles, and one block per tile would leave most of the chip
-// idle while each block reads its tile's partial sums alone.
-template <int FM, int FT, int WM, int WT, int MODE>
-__global__ __launch_bounds__(64 * WM * WT) void gemm_finish_kernel(const float *__restrict__ part, int splits, int N,
-                                                                   int n_tiles, int T, int total, int t_blocks, GemmEpi e,
-                                                                   int pm_h, int pt_w, int nb0, int parts) {
-    constexpr int NW = WM * WT, NT = 64 * NW, TB = 2 * FT * WT, NTOK = TB * 16;
-    __shared__ float rstd_s[NTOK];
-    __shared__ float ssq_lds[(MODE == DEC_RESID && 32 * FM != GEMM_SSQ_COLS) ? WM * NTOK : 1];
-    const int id = blockIdx.x / parts;
-    int bm, bt;
-    gemm_tile_of_id(id, total / t_blocks, t_blocks, pm_h, pt_w, bm, bt);      // as in the pass that wrote the partials
-    bm += nb0;
+// Second pass of a split contraction.  A block of 4 waves finishes 128 features x 32 tokens, a wave one 32 x 32 result tile:
+// it adds the tile up over the splits, in split order, and runs the epilogue (the residual epilogue's sum of squares over
+// the 128 features goes through LDS).  The partial sums come from blocks all over the chip, so every read is a trip to the
+// memory-side cache: what bounds this pass is how many of those are in flight, hence small tiles (as many waves as there
+// are 4 KB pieces) and four splits requested at a time.  Measured against one block per GEMM tile walking the splits one
+// after the other: W2 of a TP2 70B shard at 430 rows (64 tiles x 4 splits) 24.5 -> 20 us, W_O 16.4 -> 12, W_O of a 2048-wide
+// layer at 1131 rows (72 x 3) 13.0 -> 10.2, TP4 QKV at 2048 rows (80 x 3) 24.2 -> 14.9, at 117 rows (8 splits) 7.7 -> 6.1.
+template <int MODE>
+__global__ __launch_bounds__(256) void gemm_finish_kernel(const float *__restrict__ part, int splits, int N, int n_tiles, int T,
+                                                          PartGeom pg, int fb0, GemmEpi e) {
+    __shared__ float rstd_s[32], ssum[8][32];
+    __shared__ float ssq_lds[MODE == DEC_RESID ? 4 * 32 : 1];
+    const int fb = blockIdx.x / pg.tb, bt = blockIdx.x - fb * pg.tb;        // 128-feature block of the launch, 32-token block
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int wm = wave % WM, wt = wave / WM;
-    const bool mine = wave / (NW / parts) == (int)blockIdx.x - id * parts;      // this block's share of the tile's waves
-    if (MODE != DEC_RESID && e.ssq_in != nullptr) {
-        const int groups = e.norm_dim / GEMM_SSQ_COLS;
-        for (int t = tid; t < NTOK; t += NT) {
-            const int token = bt * NTOK + t;
-            float ss = 0.f;
-            if (token < T) {
-#pragma unroll 16
-                for (int gI = 0; gI < groups; ++gI) ss += e.ssq_in[(size_t)gI * T + token];
-            }
-            rstd_s[t] = 1.0f / sqrtf(ss / (float)e.norm_dim + e.eps);
+    const int nb = fb * 4 + wave;
+    const bool mine = nb < pg.nb;                                            // the last block's waves may lie beyond the matrix
+    const bool norm = MODE != DEC_RESID && e.ssq_in != nullptr;
+    // eight threads per token share its sums of squares
+    float ss = 0.f;
+    if (norm) {
+        const int groups = e.norm_dim / GEMM_SSQ_COLS, token = min(bt * 32 + (tid & 31), T - 1);
+#pragma unroll 8
+        for (int gI = tid >> 5; gI < groups; gI += 8) ss += e.ssq_in[(size_t)gI * T + token];
+    }
+    floatx16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    auto add = [&](int z0, auto count) {
+        constexpr int C = decltype(count)::value;
+        floatx4 v[C][4];
+#pragma unroll
+        for (int z = 0; z < C; ++z)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                v[z][q] = *reinterpret_cast<const floatx4 *>(part + part_offset(pg, z0 + z, nb, bt) + q * 256 + lane * 4);
+#pragma unroll
+        for (int z = 0; z < C; ++z)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) acc[4 * q + x] += v[z][q][x];
+    };
+    if (mine) {
+        int z = 0;
+        for (; z + 4 <= splits; z += 4) add(z, std::integral_constant<int, 4>{});
+        if (splits - z == 3) add(z, std::integral_constant<int, 3>{});
+        else if (splits - z == 2) add(z, std::integral_constant<int, 2>{});
+        else if (splits - z == 1) add(z, std::integral_constant<int, 1>{});
+    }
+    if (norm) {
+        ssum[tid >> 5][tid & 31] = ss;
+        __syncthreads();
+        if (tid < 32) {
+            float tot = ssum[0][tid];
+#pragma unroll
+            for (int w = 1; w < 8; ++w) tot += ssum[w][tid];
+            rstd_s[tid] = 1.0f / sqrtf(tot / (float)e.norm_dim + e.eps);
         }
+        __syncthreads();
     }
-    floatx16 acc[FM][FT];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FT; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    for (int z = 0; z < (mine ? splits : 0); ++z) {
-        const float *src = part + ((((size_t)z * total + id) * NW + wave) * (FM * FT)) * 1024 + lane * 4;
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FT; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const floatx4 v = *reinterpret_cast<const floatx4 *>(src + (i * FT + j) * 1024 + q * 256);
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) acc[i][j][4 * q + x] += v[x];
-                }
-    }
-    __syncthreads();
-    if (!mine) return;       // (parts > 1 only with an epilogue that has no block barrier)
-    gemm_epilogue<FM, FT, WM, WT, MODE>([&](int i, int j) { return acc[i][j]; }, bm, bt, wm, wt, lane, N, n_tiles, T, e, rstd_s, ssq_lds);
+    gemm_epilogue<1, 1, 4, 1, MODE>([&](int, int) { return acc; }, fb0 + fb, bt, wave, 0, lane, N, n_tiles, T, e, [&](int tl) { return rstd_s[tl]; }, ssq_lds);
+}
+
+// the finishing launch of a split contraction over feature blocks (of 32) nb32_first .. + nb32_count - 1
+template <int MODE>
+static void launch_finish(const float *part, int splits, int N, int n_tiles, int t_tiles, int T, int nb32_first, int nb32_count,
+                          const GemmEpi &e, hipStream_t s) {
+    const PartGeom pg = part_geom(n_tiles, t_tiles, nb32_first, nb32_count);
+    hipLaunchKernelGGL(gemm_finish_kernel<MODE>, dim3((pg.nb + 3) / 4 * pg.tb), dim3(256), 0, s, part, splits, N, n_tiles, T, pg,
+                       nb32_first / 4, e);
 }
 
 // -------------------------------------------------------------------------------------------------
@@ -618,7 +644,7 @@ __global__ __launch_bounds__(64 * WM * WT) void gemm_finish_kernel(const float *
 // 32x32x16 operand wants from it (two 512-byte runs per request), RING k-steps ahead, in a register ring that is
 // refilled slot by slot.  The activations of a k-step (8 KB, L2 hits) are shared by the block's waves through LDS,
 // global -> registers (same ring) -> LDS one k-step before use.  The contraction is split over blockIdx.y; result
-// tiles go to `part` in the layout gemm_finish_kernel<1, 1, 4, 1> reads (four 32-token blocks per feature block).
+// tiles go to `part`.
 // -------------------------------------------------------------------------------------------------
 constexpr int SKINNY_RING = 6;          // measured: 4, 6 and 8 run alike (the CU's load issue rate paces the kernel)
 // KG = 2: a block of 8 waves = two groups of 4, each group walking one half of the block's share of the contraction
@@ -626,8 +652,7 @@ constexpr int SKINNY_RING = 6;          // measured: 4, 6 and 8 run alike (the C
 // before anything is stored: as many waves and k-steps per wave as two blocks of 4 on two splits, half the partial sums.
 template <int KG>
 __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__restrict__ Wp, const h16_t *__restrict__ Xp,
-                                                              int k_tiles, int n_tiles, int t_tiles, int total,
-                                                              float *__restrict__ part) {
+                                                              int k_tiles, int n_tiles, int t_tiles, float *__restrict__ part) {
     constexpr int RING = SKINNY_RING;
     __shared__ h16x8 xs[KG][2][8 * 64];             // per group: two k-steps of the 8 token tiles
     const int id = blockIdx.x;                       // 128-feature block
@@ -734,14 +759,10 @@ __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__re
         }
         if (kg != 0) return;
     }
-    // result tile (32 features x token block j) of this wave, in the layout gemm_finish_kernel<1, 1, 4, 1> reads with
-    // four token blocks per feature block: the finishing pass then has four times as many (smaller) blocks
+    const PartGeom pg = part_geom(n_tiles, t_tiles, 0, gridDim.x * 4);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<floatx4 *>(part + ((((size_t)blockIdx.y * total + id) * 4 + j) * 4 + w4) * 1024 + q * 256 + lane * 4) =
-                floatx4{acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+        if (id * 4 + w4 < pg.nb && j < pg.tb) part_store(part + part_offset(pg, blockIdx.y, id * 4 + w4, j), acc[j], lane);
 }
 
 template <int FM, int FT, int WM, int WT, int S, int MODE, bool PP = false, int ABL = 0>
@@ -754,7 +775,7 @@ static void launch_cfg(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, int
     const int grid = (total + 7) / 8 * 8;
     auto kern = gemm_mfma_kernel<FM, FT, WM, WT, S, MODE, PP, ABL>;
     const int pm_h = 4, pt_w = 8;         // patch of tiles one XCD works on at a time: 4 feature blocks x 8 token blocks
-    const size_t dyn = (size_t)S * (TA + TB) * 64 * sizeof(h16x8) + (size_t)TB * 16 * sizeof(float);
+    const size_t dyn = (size_t)S * (TA + TB) * 64 * sizeof(h16x8) + (size_t)64 * WM * WT * sizeof(float);
     static bool raised = false;           // more than the default 64 KB of LDS per block
     if (!raised) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -765,26 +786,15 @@ static void launch_cfg(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, int
     // arrive at a fraction of the HBM rate: the contraction is then split over blockIdx.y (at most 8 ways, at least
     // 16 k-steps each, partials within the scratch) until the chip holds as many blocks as it can.
     int splits = 1;
-    const size_t tile_floats = (size_t)64 * WM * WT * FM * FT * 16;
+    const PartGeom pg = part_geom(n_tiles, t_tiles, nb0 * FM * WM, n_blocks * FM * WM);
     const int resident = dyn <= 72 * 1024 ? 512 : 256;       // blocks the chip holds at once (LDS: two per CU or one)
     if (part != nullptr && 2 * total <= resident && k_tiles >= 32) {
         splits = std::max(1, std::min({8, resident / total, k_tiles / 16}));
-        while (splits > 1 && (size_t)splits * total * tile_floats > part_floats) --splits;
+        while (splits > 1 && part_offset(pg, splits, 0, 0) > part_floats) --splits;
     }
     hipLaunchKernelGGL(kern, dim3(grid, splits), dim3(64 * WM * WT), dyn, s, Wp, Xp, N, k_tiles, n_tiles, t_tiles, T,
                        n_blocks, t_blocks, e, splits > 1 ? part : nullptr, pm_h, std::min(pt_w, t_blocks), nb0);
-    if (splits > 1) {
-        // Several blocks per tile, each with a share of the tile's waves, where the epilogue is the wave's own business
-        // -- as many as one round of blocks over the chip takes (a CU holds one of them): 4 up to 64 tiles, 2 up to 128.
-        // Measured on 70B TP4 shards, one prompt of 256 rows (10 / 32 / 56 / 32 tiles): 43.1 / 35.0 / 82.0 / 58.2 ->
-        // 38.2 / 32.8 / 81.0 / 54.9 us per projection, 221.6 -> 212.0 us per layer; 512 rows 282 -> 278; QKV at 2048 rows
-        // (80 tiles) 94.2 -> 92.1, while four parts there (320 blocks, two rounds) took the pass from 25.6 to 38.2 us.
-        constexpr bool wave_local = MODE != DEC_RESID || 32 * FM == GEMM_SSQ_COLS;
-        int parts = 1;
-        if (wave_local && (WM * WT) % 4 == 0) parts = total <= 64 ? 4 : (total <= 128 ? 2 : 1);
-        hipLaunchKernelGGL((gemm_finish_kernel<FM, FT, WM, WT, MODE>), dim3(total * parts), dim3(64 * WM * WT), 0, s, part,
-                           splits, N, n_tiles, T, total, t_blocks, e, pm_h, std::min(pt_w, t_blocks), nb0, parts);
-    }
+    if (splits > 1) launch_finish<MODE>(part, splits, N, n_tiles, t_tiles, T, nb0 * FM * WM, n_blocks * FM * WM, e, s);
 }
 
 // tile configuration forced for every GEMM launch of the process (0 = choose by shape); a measurement and test hook
@@ -824,11 +834,11 @@ static bool launch_skinny(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, 
                           const GemmEpi &e, float *part, size_t part_floats, hipStream_t s) {
     if (part == nullptr || t_tiles > 8 || k_tiles < 32) return false;
     const int n_blocks = (n_tiles + 7) / 8;
-    const size_t tile_floats = 4 * 4 * 1024;
+    const PartGeom pg = part_geom(n_tiles, t_tiles, 0, n_blocks * 4);
     // two blocks fit a CU (registers): about 512 blocks in flight, at most 8 splits of at least 16 k-steps
     int splits = std::max(1, std::min({8, 512 / n_blocks, k_tiles / 16}));
-    while (splits > 1 && (size_t)splits * n_blocks * tile_floats > part_floats) --splits;
-    if ((size_t)splits * n_blocks * tile_floats > part_floats) return false;
+    while (splits > 1 && part_offset(pg, splits, 0, 0) > part_floats) --splits;
+    if (part_offset(pg, splits, 0, 0) > part_floats) return false;
     // An even number of splits over enough blocks runs as half as many splits of 8-wave blocks, the pairs of splits summed
     // inside the block: half the partial sums written, and read by the finishing pass.  Measured on the TP4 shard of the
     // 70B shape at 128 rows: W1/W3 (112 blocks x 4 -> x 2) 64.8 -> 59.4 us, W2 (64 x 8 -> x 4) 43.0 -> 38.5, 158.9 -> 149.8 us
@@ -836,14 +846,11 @@ static bool launch_skinny(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, 
     // QKV 20 x 8 -> x 4: 25.6 -> 32.4), and 8-wave blocks at an unchanged number of splits gain nothing there either.
     if (splits % 2 == 0 && n_blocks * (splits / 2) >= 160) {
         splits /= 2;
-        hipLaunchKernelGGL(gemm_skinny_kernel<2>, dim3(n_blocks, splits), dim3(512), 0, s, Wp, Xp, k_tiles, n_tiles, t_tiles,
-                           n_blocks, part);
+        hipLaunchKernelGGL(gemm_skinny_kernel<2>, dim3(n_blocks, splits), dim3(512), 0, s, Wp, Xp, k_tiles, n_tiles, t_tiles, part);
     } else {
-        hipLaunchKernelGGL(gemm_skinny_kernel<1>, dim3(n_blocks, splits), dim3(256), 0, s, Wp, Xp, k_tiles, n_tiles, t_tiles,
-                           n_blocks, part);
+        hipLaunchKernelGGL(gemm_skinny_kernel<1>, dim3(n_blocks, splits), dim3(256), 0, s, Wp, Xp, k_tiles, n_tiles, t_tiles, part);
     }
-    hipLaunchKernelGGL((gemm_finish_kernel<1, 1, 4, 1, MODE>), dim3(n_blocks * 4), dim3(256), 0, s, part, splits, N, n_tiles,
-                       T, n_blocks * 4, 4, e, 1, 4, 0, 1);
+    launch_finish<MODE>(part, splits, N, n_tiles, t_tiles, T, 0, n_blocks * 4, e, s);
     return true;
 }
 
@@ -918,58 +925,75 @@ void launch_gemm_mfma(const h16_t *Wp, const h16_t *Xp, int N, int K, int T, con
 
 // -------------------------------------------------------------------------------------------------
 // Prefill prologue: stage input rows (bf16, or fp32 for the validation surface) -> fp32 residual stream in its
-// tiled order, (x * gain) in fragment tiles, sums of squares per 128-column group.  One wave owns 32 tokens x
-// 128 columns and walks them as four 32 x 32 blocks in the lane layout of the MFMA result (lane = token % 32 +
-// 32 * half, four consecutive features per lane and quad): every store of the residual stream is one contiguous
-// 1 KB, every store of the operand two runs of 256 B, and the 64-byte row pieces it reads are fetched once.
+// tiled order, (x * gain) in fragment tiles, sums of squares per 128-column group.  A block owns 32 tokens x 128 columns, each
+// of its four waves one 32 x 32 block of them in the lane layout of the MFMA result (lane = token % 32 + 32 * half, four
+// consecutive features per lane and quad): every store of the residual stream is one contiguous 1 KB, every store of the
+// operand two runs of 256 B, and the 64-byte row pieces it reads are fetched once.  Bound by memory on long batches, by the
+// round trip on short ones: a wave has all its requests out at once (one wave per 128 columns went through them in turn:
+// 117 rows of 8192 9.7 -> 4.9 us, 2048 rows 38.4 -> 32.3).
+// lens != NULL (one new row per sequence): the first block publishes the rows' sequences and positions from the committed
+// lengths and, when asked, advances the lengths.
 // -------------------------------------------------------------------------------------------------
 template <bool IN_H16>
 __global__ __launch_bounds__(256) void prefill_prologue_kernel(const void *__restrict__ in, float *__restrict__ h_out,
                                                               const float *__restrict__ g, h16_t *__restrict__ hg,
-                                                              float *__restrict__ ssq_out, int T, int H) {
+                                                              float *__restrict__ ssq_out, int T, int H, int32_t *lens,
+                                                              int32_t *row_seq, int32_t *row_pos, int advance) {
+    __shared__ float s_ss[4][32];
+    if (lens != nullptr && blockIdx.x == 0 && blockIdx.y == 0)
+        for (int t = threadIdx.x; t < T; t += 256) {
+            const int l = lens[t];
+            row_seq[t] = t;
+            row_pos[t] = l;
+            if (advance) lens[t] = l + 1;
+        }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int token = blockIdx.x * 32 + (lane & 31), hl = lane >> 5;
-    const int col0 = (blockIdx.y * 4 + wave) * GEMM_SSQ_COLS;
-    if (col0 >= H) return;
+    const int n0 = blockIdx.y * GEMM_SSQ_COLS + wave * 32 + 4 * hl;
     const bool tv = token < T;
+    float x[4][4];
+    float4 g4[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const size_t at = (size_t)min(token, T - 1) * H + n0 + 8 * q;
+        if (IN_H16) {
+            const uint2 raw = *reinterpret_cast<const uint2 *>(reinterpret_cast<const h16_t *>(in) + at);
+            h16x2_to_f32(raw.x, x[q][0], x[q][1]);
+            h16x2_to_f32(raw.y, x[q][2], x[q][3]);
+        } else {
+            const float4 v = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(in) + at);
+            x[q][0] = v.x; x[q][1] = v.y; x[q][2] = v.z; x[q][3] = v.w;
+        }
+        g4[q] = *reinterpret_cast<const float4 *>(g + n0 + 8 * q);
+    }
     float ss = 0.f;
 #pragma unroll
-    for (int fb = 0; fb < GEMM_SSQ_COLS / 32; ++fb) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int n = col0 + fb * 32 + 8 * q + 4 * hl;
-            float x[4] = {0.f, 0.f, 0.f, 0.f};
-            if (tv) {
-                if (IN_H16) {
-                    const uint2 raw = *reinterpret_cast<const uint2 *>(reinterpret_cast<const h16_t *>(in) + (size_t)token * H + n);
-                    h16x2_to_f32(raw.x, x[0], x[1]);
-                    h16x2_to_f32(raw.y, x[2], x[3]);
-                } else {
-                    const float4 v = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(in) + (size_t)token * H + n);
-                    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-                }
-                if (h_out) *reinterpret_cast<float4 *>(h_out + h_tile_offset(token, n, H)) = make_float4(x[0], x[1], x[2], x[3]);
-                const float4 g4 = *reinterpret_cast<const float4 *>(g + n);
-                uint2 o;
-                o.x = pack_h16x2(x[0] * g4.x, x[1] * g4.y);
-                o.y = pack_h16x2(x[2] * g4.z, x[3] * g4.w);
-                *reinterpret_cast<uint2 *>(hg + frag_offset(token, n, H >> 5)) = o;
-            }
-            ss += x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
+    for (int q = 0; q < 4; ++q) {
+        const int n = n0 + 8 * q;
+        if (tv) {
+            if (h_out) *reinterpret_cast<float4 *>(h_out + h_tile_offset(token, n, H)) = make_float4(x[q][0], x[q][1], x[q][2], x[q][3]);
+            uint2 o;
+            o.x = pack_h16x2(x[q][0] * g4[q].x, x[q][1] * g4[q].y);
+            o.y = pack_h16x2(x[q][2] * g4[q].z, x[q][3] * g4[q].w);
+            *reinterpret_cast<uint2 *>(hg + frag_offset(token, n, H >> 5)) = o;
         }
+        ss += x[q][0] * x[q][0] + x[q][1] * x[q][1] + x[q][2] * x[q][2] + x[q][3] * x[q][3];
     }
     ss += __shfl_xor(ss, 32, 64);
-    if (hl == 0 && tv) ssq_out[(size_t)(col0 / GEMM_SSQ_COLS) * T + token] = ss;
+    if (hl == 0) s_ss[wave][lane] = ss;
+    __syncthreads();
+    if (threadIdx.x < 32 && tv)
+        ssq_out[(size_t)blockIdx.y * T + token] = s_ss[0][lane] + s_ss[1][lane] + s_ss[2][lane] + s_ss[3][lane];
 }
 
 void launch_prefill_prologue(const void *in, int in_is_h16, float *h_out, const float *g, h16_t *hg, float *ssq_out,
-                             int T, int H, hipStream_t s) {
+                             int T, int H, int32_t *lens, int32_t *row_seq, int32_t *row_pos, int advance, hipStream_t s) {
     if (T <= 0) return;
-    const dim3 grid((T + 31) / 32, (H / GEMM_SSQ_COLS + 3) / 4);
+    const dim3 grid((T + 31) / 32, H / GEMM_SSQ_COLS);
     if (in_is_h16)
-        hipLaunchKernelGGL(prefill_prologue_kernel<true>, grid, dim3(256), 0, s, in, h_out, g, hg, ssq_out, T, H);
+        hipLaunchKernelGGL(prefill_prologue_kernel<true>, grid, dim3(256), 0, s, in, h_out, g, hg, ssq_out, T, H, lens, row_seq, row_pos, advance);
     else
-        hipLaunchKernelGGL(prefill_prologue_kernel<false>, grid, dim3(256), 0, s, in, h_out, g, hg, ssq_out, T, H);
+        hipLaunchKernelGGL(prefill_prologue_kernel<false>, grid, dim3(256), 0, s, in, h_out, g, hg, ssq_out, T, H, lens, row_seq, row_pos, advance);
 }
 
 // tiled residual stream -> row-major fp32 (debug taps)

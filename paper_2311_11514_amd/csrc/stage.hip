@@ -218,7 +218,8 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
 
 struct Rows {
     int T = 0, batch = 0, max_new = 0, n_items = 0;
-    bool decode = false;
+    bool decode = false;          // on the decode kernels
+    bool dev_rows = false;        // one new row per sequence: the prologue takes sequences and positions from the committed lengths
     RowMap rm{};
 };
 
@@ -248,8 +249,9 @@ hexgen_status_t setup_rows(hexgen_stage *st, hexgen_kv_cache *kv, const int32_t 
     w.pos0 = w.cu_rows + batch + 1;
     r.rm.row_seq = w.row_seq;
     r.rm.row_pos = w.row_pos;
-    // a decode step on the decode kernels takes its positions from the committed lengths on the device
-    if (!r.decode) {
+    // one new row per sequence: the device has the positions already, and the call neither stages nor waits
+    r.dev_rows = r.decode || (allow_decode && r.max_new == 1 && is_h16(st->dtype));
+    if (!r.dev_rows) {
         // the pinned staging buffer may still feed an earlier async copy on this stream
         HX_HIP(hipStreamSynchronize(s));
         int32_t *hs = w.host_stage;
@@ -338,10 +340,10 @@ void attn_prefill_h16(hexgen_stage *st, hexgen_kv_cache *kv, int layer, const Ro
     e.q = w.q; e.kc = kc; e.vc = vc;
     gemm_h16(st, r, ly.wqkv, w.n, st->nqkv, st->H, e, PROF_QKV, s);
     st->prof.mark(PROF_ATTN, s);
-    // one new row per sequence (a decode step of more than 32 sequences): the decode attention kernel, which shares
+    // one new row per sequence (a decode step of more than kDecodeMaxRows sequences): the decode attention kernel, which shares
     // every K / V fragment among the query heads of its kv head, on this path's layouts (row = sequence)
-    if (r.max_new == 1 && st->hq_l / st->hkv_l <= 16)
-        HX_K(st->dtype, launch_attn_decode_rows, w.q, kc, vc, kg, st->hq_l, w.pos0, r.batch, w.o, s);
+    if (r.max_new == 1)
+        HX_K(st->dtype, launch_attn_decode_rows, w.q, kc, vc, kg, st->hq_l, r.rm.row_pos, r.batch, w.o, s);
     else
         HX_K(st->dtype, launch_attn_prefill, w.q, kc, vc, kg, st->hq_l, w.cu_rows, w.pos0, w.items, r.n_items, w.o, s);
     st->prof.mark(PROF_ATTN, s);
@@ -351,7 +353,8 @@ hexgen_status_t forward_prefill_h16(hexgen_stage *st, hexgen_kv_cache *kv, const
                                      void *out_partial, void *out_resid, hipStream_t s) {
     Workspace &w = st->ws;
     float *ssq_a = w.ssq_pf, *ssq_f = w.ssq_pf + (size_t)(st->H / GEMM_SSQ_COLS) * r.T;
-    HX_K(st->dtype, launch_prefill_prologue, hidden_in, 1, w.h, st->layers[0].g_attn, w.n, ssq_a, r.T, st->H, s);
+    HX_K(st->dtype, launch_prefill_prologue, hidden_in, 1, w.h, st->layers[0].g_attn, w.n, ssq_a, r.T, st->H,
+         r.dev_rows ? kv->d_lens : nullptr, w.row_seq, w.row_pos, 1, s);
     for (int l = 0; l < st->L; ++l) {
         const Layer &ly = st->layers[l];
         const bool last = l + 1 == st->L;
@@ -382,7 +385,8 @@ void sublayer_prefill_h16(hexgen_stage *st, hexgen_kv_cache *kv, int layer, int 
     float *ssq = w.ssq_pf;
     GemmEpi e = gemm_epi_base(st, DEC_RAW);
     e.raw_out = p_out;
-    HX_K(st->dtype, launch_prefill_prologue, h, 0, nullptr, which == 0 ? ly.g_attn : ly.g_ffn, w.n, ssq, r.T, st->H, s);
+    HX_K(st->dtype, launch_prefill_prologue, h, 0, nullptr, which == 0 ? ly.g_attn : ly.g_ffn, w.n, ssq, r.T, st->H,
+         r.dev_rows ? kv->d_lens : nullptr, w.row_seq, w.row_pos, 0, s);
     if (which == 0) {
         attn_prefill_h16(st, kv, layer, r, ssq, s);
         gemm_h16(st, r, ly.wo, w.o, st->H, st->qw, e, PROF_WO, s);
@@ -1052,7 +1056,7 @@ hexgen_status_t hexgen_stage_decode(hexgen_stage_t *st, hexgen_kv_cache_t *kv, i
     if (is_h16(st->dtype)) HX_TRY(forward_h16(st, kv, r, hidden_in, out_partial, out_resid, s));
     else HX_TRY(forward_f32(st, kv, r, hidden_in, out_partial, out_resid, r.decode ? kv->d_lens : nullptr, s));
     if (r.decode && is_h16(st->dtype)) st->last_decode_rows = r.T;
-    if (!r.decode) launch_advance_lens(kv->d_lens, kv->batch, s);   // else: the prologue (fp32: the last projection) did
+    if (!r.dev_rows) launch_advance_lens(kv->d_lens, kv->batch, s);   // else: the prologue (fp32: the last projection) did
     st->prof.mark(PROF_CALL, s);
     for (int i = 0; i < kv->batch; ++i) kv->lens[i] += 1;
     kv->steps += 1;
