@@ -126,10 +126,15 @@ __global__ __launch_bounds__(1024) void row_argmax_kernel(const float *__restric
     };
     if (VEC4) {
         const int n4 = (valid + 3) >> 2;          // the pitch is a multiple of 4: the last quad stays inside the row
-#pragma unroll 8
-        for (int q = threadIdx.x; q < n4; q += 1024) {
-            const floatx4 v = *reinterpret_cast<const floatx4 *>(row + 4 * q);
-            take(v[0], 4 * q); take(v[1], 4 * q + 1); take(v[2], 4 * q + 2); take(v[3], 4 * q + 3);
+        for (int q0 = threadIdx.x; q0 < n4; q0 += 8 * 1024) {
+            floatx4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const floatx4 *>(row + 4 * min(q0 + u * 1024, n4 - 1));
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int q = min(q0 + u * 1024, n4 - 1);         // past the end: the last quad again, which changes nothing
+                take(v[u][0], 4 * q); take(v[u][1], 4 * q + 1); take(v[u][2], 4 * q + 2); take(v[u][3], 4 * q + 3);
+            }
         }
     } else {
 #pragma unroll 4
