@@ -18,7 +18,7 @@ extern "C" {
  * around each projection launch, so per-kernel time can be read without an external profiler
  * (this costs a few microseconds per timed launch: enable it for measurement passes only).
  * Slots: 0 QKV projection, 1 W_O, 2 W1/W3 (+SwiGLU), 3 W2, 4 attention, 5 the whole call, 6 (decode calls of at most
- * 48 rows only) the first kernel of the W1/W3 projection alone: where that projection is a split kernel followed by a
+ * 32 rows only) the first kernel of the W1/W3 projection alone: where that projection is a split kernel followed by a
  * finishing kernel, slot 2 brackets the pair.
  * enable(slot_mask): bit i selects slot i (0 = off, 127 = all); synchronises and clears earlier records.
  * read() synchronises and returns the summed time in milliseconds and the number of timed launches.
@@ -29,7 +29,7 @@ hexgen_status_t hexgen_stage_profile_read(hexgen_stage_t *st, int slot, double *
  * `stream`: total_ms / launches is that kernel's duration without the per-launch event overhead of the slots above
  * (every launch streams a different layer's weights, as in a decode step).  Runs on the operands the last decode call
  * left in the workspace and overwrites only the workspace's FFN operand; HEXGEN_ERR_STATE before the first decode
- * call of at most 48 rows or on an fp32 stage.  Synchronises the stream.
+ * call of at most 32 rows or on an fp32 stage.  Synchronises the stream.
  */
 hexgen_status_t hexgen_stage_time_w13_decode(hexgen_stage_t *st, int reps, double *total_ms, int64_t *launches,
                                              void *stream);

@@ -638,23 +638,26 @@ static void launch_finish(const float *part, int splits, int N, int n_tiles, int
 }
 
 // -------------------------------------------------------------------------------------------------
-// Skinny form for one 128-token tile (a short prompt): the launch is bound by streaming the weights, not by the matrix
-// cores, so it is built like the decode projections.  A block of 4 waves owns 128 features x 128 tokens, a wave 32
-// features x 128 tokens; the weights never touch LDS: a lane requests the 16 bytes of the two 16-row tiles that the
+// Skinny form for up to 128 tokens (a short prompt): the launch is bound by streaming the weights, not by the matrix
+// cores, so it is built like the decode projections.  A group of 4 waves owns 128 features x 32 NT tokens, a wave 32
+// features; the weights never touch LDS: a lane requests the 16 bytes of the two 16-row tiles that the
 // 32x32x16 operand wants from it (two 512-byte runs per request), RING k-steps ahead, in a register ring that is
-// refilled slot by slot.  The activations of a k-step (8 KB, L2 hits) are shared by the block's waves through LDS,
+// refilled slot by slot.  The activations of a k-step (2 NT KB, L2 hits) are shared by the group's waves through LDS,
 // global -> registers (same ring) -> LDS one k-step before use.  The contraction is split over blockIdx.y; result
-// tiles go to `part`.
-// -------------------------------------------------------------------------------------------------
-constexpr int SKINNY_RING = 6;          // measured: 4, 6 and 8 run alike (the CU's load issue rate paces the kernel)
+// tiles go to `part`.  NT follows the prompt: what a launch pays for tokens beside its weights (operand reads, LDS, MFMAs) is
+// paid for 32-token blocks that exist (a TP4 layer of the 70B shape at 20 / 50 / 90 rows 142 / 145 / 153 -> 117 / 132 / 144 us).
+// (Meeting at a barrier once per chunk of 4 k-steps, with the next chunk's weights requested at its start instead of slot by
+// slot, is slower: W1/W3 of a TP4 70B shard at 117 rows 51 -> 59 us.)
 // KG = 2: a block of 8 waves = two groups of 4, each group walking one half of the block's share of the contraction
 // in step with the other (one barrier serves both) and the second group's results added to the first's through LDS
 // before anything is stored: as many waves and k-steps per wave as two blocks of 4 on two splits, half the partial sums.
-template <int KG>
+// -------------------------------------------------------------------------------------------------
+template <int KG, int NT>
 __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__restrict__ Wp, const h16_t *__restrict__ Xp,
                                                               int k_tiles, int n_tiles, int t_tiles, float *__restrict__ part) {
-    constexpr int RING = SKINNY_RING;
-    __shared__ h16x8 xs[KG][2][8 * 64];             // per group: two k-steps of the 8 token tiles
+    constexpr int RING = NT <= 2 ? 8 : 6, XT = 2 * NT, XW = (XT + 3) / 4;      // 16-token tiles of the block, and per wave
+    constexpr int XBUF = 2 * XT * 64, RED = 4 * NT * 16 * 64 / 4;       // LDS in h16x8: staging per group; sums of a group
+    __shared__ h16x8 smem[KG == 2 && RED > KG * XBUF ? RED : KG * XBUF];
     const int id = blockIdx.x;                       // 128-feature block
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int kg = wave >> 2, w4 = wave & 3;         // k-group, wave inside the group (32 features each)
@@ -668,49 +671,46 @@ __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__re
     const int t16 = min(id * 8 + w4 * 2 + ((lane & 31) >> 4), n_tiles - 1);
     const h16x8 *wsrc = reinterpret_cast<const h16x8 *>(Wp) + ((size_t)k0 * n_tiles + t16) * 64 + (lane & 15) + 16 * (lane >> 5);
     const size_t wstep = (size_t)n_tiles * 64;
-    // activations: wave w of a group copies token tiles 2 w and 2 w + 1 of each k-step (clamped to the last valid tile)
-    const h16x8 *xsrc[2];
+    // activations: wave w of a group copies token tiles w and w + 4 of each k-step (clamped to the last valid tile)
+    const h16x8 *xsrc[XW];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-        xsrc[i] = reinterpret_cast<const h16x8 *>(Xp) + ((size_t)min(w4 * 2 + i, t_tiles - 1) * k_tiles + k0) * 64 + lane;
+    for (int i = 0; i < XW; ++i)
+        xsrc[i] = reinterpret_cast<const h16x8 *>(Xp) + ((size_t)min(w4 + 4 * i, t_tiles - 1) * k_tiles + k0) * 64 + lane;
+    h16x8 *xs = smem + kg * XBUF;
     const int frag = ((lane & 31) >> 4) * 64 + (lane & 15) + 16 * (lane >> 5);
 
-    floatx16 acc[4];
+    floatx16 acc[NT];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
 
-    // Ring slot = one k-step: the wave's two weight operands and its two pieces of the activations.  Every request is
+    // Ring slot = one k-step: the wave's two weight operands and its pieces of the activations.  Every request is
     // unconditional (k-steps past the end re-read the last one, an L2 hit, unused), so the compiler counts requests in
     // flight exactly; because loads return in order, a piece of the activations must not be requested later than the
     // weights it is used with, or the wait for it would drain the weight requests behind which it sits.
-    h16x8 a[RING][2], xq[RING][2];
+    h16x8 a[RING][2], xq[RING][XW];
     auto request = [&](int slot, int kt) {
         const int kc = min(kt, k_len - 1);
-        xq[slot][0] = xsrc[0][(size_t)kc * 64];
-        xq[slot][1] = xsrc[1][(size_t)kc * 64];
+#pragma unroll
+        for (int i = 0; i < XW; ++i) xq[slot][i] = xsrc[i][(size_t)kc * 64];
         const h16x8 *src = wsrc + (size_t)kc * wstep;
         a[slot][0] = __builtin_nontemporal_load(src);
         a[slot][1] = __builtin_nontemporal_load(src + 32);
     };
     auto store_x = [&](int slot, int kt) {
-        xs[kg][kt & 1][(w4 * 2) * 64 + lane] = xq[slot][0];
-        xs[kg][kt & 1][(w4 * 2 + 1) * 64 + lane] = xq[slot][1];
+#pragma unroll
+        for (int i = 0; i < XW; ++i)
+            if (w4 + 4 * i < XT) xs[((kt & 1) * XT + w4 + 4 * i) * 64 + lane] = xq[slot][i];
     };
     auto step = [&](int slot, int kt) {
         if (KG > 1 && kt >= k_len) return;          // the shorter group's last k-step (uniform over the wave)
-        const h16x8 *sb = xs[kg][kt & 1] + frag;
+        const h16x8 *sb = xs + (kt & 1) * XT * 64 + frag;
 #pragma unroll
         for (int kh = 0; kh < 2; ++kh)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < NT; ++j)
                 acc[j] = hx_mfma32(a[slot][kh], sb[j * 128 + kh * 32], acc[j]);
-    };
-    // the barrier of a k-step waits for the LDS stores only: __syncthreads() would also drain the requests in flight
-    auto lds_barrier = [&]() {
-        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
-        asm volatile("s_barrier" ::: "memory");
     };
 #pragma unroll
     for (int i = 0; i < RING; ++i) request(i, i);
@@ -720,7 +720,9 @@ __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__re
 #pragma unroll
         for (int i = 0; i < RING; ++i) {
             const int kt = rd * RING + i;
-            lds_barrier();                // k-step kt is complete in LDS; the other buffer (k-step kt - 1) is free
+            // k-step kt is complete in LDS; the other buffer (k-step kt - 1) is free; a bare s_barrier behind the LDS
+            // stores only: __syncthreads() would also drain the requests in flight
+            HX_LDS_BARRIER();
             store_x((i + 1) % RING, kt + 1);
             step(i, kt);
             request(i, kt + RING);
@@ -731,37 +733,31 @@ __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__re
     for (int i = 0; i < RING; ++i) {
         const int kt = rounds * RING + i;
         if (kt < steps) {                 // uniform over the block
-            lds_barrier();
+            HX_LDS_BARRIER();
             store_x((i + 1) % RING, kt + 1);
             step(i, kt);
         }
     }
     if constexpr (KG == 2) {
-        // group 1 hands its results to group 0, two of the four token blocks at a time, through the 32 KB of the staging
-        // buffers (4 waves x 2 tiles x 16 registers x 64 lanes of fp32); group 0 + group 1, in that order, every time
-        float *red = reinterpret_cast<float *>(&xs[0][0][0]);
+        // group 1 hands its results to group 0 through the staging buffers; group 0 + group 1, in that order, every time
+        float *red = reinterpret_cast<float *>(smem);
+        __syncthreads();
+        if (kg == 1) {
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            __syncthreads();              // the staging buffers (first pass) or the previous pass's values are no longer read
-            if (kg == 1) {
+            for (int j = 0; j < NT; ++j)
 #pragma unroll
-                for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) red[((w4 * 2 + jj) * 16 + r) * 64 + lane] = acc[2 * half + jj][r];
-            }
-            __syncthreads();
-            if (kg == 0) {
-#pragma unroll
-                for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[2 * half + jj][r] += red[((w4 * 2 + jj) * 16 + r) * 64 + lane];
-            }
+                for (int r = 0; r < 16; ++r) red[((w4 * NT + j) * 16 + r) * 64 + lane] = acc[j][r];
         }
+        __syncthreads();
         if (kg != 0) return;
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[j][r] += red[((w4 * NT + j) * 16 + r) * 64 + lane];
     }
     const PartGeom pg = part_geom(n_tiles, t_tiles, 0, gridDim.x * 4);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NT; ++j)
         if (id * 4 + w4 < pg.nb && j < pg.tb) part_store(part + part_offset(pg, blockIdx.y, id * 4 + w4, j), acc[j], lane);
 }
 
@@ -844,11 +840,16 @@ static bool launch_skinny(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, 
     // 70B shape at 128 rows: W1/W3 (112 blocks x 4 -> x 2) 64.8 -> 59.4 us, W2 (64 x 8 -> x 4) 43.0 -> 38.5, 158.9 -> 149.8 us
     // per layer; with fewer than 160 blocks left the CUs that stay empty cost more (W_O 64 x 4 -> x 2: 22.1 -> 25.9,
     // QKV 20 x 8 -> x 4: 25.6 -> 32.4), and 8-wave blocks at an unchanged number of splits gain nothing there either.
-    if (splits % 2 == 0 && n_blocks * (splits / 2) >= 160) {
-        splits /= 2;
-        hipLaunchKernelGGL(gemm_skinny_kernel<2>, dim3(n_blocks, splits), dim3(512), 0, s, Wp, Xp, k_tiles, n_tiles, t_tiles, part);
-    } else {
-        hipLaunchKernelGGL(gemm_skinny_kernel<1>, dim3(n_blocks, splits), dim3(256), 0, s, Wp, Xp, k_tiles, n_tiles, t_tiles, part);
+    const bool pair = splits % 2 == 0 && n_blocks * (splits / 2) >= 160;
+    if (pair) splits /= 2;
+    auto run = [&](auto kern, int kg) {
+        hipLaunchKernelGGL(kern, dim3(n_blocks, splits), dim3(256 * kg), 0, s, Wp, Xp, k_tiles, n_tiles, t_tiles, part);
+    };
+    switch ((t_tiles + 1) / 2) {
+        case 1: if (pair) run(gemm_skinny_kernel<2, 1>, 2); else run(gemm_skinny_kernel<1, 1>, 1); break;
+        case 2: if (pair) run(gemm_skinny_kernel<2, 2>, 2); else run(gemm_skinny_kernel<1, 2>, 1); break;
+        case 3: if (pair) run(gemm_skinny_kernel<2, 3>, 2); else run(gemm_skinny_kernel<1, 3>, 1); break;
+        default: if (pair) run(gemm_skinny_kernel<2, 4>, 2); else run(gemm_skinny_kernel<1, 4>, 1); break;
     }
     launch_finish<MODE>(part, splits, N, n_tiles, t_tiles, T, 0, n_blocks * 4, e, s);
     return true;

@@ -31,12 +31,11 @@
 
 namespace {
 
-// Rows of a decode step on the weight-streaming decode kernels; beyond, the prefill projections.  Measured per layer of
-// 70B shards at context 600, prefill path against decode path: TP8 33 / 48 / 64 rows 108 / 109 / 110 -> 92 / 98 / 112 us, TP4
-// 140 / 144 / 147 -> 128 / 136 / 156, TP2 211 / 217 / 223 -> 199 / 209 / 242, full width 375 / 380 / 391 -> 353 / 365 / 421.
-constexpr int kDecodeMaxRows = 48;
+// Rows of a decode step on the weight-streaming decode kernels (hi + lo operands); beyond, the prefill projections.  Measured
+// per layer at context 600, decode path against prefill path: TP8 of the 70B shape at 33 / 48 / 64 rows 92 / 98 / 111 against
+// 91 / 91 / 93 us, TP4 127 / 134 / 153 against 120 / 119 / 123, full width 350 / 363 / 419 against 340 / 341 / 351.
+constexpr int kDecodeMaxRows = 32;
 constexpr int kHeadRows = 64;           // rows of one pass over the LM head's weights: a second pass costs more than 64 rows in one
-constexpr int kStaticMaxRows = 32;      // rows of a decode call on the static scratch
 constexpr int kF32StreamRows = 32;      // fp32: rows of the streaming projections
 constexpr int kAttnRows = 128;            // new rows per block of the prefill attention (4 waves x 32)
 constexpr int kMaxAttnSplit = 32;         // blocks per (sequence, kv head) the workspace has partials for
@@ -1071,7 +1070,7 @@ hexgen_status_t hexgen_stage_decode_static(hexgen_stage_t *st, hexgen_kv_cache_t
     if (!kv->prefilled || kv->batch <= 0 || step != kv->steps) return HEXGEN_ERR_STATE;
     HX_TRY(check_rope(st, kv));
     const int batch = kv->batch;
-    if (batch > kStaticMaxRows) return HEXGEN_ERR_CAPACITY;
+    if (batch > kDecodeMaxRows) return HEXGEN_ERR_CAPACITY;
     for (int i = 0; i < batch; ++i)
         if ((long)kv->lens[i] + 1 > kv->max_seq) return HEXGEN_ERR_CAPACITY;
     if (carve_decode_workspace(st, batch, nullptr, nullptr) > kStaticScratchBytes) return HEXGEN_ERR_CAPACITY;

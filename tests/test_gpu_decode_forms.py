@@ -1,7 +1,7 @@
 """The forms of the decode projections at the row counts where they change: operand tiles of 8 (hi and lo in one tile), 16,
-32, 48 and 64 rows, the single kernel against the split one with its finishing pass (a layer whose W1/W3 and W2 lie just
-beyond the line between them at three rows: 2052 feature tiles, 513 k-tiles), the prefill kernels beyond 48 rows, and the LM
-head's passes of 64 rows.  Gate: the suite's per-type tolerance; the hi + lo operands keep decode steps well below it."""
+32 rows and, for the LM head, 48 and 64, the single kernel against the split one with its finishing pass (a layer whose W1/W3 and W2 lie just
+beyond the line between them at three rows: 2052 feature tiles, 513 k-tiles), the prefill kernels' 32-token blocks beyond 32
+rows, and the LM head's passes of 64 rows.  Gate: the suite's per-type tolerance; the hi + lo operands keep decode steps well below it."""
 import numpy as np
 import pytest
 import torch
@@ -24,7 +24,7 @@ def _side(cfg):
     return _sides[cfg.name]
 
 
-@pytest.mark.parametrize("cfg,rows", [(WIDE, t) for t in (3, 8, 9, 17, 32, 33, 48, 49)] + [(NARROW, t) for t in (3, 9, 16, 31, 33, 47, 48, 49)],
+@pytest.mark.parametrize("cfg,rows", [(WIDE, t) for t in (3, 8, 9, 17, 32, 33, 64, 65)] + [(NARROW, t) for t in (3, 9, 16, 31, 33, 64, 65, 97)],
                          ids=lambda v: getattr(v, "name", v))
 def test_decode_step(cfg, rows):
     print(cfg.name, rows, flush=True)
