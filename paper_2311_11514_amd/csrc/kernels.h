@@ -44,7 +44,7 @@ void launch_mfma_probe(int variant, float *sink, int iters, int blocks, hipStrea
 // ---- 16-bit path (kernels_bf16_*.hip, compiled once per element type: namespaces bf16 and f16) --------------------
 
 // ---- decode projections with fused epilogues (kernels_bf16_decode.hip) ---------------------------
-enum { DEC_RAW = 0, DEC_QKV = 1, DEC_RESID = 2, DEC_SWIGLU = 3 };
+enum { DEC_RAW = 0, DEC_QKV = 1, DEC_RESID = 2, DEC_SWIGLU = 3, DEC_BEST = 4 };
 #define DEC_SCRATCH_RSTD 64    // floats at the end of the split projections' scratch: the rows' 1 / rms
 struct DecodeEpi {
     int mode;                  // DEC_*
@@ -55,6 +55,11 @@ struct DecodeEpi {
     int ssq_units, norm_dim;
     float eps;
     float *raw_out;            // RAW: [T][N] fp32
+    // BEST (decode only): per row and unit of columns (decode_best_units) the largest of the first `valid` columns' values and
+    // its index, lowest index on ties; -infinity and 0x7fffffff where there is none
+    float *best_val;
+    int32_t *best_id;
+    int valid;
     // QKV
     int hq_l;
     KvGeom kg;
@@ -111,6 +116,9 @@ struct GemmEpi {
 // per row of logits [n][ld]: the largest of the first `valid` entries and its index + id0 (lowest index wins ties)
 void launch_row_argmax(const float *logits, int64_t ld, int valid, int n, int id0, int32_t *token_out, float *logit_out,
                        hipStream_t s);
+// the same over per-unit candidates val / id [n][units] (DEC_BEST)
+void launch_row_best(const float *val, const int32_t *id, int units, int n, int id0, int32_t *token_out, float *logit_out,
+                     hipStream_t s);
 // rows_out[i] = table[clamp(tokens[i], 0, vocab - 1)], rows of row_bytes bytes (a multiple of 4)
 void launch_embed_rows(const void *table, int64_t row_bytes, int vocab, const int32_t *tokens, int n, void *rows_out,
                        hipStream_t s);

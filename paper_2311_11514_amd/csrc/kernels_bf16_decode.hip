@@ -18,6 +18,7 @@
 //            per-unit sum of squares of the new h, from which the next kernel derives rstd
 //   SWIGLU : x rstd, silu(gate) * up -> hi/lo operand of the W2 projection (gate / up tiles interleaved)
 //   RAW    : x rstd (if the input is a normalised stream), plain fp32 partial (validation surface)
+//   BEST   : x rstd, the unit's largest value per row and its column (LM head: no logits leave the kernel)
 // RMSNorm is thus never a kernel of its own in decode: y = rstd * ((h*g) . W), with rstd a per-row
 // scalar applied after the contraction.
 #include <algorithm>
@@ -124,6 +125,28 @@ __device__ inline void decode_epilogue(const floatx4 (&v)[UT], int unit, int b, 
         for (int u = 0; u < UT; ++u) {
             const int n0 = (unit * UT + u) * 16 + 4 * g;
             if (valid) *reinterpret_cast<floatx4 *>(e.raw_out + (size_t)token * N + n0) = v[u] * r;
+        }
+    } else if (MODE == DEC_BEST) {
+        float bv = -INFINITY;
+        int bi = 0x7fffffff;
+#pragma unroll
+        for (int u = 0; u < UT; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float x = v[u][j] * r;
+                const int n = (unit * UT + u) * 16 + 4 * g + j;
+                if (n < e.valid && (x > bv || (x == bv && n < bi))) { bv = x; bi = n; }
+            }
+#pragma unroll
+        for (int o = 16; o <= 32; o <<= 1) {
+            const float x = __shfl_xor(bv, o, 64);
+            const int n = __shfl_xor(bi, o, 64);
+            if (x > bv || (x == bv && n < bi)) { bv = x; bi = n; }
+        }
+        if (g == 0 && valid) {
+            const size_t at = (size_t)token * (N / 16 / UT) + unit;
+            e.best_val[at] = bv;
+            e.best_id[at] = bi;
         }
     } else if (MODE == DEC_RESID) {
         const int n0 = unit * 16 + 4 * g;
@@ -592,8 +615,9 @@ void launch_splitk(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, 
     const int n_tiles = N / 16, groups = (n_tiles + 7) / 8, np = dec_act_tiles(T);
     // Two blocks fit a CU (registers, 64 KB of LDS), 512 on the chip.  The number of splits (at most 8, or 16 for a matrix of
     // fewer than 64 feature groups: the finishing kernel walks them one after the other; partials within the scratch)
-    // minimises rounds of blocks x chunks per block, the time of the launch in units of one chunk per block; on a tie the
-    // fewer splits (less partial-sum traffic) win.
+    // minimises rounds of blocks x chunks per block, in units of one chunk per block (512 blocks x 64 KB: about 5.6 us), plus the
+    // partial sums' way through memory and back (about 5 TB/s: a wide matrix with a short contraction is not split into
+    // eight to save half a round); on a tie the fewer splits win.
     const int chunks = (k_tiles + sk_chunk(np) - 1) / sk_chunk(np);
     const size_t part_floats = scratch_floats - DEC_SCRATCH_RSTD;      // the tail of the scratch carries the rows' rstd
     float *rstd = scratch + part_floats;
@@ -602,7 +626,8 @@ void launch_splitk(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, 
     const int cap = groups * 8 < 512 ? 16 : 8;      // a narrow matrix (TP8 QKV: 10 groups) fills more of the chip with 16
     for (int c = 1; c <= std::min(cap, chunks); ++c) {
         if (c > 1 && (size_t)c * T * N > part_floats) break;
-        const long cost = (long)((groups * c + 511) / 512) * ((chunks + c - 1) / c) * 16 + c;
+        const long traffic = c > 1 ? (long)((double)c * T * N * 8.0 / 5e6 / 5.6 * 16.0) : 0;
+        const long cost = (long)((groups * c + 511) / 512) * ((chunks + c - 1) / c) * 16 + c + traffic;
         if (best < 0 || cost < best) { best = cost; splits = c; }
     }
     const dim3 grid(groups, splits);
@@ -643,12 +668,14 @@ bool decode_single_kernel(int mode, int N, int k_tiles, int T) {
     if (T <= 2) return true;
     if (T > 32) return false;
     if (k_tiles < 8) return true;              // not one chunk of the split kernel
-    const int units = N / 16 / (mode == DEC_SWIGLU || (mode == DEC_RAW && raw_pairs(N)) ? 2 : 1);
+    const int units = N / 16 / (mode == DEC_SWIGLU || ((mode == DEC_RAW || mode == DEC_BEST) && raw_pairs(N)) ? 2 : 1);
     const size_t operand = (size_t)units * k_tiles * dec_act_tiles(T) << 10;
     if (mode == DEC_QKV) return units >= 128 && operand <= (size_t)56 << 20;
     return operand <= (size_t)128 << 20;
 }
 }  // namespace
+
+int decode_best_units(int N) { return raw_pairs(N) ? N / 32 : N / 16; }
 
 void launch_decode_proj(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, const DecodeEpi &e, float *scratch,
                         size_t scratch_floats, hipStream_t s, hipEvent_t mid) {
@@ -660,6 +687,10 @@ void launch_decode_proj(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, c
             case DEC_QKV: launch_splitk<DEC_QKV, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
             case DEC_RESID: launch_splitk<DEC_RESID, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
             case DEC_SWIGLU: launch_splitk<DEC_SWIGLU, 2>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
+            case DEC_BEST:
+                if (raw_pairs(N)) launch_splitk<DEC_BEST, 2>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid);
+                else launch_splitk<DEC_BEST, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid);
+                break;
         }
         return;
     }
@@ -671,6 +702,10 @@ void launch_decode_proj(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, c
         case DEC_QKV: launch_mode<1, DEC_QKV>(Wp, Xa, N, k_tiles, T, e, s); break;
         case DEC_RESID: launch_mode<1, DEC_RESID>(Wp, Xa, N, k_tiles, T, e, s); break;
         case DEC_SWIGLU: launch_mode<2, DEC_SWIGLU>(Wp, Xa, N, k_tiles, T, e, s); break;
+        case DEC_BEST:
+            if (raw_pairs(N)) launch_mode<2, DEC_BEST>(Wp, Xa, N, k_tiles, T, e, s);
+            else launch_mode<1, DEC_BEST>(Wp, Xa, N, k_tiles, T, e, s);
+            break;
     }
     if (mid) (void)hipEventRecord(mid, s);
 }

@@ -109,37 +109,9 @@ void launch_stream_read(const void *src, float *sink, int64_t bytes, int blocks,
 }
 
 // ---- the model's ends: greedy argmax over a row of logits, embedding row gather --------------------------------
-// One block of 1024 threads per row.  Each thread scans a strided slice (four entries per load when the row pitch
-// allows it, eight loads in flight: a 32000-entry row is one round trip) keeping (value, lowest index); waves and then the
-// block reduce with the same rule, so the result is the first maximum of the row, as numpy / torch argmax define it.
-// Latency-bound: the reduction across lanes takes two barriers where a tree in LDS took eleven.
-template <bool VEC4>
-__global__ __launch_bounds__(1024) void row_argmax_kernel(const float *__restrict__ logits, int64_t ld, int valid, int id0,
-                                                         int32_t *__restrict__ token_out, float *__restrict__ logit_out) {
-    __shared__ float sv[16];
-    __shared__ int si[16];
-    const float *row = logits + (int64_t)blockIdx.x * ld;
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
-    auto take = [&](float v, int i) {
-        if (i < valid && (v > bv || (v == bv && i < bi))) { bv = v; bi = i; }
-    };
-    if (VEC4) {
-        const int n4 = (valid + 3) >> 2;          // the pitch is a multiple of 4: the last quad stays inside the row
-        for (int q0 = threadIdx.x; q0 < n4; q0 += 8 * 1024) {
-            floatx4 v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const floatx4 *>(row + 4 * min(q0 + u * 1024, n4 - 1));
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int q = min(q0 + u * 1024, n4 - 1);         // past the end: the last quad again, which changes nothing
-                take(v[u][0], 4 * q); take(v[u][1], 4 * q + 1); take(v[u][2], 4 * q + 2); take(v[u][3], 4 * q + 3);
-            }
-        }
-    } else {
-#pragma unroll 4
-        for (int i = threadIdx.x; i < valid; i += 1024) take(row[i], i);
-    }
+// (value, lowest index) over a block of 64 W threads, result in thread 0; sv, si: one entry per wave
+__device__ __forceinline__ void argmax_block(float &bv, int &bi, float *sv, int *si) {
+    const int waves = blockDim.x >> 6;
     auto reduce = [&](int lanes) {
         for (int o = lanes >> 1; o > 0; o >>= 1) {
             const float v = __shfl_xor(bv, o, 64);
@@ -151,21 +123,76 @@ __global__ __launch_bounds__(1024) void row_argmax_kernel(const float *__restric
     if ((threadIdx.x & 63) == 0) { sv[threadIdx.x >> 6] = bv; si[threadIdx.x >> 6] = bi; }
     __syncthreads();
     if (threadIdx.x >= 64) return;
-    bv = sv[threadIdx.x & 15];
-    bi = si[threadIdx.x & 15];
-    reduce(16);
+    bv = sv[threadIdx.x & (waves - 1)];
+    bi = si[threadIdx.x & (waves - 1)];
+    reduce(waves);
+}
+// One block of 1024 threads per row (fp32 logits, pitch a multiple of 4).  Each thread scans a strided slice, eight loads of
+// four entries in flight, keeping (value, lowest index); waves and then the block reduce with the same rule, so the result is
+// the first maximum of the row, as numpy / torch argmax define it.
+__global__ __launch_bounds__(1024) void row_argmax_kernel(const float *__restrict__ logits, int64_t ld, int valid, int id0,
+                                                         int32_t *__restrict__ token_out, float *__restrict__ logit_out) {
+    __shared__ float sv[16];
+    __shared__ int si[16];
+    const float *row = logits + (int64_t)blockIdx.x * ld;
+    float bv = -INFINITY;
+    int bi = 0x7fffffff;
+    auto take = [&](float v, int i) {
+        if (i < valid && (v > bv || (v == bv && i < bi))) { bv = v; bi = i; }
+    };
+    const int n4 = (valid + 3) >> 2;          // the pitch is a multiple of 4: the last quad stays inside the row
+    for (int q0 = threadIdx.x; q0 < n4; q0 += 8 * 1024) {
+        floatx4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const floatx4 *>(row + 4 * min(q0 + u * 1024, n4 - 1));
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int q = min(q0 + u * 1024, n4 - 1);         // past the end: the last quad again, which changes nothing
+            take(v[u][0], 4 * q); take(v[u][1], 4 * q + 1); take(v[u][2], 4 * q + 2); take(v[u][3], 4 * q + 3);
+        }
+    }
+    argmax_block(bv, bi, sv, si);
     if (threadIdx.x == 0) {
         token_out[blockIdx.x] = id0 + (bi == 0x7fffffff ? 0 : bi);
         if (logit_out) logit_out[blockIdx.x] = bv;
     }
 }
+// the same rule over candidates that the projection's epilogue left, a few thousand per row
+__global__ __launch_bounds__(512) void row_best_kernel(const float *__restrict__ val, const int32_t *__restrict__ id, int units,
+                                                      int id0, int32_t *__restrict__ token_out, float *__restrict__ logit_out) {
+    __shared__ float sv[8];
+    __shared__ int si[8];
+    const size_t row = (size_t)blockIdx.x * units;
+    float bv = -INFINITY;
+    int bi = 0x7fffffff;
+    for (int u0 = threadIdx.x; u0 < units; u0 += 4 * 512) {
+        float v[4];
+        int i[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int u = min(u0 + k * 512, units - 1);            // past the end: the last candidate again, which changes nothing
+            v[k] = val[row + u];
+            i[k] = id[row + u];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (v[k] > bv || (v[k] == bv && i[k] < bi)) { bv = v[k]; bi = i[k]; }
+    }
+    argmax_block(bv, bi, sv, si);
+    if (threadIdx.x == 0) {
+        token_out[blockIdx.x] = id0 + (bi == 0x7fffffff ? 0 : bi);
+        if (logit_out) logit_out[blockIdx.x] = bv;
+    }
+}
+void launch_row_best(const float *val, const int32_t *id, int units, int n, int id0, int32_t *token_out, float *logit_out,
+                     hipStream_t s) {
+    if (n <= 0) return;
+    hipLaunchKernelGGL(row_best_kernel, dim3(n), dim3(512), 0, s, val, id, units, id0, token_out, logit_out);
+}
 void launch_row_argmax(const float *logits, int64_t ld, int valid, int n, int id0, int32_t *token_out, float *logit_out,
                        hipStream_t s) {
     if (n <= 0) return;
-    if (ld % 4 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0)
-        hipLaunchKernelGGL(row_argmax_kernel<true>, dim3(n), dim3(1024), 0, s, logits, ld, valid, id0, token_out, logit_out);
-    else
-        hipLaunchKernelGGL(row_argmax_kernel<false>, dim3(n), dim3(1024), 0, s, logits, ld, valid, id0, token_out, logit_out);
+    hipLaunchKernelGGL(row_argmax_kernel, dim3(n), dim3(1024), 0, s, logits, ld, valid, id0, token_out, logit_out);
 }
 
 __global__ void embed_rows_kernel(const uint32_t *__restrict__ table, int64_t row_words, int vocab,

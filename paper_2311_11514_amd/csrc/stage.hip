@@ -1232,7 +1232,9 @@ struct hexgen_head {
     // workspace for one chunk of rows (head_chunk_rows)
     h16_t *xa = nullptr;         // bf16: (x * g) as hi/lo operand
     float *ssq = nullptr;         // bf16: sums of squares per 16 columns
-    float *logits = nullptr;      // [rows][Vpad]
+    float *logits = nullptr;      // f32: [rows][Vpad]
+    float *best_val = nullptr;    // bf16: candidates of the arg-max, [rows][units] (decode_best_units)
+    int32_t *best_id = nullptr;
     float *scratch = nullptr;     // split partial sums of the batched projection
     size_t scratch_floats = 0;
 };
@@ -1241,7 +1243,7 @@ namespace {
 // rows of one pass over the head's weights: what the projections of either type take at a time
 int head_chunk_rows(const hexgen_head *hd) { return is_h16(hd->dtype) ? kHeadRows : kF32StreamRows; }
 void free_head(hexgen_head *hd) {
-    void *ptrs[] = {hd->w, hd->g, hd->xa, hd->ssq, hd->logits, hd->scratch};
+    void *ptrs[] = {hd->w, hd->g, hd->xa, hd->ssq, hd->logits, hd->best_val, hd->best_id, hd->scratch};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -1263,9 +1265,12 @@ hexgen_status_t hexgen_head_create(int hidden, int vocab, int tp_degree, int tp_
     hd->Vpad = round_up(hd->Vl, 16);
     const size_t rows = (size_t)head_chunk_rows(hd);
     hexgen_status_t rc = dmalloc(&hd->g, (size_t)hidden);
-    if (rc == HEXGEN_OK) rc = dmalloc(&hd->logits, rows * hd->Vpad);
+    if (rc == HEXGEN_OK && !is_h16(dtype)) rc = dmalloc(&hd->logits, rows * hd->Vpad);
     if (rc == HEXGEN_OK && is_h16(dtype)) {
-        rc = dmalloc(&hd->xa, dec_act_elems((int)rows, hidden));
+        const size_t cands = rows * (size_t)bf16::decode_best_units(hd->Vpad);      // the same for either 16-bit type
+        rc = dmalloc(&hd->best_val, cands);
+        if (rc == HEXGEN_OK) rc = dmalloc(&hd->best_id, cands);
+        if (rc == HEXGEN_OK) rc = dmalloc(&hd->xa, dec_act_elems((int)rows, hidden));
         if (rc == HEXGEN_OK) rc = dmalloc(&hd->ssq, (size_t)(hidden / 16) * rows);
         hd->scratch_floats = rows * ((size_t)512 * 128 + 2 * (size_t)hd->Vpad);
         if (rc == HEXGEN_OK) rc = dmalloc(&hd->scratch, hd->scratch_floats);
@@ -1333,17 +1338,22 @@ hexgen_status_t hexgen_head_greedy(hexgen_head_t *hd, const void *hidden_a, cons
         const char *b = hidden_b ? static_cast<const char *>(hidden_b) + (size_t)r0 * H * es : nullptr;
         if (is_h16(hd->dtype)) {
             // same kernels as a decode projection: prologue (x = a + b, x * g as hi/lo operand, sums of squares),
-            // weight-streaming projection with 1 / rms applied after the contraction, fp32 logits
+            // weight-streaming projection with 1 / rms applied after the contraction; its epilogue keeps the best column of
+            // every unit, so that no logits are written and read back
             HX_K(hd->dtype, launch_decode_prologue, a, b, 1, nullptr, hd->g, hd->xa, hd->ssq, n, H, nullptr, nullptr, 0, s);
             DecodeEpi e;
             std::memset(&e, 0, sizeof(e));
-            e.mode = DEC_RAW;
+            e.mode = DEC_BEST;
             e.ssq_in = hd->ssq;
             e.ssq_units = H / 16;
             e.norm_dim = H;
             e.eps = hd->eps;
-            e.raw_out = hd->logits;
+            e.best_val = hd->best_val;
+            e.best_id = hd->best_id;
+            e.valid = hd->Vl;
             HX_K(hd->dtype, launch_decode_proj, static_cast<const h16_t *>(hd->w), hd->xa, hd->Vpad, H, n, e, hd->scratch, hd->scratch_floats, s);
+            launch_row_best(hd->best_val, hd->best_id, bf16::decode_best_units(hd->Vpad), n, hd->r * hd->Vl, token_out + r0,
+                            logit_out ? logit_out + r0 : nullptr, s);
         } else {
             F32Proj p;
             std::memset(&p, 0, sizeof(p));
@@ -1355,8 +1365,8 @@ hexgen_status_t hexgen_head_greedy(hexgen_head_t *hd, const void *hidden_a, cons
             p.eps = hd->eps;
             p.out = hd->logits;
             f32_launch_proj(F32_PLAIN, p, nullptr, nullptr, 0, s);
+            launch_row_argmax(hd->logits, hd->Vpad, hd->Vl, n, hd->r * hd->Vl, token_out + r0, logit_out ? logit_out + r0 : nullptr, s);
         }
-        launch_row_argmax(hd->logits, hd->Vpad, hd->Vl, n, hd->r * hd->Vl, token_out + r0, logit_out ? logit_out + r0 : nullptr, s);
     }
     HX_HIP(hipGetLastError());
     return HEXGEN_OK;

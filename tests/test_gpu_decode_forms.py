@@ -63,3 +63,29 @@ def test_head_rows(hidden, vocab, rows):
     assert np.max(np.abs(val.cpu().numpy() - top[:, -1]) / np.abs(top[:, -1])) < 2e-4
     clear = top[:, -1] - top[:, -2] > 1e-3 * np.abs(top[:, -1])
     assert clear.mean() > 0.8 and np.array_equal(tok.cpu().numpy()[clear], np.argmax(logits, axis=1)[clear])
+
+
+@pytest.mark.parametrize("rows", [1, 5, 40])
+def test_head_ties_and_rows_that_are_not_finite(rows):
+    """The lowest id wins an exact tie wherever the tied columns lie; a row of NaN has no candidate: the shard's first id."""
+    import paper_2311_11514_amd as hx
+    hidden, vocab = 1024, 4104
+    cfg = StageConfig("headties", "bf16", hidden, 8, 8, 64, 1, 1, (0,), batch=1, seed=804, vocab=vocab)
+    hw = generate.head_weights(cfg)
+    w, a = hw["w_lm"].clone(), generate.hidden_rows(cfg, rows, stream_id=3).to(torch.bfloat16)
+    best = torch.argmax((a.double() * hw["g_final"].double()) @ w.double(), dim=1)
+    w[:, 4100] = w[:, 7]
+    for i in range(rows):                                   # every row's best column twice more, in a tile of its own and the last
+        w[:, (int(best[i]) + 1000) % 4000] = w[:, int(best[i])]
+    first = torch.argmax((a.double() * hw["g_final"].double()) @ w.double(), dim=1)
+    hd = hx.Head(hidden, vocab, 1, 0, "bf16", cfg.rms_eps)
+    hd.load(hw["g_final"].cuda(), w.cuda())
+    tok, val = hd.greedy(a.cuda())
+    torch.cuda.synchronize()
+    same = [torch.equal(w[:, int(t)], w[:, int(f)]) for t, f in zip(tok.cpu(), first)]
+    assert all(int(t) == int(f) for t, f, s in zip(tok.cpu(), first, same) if s) and np.mean(same) > 0.8
+    a[0] = float("nan")
+    tok2, val2 = hd.greedy(a.cuda())
+    torch.cuda.synchronize()
+    assert int(tok2[0]) == 0 and float(val2[0]) == -float("inf")
+    assert torch.equal(tok2[1:], tok[1:]) and torch.equal(val2[1:], val[1:])
