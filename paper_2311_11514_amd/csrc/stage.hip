@@ -37,6 +37,7 @@ namespace {
 constexpr int kDecodeMaxRows = 32;
 constexpr int kHeadRows = 64;           // rows of one pass over the LM head's weights: a second pass costs more than 64 rows in one
 constexpr int kF32StreamRows = 32;      // fp32: rows of the streaming projections
+constexpr int kStageSlots = 4;
 constexpr int kAttnRows = 128;            // new rows per block of the prefill attention (4 waves x 32)
 constexpr int kMaxAttnSplit = 32;         // blocks per (sequence, kv head) the workspace has partials for
 constexpr int kStaticAttnSplit = 8;       // what pick_attn_split chooses at most, and what the static scratch is laid out for
@@ -90,8 +91,12 @@ struct Workspace {
     int32_t *rowmap = nullptr;       // one block: row_seq | row_pos | cu_rows | pos0, packed by the sizes of the call
     int32_t *row_seq = nullptr, *row_pos = nullptr, *cu_rows = nullptr, *pos0 = nullptr;   // views into rowmap
     int32_t *items = nullptr;        // view into rowmap: the prefill attention's work list, (sequence, 128-row block) pairs
-    int32_t *host_stage = nullptr;   // pinned staging for the arrays above
-    int host_stage_cap = 0;
+    // Pinned staging for the arrays above: kStageSlots pieces of host_stage_cap entries, taken in turn.  The event of a piece is
+    // recorded behind the copies that read it and waited for before the host writes it again, so that a call only waits
+    // for the copies of the call kStageSlots earlier.
+    int32_t *host_stage = nullptr;
+    int host_stage_cap = 0, stage_next = 0;
+    hipEvent_t stage_ev[kStageSlots] = {};
 };
 
 }  // namespace
@@ -106,6 +111,8 @@ struct hexgen_stage {
     std::vector<void *> taps;
     Workspace ws;
     Workspace *cur = nullptr;        // the workspace the decode flow runs on: &ws, or a view of the static scratch array
+    hipStream_t last_stream = nullptr;      // stream of the last call that enqueued work (compared, never used)
+    bool has_last_stream = false;
     int last_decode_rows = 0;        // rows of the last decode call that ran on the weight-streaming kernels
     int ws_batch_cap = 0;
     int64_t weight_bytes = 0;
@@ -140,6 +147,8 @@ void free_ws(Workspace &w) {
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (w.host_stage) (void)hipHostFree(w.host_stage);
+    for (hipEvent_t e : w.stage_ev)
+        if (e) (void)hipEventDestroy(e);
     w = Workspace();
 }
 
@@ -205,8 +214,9 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
     // row_seq, row_pos, cu_rows, pos0, new lengths, attention work list (at most rows / 128 + batch pairs)
     w.host_stage_cap = 2 * rows + 3 * batch + 1 + 2 * (rows / kAttnRows + batch);
     HX_TRY(dmalloc(&w.rowmap, (size_t)w.host_stage_cap));
-    HX_HIP(hipHostMalloc(reinterpret_cast<void **>(&w.host_stage), (size_t)w.host_stage_cap * sizeof(int32_t),
+    HX_HIP(hipHostMalloc(reinterpret_cast<void **>(&w.host_stage), (size_t)kStageSlots * w.host_stage_cap * sizeof(int32_t),
                          hipHostMallocDefault));
+    for (hipEvent_t &e : w.stage_ev) HX_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     w.cap_rows = rows;
     st->ws_batch_cap = batch;
     // the zero fills above ran on the null stream; the caller's stream may be a non-blocking one that does not
@@ -217,10 +227,23 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
 
 struct Rows {
     int T = 0, batch = 0, max_new = 0, n_items = 0;
+    int slot = 0;                 // staging piece of the call (host-built row maps only)
     bool decode = false;          // on the decode kernels
     bool dev_rows = false;        // one new row per sequence: the prologue takes sequences and positions from the committed lengths
     RowMap rm{};
 };
+
+// Work that takes host-side state of this moment along (row maps, staged copies) cannot be recorded for replay.
+hexgen_status_t refuse_capture(hipStream_t s) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    HX_HIP(hipStreamIsCapturing(s, &c));
+    return c == hipStreamCaptureStatusNone ? HEXGEN_OK : HEXGEN_ERR_DEVICE;
+}
+
+void note_stream(hexgen_stage *st, hipStream_t s) {
+    st->last_stream = s;
+    st->has_last_stream = true;
+}
 
 // Validate the new rows against the cache and build the device row maps.
 hexgen_status_t setup_rows(hexgen_stage *st, hexgen_kv_cache *kv, const int32_t *seq_lens, int batch,
@@ -240,7 +263,9 @@ hexgen_status_t setup_rows(hexgen_stage *st, hexgen_kv_cache *kv, const int32_t 
     if (total > 0x3fffffff) return HEXGEN_ERR_CAPACITY;
     r.T = (int)total;
     r.decode = allow_decode && r.max_new == 1 && r.T <= (is_h16(st->dtype) ? kDecodeMaxRows : kF32StreamRows);
+    if (!r.decode) HX_TRY(refuse_capture(s));
     HX_TRY(ensure_workspace(st, r.T, batch));
+    note_stream(st, s);
     Workspace &w = st->ws;
     w.row_seq = w.rowmap;
     w.row_pos = w.rowmap + r.T;
@@ -251,9 +276,10 @@ hexgen_status_t setup_rows(hexgen_stage *st, hexgen_kv_cache *kv, const int32_t 
     // one new row per sequence: the device has the positions already, and the call neither stages nor waits
     r.dev_rows = r.decode || (allow_decode && r.max_new == 1 && is_h16(st->dtype));
     if (!r.dev_rows) {
-        // the pinned staging buffer may still feed an earlier async copy on this stream
-        HX_HIP(hipStreamSynchronize(s));
-        int32_t *hs = w.host_stage;
+        r.slot = w.stage_next;
+        w.stage_next = (w.stage_next + 1) % kStageSlots;
+        HX_HIP(hipEventSynchronize(w.stage_ev[r.slot]));
+        int32_t *hs = w.host_stage + (size_t)r.slot * w.host_stage_cap;
         int32_t *h_seq = hs, *h_pos = hs + r.T, *h_cu = hs + 2 * r.T, *h_p0 = h_cu + batch + 1;
         int row = 0;
         for (int i = 0; i < batch; ++i) {
@@ -293,6 +319,7 @@ hexgen_status_t setup_rows(hexgen_stage *st, hexgen_kv_cache *kv, const int32_t 
         w.items = w.rowmap + items_off;
         // host staging and device block share one packing: a single copy moves all the arrays
         HX_HIP(hipMemcpyAsync(w.rowmap, hs, sizeof(int32_t) * (items_off + 2 * (size_t)n_items), hipMemcpyHostToDevice, s));
+        HX_HIP(hipEventRecord(w.stage_ev[r.slot], s));
     }
     *out = r;
     return HEXGEN_OK;
@@ -1023,8 +1050,18 @@ hexgen_status_t hexgen_stage_prefill(hexgen_stage_t *st, hexgen_kv_cache_t *kv, 
     long total = 0;
     for (int i = 0; i < batch; ++i) total += seq_lens[i];
     if (total > 0x3fffffff) return HEXGEN_ERR_CAPACITY;
+    HX_TRY(refuse_capture(s));
     HX_TRY(ensure_workspace(st, (int)total, batch));     // every check that can fail comes before the cache is touched
-    HX_TRY(hexgen_kv_cache_reset(kv));
+    // Start a new batch.  On the stream of the stage's last call, stream order keeps this prefill behind everything that
+    // still uses the workspace or the cache, and the host runs ahead (a wait here left the GPU idle for the launch of the
+    // whole call: 30 .. 40 us of a 117-row prompt's 470); on any other stream, wait as the cache's reset does.
+    if (!st->has_last_stream || st->last_stream != s || s == hipStreamPerThread) HX_HIP(hipDeviceSynchronize());
+    bool stale_tail = false;                             // lengths beyond this batch that the device still holds
+    for (int i = batch; i < kv->max_batch; ++i) stale_tail = stale_tail || kv->lens[i] != 0;
+    std::fill(kv->lens.begin(), kv->lens.end(), 0);
+    kv->batch = 0;
+    kv->prefilled = false;
+    kv->steps = 0;
     Rows r;
     HX_TRY(setup_rows(st, kv, seq_lens, batch, false, s, &r));      // a prefill always takes the GEMM path
     st->prof.mark(PROF_CALL, s);
@@ -1036,9 +1073,11 @@ hexgen_status_t hexgen_stage_prefill(hexgen_stage_t *st, hexgen_kv_cache_t *kv, 
     kv->prefilled = true;
     kv->steps = 0;
     // the new lengths reach the device in stream order, behind the kernels of this call
-    int32_t *h_len = st->ws.host_stage + 2 * r.T + 2 * batch + 1;
+    int32_t *h_len = st->ws.host_stage + (size_t)r.slot * st->ws.host_stage_cap + 2 * r.T + 2 * batch + 1;
     for (int i = 0; i < batch; ++i) h_len[i] = seq_lens[i];
     HX_HIP(hipMemcpyAsync(kv->d_lens, h_len, sizeof(int32_t) * batch, hipMemcpyHostToDevice, s));
+    HX_HIP(hipEventRecord(st->ws.stage_ev[r.slot], s));
+    if (stale_tail) launch_fill_zero(kv->d_lens + batch, (size_t)(kv->max_batch - batch) * sizeof(int32_t), s);
     return HEXGEN_OK;
 }
 
@@ -1077,6 +1116,7 @@ hexgen_status_t hexgen_stage_decode_static(hexgen_stage_t *st, hexgen_kv_cache_t
     unsigned char *base = nullptr;
     HX_TRY(static_scratch_ptr(&base));
     hipStream_t s = static_cast<hipStream_t>(stream);
+    note_stream(st, s);
     Workspace view;
     (void)carve_decode_workspace(st, batch, base, &view);
     // what must start at zero: the arrival counters of the split attention and the sums of squares (a fill kernel,
@@ -1174,6 +1214,7 @@ hexgen_status_t hexgen_stage_time_w13_decode(hexgen_stage_t *st, int reps, doubl
     HX_TRY(check_loaded(st));
     if (!is_h16(st->dtype) || st->last_decode_rows <= 0) return HEXGEN_ERR_STATE;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    note_stream(st, s);
     Workspace &w = st->ws;
     Rows r;
     r.T = st->last_decode_rows;
