@@ -223,7 +223,8 @@ __device__ __forceinline__ void f32_finish4(const F32Proj &p, int t, int n, floa
 // neighbouring columns of one row).  32-deep k-steps, two LDS buffers, the next step's global loads in registers while the
 // current one is multiplied, one barrier per step.  A step is 32 MFMAs of 64 cycles per wave against 28 LDS reads: bound
 // by the matrix cores; 53 KB of LDS lets three blocks share a CU and cover each other's barriers.  Measured at 572 rows x
-// 2048 x 11264 (SwiGLU): 883 -> 315 us, 84 TFLOP/s of the 154 a large library product reaches; two layers 6270 -> 1276 us.
+// 2048 x 11264 (SwiGLU): 883 -> 297 us, 89 TFLOP/s of the 154 a large library product reaches (792 blocks: the fullest CU has
+// four, the average 3.1); two layers 6270 -> 1142 us.
 // blockIdx.z: split of the contraction (see f32_launch_proj); the splits' sums go to `part` and f32_tile_finish_kernel.
 // -------------------------------------------------------------------------------------------------
 constexpr int F32_BT = 64, F32_BN = 128, F32_BK = 32, F32_XS = 36, F32_WS = 136;     // row strides of the LDS tiles (floats)
@@ -267,24 +268,37 @@ __global__ __launch_bounds__(256) void f32_tile_kernel(F32Proj p, float *__restr
     load(k_lo);
     store(0);
     __syncthreads();
+    // operands of the 8-row group s of a step; k-slot hl of MFMA x = row 8 s + 4 hl + x
+    floatx4 x4[2];
+    floatx2 w2[2][4];
+    auto fetch = [&](int buf, int s) {
+        x4[s & 1] = *reinterpret_cast<const floatx4 *>(&sx[buf][32 * wt + l32][8 * s + 4 * hl]);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const float *row = sw[buf][8 * s + 4 * hl + x];
+            if constexpr (GLU) w2[s & 1][x] = floatx2{row[32 * wn + l32], row[64 + 32 * wn + l32]};
+            else w2[s & 1][x] = *reinterpret_cast<const floatx2 *>(row + 64 * wn + 2 * l32);
+        }
+    };
+    // The order is held by scheduling barriers: left to itself the compiler moves the next step's global loads down to their
+    // use at the end of the step and fetches every group's operands right in front of its MFMAs.
     for (int k = k_lo; k < k_hi; ++k) {
         const int buf = (k - k_lo) & 1;
         load(min(k + 1, k_hi - 1));
+        fetch(buf, 0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < F32_BK / 8; ++s) {
-            // k-slot hl of MFMA x = row 8 s + 4 hl + x of the step
-            const floatx4 x4 = *reinterpret_cast<const floatx4 *>(&sx[buf][32 * wt + l32][8 * s + 4 * hl]);
+            if (s + 1 < F32_BK / 8) fetch(buf, s + 1);
+            else store(buf ^ 1);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
-                const float *row = sw[buf][8 * s + 4 * hl + x];
-                floatx2 a;
-                if constexpr (GLU) a = floatx2{row[32 * wn + l32], row[64 + 32 * wn + l32]};
-                else a = *reinterpret_cast<const floatx2 *>(row + 64 * wn + 2 * l32);
-                acc[0] = f32_mfma32(a[0], x4[x], acc[0]);
-                acc[1] = f32_mfma32(a[1], x4[x], acc[1]);
+                acc[0] = f32_mfma32(w2[s & 1][x][0], x4[s & 1][x], acc[0]);
+                acc[1] = f32_mfma32(w2[s & 1][x][1], x4[s & 1][x], acc[1]);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        store(buf ^ 1);
         __syncthreads();
     }
     const int t = bt + 32 * wt + l32;
