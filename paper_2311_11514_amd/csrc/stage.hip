@@ -432,17 +432,20 @@ int pick_attn_split(const hexgen_stage *st, const hexgen_kv_cache *kv, int batch
     int mx = 0;
     for (int i = 0; i < batch; ++i) mx = std::max(mx, kv->lens[i] + 1);
     const int n_t32 = (mx + 31) / 32;
-    // Enough (sequence, kv head) pairs to fill the chip, or a context short enough that one block's eight waves walk it
+    // Enough (sequence, kv head) pairs to occupy the chip, or a context short enough that one block's eight waves walk it
     // in a few steps: one block per pair.  (Measured on a ragged batch of 32 x 8 pairs, contexts 240..4027: the launch
     // ends 11 us after the same bytes in equal contexts would, but every way of cutting the long contexts -- evenly, or
     // only those above the even share per CU -- costs more than that: a block's fixed part, query load and the merge of
     // its waves, is about 7 us and a CU holds one 8-wave block at a time.)
     // Otherwise every context is split evenly: a block's time falls with the number of splits (one CU's load path
-    // delivers about 150 GB/s), while every block adds its own tail (partials written through, the count, the merge);
-    // the measured optimum sits near sqrt(4 tiles / pairs).
+    // delivers about 150 GB/s), while every block adds its own tail (partials written through, the count, the merge).
+    // Few pairs: the measured optimum sits near sqrt(6 tiles / pairs).  From 32 pairs on only a walk that is long against
+    // them is cut, in three (equal contexts, us per launch unsplit / in three: 32 pairs at 2048 and 4000 positions 21.5 / 19.1 and
+    // 30.4 / 21.5, 64 pairs at 2048 and 4000 22.5 / 23.3 and 44.9 / 31.6, 128 pairs at 4000 49.0 / 57.2).
     const int pairs = batch * st->hkv_l;
-    if (pairs >= 32 || n_t32 <= 48) return 1;
-    const int s = (int)std::lround(std::sqrt(4.0 * n_t32 / pairs));
+    if (n_t32 <= 48) return 1;
+    if (pairs >= 32) return pairs <= 64 && 2 * n_t32 >= 3 * pairs + 32 ? 3 : 1;
+    const int s = (int)std::lround(std::sqrt(6.0 * n_t32 / pairs));
     return std::max(2, std::min({s, kStaticAttnSplit, (n_t32 + 7) / 8}));
 }
 
