@@ -83,8 +83,11 @@ struct DecodeEpi {
 struct QkvTail {
     const float *part;         // [splits][T][N] partial sums; NULL: q and the cache rows are complete already
     int splits, T, N;
-    const float *rstd;         // [T] 1/rms of the rows, left by the split kernel
+    const float *rstd;         // [T] 1/rms of the rows, left by the split kernel (decode kernels' layouts) ...
     const float *cos_tab, *sin_tab;
+    const float *ssq;          // ... or [norm_dim / 128][T] the rows' sums of squares (prefill kernels' layouts)
+    int norm_dim;
+    float eps;
 };
 // ---- prefill projections with fused epilogues (kernels_bf16_gemm.hip) ----------------------------
 // Same epilogue roles as in decode (DEC_* modes), on packed operands: the input Xp is (h * gain) in

@@ -34,9 +34,8 @@ struct QkvStage {
 // 8..15 the elements half a head further (the layout decode_epilogue<DEC_QKV> reads as well).  Ends with a barrier.
 template <int D, int NT>
 __device__ __forceinline__ void qkv_tail_stage(const QkvTail &tail, QkvStage<D> &st, int sq, int c, int G, int hq_l,
-                                               const KvGeom &kg, int pos, bool append, h16_t *kc, h16_t *vc) {
+                                               const KvGeom &kg, int pos, bool append, h16_t *kc, h16_t *vc, float r) {
     constexpr int TPH = D / 16, HALF = D / 2;
-    const float r = tail.rstd[sq];
     const size_t slab = (size_t)sq * kg.seq_stride + (size_t)c * kg.smax * D;
     for (int idx = threadIdx.x; idx < (G + 2) * TPH * 2; idx += NT) {
         const int hh = idx / (TPH * 2), rem = idx - hh * TPH * 2, tl = rem >> 1, q2 = rem & 1;
@@ -152,7 +151,6 @@ __global__ __launch_bounds__(512) void attn_decode_block_kernel(const h16_t *__r
                                                                const int32_t *__restrict__ row_pos,
                                                                h16_t *__restrict__ o_act, float scale_log2e, QkvTail tail) {
     constexpr int KT = D / 32, DT = D / 16, W = 8;
-    static_assert(!(PF && FUSE), "the prefill path finishes its projections in their own epilogues");
     __shared__ float s_m[W][16], s_l[W][16];
     __shared__ float s_o[W][16][D];
     __shared__ __align__(16) QkvStage<FUSE ? D : 8> s_qkv;
@@ -180,8 +178,19 @@ __global__ __launch_bounds__(512) void attn_decode_block_kernel(const h16_t *__r
     };
     if constexpr (FUSE) {
         // the wave's first tile is requested before the projection's tail is finished: the two wait side by side
-        if (wave < n_t32) load_tile(wave);
-        qkv_tail_stage<D, 512>(tail, reinterpret_cast<QkvStage<D> &>(s_qkv), sq, c, G, hq_l, kg, n_pos - 1, true, kc, vc);
+        float r;
+        if constexpr (PF) {
+            float ss = 0.f;
+            for (int i = lane; i < tail.norm_dim / GEMM_SSQ_COLS; i += 64) ss += tail.ssq[(size_t)i * tail.T + sq];
+            if (wave < n_t32) load_tile(wave);
+#pragma unroll
+            for (int x = 1; x < 64; x <<= 1) ss += __shfl_xor(ss, x, 64);
+            r = 1.0f / sqrtf(ss / (float)tail.norm_dim + tail.eps);
+        } else {
+            if (wave < n_t32) load_tile(wave);
+            r = tail.rstd[sq];
+        }
+        qkv_tail_stage<D, 512>(tail, reinterpret_cast<QkvStage<D> &>(s_qkv), sq, c, G, hq_l, kg, n_pos - 1, true, kc, vc, r);
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) {
             qf[kt] = *reinterpret_cast<const h16x8 *>(&reinterpret_cast<QkvStage<D> &>(s_qkv).qh[j][kt * 32 + 8 * g]);
@@ -333,7 +342,7 @@ __global__ __launch_bounds__(512) void attn_decode_split_kernel(const h16_t *__r
         // every block of the pair finishes q for itself; the block that holds the last tile appends the new row; the
         // wave's first tile is requested before that, so that the two wait side by side
         if (t0 + wave < t1) load_tile(t0 + wave);
-        qkv_tail_stage<D, 512>(tail, reinterpret_cast<QkvStage<D> &>(s_qkv), sq, c, G, hq_l, kg, n_pos - 1, split == nb - 1, kc, vc);
+        qkv_tail_stage<D, 512>(tail, reinterpret_cast<QkvStage<D> &>(s_qkv), sq, c, G, hq_l, kg, n_pos - 1, split == nb - 1, kc, vc, tail.rstd[sq]);
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) {
             qf[kt] = *reinterpret_cast<const h16x8 *>(&reinterpret_cast<QkvStage<D> &>(s_qkv).qh[j][kt * 32 + 8 * g]);
@@ -508,19 +517,18 @@ void launch_attn_decode(const h16_t *q, const h16_t *q_lo, h16_t *kc, h16_t *vc,
 }
 
 // one new row per sequence on the prefill path's layouts: q and o in fragment tiles (row = sequence)
-void launch_attn_decode_rows(const h16_t *q, const h16_t *kc, const h16_t *vc, KvGeom kg, int hq_l,
-                             const int32_t *row_pos, int b, h16_t *o_packed, hipStream_t s) {
+void launch_attn_decode_rows(const h16_t *q, h16_t *kc, h16_t *vc, KvGeom kg, int hq_l,
+                             const int32_t *row_pos, int b, h16_t *o_packed, const QkvTail &tail, hipStream_t s) {
     const int G = hq_l / kg.hkv_l;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)kg.d);
-    const QkvTail none{nullptr, 0, 0, 0, nullptr, nullptr, nullptr};
-    h16_t *kw = const_cast<h16_t *>(kc), *vw = const_cast<h16_t *>(vc);       // read only without a QkvTail
+    const bool fuse = tail.part != nullptr;
     dim3 grid(kg.hkv_l, b);
-    if (kg.d == 128)
-        hipLaunchKernelGGL((attn_decode_block_kernel<128, true, false>), grid, dim3(512), 0, s, q, q, kw, vw, kg, hq_l, G, row_pos,
-                           o_packed, scale_log2e, none);
-    else
-        hipLaunchKernelGGL((attn_decode_block_kernel<64, true, false>), grid, dim3(512), 0, s, q, q, kw, vw, kg, hq_l, G, row_pos,
-                           o_packed, scale_log2e, none);
+#define HX_ROWS(DD, FF)                                                                                                  \
+    hipLaunchKernelGGL((attn_decode_block_kernel<DD, true, FF>), grid, dim3(512), 0, s, q, q, kc, vc, kg, hq_l, G, row_pos, \
+                       o_packed, scale_log2e, tail)
+    if (kg.d == 128) { if (fuse) HX_ROWS(128, true); else HX_ROWS(128, false); }
+    else { if (fuse) HX_ROWS(64, true); else HX_ROWS(64, false); }
+#undef HX_ROWS
 }
 
 // -------------------------------------------------------------------------------------------------

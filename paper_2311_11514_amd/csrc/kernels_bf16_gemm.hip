@@ -654,7 +654,7 @@ static void launch_finish(const float *part, int splits, int N, int n_tiles, int
 // -------------------------------------------------------------------------------------------------
 template <int KG, int NT>
 __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__restrict__ Wp, const h16_t *__restrict__ Xp,
-                                                              int k_tiles, int n_tiles, int t_tiles, float *__restrict__ part) {
+                                                              int k_tiles, int n_tiles, int t_tiles, float *__restrict__ part, int T_rows) {
     constexpr int RING = NT <= 2 ? 8 : 6, XT = 2 * NT, XW = (XT + 3) / 4;      // 16-token tiles of the block, and per wave
     constexpr int XBUF = 2 * XT * 64, RED = 4 * NT * 16 * 64 / 4;       // LDS in h16x8: staging per group; sums of a group
     __shared__ h16x8 smem[KG == 2 && RED > KG * XBUF ? RED : KG * XBUF];
@@ -756,6 +756,20 @@ __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__re
             for (int r = 0; r < 16; ++r) acc[j][r] += red[((w4 * NT + j) * 16 + r) * 64 + lane];
     }
     const PartGeom pg = part_geom(n_tiles, t_tiles, 0, gridDim.x * 4);
+    if (T_rows > 0) {                    // row-major sums [split][row][feature] for a consumer that works on whole rows
+        const int n0 = (id * 4 + w4) * 32 + 4 * (lane >> 5), N = n_tiles * 16;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int row = 32 * j + (lane & 31);
+            if (row >= T_rows) continue;
+            float *dst = part + ((size_t)blockIdx.y * T_rows + row) * N;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (n0 + 8 * q < N)
+                    *reinterpret_cast<floatx4 *>(dst + n0 + 8 * q) = floatx4{acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+        }
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < NT; ++j)
         if (id * 4 + w4 < pg.nb && j < pg.tb) part_store(part + part_offset(pg, blockIdx.y, id * 4 + w4, j), acc[j], lane);
@@ -827,7 +841,7 @@ static double gemm_estimate_us(int tm, int tt, double step_us, int n_tiles, int 
 // one 128-token tile, at least 32 k-tiles: skinny kernel + finishing pass; returns false when it does not apply
 template <int MODE>
 static bool launch_skinny(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, int n_tiles, int t_tiles, int T,
-                          const GemmEpi &e, float *part, size_t part_floats, hipStream_t s) {
+                          const GemmEpi &e, float *part, size_t part_floats, hipStream_t s, QkvTail *tail = nullptr) {
     if (part == nullptr || t_tiles > 8 || k_tiles < 32) return false;
     const int n_blocks = (n_tiles + 7) / 8;
     const PartGeom pg = part_geom(n_tiles, t_tiles, 0, n_blocks * 4);
@@ -843,7 +857,7 @@ static bool launch_skinny(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, 
     const bool pair = splits % 2 == 0 && n_blocks * (splits / 2) >= 160;
     if (pair) splits /= 2;
     auto run = [&](auto kern, int kg) {
-        hipLaunchKernelGGL(kern, dim3(n_blocks, splits), dim3(256 * kg), 0, s, Wp, Xp, k_tiles, n_tiles, t_tiles, part);
+        hipLaunchKernelGGL(kern, dim3(n_blocks, splits), dim3(256 * kg), 0, s, Wp, Xp, k_tiles, n_tiles, t_tiles, part, tail != nullptr ? T : 0);
     };
     switch ((t_tiles + 1) / 2) {
         case 1: if (pair) run(gemm_skinny_kernel<2, 1>, 2); else run(gemm_skinny_kernel<1, 1>, 1); break;
@@ -851,7 +865,8 @@ static bool launch_skinny(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, 
         case 3: if (pair) run(gemm_skinny_kernel<2, 3>, 2); else run(gemm_skinny_kernel<1, 3>, 1); break;
         default: if (pair) run(gemm_skinny_kernel<2, 4>, 2); else run(gemm_skinny_kernel<1, 4>, 1); break;
     }
-    launch_finish<MODE>(part, splits, N, n_tiles, t_tiles, T, 0, n_blocks * 4, e, s);
+    if (tail != nullptr) *tail = QkvTail{part, splits, T, N, nullptr, e.cos_tab, e.sin_tab, e.ssq_in, e.norm_dim, e.eps};
+    else launch_finish<MODE>(part, splits, N, n_tiles, t_tiles, T, 0, n_blocks * 4, e, s);
     return true;
 }
 
@@ -922,6 +937,22 @@ void launch_gemm_mfma(const h16_t *Wp, const h16_t *Xp, int N, int K, int T, con
         case DEC_RESID: launch_mode<DEC_RESID>(Wp, Xp, N, K, T, e, part, part_floats, s); break;
         case DEC_SWIGLU: launch_mode<DEC_SWIGLU>(Wp, Xp, N, K, T, e, part, part_floats, s); break;
     }
+}
+
+// A row's finishing pass -- its heads' sums over the splits, rotary embedding, cache append -- is a few KB that the attention
+// block of the same (sequence, kv head) reads while its first K / V tiles are on their way: one launch and one trip of q
+// through memory less.  It lengthens every block by about 3 us, so it is left to the attention only where all of the blocks
+// run at once (512: two per CU).  Measured per layer at 33 / 64 / 100 / 128 rows, 600 positions, without -> with: TP8 shard of
+// the 70B shape 90.6 / 92.7 / 108.4 / 111.7 -> 86.2 / 89.8 / 106.1 / 109.8 us, TP4 119.4 / 123.5 / 144.4 / 152.2 -> 115.0 /
+// 120.6 / 141.6 / 149.3; 8 kv heads of a 4096-wide model 126.5 / 143.5 / 185.5 / 197.5 -> 124.2 / 142.5 / 189.6 / 199.8, of a
+// 2048-wide one 69.5 / 77.5 / 98.6 / 104.3 -> 68.5 / 76.8 / 102.9 / 107.3: beyond 512 blocks it loses.
+void launch_gemm_qkv_rows(const h16_t *Wp, const h16_t *Xp, int N, int K, int T, const GemmEpi &e, float *part,
+                          size_t part_floats, QkvTail *tail, hipStream_t s) {
+    *tail = QkvTail{};
+    if (T * e.kg.hkv_l <= 512 && e.ssq_in != nullptr && g_force_tile.load(std::memory_order_relaxed) == 0 &&
+        launch_skinny<DEC_QKV>(Wp, Xp, N, K / 32, N / 16, (T + 15) / 16, T, e, part, part_floats, s, tail))
+        return;
+    launch_gemm_mfma(Wp, Xp, N, K, T, e, part, part_floats, s);
 }
 
 // -------------------------------------------------------------------------------------------------

@@ -364,12 +364,21 @@ void attn_prefill_h16(hexgen_stage *st, hexgen_kv_cache *kv, int layer, const Ro
     e.ssq_in = ssq_in;
     e.hq_l = st->hq_l; e.kg = kg; e.rm = r.rm; e.cos_tab = kv->cos_tab; e.sin_tab = kv->sin_tab;
     e.q = w.q; e.kc = kc; e.vc = vc;
-    gemm_h16(st, r, ly.wqkv, w.n, st->nqkv, st->H, e, PROF_QKV, s);
-    st->prof.mark(PROF_ATTN, s);
     // one new row per sequence (a decode step of more than kDecodeMaxRows sequences): the decode attention kernel, which shares
     // every K / V fragment among the query heads of its kv head, on this path's layouts (row = sequence)
-    if (r.max_new == 1)
-        HX_K(st->dtype, launch_attn_decode_rows, w.q, kc, vc, kg, st->hq_l, r.rm.row_pos, r.batch, w.o, s);
+    const bool rows = r.max_new == 1;
+    QkvTail tail{};
+    st->prof.mark(PROF_QKV, s);
+    if (rows)
+        HX_K(st->dtype, launch_gemm_qkv_rows, static_cast<const h16_t *>(ly.wqkv), w.n, st->nqkv, st->H, r.T, e, w.gemm_part,
+             w.gemm_part_floats, &tail, s);
+    else
+        HX_K(st->dtype, launch_gemm_mfma, static_cast<const h16_t *>(ly.wqkv), w.n, st->nqkv, st->H, r.T, e, w.gemm_part,
+             w.gemm_part_floats, s);
+    st->prof.mark(PROF_QKV, s);
+    st->prof.mark(PROF_ATTN, s);
+    if (rows)
+        HX_K(st->dtype, launch_attn_decode_rows, w.q, kc, vc, kg, st->hq_l, r.rm.row_pos, r.batch, w.o, tail, s);
     else
         HX_K(st->dtype, launch_attn_prefill, w.q, kc, vc, kg, st->hq_l, w.cu_rows, w.pos0, w.items, r.n_items, w.o, s);
     st->prof.mark(PROF_ATTN, s);

@@ -47,6 +47,30 @@ def test_decode_step(cfg, rows):
         check(f"{rows} rows step {k} partial", p, p_ref, TOL[cfg.dtype])
 
 
+@pytest.mark.parametrize("cfg,rows", [(NARROW, 35), (NARROW, 128), (NARROW, 129), (WIDE, 64), (WIDE, 65), (WIDE, 129)], ids=lambda v: getattr(v, "name", v))
+def test_decode_rows_around_position_tiles(cfg, rows):
+    """More than 32 sequences: the attention finishes the QKV projection (up to 128 rows and 512 (row, kv head) pairs, beyond
+    that the projection does) and appends the new row, at contexts on both sides of the 32-position tiles and of the 8 tiles that its waves take in one go."""
+    print(cfg.name, rows, flush=True)
+    ora, st = _side(cfg)
+    edge = (1, 31, 32, 33, 63, 64, 255, 256, 257, 290)
+    lens = [edge[i % len(edge)] for i in range(rows)]
+    oc = ora.new_cache(rows)
+    kv = st.kv_cache_create(rows, 320)
+    for l in range(cfg.n_layers):
+        for i in range(rows):
+            k, v = generate.synthetic_kv(cfg, l, i, lens[i])
+            kv.fill(l, i, k, v)
+            oc.fill(l, i, k, v)
+    kv.set_lengths(lens)
+    for k in range(2):
+        x = generate.hidden_rows(cfg, rows, stream_id=1 + k)
+        p_ref, h_ref = ora.decode(oc, x)
+        p, hh = gpu_decode(st, kv, cfg, k, x)
+        check(f"{rows} rows step {k} resid", hh, h_ref, TOL[cfg.dtype])
+        check(f"{rows} rows step {k} partial", p, p_ref, TOL[cfg.dtype])
+
+
 @pytest.mark.parametrize("hidden,vocab,rows", [(128, 1000, 40), (1024, 4104, 33), (1024, 4104, 48), (1024, 4104, 49), (1024, 4104, 64), (1024, 4104, 65)])
 def test_head_rows(hidden, vocab, rows):
     import paper_2311_11514_amd as hx
