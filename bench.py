@@ -198,8 +198,8 @@ def hbm_roofline(cfg, b, k):
     achieved = k["bytes_per_launch"] / (k["avg_launch_us"] * 1e-6) / 1e9
     name = ("decode_splitk_kernel<4> (W1/W3 projection, 17..32 rows; its finishing kernel with the SwiGLU epilogue "
             "follows)" if b > 16 else
-            "decode_splitk_kernel<1> (W1/W3 projection, 3..16 rows; finishing kernel follows)" if b > 2 else
-            "decode_proj_kernel<1,2,8,4,SWIGLU> (W1/W3 projection + SwiGLU epilogue)")
+            "decode_proj_kernel or decode_splitk_kernel, by size (W1/W3 projection, 3..16 rows)" if b > 2 else
+            "decode_proj_kernel (W1/W3 projection + SwiGLU epilogue, one or two rows)")
     traffic, src = measured_traffic(cfg.name)
     return {"bound": "hbm", "kernel": name, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "traffic_source": src, **k}

@@ -237,6 +237,7 @@ constexpr int kXldsMaxBytes = 64 * 1024;      // activation operand staged in LD
 // NP = 0: one or two rows, compact operand.  XLDS: the whole operand is staged once per block in LDS, so the main loop
 // issues nothing but weight loads; otherwise each lane fetches its 16-byte pieces per k-tile (L2 hits).
 // NP = 1, 2, 4: 3 to 8, 16, 32 rows, NP operand tiles per k-tile (dec_act_offset), each one contiguous 1 KB request.
+// UT: feature tiles of a block: one unit of the epilogue (a gate and an up tile for SWIGLU), or two of them (unit_pairs).
 template <int NP, int UT, int WAVES, int UNROLL, int MODE, bool XLDS, int XR>
 __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__restrict__ Wp,
                                                                 const h16_t *__restrict__ Xa, int N, int k_tiles,
@@ -276,8 +277,11 @@ __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__
     // (every request below is unconditional, out-of-range ones re-read a valid address: the compiler can only count
     // requests in flight exactly, and so wait for the oldest alone, when none of them sits behind a branch)
     EpiPre pre;
-    const bool finisher = wave < NB;          // wave b finishes token tile b
-    if (finisher) epi_request_first<MODE>(pre, unit, wave, lane, N, T, e);
+    // wave b finishes token tile b; the two feature tiles of a residual block are finished by waves of their own
+    constexpr int FU = MODE == DEC_RESID || MODE == DEC_QKV ? 1 : MODE == DEC_SWIGLU ? 2 : UT, FG = UT / FU;
+    const int fb = wave % NB, fu = wave / NB;
+    const bool finisher = wave < NB * FG;
+    if (finisher) epi_request_first<MODE>(pre, unit * FG + fu, fb, lane, N, T, e);
     h16x8 xr[XLDS ? XR : 1];
     const int n16 = T * k_tiles * 8;
     if (XLDS) {
@@ -306,7 +310,7 @@ __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__
     };
 #pragma unroll
     for (int i = 0; i < UNROLL; ++i) request(i, min(wave + i * WAVES, k_tiles - 1));
-    if (finisher) epi_request_second<MODE>(pre, unit, lane, e);
+    if (finisher) epi_request_second<MODE>(pre, unit * FG + fu, lane, e);
     if (XLDS) {
 #pragma unroll
         for (int j = 0; j < XR; ++j) {
@@ -377,19 +381,19 @@ __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__
     __syncthreads();
     if (!finisher) return;
 
-    const int b = wave;
-    floatx4 v[UT];
+    floatx4 v[FU];
 #pragma unroll
-    for (int u = 0; u < UT; ++u) {
-        v[u] = red[0][u * NB + b][lane];
+    for (int u = 0; u < FU; ++u) {
+        const int at = (fu * FU + u) * NB + fb;
+        v[u] = red[0][at][lane];
 #pragma unroll
-        for (int w = 1; w < WAVES; ++w) v[u] += red[w][u * NB + b][lane];
+        for (int w = 1; w < WAVES; ++w) v[u] += red[w][at][lane];
         if (NP == 1) {          // token columns 8 .. 15 hold the lo parts of tokens 0 .. 7
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[u][r] += __shfl_xor(v[u][r], 8, 64);
         }
     }
-    decode_epilogue<MODE, UT>(v, unit, b, lane, N, T, e, s_rstd, pre);
+    decode_epilogue<MODE, FU>(v, unit * FG + fu, fb, lane, N, T, e, s_rstd, pre);
 }
 
 // -------------------------------------------------------------------------------------------------
@@ -586,7 +590,8 @@ void launch_mode(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, co
         if (short_k) launch_one<NP, UT, 4, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);                        \
         else launch_one<NP, UT, 8 / UT, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);                           \
     } while (0)
-    if (T > 16) HX_ONE(4);
+    constexpr int NPM = UT == 4 ? 2 : 4;          // (blocks of four feature tiles take 16 rows at most: unit_pairs)
+    if (T > 16) HX_ONE(NPM);
     else if (T > 8) HX_ONE(2);
     else if (T > 2) HX_ONE(1);
     // One or two rows.  With W_O, W2 and W1/W3 each wave fetches its operand pieces through its request ring instead of the
@@ -650,8 +655,44 @@ void launch_splitk(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, 
 }  // namespace
 
 namespace {
-// two feature tiles per block (2 KB of weights per wave and k-tile) stream a few percent faster than one
-bool raw_pairs(int N) { return (N / 16) % 2 == 0 && N / 32 >= 512; }
+// two feature tiles per unit of the LM head from 1024 tiles on: 2 KB of weights per wave and k-tile stream a few percent faster
+bool best_pairs(int N) { return (N / 16) % 2 == 0 && N / 32 >= 512; }
+
+// Single kernel: one unit (16 result features) per block, or two?  Two halve what the blocks read of the operand and the number
+// of blocks; a CU holds both of its blocks either way, so what decides is how evenly they go over the 256 CUs -- with n units the
+// fullest CU has ceil(n / 256) of them, or 2 ceil(n / 512) in pairs -- and, on a long stream of weights, the requests in flight.
+// Measured per layer, one unit -> two (us):
+//   RESID  n = 512 (8192 wide), weights up to 112 MiB, 3 rows on: TP8 of the 70B shape at 3 / 16 / 32 rows 58.8 / 66.4 / 81.2 ->
+//          58.1 / 63.8 / 74.1, TP4 92.3 / 102.4 / 120.9 -> 90.3 / 100.1 / 114.6; one and two rows: +0 .. +0.3, and +4 for the 224 MiB
+//          of TP2's W2; 128 MiB: +0 .. +2.
+//          n = 288 .. 448 (equal rounds, uneven ones): 5120 wide (two ranks) 1 / 3 / 16 / 32 rows 74.4 / 80.3 / 95.0 / 118.4 -> 66.1 /
+//          73.5 / 90.3 / 112.2, 6144 wide 82.7 / 88.3 / 98.9 / 117.4 -> 76.9 / 82.3 / 92.9 / 111.6; one and two rows gain at any size
+//          (6144 x 16384, one rank: 150.2 -> 142.1), more rows lose beyond 120 MiB (4096 x 20480 at 3 rows: 126.1 -> 131.2).
+//          n = 256: 4096 x 11264 at 1 / 3 / 8 rows 80.2 / 83.7 / 85.0 -> 75.1 / 82.0 / 83.8, 16 rows 97.6 -> 98.2.  n = 128: +4.
+//   QKV    up to 8 rows, n = 288 / 320 / 384: 7168 wide 109.1 -> 106.1, TP2 155.1 -> 152.9, 3072 wide at 1 / 8 rows 51.3 / 55.9 ->
+//          50.1 / 53.4, 4096 wide at 8 rows 83.8 -> 82.1; n = 160, 192, 480, 640: +0.6 .. +4.4.
+//   W1/W3  (a unit is a gate and an up tile) up to 16 rows, n = 288 / 352 / 432 / 448 / 512: 2048 wide at 1 / 8 / 16 rows 35.4 / 36.9 /
+//          42.8 -> 34.4 / 35.6 / 40.6, TP4 at 8 / 16 rows 91.6 / 99.8 -> 89.5 / 95.1 (16: the split contraction before), 5120 wide at
+//          16 rows 95.0 -> 89.9; one and two rows gain below 384 and lose 0.4 .. 0.8 at 432, 448; up to 8 rows at n = 864 / 896 (TP2
+//          at 1 / 3 / 8 rows 152.9 / 155.5 / 157.7 -> 150.9 / 154.4 / 155.6; 3 and 8: split before).
+//          n = 224, 640, 704, 1280 (more units on the fullest CU): +1.5 .. +7.
+bool unit_pairs(int mode, int N, int k_tiles, int T) {
+    const int n = N / 16 / (mode == DEC_SWIGLU ? 2 : 1);
+    if (n % 2 != 0) return false;
+    const bool moderate = (size_t)N * k_tiles * 64 <= (size_t)120 << 20;
+    switch (mode) {
+        case DEC_RAW: case DEC_BEST: return best_pairs(N);
+        case DEC_RESID:
+            if (n < 256) return false;
+            if (n < 512 && T <= 2) return true;
+            return moderate && (n >= 512 ? T > 2 : n > 256 || T <= 8);
+        case DEC_QKV: return n > 256 && n <= 384 && T <= 8;
+        case DEC_SWIGLU:
+            if (n > 768 && n <= 896) return T <= 8;
+            return n > 256 && (T <= 2 ? n <= 384 : n <= 512 && T <= 16);
+    }
+    return false;
+}
 
 // One kernel with complete dot products per block, or a contraction split over blocks and a finishing pass?  One or two
 // rows: always one kernel.  More: the single kernel saves the partial sums and the second launch (4 .. 5 us), and pays with
@@ -668,14 +709,15 @@ bool decode_single_kernel(int mode, int N, int k_tiles, int T) {
     if (T <= 2) return true;
     if (T > 32) return false;
     if (k_tiles < 8) return true;              // not one chunk of the split kernel
-    const int units = N / 16 / (mode == DEC_SWIGLU || ((mode == DEC_RAW || mode == DEC_BEST) && raw_pairs(N)) ? 2 : 1);
-    const size_t operand = (size_t)units * k_tiles * dec_act_tiles(T) << 10;
-    if (mode == DEC_QKV) return units >= 128 && operand <= (size_t)56 << 20;
+    const int units = N / 16 / (mode == DEC_SWIGLU ? 2 : 1), pair = unit_pairs(mode, N, k_tiles, T) ? 2 : 1;
+    const size_t operand = (size_t)(units / pair) * k_tiles * dec_act_tiles(T) << 10;
+    if (mode == DEC_QKV) return units >= 128 && operand * pair <= (size_t)56 << 20;
+    if (mode == DEC_RESID && pair == 2) return true;
     return operand <= (size_t)128 << 20;
 }
 }  // namespace
 
-int decode_best_units(int N) { return raw_pairs(N) ? N / 32 : N / 16; }
+int decode_best_units(int N) { return best_pairs(N) ? N / 32 : N / 16; }
 
 void launch_decode_proj(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, const DecodeEpi &e, float *scratch,
                         size_t scratch_floats, hipStream_t s, hipEvent_t mid) {
@@ -688,24 +730,25 @@ void launch_decode_proj(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, c
             case DEC_RESID: launch_splitk<DEC_RESID, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
             case DEC_SWIGLU: launch_splitk<DEC_SWIGLU, 2>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
             case DEC_BEST:
-                if (raw_pairs(N)) launch_splitk<DEC_BEST, 2>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid);
+                if (best_pairs(N)) launch_splitk<DEC_BEST, 2>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid);
                 else launch_splitk<DEC_BEST, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid);
                 break;
         }
         return;
     }
+    const bool pair = unit_pairs(e.mode, N, k_tiles, T);
     switch (e.mode) {
-        case DEC_RAW:
-            if (raw_pairs(N)) launch_mode<2, DEC_RAW>(Wp, Xa, N, k_tiles, T, e, s);
-            else launch_mode<1, DEC_RAW>(Wp, Xa, N, k_tiles, T, e, s);
-            break;
-        case DEC_QKV: launch_mode<1, DEC_QKV>(Wp, Xa, N, k_tiles, T, e, s); break;
-        case DEC_RESID: launch_mode<1, DEC_RESID>(Wp, Xa, N, k_tiles, T, e, s); break;
-        case DEC_SWIGLU: launch_mode<2, DEC_SWIGLU>(Wp, Xa, N, k_tiles, T, e, s); break;
-        case DEC_BEST:
-            if (raw_pairs(N)) launch_mode<2, DEC_BEST>(Wp, Xa, N, k_tiles, T, e, s);
-            else launch_mode<1, DEC_BEST>(Wp, Xa, N, k_tiles, T, e, s);
-            break;
+#define HX_UNITS(MODE, U)                                                          \
+    case MODE:                                                                     \
+        if (pair) launch_mode<2 * U, MODE>(Wp, Xa, N, k_tiles, T, e, s);           \
+        else launch_mode<U, MODE>(Wp, Xa, N, k_tiles, T, e, s);                    \
+        break;
+        HX_UNITS(DEC_RAW, 1)
+        HX_UNITS(DEC_QKV, 1)
+        HX_UNITS(DEC_RESID, 1)
+        HX_UNITS(DEC_SWIGLU, 2)
+        HX_UNITS(DEC_BEST, 1)
+#undef HX_UNITS
     }
     if (mid) (void)hipEventRecord(mid, s);
 }

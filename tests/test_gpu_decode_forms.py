@@ -14,6 +14,9 @@ pytestmark = pytest.mark.gpu
 
 WIDE = StageConfig("wide", "bf16", 4096, 32, 8, 16416, 1, 1, (0,), batch=1, seed=801)
 NARROW = StageConfig("narrow", "f16", 512, 8, 2, 1472, 2, 2, (1,), batch=1, seed=802)      # W_O: 8 k-tiles, W2: 23
+# the single kernel's blocks of two units: QKV 352 feature tiles, W_O and W2 288, W1/W3 290 gate / up pairs; and W1/W3 at 772
+PAIRS = StageConfig("pairs", "bf16", 4608, 36, 4, 4640, 1, 1, (0,), batch=1, seed=806)
+GATED = StageConfig("gated", "f16", 1024, 8, 2, 12352, 2, 1, (0,), batch=1, seed=807)
 _sides = {}
 
 
@@ -24,7 +27,8 @@ def _side(cfg):
     return _sides[cfg.name]
 
 
-@pytest.mark.parametrize("cfg,rows", [(WIDE, t) for t in (3, 8, 9, 17, 32, 33, 64, 65)] + [(NARROW, t) for t in (3, 9, 16, 31, 33, 64, 65, 97)],
+@pytest.mark.parametrize("cfg,rows", [(WIDE, t) for t in (3, 8, 9, 17, 32, 33, 64, 65)] + [(NARROW, t) for t in (3, 9, 16, 31, 33, 64, 65, 97)] +
+                         [(PAIRS, t) for t in (1, 2, 3, 8, 9, 16, 17, 32)] + [(GATED, t) for t in (1, 2, 3)],
                          ids=lambda v: getattr(v, "name", v))
 def test_decode_step(cfg, rows):
     print(cfg.name, rows, flush=True)
