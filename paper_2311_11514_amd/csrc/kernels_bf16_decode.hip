@@ -702,7 +702,9 @@ bool unit_pairs(int mode, int N, int k_tiles, int T) {
 //          16 rows:  46 -2.9 (2048-wide), 117 -1.3 (TP8), 235 +3.0 (TP4)
 //   W2      8 rows:  23 -4.1 (2048-wide), 59 -2.0 (TP8), 117 0.0 (TP4), 235 +1.7    16 rows: 46 -3.3, 117 -0.9, 185 +1.4, 235 +3.7
 //   W_O     8 rows:  17 -3.5, 33 -2.3, 134 -0.8    16 rows: 34 -2.8, 134 -0.2, 268 +3.8    32 rows: 67 -3.2, 134 -2.7, 268 +2.0
-// The line is 128 MiB.  The QKV projection has no finishing launch to save (the attention sums its partials):
+// with one unit per block.  The line is 128 MiB.  Blocks of two units halve the reads: W1/W3 is counted so (TP4 at 16 rows 99.8 ->
+// 95.1 us per layer, one kernel instead of two), W_O and W2 are one kernel wherever unit_pairs admits them (TP8 W2 at 32 rows 79.6 ->
+// 74.3, TP2 W_O 187.5 -> 182.5, TP4 W2, 224 MiB, 116.7 -> 114.7).  The QKV projection has no finishing launch to save (the attention sums its partials):
 //           8 rows:  42 -0.9 (TP4), 50 -0.6, 84 +3.5 (TP2)    16 rows: 25 -1.0, 84 +1.5
 // 56 MiB, and at least 128 blocks (TP8 has 80: +0.9 .. +4.7).
 bool decode_single_kernel(int mode, int N, int k_tiles, int T) {
