@@ -91,7 +91,9 @@ hexgen_status_t hexgen_kv_cache_reset(hexgen_kv_cache_t *kv);
 
 /* ---- prefill (paper Section 2, prefill equations) ------------------------------------------
  * Packed (varlen) rows: sequence i occupies rows [cu_i, cu_i + seq_lens[i]) with cu the running
- * sum, at positions 0 .. seq_lens[i]-1.  Starts a new batch: the cache is reset first.
+ * sum, at positions 0 .. seq_lens[i]-1.  Starts a new batch: the cache is reset first, behind everything that is on the
+ * device at that time, whatever stream it is on (recorded steps being replayed among it); the call does not wait for the
+ * kernels it then enqueues.  It cannot be recorded into a graph (HEXGEN_ERR_DEVICE).
  *   hidden_in   device [total_rows, hidden], dtype           (activations from the previous stage)
  *   seq_lens    HOST int32 [batch], every entry >= 1
  *   out_partial device [total_rows, hidden], dtype: last layer's FFN partial P_ffn^(r), no residual

@@ -111,8 +111,6 @@ struct hexgen_stage {
     std::vector<void *> taps;
     Workspace ws;
     Workspace *cur = nullptr;        // the workspace the decode flow runs on: &ws, or a view of the static scratch array
-    hipStream_t last_stream = nullptr;      // stream of the last call that enqueued work (compared, never used)
-    bool has_last_stream = false;
     int last_decode_rows = 0;        // rows of the last decode call that ran on the weight-streaming kernels
     int ws_batch_cap = 0;
     int64_t weight_bytes = 0;
@@ -240,12 +238,10 @@ hexgen_status_t refuse_capture(hipStream_t s) {
     return c == hipStreamCaptureStatusNone ? HEXGEN_OK : HEXGEN_ERR_DEVICE;
 }
 
-void note_stream(hexgen_stage *st, hipStream_t s) {
-    st->last_stream = s;
-    st->has_last_stream = true;
-}
-
-// Validate the new rows against the cache and build the device row maps.
+// Validate the new rows against the cache and build the device row maps.  A prefill (allow_decode false) starts a new batch:
+// whatever still uses the cache, the workspace or the caller's buffers may sit on any stream, also on one that this stage has
+// never seen (a recorded step that is being replayed, the producer of hidden_in), so it waits for the device, as the cache's
+// reset does, once the host has its maps ready and before anything is enqueued.
 hexgen_status_t setup_rows(hexgen_stage *st, hexgen_kv_cache *kv, const int32_t *seq_lens, int batch,
                            bool allow_decode, hipStream_t s, Rows *out) {
     if (batch <= 0) return HEXGEN_ERR_INVALID_ARG;
@@ -265,7 +261,6 @@ hexgen_status_t setup_rows(hexgen_stage *st, hexgen_kv_cache *kv, const int32_t 
     r.decode = allow_decode && r.max_new == 1 && r.T <= (is_h16(st->dtype) ? kDecodeMaxRows : kF32StreamRows);
     if (!r.decode) HX_TRY(refuse_capture(s));
     HX_TRY(ensure_workspace(st, r.T, batch));
-    note_stream(st, s);
     Workspace &w = st->ws;
     w.row_seq = w.rowmap;
     w.row_pos = w.rowmap + r.T;
@@ -317,6 +312,7 @@ hexgen_status_t setup_rows(hexgen_stage *st, hexgen_kv_cache *kv, const int32_t 
         }
         r.n_items = n_items;
         w.items = w.rowmap + items_off;
+        if (!allow_decode) HX_HIP(hipDeviceSynchronize());
         // host staging and device block share one packing: a single copy moves all the arrays
         HX_HIP(hipMemcpyAsync(w.rowmap, hs, sizeof(int32_t) * (items_off + 2 * (size_t)n_items), hipMemcpyHostToDevice, s));
         HX_HIP(hipEventRecord(w.stage_ev[r.slot], s));
@@ -1064,22 +1060,22 @@ hexgen_status_t hexgen_stage_prefill(hexgen_stage_t *st, hexgen_kv_cache_t *kv, 
     if (total > 0x3fffffff) return HEXGEN_ERR_CAPACITY;
     HX_TRY(refuse_capture(s));
     HX_TRY(ensure_workspace(st, (int)total, batch));     // every check that can fail comes before the cache is touched
-    // Start a new batch.  On the stream of the stage's last call, stream order keeps this prefill behind everything that
-    // still uses the workspace or the cache, and the host runs ahead (a wait here left the GPU idle for the launch of the
-    // whole call: 30 .. 40 us of a 117-row prompt's 470); on any other stream, wait as the cache's reset does.
-    if (!st->has_last_stream || st->last_stream != s || s == hipStreamPerThread) HX_HIP(hipDeviceSynchronize());
-    bool stale_tail = false;                             // lengths beyond this batch that the device still holds
-    for (int i = batch; i < kv->max_batch; ++i) stale_tail = stale_tail || kv->lens[i] != 0;
     std::fill(kv->lens.begin(), kv->lens.end(), 0);
     kv->batch = 0;
     kv->prefilled = false;
     kv->steps = 0;
     Rows r;
-    HX_TRY(setup_rows(st, kv, seq_lens, batch, false, s, &r));      // a prefill always takes the GEMM path
-    st->prof.mark(PROF_CALL, s);
-    if (is_h16(st->dtype)) HX_TRY(forward_h16(st, kv, r, hidden_in, out_partial, out_resid, s));
-    else HX_TRY(forward_f32(st, kv, r, hidden_in, out_partial, out_resid, nullptr, s));
-    st->prof.mark(PROF_CALL, s);
+    hexgen_status_t rc = setup_rows(st, kv, seq_lens, batch, false, s, &r);      // a prefill always takes the GEMM path
+    if (rc == HEXGEN_OK) {
+        st->prof.mark(PROF_CALL, s);
+        rc = is_h16(st->dtype) ? forward_h16(st, kv, r, hidden_in, out_partial, out_resid, s)
+                               : forward_f32(st, kv, r, hidden_in, out_partial, out_resid, nullptr, s);
+        st->prof.mark(PROF_CALL, s);
+    }
+    if (rc != HEXGEN_OK) {      // the cache is empty, on the device as well
+        (void)hexgen_kv_cache_reset(kv);
+        return rc;
+    }
     for (int i = 0; i < batch; ++i) kv->lens[i] = seq_lens[i];
     kv->batch = batch;
     kv->prefilled = true;
@@ -1089,7 +1085,8 @@ hexgen_status_t hexgen_stage_prefill(hexgen_stage_t *st, hexgen_kv_cache_t *kv, 
     for (int i = 0; i < batch; ++i) h_len[i] = seq_lens[i];
     HX_HIP(hipMemcpyAsync(kv->d_lens, h_len, sizeof(int32_t) * batch, hipMemcpyHostToDevice, s));
     HX_HIP(hipEventRecord(st->ws.stage_ev[r.slot], s));
-    if (stale_tail) launch_fill_zero(kv->d_lens + batch, (size_t)(kv->max_batch - batch) * sizeof(int32_t), s);
+    // lengths beyond this batch: replayed steps may have advanced them without the host's knowledge
+    if (kv->max_batch > batch) launch_fill_zero(kv->d_lens + batch, (size_t)(kv->max_batch - batch) * sizeof(int32_t), s);
     return HEXGEN_OK;
 }
 
@@ -1128,7 +1125,6 @@ hexgen_status_t hexgen_stage_decode_static(hexgen_stage_t *st, hexgen_kv_cache_t
     unsigned char *base = nullptr;
     HX_TRY(static_scratch_ptr(&base));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    note_stream(st, s);
     Workspace view;
     (void)carve_decode_workspace(st, batch, base, &view);
     // what must start at zero: the arrival counters of the split attention and the sums of squares (a fill kernel,
@@ -1226,7 +1222,6 @@ hexgen_status_t hexgen_stage_time_w13_decode(hexgen_stage_t *st, int reps, doubl
     HX_TRY(check_loaded(st));
     if (!is_h16(st->dtype) || st->last_decode_rows <= 0) return HEXGEN_ERR_STATE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    note_stream(st, s);
     Workspace &w = st->ws;
     Rows r;
     r.T = st->last_decode_rows;

@@ -1,5 +1,6 @@
-"""Calls that follow one another without the host waiting: prefills share a small ring of staging buffers and leave the cache's
-lengths on the device in stream order, so every one of a row of calls has to see its own row maps and lengths."""
+"""The order of calls on streams: every one of a row of calls sees its own row maps and lengths (they share a small ring of
+staging buffers, and a prefill leaves the cache's lengths on the device in stream order), and a prefill comes behind whatever
+is on the device, on streams that the stage has never seen as well."""
 import numpy as np
 import pytest
 import torch
@@ -85,3 +86,82 @@ def test_prefill_refuses_to_be_recorded():
         g.capture_end()
     torch.cuda.synchronize()
     assert kv.get_lengths(2) == LENS[0]
+
+
+def _recorded_step(st, kv, n):
+    """A decode_static step of n sequences, recorded on a stream of its own (the recording itself runs nothing)."""
+    x = torch.randn(n, 512, device="cuda").to(torch.bfloat16)
+    p, r = torch.empty_like(x), torch.empty_like(x)
+    st.decode_static(kv, 0, x, p, r)                    # once eagerly: looks the scratch array up
+    torch.cuda.synchronize()
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        g.capture_begin()
+        st.decode_static(kv, 1, x, p, r, stream=s)
+        g.capture_end()
+    torch.cuda.synchronize()
+    return g, s, (x, p, r)
+
+
+def _late(stream):
+    """Keeps `stream` busy for some milliseconds, so that what follows on it runs late."""
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(20_000_000)
+
+
+@pytest.mark.parametrize("again_on_recording_stream", [True, False])
+def test_prefill_comes_behind_a_replayed_step(again_on_recording_stream):
+    _, st, xs, ds = _setup("bf16")
+    kv = st.kv_cache_create(4, 256)
+    want = _one(st, kv, xs[6], ds[6], LENS[6])
+    torch.cuda.synchronize()
+    st.prefill(kv, xs[3], LENS[3], torch.empty_like(xs[3]), torch.empty_like(xs[3]))
+    g, rec, keep = _recorded_step(st, kv, 4)
+    other = torch.cuda.Stream()
+    mine = rec if again_on_recording_stream else None
+    if mine is None:                                    # the stage's last eager call is on the stream of the prefill below
+        st.decode(kv, 2, *keep)
+    torch.cuda.synchronize()
+    _late(other)
+    with torch.cuda.stream(other):
+        g.replay()
+    got = _one(st, kv, xs[6], ds[6], LENS[6], mine)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_lengths_that_a_replay_advanced_are_cleared():
+    """The recorded step of four sequences, replayed behind a prefill of one: the host does not know of the other three."""
+    cfg, st, xs, _ = _setup("bf16")
+    h = generate.hidden_rows(cfg, 4, stream_id=90).to("cuda", torch.float32)
+    p = [torch.empty_like(xs[5]), torch.empty_like(xs[5])]
+    part = [torch.empty_like(h), torch.empty_like(h)]
+    fresh = st.kv_cache_create(4, 256)
+    st.prefill(fresh, xs[5], LENS[5], *p)
+    st.run_sublayer(fresh, 0, 0, h, None, 4, part[0])
+    kv = st.kv_cache_create(4, 256)
+    st.prefill(kv, xs[3], LENS[3], torch.empty_like(xs[3]), torch.empty_like(xs[3]))
+    g, _, keep = _recorded_step(st, kv, 4)
+    st.prefill(kv, xs[5], LENS[5], *p)
+    g.replay()
+    st.prefill(kv, xs[5], LENS[5], *p)
+    st.run_sublayer(kv, 0, 0, h, None, 4, part[1])
+    torch.cuda.synchronize()
+    assert kv.get_lengths(4) == [2, 0, 0, 0]
+    assert torch.equal(part[0], part[1])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_prefill_comes_behind_the_producer_of_its_rows(dtype):
+    _, st, xs, ds = _setup(dtype)
+    kv = st.kv_cache_create(4, 256)
+    want = _one(st, kv, xs[0], ds[0], LENS[0])
+    torch.cuda.synchronize()
+    x, other = torch.zeros_like(xs[0]), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    _late(other)
+    with torch.cuda.stream(other):
+        x.copy_(xs[0])
+    got = _one(st, kv, x, ds[0], LENS[0])
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
