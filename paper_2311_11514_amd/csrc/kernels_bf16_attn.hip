@@ -42,8 +42,14 @@ __device__ __forceinline__ void qkv_tail_stage(const QkvTail &tail, QkvStage<D> 
         const int head_g = hh < G ? c * G + hh : (hh == G ? hq_l + c : hq_l + kg.hkv_l + c);
         const size_t col = ((size_t)head_g * TPH + tl) * 16 + 4 * q2;
         const int i0 = tl * 8 + 4 * q2;              // first of this thread's four rotary pairs
-        const floatx4 c4 = *reinterpret_cast<const floatx4 *>(tail.cos_tab + (size_t)pos * HALF + i0);      // (used by q and k)
-        const floatx4 s4 = *reinterpret_cast<const floatx4 *>(tail.sin_tab + (size_t)pos * HALF + i0);
+        // The rotary entries (used by q and k) are requested beside the partial sums at head dim 128.  At 64 their eight registers
+        // would push the kernels past 128 (136 .. 142), that is from two blocks on a CU to one, and they are fetched behind the sums.
+        floatx4 c4, s4;
+        auto load_rotary = [&]() {
+            c4 = *reinterpret_cast<const floatx4 *>(tail.cos_tab + (size_t)pos * HALF + i0);
+            s4 = *reinterpret_cast<const floatx4 *>(tail.sin_tab + (size_t)pos * HALF + i0);
+        };
+        if constexpr (D == 128) load_rotary();
         floatx4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
         for (int ks0 = 0; ks0 < tail.splits; ks0 += 8) {         // eight splits' partials in flight at a time
             floatx4 pl[8], ph[8];
@@ -61,6 +67,7 @@ __device__ __forceinline__ void qkv_tail_stage(const QkvTail &tail, QkvStage<D> 
         hi *= r;
         float ol[4], oh[4];
         if (hh <= G) {
+            if constexpr (D != 128) load_rotary();
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
                 ol[x] = lo[x] * c4[x] - hi[x] * s4[x];
@@ -144,8 +151,9 @@ __device__ __forceinline__ void qkv_tail_patch(const QkvStage<D> &st, int p32, i
 // prefill kernels otherwise serve): q is read from fragment tiles (row = sequence, no lo part), o is written to them.
 // FUSE: the QKV projection of this step left split partial sums (QkvTail): the block finishes them for its own heads
 // first, appends the new K / V row to the cache and takes q and that row from LDS.
+// Launch bounds: the registers leave room for two blocks on a CU at head dim 64, for one at 128.
 template <int D, bool PF, bool FUSE>
-__global__ __launch_bounds__(512) void attn_decode_block_kernel(const h16_t *__restrict__ q,
+__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_decode_block_kernel(const h16_t *__restrict__ q,
                                                                const h16_t *__restrict__ q_lo, h16_t *kc, h16_t *vc,
                                                                KvGeom kg, int hq_l, int G,
                                                                const int32_t *__restrict__ row_pos,
@@ -299,7 +307,7 @@ __global__ __launch_bounds__(512) void attn_decode_block_kernel(const h16_t *__r
 // loads (no fence: a fence would write back and invalidate the die's whole L2); a block counts itself once every
 // lane's store counter has drained.
 template <int D, bool FUSE>
-__global__ __launch_bounds__(512) void attn_decode_split_kernel(const h16_t *__restrict__ q,
+__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_decode_split_kernel(const h16_t *__restrict__ q,
                                                                const h16_t *__restrict__ q_lo, h16_t *kc, h16_t *vc,
                                                                KvGeom kg, int hq_l, int G,
                                                                const int32_t *__restrict__ row_pos, int nsplit,
