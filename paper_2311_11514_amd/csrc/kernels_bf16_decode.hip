@@ -659,62 +659,99 @@ namespace {
 bool best_pairs(int N) { return (N / 16) % 2 == 0 && N / 32 >= 512; }
 
 // Single kernel: one unit (16 result features) per block, or two?  Two halve what the blocks read of the operand and the number
-// of blocks; a CU holds both of its blocks either way, so what decides is how evenly they go over the 256 CUs -- with n units the
-// fullest CU has ceil(n / 256) of them, or 2 ceil(n / 512) in pairs -- and, on a long stream of weights, the requests in flight.
-// Measured per layer, one unit -> two (us):
-//   RESID  n = 512 (8192 wide), weights up to 112 MiB, 3 rows on: TP8 of the 70B shape at 3 / 16 / 32 rows 58.8 / 66.4 / 81.2 ->
-//          58.1 / 63.8 / 74.1, TP4 92.3 / 102.4 / 120.9 -> 90.3 / 100.1 / 114.6; one and two rows: +0 .. +0.3, and +4 for the 224 MiB
-//          of TP2's W2; 128 MiB: +0 .. +2.
-//          n = 288 .. 448 (equal rounds, uneven ones): 5120 wide (two ranks) 1 / 3 / 16 / 32 rows 74.4 / 80.3 / 95.0 / 118.4 -> 66.1 /
-//          73.5 / 90.3 / 112.2, 6144 wide 82.7 / 88.3 / 98.9 / 117.4 -> 76.9 / 82.3 / 92.9 / 111.6; one and two rows gain at any size
-//          (6144 x 16384, one rank: 150.2 -> 142.1), more rows lose beyond 120 MiB (4096 x 20480 at 3 rows: 126.1 -> 131.2).
-//          n = 256: 4096 x 11264 at 1 / 3 / 8 rows 80.2 / 83.7 / 85.0 -> 75.1 / 82.0 / 83.8, 16 rows 97.6 -> 98.2.  n = 128: +4.
-//   QKV    up to 8 rows, n = 288 / 320 / 384: 7168 wide 109.1 -> 106.1, TP2 155.1 -> 152.9, 3072 wide at 1 / 8 rows 51.3 / 55.9 ->
-//          50.1 / 53.4, 4096 wide at 8 rows 83.8 -> 82.1; n = 160, 192, 480, 640: +0.6 .. +4.4.
+// of blocks; what decides is how evenly the blocks go over the 256 CUs -- with n units the fullest CU has ceil(n / 256) units, or
+// 2 ceil(n / 512) in pairs -- how long a contraction a block walks (see decode_single_kernel: one CU's load path, not HBM, sets the
+// pace of a block) and, on a long stream of weights, the requests in flight.  The lines stand where measurements on both sides put them.
+//   RESID, one or two rows: pairs for n = 256 .. 511 (5120 wide, two ranks, at one row 74.4 -> 66.1 us per layer, 6144 wide 82.7 ->
+//          76.9, 6144 x 16384 150.2 -> 142.1); n = 512: +0 .. +0.3, +4 for the 224 MiB of TP2's W2; beyond: -0.7 .. +1.1.
+//   RESID, 3 rows on, weights up to 120 MiB (128 MiB: +0 .. +2), k = k-tiles, at 3 .. 8 / 9 .. 16 / 17 .. 32 rows (one, two or four
+//          operand tiles), the best other form -> two, us per projection:
+//          n = 256  one unit is as good from 9 rows on; up to 8 rows k = 192 16.6 -> 15.8, 320 23.5 -> 23.0, 448 29.1 -> 30.3
+//          n = 288  k = 144 17.0 -> 13.9 / 18.6 -> 16.4 / 20.7 -> 20.2;  272 21.1 -> 21.4 / 23.4 -> 26.4 / 26.2 -> 33.4
+//          n = 320  k = 160 17.7 -> 14.8 / 19.6 -> 17.8 / 21.8 -> 21.6;  256 22.4 -> 20.9 / 24.4 -> 25.0 / 27.0 -> 31.6
+//          n = 384  k = 192 20.2 -> 17.5 / 23.1 -> 20.5 / 25.3 -> 26.0;  312 28.4 -> 25.1 / 29.8 -> 30.2 / 32.4 -> 39.2
+//          n = 448  k = 176 20.1 -> 19.0 / 23.3 -> 20.9 / 25.5 -> 25.5;  272 27.8 -> 26.7 / 28.9 -> 29.0 / 31.8 -> 35.9
+//          n = 512  k = 224 26.9 -> 25.7 / 28.8 -> 27.9 / 31.7 -> 31.4
+//          n = 416  k = 208 at 17 / 30 rows 25.6 -> 28.5 / 28.3 -> 29.2
+//          hence k up to n, 3 n / 4, 3 n / 8 (n / 2 at 512: every CU has one block).  Two blocks of pairs on the fullest CU, n = 513 .. 1024:
+//          n = 576  k = 36 11.0 -> 10.7 / 12.8 -> 11.7 / 18.9 -> 15.0;  144 at 3 rows 21.4 -> 25.0;  200 31.4 -> 32.7 / 28.9 -> 37.4 / 34.3 -> 48.1
+//          n = 704  k = 44 13.5 -> 12.0 / 14.3 -> 13.7 / 20.4 -> 17.0;  160 26.9 -> 26.0 / 27.9 -> 30.1 / 33.2 -> 39.7
+//          n = 768  k = 48 14.5 -> 12.5 / 15.2 -> 14.4 / 22.4 -> 17.9;  160 29.6 -> 26.7 / 29.1 -> 30.7 / 34.1 -> 39.9
+//          n = 896  k = 56 15.4 -> 13.7 / 19.0 -> 15.5 / 23.0 -> 19.8;  128 26.0 -> 23.1 / 27.6 -> 26.5 / 33.2 -> 34.7
+//          n = 1024 k = 64 17.1 -> 14.8 / 21.3 -> 16.7 / 25.1 -> 21.7;  120 27.8 -> 23.3 / 28.8 -> 26.6 / 33.9 -> 34.9
+//          hence k up to n / 8, n / 8, n / 16 where pairs are the more uneven (n up to 768), beyond that any, any, n / 8.
+//   QKV    up to 8 rows, n = 288 / 320 / 384: 7168 wide 109.1 -> 106.1 us per layer, TP2 155.1 -> 152.9, 3072 wide at 1 / 8 rows 51.3 /
+//          55.9 -> 50.1 / 53.4, 4096 wide at 8 rows 83.8 -> 82.1; n = 160, 192, 480, 640: +0.6 .. +4.4.
 //   W1/W3  (a unit is a gate and an up tile) up to 16 rows, n = 288 / 352 / 432 / 448 / 512: 2048 wide at 1 / 8 / 16 rows 35.4 / 36.9 /
-//          42.8 -> 34.4 / 35.6 / 40.6, TP4 at 8 / 16 rows 91.6 / 99.8 -> 89.5 / 95.1 (16: the split contraction before), 5120 wide at
-//          16 rows 95.0 -> 89.9; one and two rows gain below 384 and lose 0.4 .. 0.8 at 432, 448; up to 8 rows at n = 864 / 896 (TP2
-//          at 1 / 3 / 8 rows 152.9 / 155.5 / 157.7 -> 150.9 / 154.4 / 155.6; 3 and 8: split before).
-//          n = 224, 640, 704, 1280 (more units on the fullest CU): +1.5 .. +7.
+//          42.8 -> 34.4 / 35.6 / 40.6 us per layer, TP4 at 8 / 16 rows 91.6 / 99.8 -> 89.5 / 95.1 (16: the split contraction before), 5120
+//          wide at 16 rows 95.0 -> 89.9; one and two rows gain below 384 and lose 0.4 .. 0.8 at 432, 448; up to 8 rows at n = 800 (4096
+//          wide at 1 / 3 / 8 rows 85.8 / 91.8 / 93.4 -> 83.7 / 88.9 / 91.0) and 864 / 896 (TP2 152.9 / 155.5 / 157.7 -> 150.9 / 154.4 /
+//          155.6; 3 and 8: split before).  n = 928, 960, 1024: +0.2 .. +1.3 at one row, -2.6 .. +0.8 at 3 and 8: not taken.
+//          n = 224, 640, 704, 1280 (more units on the fullest CU): +1.5 .. +7.  A long contraction is split instead (n = 280, k = 320 at
+//          8 / 16 rows 37.5 -> 38.6 / 39.0 -> 45.3, n = 288, k = 288 at 15 rows 36.5 -> 41.1): k up to n, 3 n / 4.
 bool unit_pairs(int mode, int N, int k_tiles, int T) {
-    const int n = N / 16 / (mode == DEC_SWIGLU ? 2 : 1);
+    const int n = N / 16 / (mode == DEC_SWIGLU ? 2 : 1), np = dec_act_tiles(T);
     if (n % 2 != 0) return false;
-    const bool moderate = (size_t)N * k_tiles * 64 <= (size_t)120 << 20;
     switch (mode) {
         case DEC_RAW: case DEC_BEST: return best_pairs(N);
         case DEC_RESID:
-            if (n < 256) return false;
-            if (n < 512 && T <= 2) return true;
-            return moderate && (n >= 512 ? T > 2 : n > 256 || T <= 8);
+            if (T <= 2) return n >= 256 && n < 512;
+            if (n < 256 || n > 1024 || (size_t)N * k_tiles * 64 > (size_t)120 << 20) return false;
+            if (n == 256 && T > 8) return false;
+            if (n <= 512) return 8 * k_tiles <= n * (np == 1 ? 8 : np == 2 ? 6 : n == 512 ? 4 : 3);
+            if (n <= 768) return (np <= 2 ? 8 : 16) * k_tiles <= n;
+            return np <= 2 || 8 * k_tiles <= n;
         case DEC_QKV: return n > 256 && n <= 384 && T <= 8;
         case DEC_SWIGLU:
             if (n > 768 && n <= 896) return T <= 8;
-            return n > 256 && (T <= 2 ? n <= 384 : n <= 512 && T <= 16);
+            if (n <= 256 || n > 512) return false;
+            return T <= 2 ? n <= 384 : T <= 8 ? k_tiles <= n : T <= 16 && 4 * k_tiles <= 3 * n;
     }
     return false;
 }
 
 // One kernel with complete dot products per block, or a contraction split over blocks and a finishing pass?  One or two
 // rows: always one kernel.  More: the single kernel saves the partial sums and the second launch (4 .. 5 us), and pays with
-// the operand, which every block reads for itself from L2 where the split kernel's eight feature tiles share it through LDS:
-// blocks x k-tiles x operand tiles x 1 KB.  Measured (single minus split, us per projection, against those bytes):
-//   W1/W3   8 rows:  58 MB -2.9 (TP8 of the 70B shape), 92 -6.4 (4096-wide layer), 117 -2.2 (TP4), 235 +2.4 (TP2), 470 +9.5
-//          16 rows:  46 -2.9 (2048-wide), 117 -1.3 (TP8), 235 +3.0 (TP4)
-//   W2      8 rows:  23 -4.1 (2048-wide), 59 -2.0 (TP8), 117 0.0 (TP4), 235 +1.7    16 rows: 46 -3.3, 117 -0.9, 185 +1.4, 235 +3.7
-//   W_O     8 rows:  17 -3.5, 33 -2.3, 134 -0.8    16 rows: 34 -2.8, 134 -0.2, 268 +3.8    32 rows: 67 -3.2, 134 -2.7, 268 +2.0
-// with one unit per block.  The line is 128 MiB.  Blocks of two units halve the reads: W1/W3 is counted so (TP4 at 16 rows 99.8 ->
-// 95.1 us per layer, one kernel instead of two), W_O and W2 are one kernel wherever unit_pairs admits them (TP8 W2 at 32 rows 79.6 ->
-// 74.3, TP2 W_O 187.5 -> 182.5, TP4 W2, 224 MiB, 116.7 -> 114.7).  The QKV projection has no finishing launch to save (the attention sums its partials):
+// the operand, which every block reads for itself from L2 where the split kernel's eight feature tiles share it through LDS, and
+// with blocks that walk the whole contraction: a block takes about 5 us plus 0.024 + 0.012 x operand tiles per k-tile (twice
+// that where the fullest CU has two), however few blocks there are.
+//   * Operand reads, blocks x k-tiles x operand tiles x 1 KB (single minus split, us per projection, one unit per block):
+//     W1/W3  8 rows:  58 MB -2.9 (TP8 of the 70B shape), 92 -6.4 (4096-wide layer), 117 -2.2 (TP4), 235 +2.4 (TP2), 470 +9.5
+//           16 rows:  46 -2.9 (2048-wide), 117 -1.3 (TP8), 235 +3.0 (TP4)
+//     W2     8 rows:  23 -4.1 (2048-wide), 59 -2.0 (TP8), 117 0.0 (TP4), 235 +1.7    16 rows: 46 -3.3, 117 -0.9, 185 +1.4, 235 +3.7
+//     W_O    8 rows:  17 -3.5, 33 -2.3, 134 -0.8    16 rows: 34 -2.8, 134 -0.2, 268 +3.8    32 rows: 67 -3.2, 134 -2.7, 268 +2.0
+//     The line is 128 MiB; blocks of two units halve the reads (TP4's W1/W3 at 16 rows 99.8 -> 95.1 us per layer).
+//   * W_O and W2 with 257 .. 1024 units, but for 512, are one kernel exactly where pairs are: lone units fill the CUs unevenly
+//     and lose to the split contraction wherever pairs do (n = 288, k = 400 at 3 rows: one unit 36.6, two 29.1, split 27.0).
+//   * Few blocks (fewer than 192): the contraction a block may walk grows with their number.  Split -> single at 3 .. 8 / 16 / 32 rows:
+//     W2     n =  64, k = 88 11.1 -> 8.5 / 11.7 -> 9.5 / 12.7 -> 12.2;  176 13.0 -> 10.9 / 13.7 -> 13.3 / 14.9 -> 17.5;  352 15.6 -> 16.8 / 16.4
+//            -> 21.7 / 18.1 -> 29.9
+//            n = 128, k = 128 12.3 -> 9.5 / 13.1 -> 11.2 / 15.3 -> 14.4;  256 16.5 -> 14.1 / 17.6 -> 17.5 / 20.0 -> 23.4;  352 17.6 -> 18.1 /
+//            18.6 -> 22.7 / 21.1 -> 31.2
+//     W1/W3  n =  44, k = 128 12.7 -> 11.9 / 14.1 -> 13.7 / 15.3 -> 20.0;  256 14.9 -> 18.5 / 16.3 -> 22.2 / 17.8 -> 34.1
+//            n =  88, k = 128 14.7 -> 12.3 / 16.7 -> 14.0 / 19.4 -> 20.0;  256 18.4 -> 19.8 / 21.0 -> 22.9 / 24.7 -> 34.6
+//            n = 176, k = 128 17.0 -> 13.5 / 18.8 -> 15.7 / 21.9 -> 20.9
+//     (W2 at 19 rows, n = 160, k = 132: 14.9 -> 16.0.)
+//     From 192 units on the operand line is the tighter one, except for one operand tile of a long stream (n = 256: 80 MB 23.2 ->
+//     23.5, 112 MB 29.1 -> 30.3).
+//   * W1/W3 in lone units: the last round of 256 has to be filled.  Split -> single at 3 .. 8 rows n = 540 48.6 -> 50.3, 560 43.2 -> 44.1, 600
+//     40.9 -> 43.2, but 512 28.0 -> 23.9, 640 27.1 -> 25.5, 704 24.3 -> 19.6; at 19 .. 32 rows n = 264 20.4 -> 23.3, 300 16.6 -> 17.6, 352 21.7 ->
+//     22.2, but 512 24.2 -> 23.5.
+//   * The QKV projection has no finishing launch to save (the attention sums its partials):
 //           8 rows:  42 -0.9 (TP4), 50 -0.6, 84 +3.5 (TP2)    16 rows: 25 -1.0, 84 +1.5
-// 56 MiB, and at least 128 blocks (TP8 has 80: +0.9 .. +4.7).
+//     56 MiB, and at least 128 blocks (TP8 has 80: +0.9 .. +4.7).
 bool decode_single_kernel(int mode, int N, int k_tiles, int T) {
     if (T <= 2) return true;
     if (T > 32) return false;
     if (k_tiles < 8) return true;              // not one chunk of the split kernel
-    const int units = N / 16 / (mode == DEC_SWIGLU ? 2 : 1), pair = unit_pairs(mode, N, k_tiles, T) ? 2 : 1;
-    const size_t operand = (size_t)(units / pair) * k_tiles * dec_act_tiles(T) << 10;
+    const int tiles = mode == DEC_SWIGLU ? 2 : 1, units = N / 16 / tiles, pair = unit_pairs(mode, N, k_tiles, T) ? 2 : 1, np = dec_act_tiles(T);
+    const size_t operand = (size_t)(units / pair) * k_tiles * np << 10;
     if (mode == DEC_QKV) return units >= 128 && operand * pair <= (size_t)56 << 20;
+    if (mode == DEC_RESID && units > 256 && units <= 1024 && units != 512) return pair == 2;
     if (mode == DEC_RESID && pair == 2) return true;
+    if (units < 192) return k_tiles * (tiles + np) <= (np < 4 ? 6 : 3 + tiles) * units;
+    if (mode == DEC_SWIGLU && pair == 1 && units > 256 && 5 * units < 4 * 256 * ((units + 255) / 256)) return false;
+    if (mode == DEC_RESID && units <= 256 && (size_t)N * k_tiles * 64 > (size_t)80 << 20) return false;
     return operand <= (size_t)128 << 20;
 }
 }  // namespace

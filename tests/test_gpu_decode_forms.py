@@ -14,8 +14,11 @@ pytestmark = pytest.mark.gpu
 
 WIDE = StageConfig("wide", "bf16", 4096, 32, 8, 16416, 1, 1, (0,), batch=1, seed=801)
 NARROW = StageConfig("narrow", "f16", 512, 8, 2, 1472, 2, 2, (1,), batch=1, seed=802)      # W_O: 8 k-tiles, W2: 23
-# the single kernel's blocks of two units: QKV 352 feature tiles, W_O and W2 288, W1/W3 290 gate / up pairs; and W1/W3 at 772
+# the single kernel's blocks of two units: QKV 352 feature tiles, W_O and W2 288 (beyond 16 rows up to 108 k-tiles, longer ones are split:
+# HALVED has 72 each), W1/W3 290 gate / up pairs; and W1/W3 at 772
 PAIRS = StageConfig("pairs", "bf16", 4608, 36, 4, 4640, 1, 1, (0,), batch=1, seed=806)
+HALVED = StageConfig("halved", "bf16", 4608, 36, 4, 4608, 1, 2, (1,), batch=1, seed=808)
+# ... and few blocks whose contraction is too long for one kernel (GATED: W2, 386 k-tiles for 64 units)
 GATED = StageConfig("gated", "f16", 1024, 8, 2, 12352, 2, 1, (0,), batch=1, seed=807)
 _sides = {}
 
@@ -28,7 +31,7 @@ def _side(cfg):
 
 
 @pytest.mark.parametrize("cfg,rows", [(WIDE, t) for t in (3, 8, 9, 17, 32, 33, 64, 65)] + [(NARROW, t) for t in (3, 9, 16, 31, 33, 64, 65, 97)] +
-                         [(PAIRS, t) for t in (1, 2, 3, 8, 9, 16, 17, 32)] + [(GATED, t) for t in (1, 2, 3)],
+                         [(PAIRS, t) for t in (1, 2, 3, 8, 9, 16, 17, 32)] + [(GATED, t) for t in (1, 2, 3, 9, 17)] + [(HALVED, t) for t in (17, 32)],
                          ids=lambda v: getattr(v, "name", v))
 def test_decode_step(cfg, rows):
     print(cfg.name, rows, flush=True)
@@ -75,7 +78,7 @@ def test_decode_rows_around_position_tiles(cfg, rows):
         check(f"{rows} rows step {k} partial", p, p_ref, TOL[cfg.dtype])
 
 
-@pytest.mark.parametrize("hidden,vocab,rows", [(128, 1000, 40), (1024, 4104, 33), (1024, 4104, 48), (1024, 4104, 49), (1024, 4104, 64), (1024, 4104, 65)])
+@pytest.mark.parametrize("hidden,vocab,rows", [(128, 1000, 40), (1024, 1000, 20), (4096, 1000, 20), (1024, 4104, 33), (1024, 4104, 48), (1024, 4104, 49), (1024, 4104, 64), (1024, 4104, 65)])
 def test_head_rows(hidden, vocab, rows):
     import paper_2311_11514_amd as hx
     cfg = StageConfig("headrows", "bf16", hidden, 8, 8, 64, 1, 1, (0,), batch=1, seed=803, vocab=vocab)
