@@ -583,8 +583,9 @@ void launch_one(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, con
 template <int UT, int MODE>
 void launch_mode(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, const DecodeEpi &e, hipStream_t s) {
     const size_t xbytes = (size_t)T * k_tiles * 8 * sizeof(h16x8);
-    // a contraction of at most 32 k-tiles gives a wave 4 of them: a ring of 4 requests nothing it does not use
-    const bool short_k = UT == 1 && MODE == DEC_RESID && k_tiles <= 32;
+    // a contraction of at most 32 k-tiles gives a wave 4 of them: a ring of 4 requests nothing it does not use (and lets a CU hold
+    // two blocks at 17 .. 32 rows, 106 registers for 186: 1000 units of the LM head, 32 rows of 512 / 1024 x 16000, 31.3 / 34.2 -> 19.7 / 22.0 us)
+    const bool short_k = UT == 1 && (MODE == DEC_RESID || MODE == DEC_BEST) && k_tiles <= 32;
 #define HX_ONE(NP)                                                                                              \
     do {                                                                                                        \
         if (short_k) launch_one<NP, UT, 4, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);                        \
@@ -731,12 +732,14 @@ bool unit_pairs(int mode, int N, int k_tiles, int T) {
 //     W1/W3  n =  44, k = 128 12.7 -> 11.9 / 14.1 -> 13.7 / 15.3 -> 20.0;  256 14.9 -> 18.5 / 16.3 -> 22.2 / 17.8 -> 34.1
 //            n =  88, k = 128 14.7 -> 12.3 / 16.7 -> 14.0 / 19.4 -> 20.0;  256 18.4 -> 19.8 / 21.0 -> 22.9 / 24.7 -> 34.6
 //            n = 176, k = 128 17.0 -> 13.5 / 18.8 -> 15.7 / 21.9 -> 20.9
-//     (W2 at 19 rows, n = 160, k = 132: 14.9 -> 16.0.)
+//     (W2 at 19 rows, n = 160, k = 132: 14.9 -> 16.0.)  k x (weight + operand tiles) up to 384 + 3 n, beyond 16 rows 320 + 2 n (W1/W3 300 + 3 n).
 //     From 192 units on the operand line is the tighter one, except for one operand tile of a long stream (n = 256: 80 MB 23.2 ->
 //     23.5, 112 MB 29.1 -> 30.3).
 //   * W1/W3 in lone units: the last round of 256 has to be filled.  Split -> single at 3 .. 8 rows n = 540 48.6 -> 50.3, 560 43.2 -> 44.1, 600
-//     40.9 -> 43.2, but 512 28.0 -> 23.9, 640 27.1 -> 25.5, 704 24.3 -> 19.6; at 19 .. 32 rows n = 264 20.4 -> 23.3, 300 16.6 -> 17.6, 352 21.7 ->
+//     40.9 -> 43.2, 640 44.5 -> 46.3 (k = 192) and 27.1 -> 25.5 (96), but 512 28.0 -> 23.9, 704 24.3 -> 19.6; at 19 .. 32 rows n = 264 20.4 -> 23.3, 300 16.6 -> 17.6, 352 21.7 ->
 //     22.2, but 512 24.2 -> 23.5.
+//   * LM head beyond 16 rows in pairs: one block on a CU (148 registers), four rounds of them with little to do each where the contraction is
+//     short.  Whole call at 32 rows, split -> single: 512 x 32000 22.7 -> 28.1 us, 1024 x 32000 27.7 -> 31.8, 1024 x 50304 34.4 -> 34.7.
 //   * The QKV projection has no finishing launch to save (the attention sums its partials):
 //           8 rows:  42 -0.9 (TP4), 50 -0.6, 84 +3.5 (TP2)    16 rows: 25 -1.0, 84 +1.5
 //     56 MiB, and at least 128 blocks (TP8 has 80: +0.9 .. +4.7).
@@ -749,8 +752,9 @@ bool decode_single_kernel(int mode, int N, int k_tiles, int T) {
     if (mode == DEC_QKV) return units >= 128 && operand * pair <= (size_t)56 << 20;
     if (mode == DEC_RESID && units > 256 && units <= 1024 && units != 512) return pair == 2;
     if (mode == DEC_RESID && pair == 2) return true;
-    if (units < 192) return k_tiles * (tiles + np) <= (np < 4 ? 6 : 3 + tiles) * units;
-    if (mode == DEC_SWIGLU && pair == 1 && units > 256 && 5 * units < 4 * 256 * ((units + 255) / 256)) return false;
+    if (units < 192) return k_tiles * (tiles + np) <= (np < 4 ? 384 + 3 * units : mode == DEC_SWIGLU ? 300 + 3 * units : 320 + 2 * units);
+    if (mode == DEC_SWIGLU && pair == 1 && units > 256 && 20 * units < 17 * 256 * ((units + 255) / 256)) return false;
+    if (mode == DEC_BEST && pair == 2 && np == 4 && k_tiles <= 32) return false;
     if (mode == DEC_RESID && units <= 256 && (size_t)N * k_tiles * 64 > (size_t)80 << 20) return false;
     return operand <= (size_t)128 << 20;
 }

@@ -78,7 +78,9 @@ def test_decode_rows_around_position_tiles(cfg, rows):
         check(f"{rows} rows step {k} partial", p, p_ref, TOL[cfg.dtype])
 
 
-@pytest.mark.parametrize("hidden,vocab,rows", [(128, 1000, 40), (1024, 1000, 20), (4096, 1000, 20), (1024, 4104, 33), (1024, 4104, 48), (1024, 4104, 49), (1024, 4104, 64), (1024, 4104, 65)])
+@pytest.mark.parametrize("hidden,vocab,rows", [(128, 1000, 40), (1024, 1000, 20), (4096, 1000, 20), (1024, 4104, 33), (1024, 4104, 48), (1024, 4104, 49), (1024, 4104, 64), (1024, 4104, 65)] +
+                         # units of two tiles (from 1024 tiles on) and columns beyond the last: one kernel at 7, 9 and 17 rows, split at 17 of a short contraction and from 33 on
+                         [(1536, 16411, 7), (1536, 16411, 9), (1536, 16411, 17), (1024, 16411, 17), (1024, 16411, 32), (1024, 16411, 48), (1024, 16411, 64)])
 def test_head_rows(hidden, vocab, rows):
     import paper_2311_11514_amd as hx
     cfg = StageConfig("headrows", "bf16", hidden, 8, 8, 64, 1, 1, (0,), batch=1, seed=803, vocab=vocab)
@@ -96,18 +98,21 @@ def test_head_rows(hidden, vocab, rows):
     assert clear.mean() > 0.8 and np.array_equal(tok.cpu().numpy()[clear], np.argmax(logits, axis=1)[clear])
 
 
-@pytest.mark.parametrize("rows", [1, 5, 40])
-def test_head_ties_and_rows_that_are_not_finite(rows):
-    """The lowest id wins an exact tie wherever the tied columns lie; a row of NaN has no candidate: the shard's first id."""
+@pytest.mark.parametrize("rows,vocab", [(1, 4104), (5, 4104), (40, 4104), (2, 16411), (7, 16411), (17, 16411), (48, 16411)])
+def test_head_ties_and_rows_that_are_not_finite(rows, vocab):
+    """The lowest id wins an exact tie wherever the tied columns lie (with units of two tiles also in either tile of one unit); a row
+    of NaN has no candidate: the shard's first id."""
     import paper_2311_11514_amd as hx
-    hidden, vocab = 1024, 4104
+    hidden, end = 1024, vocab - 4
     cfg = StageConfig("headties", "bf16", hidden, 8, 8, 64, 1, 1, (0,), batch=1, seed=804, vocab=vocab)
     hw = generate.head_weights(cfg)
     w, a = hw["w_lm"].clone(), generate.hidden_rows(cfg, rows, stream_id=3).to(torch.bfloat16)
     best = torch.argmax((a.double() * hw["g_final"].double()) @ w.double(), dim=1)
-    w[:, 4100] = w[:, 7]
-    for i in range(rows):                                   # every row's best column twice more, in a tile of its own and the last
+    w[:, end] = w[:, 7]
+    for i in range(rows):                                   # every row's best column once more, in a tile of its own ...
         w[:, (int(best[i]) + 1000) % 4000] = w[:, int(best[i])]
+        if vocab > 16384:                                   # ... and in the other tile of its unit
+            w[:, min(int(best[i]) ^ 16, vocab - 1)] = w[:, int(best[i])]
     first = torch.argmax((a.double() * hw["g_final"].double()) @ w.double(), dim=1)
     hd = hx.Head(hidden, vocab, 1, 0, "bf16", cfg.rms_eps)
     hd.load(hw["g_final"].cuda(), w.cuda())
@@ -120,3 +125,26 @@ def test_head_ties_and_rows_that_are_not_finite(rows):
     torch.cuda.synchronize()
     assert int(tok2[0]) == 0 and float(val2[0]) == -float("inf")
     assert torch.equal(tok2[1:], tok[1:]) and torch.equal(val2[1:], val[1:])
+
+
+@pytest.mark.parametrize("dtype,heads", [("bf16", 8), ("f16", 4)])
+def test_decode_attention_cut_in_three(dtype, heads):
+    """32 to 64 (sequence, kv head) pairs with one context long enough: every context is cut in three, the short ones into fewer
+    pieces than that (one of them within a single tile)."""
+    cfg = StageConfig("cut3", dtype, 512, heads, heads, 96, 2, 1, (0,), batch=1, seed=809)
+    lens = [2100, 33, 1, 700, 2047, 64, 257, 96][:32 // heads]
+    w = [generate.layer_weights(cfg, l) for l in range(2)]
+    ora, st = make_oracle(cfg, 0, w), make_gpu_stage(cfg, 0, w)
+    oc, kv = ora.new_cache(len(lens)), st.kv_cache_create(len(lens), 2200)
+    for l in range(2):
+        for i, n in enumerate(lens):
+            k, v = generate.synthetic_kv(cfg, l, i, n)
+            kv.fill(l, i, k, v)
+            oc.fill(l, i, k, v)
+    kv.set_lengths(lens)
+    for k in range(2):
+        x = generate.hidden_rows(cfg, len(lens), stream_id=1 + k)
+        p_ref, h_ref = ora.decode(oc, x)
+        p, h = gpu_decode(st, kv, cfg, k, x)
+        check(f"step {k} resid", h, h_ref, TOL[dtype])
+        check(f"step {k} partial", p, p_ref, TOL[dtype])
