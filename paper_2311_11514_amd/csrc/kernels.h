@@ -13,6 +13,10 @@ struct RowMap {
     const int32_t *row_pos;   // [T]
 };
 
+// Blocks that the decode attention cuts a context into at most: what its merge holds in registers, what the workspaces have
+// room for, and what the rule and the hook that choose the number may ask for.
+constexpr int kAttnMaxSplit = 8;
+
 // KV cache geometry of one (layer, sequence, kv head) slab; see kernels_bf16_attn.hip
 struct KvGeom {
     int d;            // head dim (64 | 128)

@@ -8,11 +8,12 @@
 // fragment is fetched from HBM exactly once per sequence and serves the whole query group inside one
 // MFMA.  A long context with few sequences is split over several blocks, whose partial (m, l, o) triples the
 // last block to finish merges by log-sum-exp, in split order.
+#include <algorithm>
+
 #include "kernels.h"
 #include "kvlayout.h"
 
 #define NEG_INF (-INFINITY)
-constexpr int ATTN_MAX_SPLIT = 8;      // blocks a context is split over at most
 
 namespace HX_NS {
 
@@ -465,10 +466,10 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_decode_split_kernel
         const size_t e0 = ((size_t)sq * hq_l + c * G + hh) * nsplit;
         // every partial is requested before the first is used: one round trip past the dies' caches, where a loop over the
         // splits made two per split (8 splits of a context of 4000: 1.5 us of 17)
-        float ms[ATTN_MAX_SPLIT], ls[ATTN_MAX_SPLIT];
-        floatx4 os[ATTN_MAX_SPLIT];
+        float ms[kAttnMaxSplit], ls[kAttnMaxSplit];
+        floatx4 os[kAttnMaxSplit];
 #pragma unroll
-        for (int u = 0; u < ATTN_MAX_SPLIT; ++u) {
+        for (int u = 0; u < kAttnMaxSplit; ++u) {
             ms[u] = NEG_INF;
             if (u < nb) {                                 // uniform over the block
                 const size_t e = e0 + u;
@@ -480,11 +481,11 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_decode_split_kernel
         }
         float M = NEG_INF;
 #pragma unroll
-        for (int u = 0; u < ATTN_MAX_SPLIT; ++u) M = fmaxf(M, ms[u]);
+        for (int u = 0; u < kAttnMaxSplit; ++u) M = fmaxf(M, ms[u]);
         float L = 0.f;
         floatx4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int u = 0; u < ATTN_MAX_SPLIT; ++u)
+        for (int u = 0; u < kAttnMaxSplit; ++u)
             if (u < nb) {
                 const float wt = (ms[u] == NEG_INF) ? 0.f : exp2f(ms[u] - M);
                 L += ls[u] * wt;
@@ -505,6 +506,7 @@ void launch_attn_decode(const h16_t *q, const h16_t *q_lo, h16_t *kc, h16_t *vc,
     const int G = hq_l / kg.hkv_l;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)kg.d);
     const bool fuse = tail.part != nullptr;
+    nsplit = std::min(nsplit, kAttnMaxSplit);
 #define HX_BLK(DD, FF)                                                                                                   \
     hipLaunchKernelGGL((attn_decode_block_kernel<DD, false, FF>), grid, dim3(512), 0, s, q, q_lo, kc, vc, kg, hq_l, G, row_pos, \
                        o_act, scale_log2e, tail)

@@ -39,8 +39,6 @@ constexpr int kHeadRows = 64;           // rows of one pass over the LM head's w
 constexpr int kF32StreamRows = 32;      // fp32: rows of the streaming projections
 constexpr int kStageSlots = 4;
 constexpr int kAttnRows = 128;            // new rows per block of the prefill attention (4 waves x 32)
-constexpr int kMaxAttnSplit = 32;         // blocks per (sequence, kv head) the workspace has partials for
-constexpr int kStaticAttnSplit = 8;       // what pick_attn_split chooses at most, and what the static scratch is laid out for
 
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
@@ -186,8 +184,8 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
         }
         w.gemm_part_floats = (size_t)16 << 20;      // 64 MB: 8 splits of the widest short-prompt launch
         HX_TRY(dmalloc(&w.gemm_part, w.gemm_part_floats));
-        HX_TRY(dmalloc(&w.att_o, drows * st->hq_l * kMaxAttnSplit * st->d));
-        HX_TRY(dmalloc(&w.att_ml, drows * st->hq_l * kMaxAttnSplit * 2));
+        HX_TRY(dmalloc(&w.att_o, drows * st->hq_l * kAttnMaxSplit * st->d));
+        HX_TRY(dmalloc(&w.att_ml, drows * st->hq_l * kAttnMaxSplit * 2));
         HX_TRY(dmalloc(&w.att_arrived, drows * st->hkv_l));
         HX_HIP(hipMemset(w.att_arrived, 0, drows * st->hkv_l * sizeof(unsigned int)));
         const size_t ssq_n = 2 * (size_t)(st->H / 16) * kDecodeMaxRows;
@@ -451,7 +449,7 @@ int pick_attn_split(const hexgen_stage *st, const hexgen_kv_cache *kv, int batch
     if (n_t32 <= 48) return 1;
     if (pairs >= 32) return pairs <= 64 && 2 * n_t32 >= 3 * pairs + 32 ? 3 : 1;
     const int s = (int)std::lround(std::sqrt(6.0 * n_t32 / pairs));
-    return std::max(2, std::min({s, kStaticAttnSplit, (n_t32 + 7) / 8}));
+    return std::max(2, std::min({s, kAttnMaxSplit, (n_t32 + 7) / 8}));
 }
 
 DecodeEpi epi_base(hexgen_stage *st, int mode) {
@@ -706,8 +704,8 @@ size_t carve_decode_workspace(const hexgen_stage *st, int rows, unsigned char *b
         v.dec_part_floats = T * ((size_t)512 * 128 + 2 * nmax);
         v.dec_part = static_cast<float *>(take(v.dec_part_floats * sizeof(float)));
     }
-    v.att_o = static_cast<float *>(take(T * st->hq_l * kStaticAttnSplit * st->d * sizeof(float)));
-    v.att_ml = static_cast<float *>(take(T * st->hq_l * kStaticAttnSplit * 2 * sizeof(float)));
+    v.att_o = static_cast<float *>(take(T * st->hq_l * kAttnMaxSplit * st->d * sizeof(float)));
+    v.att_ml = static_cast<float *>(take(T * st->hq_l * kAttnMaxSplit * 2 * sizeof(float)));
     v.att_arrived = static_cast<unsigned int *>(take(T * st->hkv_l * sizeof(unsigned int)));
     v.ssq = static_cast<float *>(take(2 * (size_t)(st->H / 16) * kDecodeMaxRows * sizeof(float)));
     v.row_pos = static_cast<int32_t *>(take(T * sizeof(int32_t)));
@@ -1432,7 +1430,7 @@ hexgen_status_t hexgen_embed_rows(const void *table, hexgen_dtype_t dtype, int h
 }
 
 hexgen_status_t hexgen_set_attn_split(int nsplit) {
-    if (nsplit < 0 || nsplit > kStaticAttnSplit) return HEXGEN_ERR_INVALID_ARG;
+    if (nsplit < 0 || nsplit > kAttnMaxSplit) return HEXGEN_ERR_INVALID_ARG;
     g_attn_split_forced = nsplit;
     return HEXGEN_OK;
 }
