@@ -31,8 +31,6 @@ typedef __bf16 hx_elem;
 #endif
 typedef __attribute__((__vector_size__(8 * sizeof(hx_elem)))) hx_elem h16x8;
 
-#define HX_WAVE 64
-
 // Decode activations are hi + lo pairs (split_h16), laid out by the number of rows T of the call:
 //   T <= 2: compact token-major, per token and k-tile one 128-byte line holding the 32 hi values then the 32 lo values; a
 //           projection touches one cache line per (token, k-tile) where a 16-token tile would cost it eight;
@@ -145,11 +143,6 @@ __device__ inline float wave_sum(float v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-__device__ inline float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
 
 // block-wide sum for blockDim.x = 256 (4 waves); `red` is >= 4 floats of LDS
 __device__ inline float block_sum_256(float v, float *red) {
@@ -158,11 +151,4 @@ __device__ inline float block_sum_256(float v, float *red) {
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     return red[0] + red[1] + red[2] + red[3];
-}
-__device__ inline float block_max_256(float v, float *red) {
-    v = wave_max(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }

@@ -41,11 +41,6 @@ __device__ inline void rstd_row(const DecodeEpi &e, int t, int lane, float *s_rs
     }
     if (lane == 0) s_rstd[t] = r;
 }
-// wave w handles tokens w, w + WAVES, ...
-template <int WAVES>
-__device__ inline void load_rstd(const DecodeEpi &e, int T, int wave, int lane, float *s_rstd) {
-    for (int t = wave; t < T; t += WAVES) rstd_row(e, t, lane, s_rstd);
-}
 // The same in two halves, so that the loads can be requested ahead of other memory traffic and summed later: the
 // first RSTD_REGS * 64 units wait in registers (hidden sizes up to 8192), any further ones are fetched in the second half.
 constexpr int RSTD_REGS = 8;
@@ -582,14 +577,13 @@ void launch_one(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, con
 
 template <int UT, int MODE>
 void launch_mode(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, const DecodeEpi &e, hipStream_t s) {
-    const size_t xbytes = (size_t)T * k_tiles * 8 * sizeof(h16x8);
     // a contraction of at most 32 k-tiles gives a wave 4 of them: a ring of 4 requests nothing it does not use (and lets a CU hold
     // two blocks at 17 .. 32 rows, 106 registers for 186: 1000 units of the LM head, 32 rows of 512 / 1024 x 16000, 31.3 / 34.2 -> 19.7 / 22.0 us)
-    const bool short_k = UT == 1 && (MODE == DEC_RESID || MODE == DEC_BEST) && k_tiles <= 32;
+    constexpr int RING = 8 / UT, SHORT = UT == 1 && (MODE == DEC_RESID || MODE == DEC_BEST) ? 4 : RING;
 #define HX_ONE(NP)                                                                                              \
     do {                                                                                                        \
-        if (short_k) launch_one<NP, UT, 4, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);                        \
-        else launch_one<NP, UT, 8 / UT, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);                           \
+        if (k_tiles <= 32) launch_one<NP, UT, SHORT, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);              \
+        else launch_one<NP, UT, RING, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);                             \
     } while (0)
     constexpr int NPM = UT == 4 ? 2 : 4;          // (blocks of four feature tiles take 16 rows at most: unit_pairs)
     if (T > 16) HX_ONE(NPM);
@@ -599,9 +593,13 @@ void launch_mode(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, co
     // block staging the operand in LDS behind a barrier (measured: W_O 17.9 -> 16.6 us and W2 44.0 -> 43.4 at one row, W1/W3
     // 81.0 -> 77.9 at two rows and unchanged at one).  The QKV projection keeps the staged operand -- XR 16-byte pieces per
     // thread (512 threads), 4 up to 32 KB, 8 up to 64 KB: through the ring it loses 3.5 us.
-    else if (MODE == DEC_RESID || MODE == DEC_SWIGLU || xbytes > (size_t)kXldsMaxBytes) HX_ONE(0);
-    else if (xbytes <= (size_t)kXldsMaxBytes / 2) launch_one<0, UT, 8 / UT, MODE, true, 4>(Wp, Xa, N, k_tiles, T, e, s);
-    else launch_one<0, UT, 8 / UT, MODE, true, 8>(Wp, Xa, N, k_tiles, T, e, s);
+    else if constexpr (MODE == DEC_RESID || MODE == DEC_SWIGLU) HX_ONE(0);
+    else {
+        const size_t xbytes = (size_t)T * k_tiles * 8 * sizeof(h16x8);
+        if (xbytes > (size_t)kXldsMaxBytes) HX_ONE(0);
+        else if (xbytes <= (size_t)kXldsMaxBytes / 2) launch_one<0, UT, 8 / UT, MODE, true, 4>(Wp, Xa, N, k_tiles, T, e, s);
+        else launch_one<0, UT, 8 / UT, MODE, true, 8>(Wp, Xa, N, k_tiles, T, e, s);
+    }
 #undef HX_ONE
 }
 }  // namespace
@@ -645,13 +643,13 @@ void launch_splitk(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, 
         default: launch_splitk_main<8>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
     }
     if (mid) (void)hipEventRecord(mid, s);
-    if (tail != nullptr) {          // the consumer finishes the projection (QKV -> decode attention)
+    if constexpr (MODE == DEC_QKV) {          // the decode attention finishes the projection
         *tail = QkvTail{scratch, splits, T, N, rstd, e.cos_tab, e.sin_tab};
-        return;
+    } else {
+        const int n_units = n_tiles / UT, nbt = (T + 15) / 16;
+        hipLaunchKernelGGL((decode_finish_kernel<MODE, UT>), dim3((n_units * nbt + 3) / 4), dim3(256), 0, s, scratch, splits, N, T,
+                           n_units, e, rstd);
     }
-    const int n_units = n_tiles / UT, nbt = (T + 15) / 16;
-    hipLaunchKernelGGL((decode_finish_kernel<MODE, UT>), dim3((n_units * nbt + 3) / 4), dim3(256), 0, s, scratch, splits, N, T,
-                       n_units, e, rstd);
 }
 }  // namespace
 
@@ -694,7 +692,7 @@ bool unit_pairs(int mode, int N, int k_tiles, int T) {
     const int n = N / 16 / (mode == DEC_SWIGLU ? 2 : 1), np = dec_act_tiles(T);
     if (n % 2 != 0) return false;
     switch (mode) {
-        case DEC_RAW: case DEC_BEST: return best_pairs(N);
+        case DEC_BEST: return best_pairs(N);
         case DEC_RESID:
             if (T <= 2) return n >= 256 && n < 512;
             if (n < 256 || n > 1024 || (size_t)N * k_tiles * 64 > (size_t)120 << 20) return false;
@@ -766,10 +764,9 @@ void launch_decode_proj(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, c
                         size_t scratch_floats, hipStream_t s, hipEvent_t mid) {
     const int k_tiles = K / 32;
     const bool single = decode_single_kernel(e.mode, N, k_tiles, T);
-    if (!single && scratch != nullptr && scratch_floats >= (size_t)T * N + DEC_SCRATCH_RSTD) {
+    if (!single && e.mode != DEC_QKV && scratch != nullptr && scratch_floats >= (size_t)T * N + DEC_SCRATCH_RSTD) {
         switch (e.mode) {
             case DEC_RAW: launch_splitk<DEC_RAW, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
-            case DEC_QKV: launch_splitk<DEC_QKV, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
             case DEC_RESID: launch_splitk<DEC_RESID, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
             case DEC_SWIGLU: launch_splitk<DEC_SWIGLU, 2>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
             case DEC_BEST:
@@ -786,7 +783,7 @@ void launch_decode_proj(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, c
         if (pair) launch_mode<2 * U, MODE>(Wp, Xa, N, k_tiles, T, e, s);           \
         else launch_mode<U, MODE>(Wp, Xa, N, k_tiles, T, e, s);                    \
         break;
-        HX_UNITS(DEC_RAW, 1)
+        case DEC_RAW: launch_mode<1, DEC_RAW>(Wp, Xa, N, k_tiles, T, e, s); break;
         HX_UNITS(DEC_QKV, 1)
         HX_UNITS(DEC_RESID, 1)
         HX_UNITS(DEC_SWIGLU, 2)
