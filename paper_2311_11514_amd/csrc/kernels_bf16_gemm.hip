@@ -941,11 +941,12 @@ void launch_gemm_mfma(const h16_t *Wp, const h16_t *Xp, int N, int K, int T, con
 
 // A row's finishing pass -- its heads' sums over the splits, rotary embedding, cache append -- is a few KB that the attention
 // block of the same (sequence, kv head) reads while its first K / V tiles are on their way: one launch and one trip of q
-// through memory less.  It lengthens every block by about 3 us, so it is left to the attention only where all of the blocks
-// run at once (512: two per CU).  Measured per layer at 33 / 64 / 100 / 128 rows, 600 positions, without -> with: TP8 shard of
+// through memory less.  It lengthens every block by about 3 us, so it is left to the attention only up to two blocks per CU (at
+// head dim 64 both run at once, at 128 one after the other: 176 registers).  Measured per layer at 33 / 64 / 100 / 128 rows, 600 positions, without -> with: TP8 shard of
 // the 70B shape 90.6 / 92.7 / 108.4 / 111.7 -> 86.2 / 89.8 / 106.1 / 109.8 us, TP4 119.4 / 123.5 / 144.4 / 152.2 -> 115.0 /
 // 120.6 / 141.6 / 149.3; 8 kv heads of a 4096-wide model 126.5 / 143.5 / 185.5 / 197.5 -> 124.2 / 142.5 / 189.6 / 199.8, of a
-// 2048-wide one 69.5 / 77.5 / 98.6 / 104.3 -> 68.5 / 76.8 / 102.9 / 107.3: beyond 512 blocks it loses.
+// 2048-wide one 69.5 / 77.5 / 98.6 / 104.3 -> 68.5 / 76.8 / 102.9 / 107.3 (64-wide heads, since then two blocks on a CU: at 40 / 60 rows
+// 68.2 / 72.6 -> 64.8 / 69.3): beyond 512 blocks it loses.
 void launch_gemm_qkv_rows(const h16_t *Wp, const h16_t *Xp, int N, int K, int T, const GemmEpi &e, float *part,
                           size_t part_floats, QkvTail *tail, hipStream_t s) {
     *tail = QkvTail{};

@@ -439,12 +439,14 @@ int pick_attn_split(const hexgen_stage *st, const hexgen_kv_cache *kv, int batch
     // in a few steps: one block per pair.  (Measured on a ragged batch of 32 x 8 pairs, contexts 240..4027: the launch
     // ends 11 us after the same bytes in equal contexts would, but every way of cutting the long contexts -- evenly, or
     // only those above the even share per CU -- costs more than that: a block's fixed part, query load and the merge of
-    // its waves, is about 7 us and a CU holds one 8-wave block at a time.)
+    // its waves, is about 7 us and a CU holds one 8-wave block of head dim 128 at a time.)
     // Otherwise every context is split evenly: a block's time falls with the number of splits (one CU's load path
     // delivers about 150 GB/s), while every block adds its own tail (partials written through, the count, the merge).
     // Few pairs: the measured optimum sits near sqrt(6 tiles / pairs).  From 32 pairs on only a walk that is long against
     // them is cut, in three (equal contexts, us per launch unsplit / in three: 32 pairs at 2048 and 4000 positions 21.5 / 19.1 and
-    // 30.4 / 21.5, 64 pairs at 2048 and 4000 22.5 / 23.3 and 44.9 / 31.6, 128 pairs at 4000 49.0 / 57.2).
+    // 30.4 / 21.5, 64 pairs at 2048 and 4000 22.5 / 23.3 and 44.9 / 31.6, 128 pairs at 4000 49.0 / 57.2).  The longest context decides
+    // there, however short the others are: one of 4000 among 240s, 32 and 64 pairs, 28.2 / 19.2 and 29.7 / 21.4; every other one of 300
+    // 28.8 / 19.9 and 32.1 / 24.5; an even ramp from 240 to 4000 28.3 / 19.6 and 31.2 / 25.3.
     const int pairs = batch * st->hkv_l;
     if (n_t32 <= 48) return 1;
     if (pairs >= 32) return pairs <= 64 && 2 * n_t32 >= 3 * pairs + 32 ? 3 : 1;
@@ -893,7 +895,7 @@ hexgen_status_t hexgen_stage_load_layer(hexgen_stage_t *st, int layer, const voi
 // ---- KV cache ------------------------------------------------------------------------------------
 hexgen_status_t hexgen_kv_cache_create(hexgen_stage_t *st, int max_batch, int max_seq, hexgen_kv_cache_t **out) {
     if (!st || !out || max_batch <= 0 || max_seq <= 0) return HEXGEN_ERR_INVALID_ARG;
-    if (st->dtype == HEXGEN_F32 && max_seq > 8192) return HEXGEN_ERR_CAPACITY;
+    if (st->dtype == HEXGEN_F32 && max_seq > 8192) return HEXGEN_ERR_CAPACITY;     // the fp32 stage's range; no kernel depends on it
     hexgen_kv_cache *kv = new (std::nothrow) hexgen_kv_cache();
     if (!kv) return HEXGEN_ERR_OOM;
     kv->st = st;
