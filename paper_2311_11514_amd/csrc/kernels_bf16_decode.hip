@@ -577,13 +577,15 @@ void launch_one(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, con
 
 template <int UT, int MODE>
 void launch_mode(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, const DecodeEpi &e, hipStream_t s) {
-    // a contraction of at most 32 k-tiles gives a wave 4 of them: a ring of 4 requests nothing it does not use (and lets a CU hold
-    // two blocks at 17 .. 32 rows, 106 registers for 186: 1000 units of the LM head, 32 rows of 512 / 1024 x 16000, 31.3 / 34.2 -> 19.7 / 22.0 us)
+    // a contraction of at most 32 k-tiles gives a wave 4 of them: a ring of 4 requests nothing it does not use.  The LM head beyond 16
+    // rows takes it at any length: 106 registers for 186, so that a CU holds two blocks (32 rows of 512 / 1024 x 16000 31.3 / 34.2 ->
+    // 19.7 / 22.0 us, of 1536 / 2048 x 8000 22.6 / 23.8 -> 18.6 / 20.1, of 4096 x 4000 20.9 -> 20.8).
     constexpr int RING = 8 / UT, SHORT = UT == 1 && (MODE == DEC_RESID || MODE == DEC_BEST) ? 4 : RING;
 #define HX_ONE(NP)                                                                                              \
     do {                                                                                                        \
+        constexpr int LONG = MODE == DEC_BEST && (NP) == 4 ? SHORT : RING;                                      \
         if (k_tiles <= 32) launch_one<NP, UT, SHORT, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);              \
-        else launch_one<NP, UT, RING, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);                             \
+        else launch_one<NP, UT, LONG, MODE, false, 1>(Wp, Xa, N, k_tiles, T, e, s);                             \
     } while (0)
     constexpr int NPM = UT == 4 ? 2 : 4;          // (blocks of four feature tiles take 16 rows at most: unit_pairs)
     if (T > 16) HX_ONE(NPM);

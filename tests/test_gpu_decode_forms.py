@@ -78,7 +78,7 @@ def test_decode_rows_around_position_tiles(cfg, rows):
         check(f"{rows} rows step {k} partial", p, p_ref, TOL[cfg.dtype])
 
 
-@pytest.mark.parametrize("hidden,vocab,rows", [(128, 1000, 40), (1024, 1000, 20), (4096, 1000, 20), (1024, 4104, 33), (1024, 4104, 48), (1024, 4104, 49), (1024, 4104, 64), (1024, 4104, 65)] +
+@pytest.mark.parametrize("hidden,vocab,rows", [(128, 1000, 40), (1024, 1000, 20), (4096, 1000, 20), (2048, 3208, 17), (2048, 3208, 32), (1024, 4104, 33), (1024, 4104, 48), (1024, 4104, 49), (1024, 4104, 64), (1024, 4104, 65)] +
                          # units of two tiles (from 1024 tiles on) and columns beyond the last: one kernel at 7, 9 and 17 rows, split at 17 of a short contraction and from 33 on
                          [(1536, 16411, 7), (1536, 16411, 9), (1536, 16411, 17), (1024, 16411, 17), (1024, 16411, 32), (1024, 16411, 48), (1024, 16411, 64)])
 def test_head_rows(hidden, vocab, rows):
