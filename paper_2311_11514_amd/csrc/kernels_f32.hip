@@ -2,7 +2,7 @@
 // fused multiply-add, so operands, products and sums keep full precision).
 //   * up to 32 rows: f32_stream_kernel -- a block streams the weights of 16 or 32 output columns over the whole
 //     contraction and finishes them in registers (norm, residual, SwiGLU): five launches per layer in a decode step;
-//   * more rows: f32_tile_kernel -- 64 x 128 tiles through LDS, the contraction split where the tiles leave CUs idle;
+//   * more rows: f32_tile_kernel -- 64 x 128 tiles through LDS, their k-steps dealt out evenly over the CUs;
 //   * attention: f32_attn_kernel -- 16 query columns (rows of one head, or the heads of one kv group) against the cache.
 // Weight rows are padded with zeros to a multiple of 32 and matrix widths to a multiple of 16 (stage.hip), so no loop here
 // has a ragged end in either direction.
@@ -20,12 +20,28 @@ __device__ __forceinline__ float f32_silu_mul(float a, float b) { return a / (1.
 __global__ __launch_bounds__(256) void f32_rmsnorm_kernel(const float *__restrict__ in, const float *__restrict__ g,
                                                          float *__restrict__ out, int H, float eps) {
     __shared__ float red[4];
-    const int t = blockIdx.x;
+    constexpr int R = 4;                       // 16-byte pieces a thread keeps: rows of up to 4096 are read once
+    const size_t row = (size_t)blockIdx.x * H;
+    floatx4 x[R], gv[R];
     float ss = 0.f;
-    for (int c = threadIdx.x; c < H; c += 256) { float x = in[(size_t)t * H + c]; ss += x * x; }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int c = min(4 * ((int)threadIdx.x + 256 * i), H - 4);
+        x[i] = *reinterpret_cast<const floatx4 *>(in + row + c);
+        gv[i] = *reinterpret_cast<const floatx4 *>(g + c);
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+        if (4 * ((int)threadIdx.x + 256 * i) < H) ss += x[i][0] * x[i][0] + x[i][1] * x[i][1] + x[i][2] * x[i][2] + x[i][3] * x[i][3];
+    for (int c = threadIdx.x + 1024 * R; c < H; c += 256) ss += in[row + c] * in[row + c];
     ss = block_sum_256(ss, red);
     const float rstd = 1.0f / sqrtf(ss / (float)H + eps);
-    for (int c = threadIdx.x; c < H; c += 256) out[(size_t)t * H + c] = in[(size_t)t * H + c] * rstd * g[c];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int c = 4 * ((int)threadIdx.x + 256 * i);
+        if (c < H) *reinterpret_cast<floatx4 *>(out + row + c) = x[i] * rstd * gv[i];
+    }
+    for (int c = threadIdx.x + 1024 * R; c < H; c += 256) out[row + c] = in[row + c] * rstd * g[c];
 }
 void f32_launch_rmsnorm(const float *in, const float *g, float *out, int T, int H, float eps, hipStream_t s) {
     if (T <= 0) return;
@@ -197,15 +213,15 @@ __global__ __launch_bounds__(512) void f32_stream_kernel(F32Proj p) {
 }
 
 // What leaves a tile or the sum of the splits: four consecutive columns n .. n + 3 of row t (for SwiGLU: a = gate, b = up)
+// h: the residual at the same place (F32_RESID)
 template <int MODE>
-__device__ __forceinline__ void f32_finish4(const F32Proj &p, int t, int n, floatx4 a, floatx4 b) {
+__device__ __forceinline__ void f32_finish4(const F32Proj &p, int t, int n, floatx4 a, floatx4 b, floatx4 h) {
     const size_t o = (size_t)t * p.cols + n;
     if (MODE == F32_SWIGLU) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) a[r] = f32_silu_mul(a[r], b[r]);
         *reinterpret_cast<floatx4 *>(p.out + o) = a;
     } else if (MODE == F32_RESID) {
-        const floatx4 h = *reinterpret_cast<const floatx4 *>(p.resid + o);
         if (p.resid_out) {
             *reinterpret_cast<floatx4 *>(p.resid_out + o) = h + a;
         } else {
@@ -218,134 +234,261 @@ __device__ __forceinline__ void f32_finish4(const F32Proj &p, int t, int n, floa
 }
 
 // -------------------------------------------------------------------------------------------------
-// T > 32 rows: 64 rows x 128 columns (SwiGLU: 64 gate columns and their 64 up columns) per block of 4 waves, a wave 32 rows
-// x 64 columns as two 32x32 results of v_mfma_f32_32x32x2_f32 (operand A = columns, so that a lane ends up with
-// neighbouring columns of one row).  32-deep k-steps, two LDS buffers, the next step's global loads in registers while the
-// current one is multiplied, one barrier per step.  A step is 32 MFMAs of 64 cycles per wave against 28 LDS reads: bound
-// by the matrix cores; 53 KB of LDS lets three blocks share a CU and cover each other's barriers.  Measured at 572 rows x
-// 2048 x 11264 (SwiGLU): 883 -> 297 us, 89 TFLOP/s of the 154 a large library product reaches (792 blocks: the fullest CU has
-// four, the average 3.1); two layers 6270 -> 1142 us.
-// blockIdx.z: split of the contraction (see f32_launch_proj); the splits' sums go to `part` and f32_tile_finish_kernel.
+// T > 32 rows: tiles of 64 rows x 128 columns (SwiGLU: 64 gate columns and their 64 up columns), one block of 8 waves per CU,
+// a wave 32 rows x 32 columns on v_mfma_f32_32x32x2_f32 (operand A = columns, so that a lane ends up with neighbouring
+// columns of one row).  A 32-deep k-step is 32 MFMAs of 64 cycles on every SIMD: bound by the matrix cores, as long as
+//   * operands come in time: direct-to-LDS loads, four stages resident, three k-steps ahead of their use (with one step ahead, in
+//     registers, memory latency showed in every step);
+//   * LDS latency and barriers stay behind MFMAs: the operands of 8 rows are fetched while the 8 rows before them are multiplied,
+//     and the step's one barrier sits in its middle, so that the next step's first operands are fetched before this one ends;
+//   * every CU has the same number of k-steps: the blocks are persistent.  Each takes an equal share of the k-steps of the tiles
+//     that whole rounds of 256 leave over -- partial sums, which f32_tile_finish_kernel adds up -- and then its share of whole tiles.  792 tiles as blocks of their own gave the fullest CU four tiles where 3.1 is the average.
+// The stages run on over tile boundaries.  Measured, two layers of a 2048-wide stage at 572 rows (three prompts), whole call 1154 -> 948 us; 33 .. 3000 rows of 512- to 4096-wide stages 0 .. 23 % less, 10 % on average;
+// cycles of the matrix cores / of the launch: QKV (2048 x 3072, whole tiles) 0.96 on the CUs that have one, W1/W3 (2048 x 11264) 0.87, W2 (5632 x
+// 2048, all dealt out, so that blocks on a die are at different k and share little in its L2) 0.86.  Six stages, or a barrier every
+// other step, change nothing.
 // -------------------------------------------------------------------------------------------------
-constexpr int F32_BT = 64, F32_BN = 128, F32_BK = 32, F32_XS = 36, F32_WS = 136;     // row strides of the LDS tiles (floats)
-template <int MODE>
-__global__ __launch_bounds__(256) void f32_tile_kernel(F32Proj p, float *__restrict__ part) {
-    constexpr bool GLU = MODE == F32_SWIGLU;
-    __shared__ __align__(16) float sx[2][F32_BT][F32_XS], sw[2][F32_BK][F32_WS];
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hl = lane >> 5;
-    const int bt = blockIdx.y * F32_BT, bn = blockIdx.x * (GLU ? F32_BN / 2 : F32_BN);
-    const int wt = wave & 1, wn = wave >> 1;
-    const int ksteps = p.Kp / F32_BK;
-    const int k_lo = (int)((long)blockIdx.z * ksteps / gridDim.z), k_hi = (int)((long)(blockIdx.z + 1) * ksteps / gridDim.z);
+constexpr int F32_BT = 64, F32_BN = 128, F32_BK = 32, F32_ST = 4, F32_CUS = 256;
+constexpr int F32_SLOT = F32_BT * F32_BN;                 // floats of one tile's partial sums
 
-    // staging: rows tid / 8 (+ 32) x 16 bytes of the token rows; weight rows tid / 32 (+ 8, 16, 24) x 16 bytes
-    const float *xsrc[2], *wsrc;
-#pragma unroll
-    for (int q = 0; q < 2; ++q) xsrc[q] = p.x + (size_t)min(bt + (tid >> 3) + 32 * q, p.T - 1) * p.K + 4 * (tid & 7);
-    {
-        const int c = 4 * (tid & 31);
-        const int n = GLU ? min(bn + (c & 63), p.cols - 4) + (c >> 6) * p.cols : min(bn + c, p.cols - 4);
-        wsrc = p.w + (size_t)(tid >> 5) * p.N + n;
-    }
-    floatx4 rx[2], rw[4];
-    auto load = [&](int k) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) rx[q] = *reinterpret_cast<const floatx4 *>(xsrc[q] + (size_t)k * F32_BK);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) rw[q] = *reinterpret_cast<const floatx4 *>(wsrc + (size_t)(k * F32_BK + 8 * q) * p.N);
-    };
-    auto store = [&](int buf) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) *reinterpret_cast<floatx4 *>(&sx[buf][(tid >> 3) + 32 * q][4 * (tid & 7)]) = rx[q];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) *reinterpret_cast<floatx4 *>(&sw[buf][(tid >> 5) + 8 * q][4 * (tid & 31)]) = rw[q];
-    };
-    floatx16 acc[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-    load(k_lo);
-    store(0);
-    __syncthreads();
-    // operands of the 8-row group s of a step; k-slot hl of MFMA x = row 8 s + 4 hl + x
-    floatx4 x4[2];
-    floatx2 w2[2][4];
-    auto fetch = [&](int buf, int s) {
-        x4[s & 1] = *reinterpret_cast<const floatx4 *>(&sx[buf][32 * wt + l32][8 * s + 4 * hl]);
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const float *row = sw[buf][8 * s + 4 * hl + x];
-            if constexpr (GLU) w2[s & 1][x] = floatx2{row[32 * wn + l32], row[64 + 32 * wn + l32]};
-            else w2[s & 1][x] = *reinterpret_cast<const floatx2 *>(row + 64 * wn + 2 * l32);
-        }
-    };
-    // The order is held by scheduling barriers: left to itself the compiler moves the next step's global loads down to their
-    // use at the end of the step and fetches every group's operands right in front of its MFMAs.
-    for (int k = k_lo; k < k_hi; ++k) {
-        const int buf = (k - k_lo) & 1;
-        load(min(k + 1, k_hi - 1));
-        fetch(buf, 0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < F32_BK / 8; ++s) {
-            if (s + 1 < F32_BK / 8) fetch(buf, s + 1);
-            else store(buf ^ 1);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                acc[0] = f32_mfma32(w2[s & 1][x][0], x4[s & 1][x], acc[0]);
-                acc[1] = f32_mfma32(w2[s & 1][x][1], x4[s & 1][x], acc[1]);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        __syncthreads();
-    }
-    const int t = bt + 32 * wt + l32;
+// What the blocks of a launch walk, see above.  Tiles are numbered token block fastest.
+struct F32Walk {
+    int gy, tiles, ksteps;
+    int rounds;                // tiles that block w takes whole: w, w + workers, ... (rounds of them, as far as there are tiles)
+    int first, count;          // tiles whose k-steps are dealt out: first .. first + count - 1
+    int workers, dealers;      // blocks of the launch; the first of them that get a share of the dealt-out k-steps, each at least one of them
+};
+// first dealt-out k-step of block w (256 x k-steps fits 31 bits: f32_proj_mode)
+__device__ inline int f32_share(const F32Walk &k, int w) {
+    return (int)((unsigned)min(w, k.dealers) * (unsigned)(k.count * k.ksteps) / (unsigned)k.dealers);
+}
+
+typedef __attribute__((address_space(3))) void *f32_lds_ptr;
+#define F32_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
+#define F32_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14))
+
+// A wave's 32 x 32 result: lane l holds row l % 32 and, in register 4 q + r, column 8 q + 4 (l / 32) + r of the wave's columns (SwiGLU:
+// quads 0, 1 are 16 gate columns, quads 2, 3 the up columns that belong to them)
+template <int MODE>
+__device__ __forceinline__ void f32_tile_store(const F32Proj &p, int bn, int bt, int wave, int lane, const floatx16 &c) {
+    const int t = bt + 32 * (wave & 1) + (lane & 31), hl = lane >> 5, wn = wave >> 1;
     if (t >= p.T) return;
+    constexpr int Q = MODE == F32_SWIGLU ? 2 : 4;
+    floatx4 h[Q];
+    if (MODE == F32_RESID) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if constexpr (GLU) {
-            // register 4 q + r: gate (acc[0]) and up (acc[1]) column bn + 32 wn + 8 q + 4 hl + r
-            const int n = bn + 32 * wn + 8 * q + 4 * hl;
-            if (n >= p.cols) continue;
-            const floatx4 a = {acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]};
-            const floatx4 b = {acc[1][4 * q], acc[1][4 * q + 1], acc[1][4 * q + 2], acc[1][4 * q + 3]};
-            if (part != nullptr) {
-                float *dst = part + ((size_t)blockIdx.z * p.T + t) * p.N + n;
-                *reinterpret_cast<floatx4 *>(dst) = a;
-                *reinterpret_cast<floatx4 *>(dst + p.cols) = b;
-            } else {
-                f32_finish4<MODE>(p, t, n, a, b);
-            }
-        } else {
-            // register 4 q + r of acc[j]: column bn + 64 wn + 2 (8 q + 4 hl + r) + j
+        for (int q = 0; q < Q; ++q) h[q] = *reinterpret_cast<const floatx4 *>(p.resid + (size_t)t * p.cols + min(bn + 32 * wn + 8 * q + 4 * hl, p.cols - 4));
+    }
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const int n = bn + 64 * wn + 16 * q + 8 * hl + 4 * half, r = 4 * q + 2 * half;
-                if (n >= p.cols) continue;
-                const floatx4 a = {acc[0][r], acc[1][r], acc[0][r + 1], acc[1][r + 1]};
-                if (part != nullptr) *reinterpret_cast<floatx4 *>(part + ((size_t)blockIdx.z * p.T + t) * p.N + n) = a;
-                else f32_finish4<MODE>(p, t, n, a, a);
-            }
-        }
+    for (int q = 0; q < Q; ++q) {
+        const int n = bn + (MODE == F32_SWIGLU ? 16 : 32) * wn + 8 * q + 4 * hl;
+        if (n >= p.cols) continue;
+        const floatx4 a = {c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+        const int u = MODE == F32_SWIGLU ? 4 * (q + 2) : 0;
+        f32_finish4<MODE>(p, t, n, a, floatx4{c[u], c[u + 1], c[u + 2], c[u + 3]}, h[q]);
     }
 }
 
-// adds the splits up in split order; one thread per row and four columns
 template <int MODE>
-__global__ __launch_bounds__(256) void f32_tile_finish_kernel(F32Proj p, const float *__restrict__ part, int splits) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int per = p.cols >> 2;
-    if (idx >= (int64_t)p.T * per) return;
-    const int t = (int)(idx / per), n = 4 * (int)(idx % per);
-    floatx4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
-    for (int z = 0; z < splits; ++z) {
-        const float *src = part + ((size_t)z * p.T + t) * p.N + n;
-        a += *reinterpret_cast<const floatx4 *>(src);
-        if (MODE == F32_SWIGLU) b += *reinterpret_cast<const floatx4 *>(src + p.cols);
+__global__ __launch_bounds__(512) void f32_tile_kernel(F32Proj p, F32Walk k, float *__restrict__ part) {
+    constexpr bool GLU = MODE == F32_SWIGLU;
+    constexpr int SW = F32_BK * F32_BN, STAGE = SW + F32_BT * F32_BK;          // floats: weight rows, then token rows
+    __shared__ __align__(16) float smem[F32_ST * STAGE];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hl = lane >> 5;
+    // consecutive tiles on one die: they share weight columns (blocks are dealt to the eight dies in turn)
+    const int w = (blockIdx.x & 7) * (k.workers >> 3) + (blockIdx.x >> 3);
+
+    // This block's pieces: up to two ranges of k-steps of dealt-out tiles, then whole tiles (the last ones end everywhere at once).
+    // All of this is uniform: said to the compiler, which divides in vector registers, so that the loop counts in scalar ones.
+    int whole = 0;
+    while (whole < k.rounds && w + whole * k.workers < k.tiles) ++whole;
+    const int u0 = __builtin_amdgcn_readfirstlane(f32_share(k, w)), u1 = __builtin_amdgcn_readfirstlane(f32_share(k, w + 1));
+    const int t0 = __builtin_amdgcn_readfirstlane(u0 / k.ksteps), cut = min(u1, (t0 + 1) * k.ksteps);
+    const int ranges = __builtin_amdgcn_readfirstlane((u1 > u0 ? 1 : 0) + (u1 > cut ? 1 : 0));
+    const int n_pieces = ranges + whole, steps = whole * k.ksteps + u1 - u0;
+    if (steps == 0) return;                           // the whole block leaves
+    struct Piece { int tile, lo, hi; };
+    auto piece = [&](int i) {
+        if (i >= ranges) return Piece{w + (i - ranges) * k.workers, 0, k.ksteps};
+        if (i == 0) return Piece{k.first + t0, u0 - t0 * k.ksteps, cut - t0 * k.ksteps};
+        return Piece{k.first + t0 + 1, 0, u1 - cut};
+    };
+    const int bnw = GLU ? F32_BN / 2 : F32_BN;
+
+    // Loads: a wave copies weight rows 2 wave, 2 wave + 1 and those + 16 (512 bytes each) and token rows 8 wave .. + 7 (128 bytes each) of
+    // every k-step; a lane's 16 bytes land at its slot of the 1 KB piece.  Which column it fetches spreads the later reads over the
+    // banks: weight rows 4 .. 7 of every eight swap neighbouring 32-column blocks, a token row's 16-byte pieces are XORed
+    // with the row.
+    int li = 0, lleft = 0;                            // piece of the next load, k-steps left of it
+    const float *wsrc = p.w, *xsrc = p.x;
+    unsigned woff = 0, xoff = 0;
+    const size_t wstep = (size_t)F32_BK * p.N, whalf = (size_t)16 * p.N;
+    auto load_tile = [&]() {
+        const Piece q = piece(li);
+        const int col = __builtin_amdgcn_readfirstlane(q.tile / k.gy), bn = col * bnw, bt = (q.tile - col * k.gy) * F32_BT;
+        lleft = __builtin_amdgcn_readfirstlane(q.hi - q.lo);
+        const int c = (4 * l32) ^ ((wave & 2) ? 32 : 0);
+        const int n = GLU ? min(bn + 16 * (c >> 5) + (c & 15), p.cols - 4) + ((c & 16) ? p.cols : 0) : min(bn + c, p.cols - 4);
+        woff = ((unsigned)hl * (unsigned)p.N + (unsigned)n) * 4u;
+        const int row = 8 * wave + (lane >> 3), t = min(bt + row, p.T - 1) - bt;
+        xoff = ((unsigned)t * (unsigned)p.K + 4u * ((lane & 7) ^ (row & 7))) * 4u;
+        xsrc = p.x + (size_t)bt * p.K + q.lo * F32_BK;
+        wsrc = p.w + (size_t)(q.lo * F32_BK + 2 * wave) * p.N;
+    };
+    // the x-th of the three loads of a k-step into stage buffer `buf` (floats from the start of LDS)
+    const unsigned lds0 = (unsigned)reinterpret_cast<uintptr_t>((f32_lds_ptr)smem) + wave * 1024u;
+    auto issue = [&](int buf, int x) {
+        const unsigned lds = lds0 + 4u * buf + (x == 0 ? 0u : x == 1 ? 8192u : 4u * SW);
+        const float *src = x == 0 ? wsrc : x == 1 ? wsrc + whalf : xsrc;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(x < 2 ? woff : xoff), "s"(src) : "memory");
+    };
+    size_t wadv = wstep;
+    int xadv = F32_BK;
+    auto advance = [&]() {       // past the last piece the last k-step is loaded again, into a stage nobody reads
+        wsrc += wadv;
+        xsrc += xadv;
+        lleft = __builtin_amdgcn_readfirstlane(lleft - 1);
+        if (lleft == 0) {
+            ++li;
+            if (li < n_pieces) {
+                load_tile();
+            } else {
+                wsrc -= wadv;
+                xsrc -= xadv;
+                wadv = 0;
+                xadv = 0;
+                lleft = 0x7fffffff;
+            }
+        }
+    };
+
+    // operands of the 8-row group s of a stage; k-slot hl of MFMA x = row 8 s + 4 hl + x
+    floatx4 x4[2];
+    float wv[2][4];
+    const unsigned xrow = (32 * (wave & 1) + l32) * F32_BK + 4 * (hl ^ (l32 & 7));
+    const unsigned wcol = 4 * hl * F32_BN + 32 * ((wave >> 1) ^ hl) + l32;
+    auto fetch = [&](int buf, int s) {
+        const float *st = smem + buf;
+        x4[s & 1] = *reinterpret_cast<const floatx4 *>(st + SW + (xrow ^ (8 * s)));
+#pragma unroll
+        for (int x = 0; x < 4; ++x) wv[s & 1][x] = st[wcol + (8 * s + x) * F32_BN];
+    };
+    floatx16 acc[2];
+    auto mfma = [&](int s, int x) { acc[x & 1] = f32_mfma32(wv[s & 1][x], x4[s & 1][x], acc[x & 1]); };
+    auto multiply = [&](int s) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) mfma(s, x);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto clear = [&]() {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    };
+    load_tile();
+#pragma unroll
+    for (int i = 0; i < F32_ST - 1; ++i) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) issue(i * STAGE, x);
+        advance();
     }
-    f32_finish4<MODE>(p, t, n, a, b);
+    clear();
+    F32_WAIT_VM((F32_ST - 2) * 3);
+    asm volatile("s_barrier" ::: "memory");
+    fetch(0, 0);
+    int ci = 0, buf = 0, lbuf = (F32_ST - 1) * STAGE;
+    Piece now = piece(0);
+    int left = now.hi - now.lo;
+    // The order below is held by scheduling barriers.  Nothing but the two waits stands between the barrier and the next MFMA: what the step
+    // computes for its loads is done ahead of it, the loads go between the MFMAs behind it.
+    for (int u = 0; u < steps; ++u) {
+        const int nbuf = buf + STAGE == F32_ST * STAGE ? 0 : buf + STAGE;
+        fetch(buf, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0);
+        fetch(buf, 2);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1);
+        F32_WAIT_VM((F32_ST - 3) * 3);          // this wave's loads of step u + 1 have landed ...
+        F32_WAIT_LGKM0();
+        asm volatile("s_barrier" ::: "memory");       // ... and everybody's; nobody reads step u - 1 any more
+        fetch(buf, 3);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            mfma(2, x);
+            if (x < 3) issue(lbuf, x);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        fetch(nbuf, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(3);
+        advance();
+        lbuf = buf;
+        buf = nbuf;
+        if (--left == 0) {
+            floatx16 c;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) c[r] = acc[0][r] + acc[1][r];
+            if (now.hi - now.lo == k.ksteps) {
+                f32_tile_store<MODE>(p, now.tile / k.gy * bnw, now.tile % k.gy * F32_BT, wave, lane, c);
+            } else {
+                float *dst = part + (size_t)(2 * w + ci) * F32_SLOT + wave * 1024 + lane * 4;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) *reinterpret_cast<floatx4 *>(dst + q * 256) = floatx4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+            }
+            clear();
+            // (loads and stores complete in the order of their issue: with results still in flight the waits above only wait for more)
+            now = piece(++ci);
+            left = now.hi - now.lo;
+        }
+    }
+    F32_WAIT_VM(0);
+}
+
+// The dealt-out tiles: adds a tile's pieces up in the order of the contraction.  One wave per 32 x 8 results (SwiGLU: 32 x 8 gate and
+// the up columns that belong to them), eight pieces requested at a time: round trips to the memory-side cache bound it.
+template <int MODE>
+__global__ __launch_bounds__(256) void f32_tile_finish_kernel(F32Proj p, F32Walk k, const float *__restrict__ part) {
+    constexpr bool GLU = MODE == F32_SWIGLU;
+    constexpr int Q = GLU ? 2 : 4;                              // waves per 32 x 32
+    const int lane = threadIdx.x & 63, idx = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = idx / (8 * Q), wave = idx / Q % 8, q = idx % Q;
+    // workers whose shares meet k-steps t * ksteps .. (t + 1) * ksteps - 1
+    const int s0 = t * k.ksteps, s1 = s0 + k.ksteps;
+    int w0 = t * k.dealers / k.count;
+    while (w0 > 0 && f32_share(k, w0) > s0) --w0;
+    while (f32_share(k, w0 + 1) <= s0) ++w0;
+    int w1 = w0;                                                // the last of them
+    while (f32_share(k, w1 + 1) < s1) ++w1;
+    if (f32_share(k, w0) <= s0 && w1 == w0) return;             // one worker had all of it and has finished it
+    const int tile = k.first + t;
+    const int row = tile % k.gy * F32_BT + 32 * (wave & 1) + (lane & 31);
+    const int n = tile / k.gy * (GLU ? F32_BN / 2 : F32_BN) + (GLU ? 16 : 32) * (wave >> 1) + 8 * q + 4 * (lane >> 5);
+    // only the first worker's piece can be its second one
+    const float *src = part + (size_t)(2 * w0 + (f32_share(k, w0) < s0 && f32_share(k, w0) / k.ksteps < t)) * F32_SLOT + wave * 1024 + q * 256 + lane * 4;
+    const float *next = part + (size_t)(2 * w0 + 2) * F32_SLOT + wave * 1024 + q * 256 + lane * 4;
+    floatx4 a = {0.f, 0.f, 0.f, 0.f}, b = a, h = a;
+    const bool inside = row < p.T && n < p.cols;
+    if (MODE == F32_RESID && inside) h = *reinterpret_cast<const floatx4 *>(p.resid + (size_t)row * p.cols + n);
+    for (int w = w0; w <= w1; w += 8) {
+        floatx4 va[8], vb[GLU ? 8 : 1];
+#pragma unroll
+        for (int z = 0; z < 8; ++z) {
+            const int wz = min(w + z, w1);
+            const float *at = wz == w0 ? src : next + (size_t)(wz - w0 - 1) * 2 * F32_SLOT;
+            va[z] = *reinterpret_cast<const floatx4 *>(at);
+            if constexpr (GLU) vb[z] = *reinterpret_cast<const floatx4 *>(at + 512);
+        }
+#pragma unroll
+        for (int z = 0; z < 8; ++z)
+            if (w + z <= w1) {
+                a += va[z];
+                if constexpr (GLU) b += vb[z];
+            }
+    }
+    if (inside) f32_finish4<MODE>(p, row, n, a, b, h);
 }
 
 namespace {
@@ -384,22 +527,35 @@ void f32_proj_mode(const F32Proj &p, float *n_buf, float *part, size_t part_floa
         t.x = n_buf;
     }
     const int bn = MODE == F32_SWIGLU ? F32_BN / 2 : F32_BN;
-    const int gx = (p.cols + bn - 1) / bn, gy = (p.T + F32_BT - 1) / F32_BT, ksteps = p.Kp / F32_BK;
-    // The blocks of a CU share its matrix cores, so a launch takes (blocks on the fullest CU) x (k-steps of a block); a step
-    // is 0.9 us at the matrix rate.  Splitting the contraction evens out the CUs and costs the partial sums' way through
-    // memory (written and read, about 4 TB/s) and a second launch: the cheapest of 1 .. 16 splits of 4 k-steps or more.
-    int splits = 1;
-    double best = 0.0;
-    for (int c = 1; c <= 16 && (c == 1 || c * 4 <= ksteps); ++c) {
-        if (c > 1 && (part == nullptr || (size_t)c * p.T * p.N > part_floats)) break;
-        const double us = 0.9 * ((gx * gy * c + 255) / 256) * ((ksteps + c - 1) / c) + (c > 1 ? 5.0 + (double)c * p.T * p.N * 8.0 / 4e6 : 0.0);
-        if (c == 1 || us < best) { best = us; splits = c; }
+    F32Walk k;
+    k.gy = (p.T + F32_BT - 1) / F32_BT;
+    k.tiles = (p.cols + bn - 1) / bn * k.gy;
+    k.ksteps = p.Kp / F32_BK;
+    // Whole tiles only: the fullest CU has ceil(tiles / 256) of them, a k-step is 0.95 us.  Dealing out the k-steps of the last, incomplete
+    // round evens that out and costs the partial sums' way through memory (written and read, about 4 TB/s) and a second launch, for which
+    // 3 us are charged: with 6 / 9 / 12 two layers take, 512 wide at 130 rows 161 -> 173 / 185 / 204 us, at 1000 rows 289 -> 309 / 310 / 310,
+    // 1024 wide at 572 rows 364 -> 364 / 379 / 404, 2048 wide at 100 rows 312 -> 312 / 312 / 337, wider and longer ones the same.
+    const int full = k.tiles / F32_CUS, rest = k.tiles % F32_CUS;
+    const double step = 0.95;
+    k.rounds = full + (rest > 0);
+    k.first = k.count = 0;
+    k.workers = F32_CUS;
+    k.dealers = 1;
+    double best = step * k.rounds * k.ksteps;
+    const int most = std::min(F32_CUS, (int)((long)rest * k.ksteps / 4) / 8 * 8);       // blocks that share the rest: at least 4 k-steps each
+    if (rest > 0 && part != nullptr && most >= std::max(8, rest) && (long)rest * k.ksteps < (1l << 23)) {      // (no share longer than a tile)
+        const size_t slots = 2 * (size_t)most;
+        const double us = step * (full * k.ksteps + ((double)rest * k.ksteps + most - 1) / most) + 3.0 + (most + rest) * (double)F32_SLOT * 8.0 / 4e6;
+        if (us < best && slots * F32_SLOT <= part_floats) {
+            k.rounds = full;
+            k.first = full * F32_CUS;
+            k.count = rest;
+            k.workers = full > 0 ? F32_CUS : most;
+            k.dealers = most;
+        }
     }
-    hipLaunchKernelGGL((f32_tile_kernel<MODE>), dim3(gx, gy, splits), dim3(256), 0, s, t, splits > 1 ? part : nullptr);
-    if (splits > 1) {
-        const int64_t n4 = (int64_t)p.T * (p.cols / 4);
-        hipLaunchKernelGGL((f32_tile_finish_kernel<MODE>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, t, part, splits);
-    }
+    hipLaunchKernelGGL((f32_tile_kernel<MODE>), dim3(k.workers), dim3(512), 0, s, t, k, part);
+    if (k.count > 0) hipLaunchKernelGGL((f32_tile_finish_kernel<MODE>), dim3((MODE == F32_SWIGLU ? 4 : 8) * k.count), dim3(256), 0, s, t, k, part);
 }
 }  // namespace
 

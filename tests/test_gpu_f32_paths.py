@@ -58,6 +58,23 @@ def test_f32_prefill_then_decode(case):
         check(f"V layer {layer}", vv.numpy().reshape(-1, d), oc.v[layer][s].reshape(-1, d), TOL["f32"])
 
 
+# the tiled products' ways of dealing tiles out to the CUs: a launch of fewer than 256 tiles cut along the contraction, of whole
+# tiles, of two full rounds and a few tiles whose k-steps go round (258 x 2 in W1/W3, the last one
+# 52 columns wide), contractions of two and four k-steps
+DEALT = [
+    (1024, 8, 2, 1500, 1, 0, [200, 33]),
+    (64, 1, 1, 4096, 1, 0, [40, 60]),
+    (128, 2, 1, 130, 1, 0, [1000, 88]),
+    (512, 4, 2, 16500, 1, 0, [100]),
+    (1024, 8, 2, 16700, 1, 0, [80]),
+]
+
+
+@pytest.mark.parametrize("case", DEALT, ids=[f"H{c[0]}F{c[3]}T{sum(c[6])}" for c in DEALT])
+def test_f32_tiles_dealt_out(case):
+    test_f32_prefill_then_decode(case)
+
+
 @pytest.mark.parametrize("rows", [24, 70])
 def test_f32_non_finite_rows_stay_with_their_successors(rows):
     """A row that is not finite reaches the rows behind it through the cache, and none before it."""
