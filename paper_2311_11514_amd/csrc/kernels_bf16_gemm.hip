@@ -46,10 +46,23 @@ namespace HX_NS {
 // therefore sit in the same lane, in quads q and q ^ 1 respectively q and q + 2: no cross-lane traffic.
 // acc_of(i, j): the wave's result tile (i, j) of its FM x FT tiles of block (bm, bt), wave (wm, wt), each asked for once
 // (the two-phase loop converts its 16 x 16 results tile by tile on demand); rstd_of(t): 1 / rms of the block's token column t.
+// pre (RESID, FM = FT = 1; else nullptr): residual and next gain per quad, requested by the caller ahead of its sums.
+struct ResidPre {
+    floatx4 h[4], g[4];
+};
+// token column `token`, features n0 .. n0 + 31 of a lane's 32 x 32 tile; entries outside the matrix re-read valid ones
+__device__ __forceinline__ void resid_request(ResidPre &p, int token, int n0, int hl, int N, int T, const GemmEpi &e) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int n = min(n0 + 8 * q, N - 8) + 4 * hl;
+        p.h[q] = *reinterpret_cast<const floatx4 *>(e.h + h_tile_offset(min(token, T - 1), n, N));
+        if (!e.last_layer) p.g[q] = *reinterpret_cast<const floatx4 *>(e.g_next + n);
+    }
+}
 template <int FM, int FT, int WM, int WT, int MODE, typename AccF, typename RstdF>
 __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int wm, int wt, int lane, int N,
                                               int n_tiles, int T, const GemmEpi &e, RstdF rstd_of,
-                                              float *ssq_lds = nullptr) {
+                                              float *ssq_lds = nullptr, const ResidPre *pre = nullptr) {
     constexpr int TA = 2 * FM * WM, TB = 2 * FT * WT, NTOK = TB * 16;
     const int hl = lane >> 5;
     if (MODE == DEC_RESID) {
@@ -76,14 +89,20 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
                                     : floatx4{0.f, 0.f, 0.f, 0.f};
                 }
         };
-        load_h(hv[0], 0);
+        if (pre == nullptr) {
+            load_h(hv[0], 0);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) hv[0][0][q] = pre->h[q];
+        }
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
             floatx4 gv[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int n = (bm * TA + (wm * FM + i) * 2) * 16 + 8 * q + 4 * hl;
-                gv[q] = (n < N && !e.last_layer) ? *reinterpret_cast<const floatx4 *>(e.g_next + n)
+                if (pre != nullptr) gv[q] = pre->g[q];
+                else gv[q] = (n < N && !e.last_layer) ? *reinterpret_cast<const floatx4 *>(e.g_next + n)
                                                  : floatx4{0.f, 0.f, 0.f, 0.f};
             }
             if (i + 1 < FM) load_h(hv[(i + 1) & 1], i + 1);
@@ -589,10 +608,11 @@ __global__ __launch_bounds__(256) void gemm_finish_kernel(const float *__restric
 #pragma unroll 8
         for (int gI = tid >> 5; gI < groups; gI += 8) ss += e.ssq_in[(size_t)gI * T + token];
     }
+    ResidPre pre;          // residual and gain are here with the first sums (W2 at 117 rows of a TP4 70B shard 6.8 -> 6.0 us, at 90 rows 5.8 -> 5.2)
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    auto add = [&](int z0, auto count) {
+    auto add = [&](int z0, auto count, bool first) {
         constexpr int C = decltype(count)::value;
         floatx4 v[C][4];
 #pragma unroll
@@ -600,6 +620,7 @@ __global__ __launch_bounds__(256) void gemm_finish_kernel(const float *__restric
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 v[z][q] = *reinterpret_cast<const floatx4 *>(part + part_offset(pg, z0 + z, nb, bt) + q * 256 + lane * 4);
+        if (MODE == DEC_RESID && first) resid_request(pre, bt * 32 + (lane & 31), ((fb0 + fb) * 4 + wave) * 32, lane >> 5, N, T, e);
 #pragma unroll
         for (int z = 0; z < C; ++z)
 #pragma unroll
@@ -608,11 +629,13 @@ __global__ __launch_bounds__(256) void gemm_finish_kernel(const float *__restric
                 for (int x = 0; x < 4; ++x) acc[4 * q + x] += v[z][q][x];
     };
     if (mine) {
-        int z = 0;
-        for (; z + 4 <= splits; z += 4) add(z, std::integral_constant<int, 4>{});
-        if (splits - z == 3) add(z, std::integral_constant<int, 3>{});
-        else if (splits - z == 2) add(z, std::integral_constant<int, 2>{});
-        else if (splits - z == 1) add(z, std::integral_constant<int, 1>{});
+        // the first one to four splits, whatever their number is modulo four, then four at a time
+        int z = (splits - 1) % 4 + 1;
+        if (z == 4) add(0, std::integral_constant<int, 4>{}, true);
+        else if (z == 3) add(0, std::integral_constant<int, 3>{}, true);
+        else if (z == 2) add(0, std::integral_constant<int, 2>{}, true);
+        else add(0, std::integral_constant<int, 1>{}, true);
+        for (; z < splits; z += 4) add(z, std::integral_constant<int, 4>{}, false);
     }
     if (norm) {
         ssum[tid >> 5][tid & 31] = ss;
@@ -625,7 +648,7 @@ __global__ __launch_bounds__(256) void gemm_finish_kernel(const float *__restric
         }
         __syncthreads();
     }
-    gemm_epilogue<1, 1, 4, 1, MODE>([&](int, int) { return acc; }, fb0 + fb, bt, wave, 0, lane, N, n_tiles, T, e, [&](int tl) { return rstd_s[tl]; }, ssq_lds);
+    gemm_epilogue<1, 1, 4, 1, MODE>([&](int, int) { return acc; }, fb0 + fb, bt, wave, 0, lane, N, n_tiles, T, e, [&](int tl) { return rstd_s[tl]; }, ssq_lds, MODE == DEC_RESID ? &pre : nullptr);
 }
 
 // the finishing launch of a split contraction over feature blocks (of 32) nb32_first .. + nb32_count - 1
