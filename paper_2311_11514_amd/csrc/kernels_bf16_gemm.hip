@@ -141,8 +141,7 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
         }
         if (!e.last_layer) {
             // sum of squares of each token over the 128 features of one partial: the two lane halves hold disjoint rows
-            static_assert(MODE != DEC_RESID || 32 * FM == GEMM_SSQ_COLS || (32 * FM * WM == GEMM_SSQ_COLS && WT == 1),
-                          "one partial per wave, or per block, and token");
+            static_assert(MODE != DEC_RESID || 32 * FM == GEMM_SSQ_COLS || 32 * FM * WM == GEMM_SSQ_COLS, "one partial per wave, or per block, and token");
             if constexpr (32 * FM == GEMM_SSQ_COLS) {
                 const int grp = (bm * TA + wm * FM * 2) * 16 / GEMM_SSQ_COLS;
 #pragma unroll
@@ -155,7 +154,7 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
 #pragma unroll
                 for (int j = 0; j < FT; ++j) {
                     const float tot = ssq[j] + __shfl_xor(ssq[j], 32, 64);
-                    if (hl == 0) ssq_lds[wm * NTOK + j * 32 + (lane & 31)] = tot;
+                    if (hl == 0) ssq_lds[wm * NTOK + (wt * FT + j) * 32 + (lane & 31)] = tot;
                 }
                 __syncthreads();
                 if (wm == 0) {
@@ -163,7 +162,7 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
                     for (int j = 0; j < FT; ++j) {
                         float tot = 0.f;
 #pragma unroll
-                        for (int w = 0; w < WM; ++w) tot += ssq_lds[w * NTOK + j * 32 + (lane & 31)];
+                        for (int w = 0; w < WM; ++w) tot += ssq_lds[w * NTOK + (wt * FT + j) * 32 + (lane & 31)];
                         if (hl == 0 && token[j] < T) e.ssq_out[(size_t)bm * T + token[j]] = tot;
                     }
                 }
@@ -798,6 +797,185 @@ __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__re
         if (id * 4 + w4 < pg.nb && j < pg.tb) part_store(part + part_offset(pg, blockIdx.y, id * 4 + w4, j), acc[j], lane);
 }
 
+// -------------------------------------------------------------------------------------------------
+// 128 features x 128 tokens per block, for launches of more than 128 rows that larger tiles would leave with few blocks and a split
+// contraction (takes_panel): no partial sums, no finishing pass.  Eight waves of 64 x 64, four on the even and four on the odd k-steps, which
+// takes a third off what 64 x 32 wave tiles read from LDS; their sums meet through LDS at the end.  A stage holds two k-steps (32 KB, four
+// stages).  A wave's operands of the next stage are read under the MFMAs of this one, so that at its one barrier a stage's buffer is already
+// in registers everywhere and free to be loaded again.  Bound by LDS (48 KB read and written per k-step, 384 cycles against 256 of
+// MFMAs) and by cache misses: a k-step takes 0.14 .. 0.2 us on cached operands, 0.16 .. 0.25 in earnest.
+// -------------------------------------------------------------------------------------------------
+template <int MODE>
+__global__ __launch_bounds__(512) void gemm_panel_kernel(const h16_t *__restrict__ Wp, const h16_t *__restrict__ Xp, int N, int k_tiles,
+                                                         int n_tiles, int t_tiles, int T, int n_blocks, int t_blocks, GemmEpi e) {
+    constexpr int S = 4, STEP = 16 * 64, STAGE = 2 * STEP;        // h16x8: a k-step holds 8 weight, then 8 activation tiles
+    constexpr int NTOK = 128, SSP = 512 / NTOK;
+    extern __shared__ h16x8 smem[];                               // [S][2][16][64], then 512 floats
+    float *ssq_s = reinterpret_cast<float *>(smem + S * STAGE);
+    const int total = n_blocks * t_blocks, per_xcd = (total + 7) / 8, id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per_xcd || id >= total) return;
+    int bm, bt;
+    gemm_tile_of_id(id, n_blocks, t_blocks, 4, min(8, t_blocks), bm, bt);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int grp = wave >> 2, wm = wave & 1, wt = (wave >> 1) & 1;
+    const int stages = (k_tiles + 1) >> 1;
+
+    // the sums of squares of the block's token columns, four threads per token (gemm_mfma_kernel)
+    if (MODE != DEC_RESID && e.ssq_in != nullptr) {
+        const int groups = e.norm_dim / GEMM_SSQ_COLS, token = min(bt * NTOK + tid % NTOK, T - 1);
+        float ss = 0.f;
+#pragma unroll 16
+        for (int gI = tid / NTOK; gI < groups; gI += SSP) ss += e.ssq_in[(size_t)gI * T + token];
+        ssq_s[tid] = ss;
+        HX_WAIT_VM(0);
+    }
+    auto rstd_of = [&](int tl) {
+        float ss = ssq_s[tl];
+#pragma unroll
+        for (int w = 1; w < SSP; ++w) ss += ssq_s[w * NTOK + tl];
+        return 1.0f / sqrtf(ss / (float)e.norm_dim + e.eps);
+    };
+
+    // Wave w copies weight tile w and activation tile w of both k-steps of a stage; k-steps past the end re-read the last one (the odd one of
+    // an odd contraction is not multiplied, later stages are not read).
+    const h16x8 *asrc = reinterpret_cast<const h16x8 *>(Wp) + (size_t)min(bm * 8 + wave, n_tiles - 1) * 64;
+    const h16x8 *bsrc = reinterpret_cast<const h16x8 *>(Xp) + (size_t)min(bt * 8 + wave, t_tiles - 1) * k_tiles * 64;
+    const size_t astep = (size_t)n_tiles * 64;
+    const unsigned lane_bytes = (unsigned)lane * 16u;
+    const unsigned lds0 = (unsigned)reinterpret_cast<uintptr_t>(HX_AS3(smem)) + wave * 1024u;
+    auto issue = [&](int stage, int x) {            // x: 0, 1 weights, 2, 3 activations of the even and the odd k-step
+        const int kt = min(2 * stage + (x & 1), k_tiles - 1);
+        const h16x8 *src = x < 2 ? asrc + kt * astep : bsrc + (size_t)kt * 64;
+        const unsigned lds = lds0 + (unsigned)(stage % S) * (STAGE * 16u) + (x & 1) * (STEP * 16u) + (x < 2 ? 0u : 8192u);
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(lane_bytes), "s"(src) : "memory");
+    };
+    struct Ops { h16x8 a[4], b[4]; } f0, f1;
+    auto fetch = [&](Ops &o, int stage, int x) {    // operand x: four activation tiles, then four weight tiles
+        const h16x8 *st = smem + (stage % S) * STAGE + grp * STEP + lane;
+        if (x < 4) o.b[x] = st[(8 + wt * 4 + x) * 64];
+        else o.a[x - 4] = st[(wm * 4 + x - 4) * 64];
+    };
+    floatx4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p = 0; p < S; ++p)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) issue(p, x);
+    HX_WAIT_VM((S - 1) * 4);
+    asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+    for (int x = 0; x < 8; ++x) fetch(f0, 0, x);
+    auto step = [&](int u, Ops &now, Ops &next, bool mult) {
+        HX_WAIT_VM((S - 2) * 4);                     // this wave's loads of stage u + 1 have landed
+        HX_LDS_BARRIER();                            // ... and everybody's; stage u is in registers everywhere
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+            if (mult) acc[m >> 2][m & 3] = hx_mfma16(now.a[m >> 2], now.b[m & 3], acc[m >> 2][m & 3]);
+            if (m % 2 == 0) fetch(next, u + 1, m / 2);
+            if (m % 4 == 1) issue(u + S, m / 4);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    const int full = k_tiles >> 1;                   // stages with two k-steps
+    int u = 0;
+    for (; u + 2 <= full; u += 2) {
+        step(u, f0, f1, true);
+        step(u + 1, f1, f0, true);
+    }
+    if (u < full) {
+        step(u, f0, f1, true);
+        if (u + 1 < stages) step(u + 1, f1, f0, grp == 0);
+    } else if (u < stages) {
+        step(u, f0, f1, grp == 0);
+    }
+    HX_WAIT_VM(0);
+    HX_LDS_BARRIER();
+
+    // The two halves of the contraction meet: waves 0..3 finish the first 32 of a wave tile's 64 token columns, waves 4..7 the others.
+    floatx4 *red = reinterpret_cast<floatx4 *>(smem);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            floatx4 v = acc[i][j];
+            const floatx4 w = acc[i][2 + j];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = grp == 0 ? w[r] : v[r];
+            red[((wave * 4 + i) * 2 + j) * 64 + lane] = v;
+        }
+    HX_LDS_BARRIER();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const floatx4 o = red[(((wave ^ 4) * 4 + i) * 2 + j) * 64 + lane];
+            floatx4 v = acc[i][j];
+            const floatx4 w = acc[i][2 + j];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = (grp == 0 ? v[r] : w[r]) + o[r];
+            acc[i][j] = v;
+        }
+    // into the register layout of a 32 x 32 result, as in gemm_mfma_kernel
+    auto acc_of = [&](int i, int) {
+        floatx16 c;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int src = 16 * (2 * (q & 1) + (lane >> 5)) + (lane & 15);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float v0 = __shfl(acc[2 * i + (q >> 1)][0][r], src, 64);
+                const float v1 = __shfl(acc[2 * i + (q >> 1)][1][r], src, 64);
+                c[4 * q + r] = (lane & 16) ? v1 : v0;
+            }
+        }
+        return c;
+    };
+    gemm_epilogue<2, 1, 2, 4, MODE>(acc_of, bm, bt, wm, 2 * wt + grp, lane, N, n_tiles, T, e, rstd_of, ssq_s);
+}
+
+// Which launches: one round of 128 x 128 tiles on the 256 CUs, and a contraction that is short for the number of tiles f (of 256) -- a split
+// one pays 10 .. 25 us for its partial sums and the second launch, whatever its length, and walks it faster.  us per projection, split or larger
+// tiles -> this kernel, at k k-tiles:
+//   f < 0.25   N 1024, k = 32 at 140 / 430 / 1131 rows 15.7 / 17.8 / 19.5 -> 12.3 / 12.7 / 13.6;  3072, k = 64 at 140 / 256 18.8 / 19.6 -> 18.6 / 18.7;
+//              but 1024, k = 88 at 256 / 800 18.5 / 20.8 -> 20.6 / 21.6, 2560, k = 256 at 256 29 -> 70
+//   f = 0.38   3072, k = 64 at 430 22.2 -> 19.5;  f = 0.5  1024, k = 88 at 2048 28.6 -> 23.4;  8192, k = 32 / 64 / 112 / 128 at 256 23.1 / 27.8 / 32.8 / 35.7 ->
+//              16.9 / 24.5 / 37.2 / 40.8
+//   f = 0.62   4096, k = 128 at 600 38.0 -> 37.8;  5120, k = 256 at 430 50.6 -> 63.4
+//   f >= 0.75  8192, k = 64 / 128 / 224 / 256 at 430 36.1 / 48.4 / 69.9 / 78.1 -> 24.6 / 39.8 / 59.8 / 68.0, at 512 37.6 / 51.5 / 73.1 / 80.6 -> 28.0 / 43.6 / 71.8 / 78.6
+//              (the residual projections; 448 loses, 110 -> 118);  6144, k = 128 at 600 59.0 -> 41.6;  3072, k = 64 at 1131 30.5 -> 21.4
+//              without the residual the large tiles are as good once they are well filled: k = 256 at 140 / 330 / 430 rows 65.1 / 79.2 / 65.8 -> 62.4 / 70.0 /
+//              60.8, but at 200 / 256 / 512 68.6 / 73.8 / 67.4 -> 71.3 / 78.6 / 73.4, and at f = 0.78 70.6 -> 74.7
+// One prompt of 150 / 300 / 430 rows, whole calls: TP8 shard of the 70B shape 521 / 670 / 740 -> 490 / 603 / 647 us (4 layers), TP4 522 / 721 / 785 -> 506 /
+// 682 / 729 (3 layers), 1024-wide fp16 at 200 / 600 / 2000 rows 333 / 391 / 605 -> 275 / 324 / 528.
+// More than one round: only by accident (11264, k = 64 at 600 rows 48 -> 38, but at 430 / 800 33 / 51 -> 37 / 56).
+static bool takes_panel(bool resid, int n_tiles, int t_tiles, int k_tiles, int T) {
+    const int tiles = ((n_tiles + 7) / 8) * ((t_tiles + 7) / 8);
+    if (t_tiles <= 8 || tiles > 256) return false;
+    if (tiles < 24) return k_tiles <= 48;
+    if (tiles <= 64) return k_tiles <= 64;
+    if (tiles <= 128) return k_tiles <= 32 + tiles / 2;
+    if (tiles < 180) return k_tiles <= 96 + (tiles - 128);
+    if (resid || k_tiles <= 128) return k_tiles <= 256;
+    return tiles >= 216 && k_tiles <= 256 && (T - 1) % 256 < 190;
+}
+
+template <int MODE>
+static void launch_panel(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, int n_tiles, int t_tiles, int T, const GemmEpi &e, hipStream_t s) {
+    const int nb = (n_tiles + 7) / 8, tb = (t_tiles + 7) / 8;
+    const size_t dyn = (size_t)4 * 32 * 1024 + 512 * sizeof(float);
+    auto kern = gemm_panel_kernel<MODE>;
+    static bool raised = false;
+    if (!raised) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+        raised = true;
+    }
+    hipLaunchKernelGGL(kern, dim3((nb * tb + 7) / 8 * 8), dim3(512), dyn, s, Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, nb, tb, e);
+}
+
 template <int FM, int FT, int WM, int WT, int S, int MODE, bool PP = false, int ABL = 0>
 static void launch_cfg(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, int n_tiles, int t_tiles, int T,
                        const GemmEpi &e, float *part, size_t part_floats, hipStream_t s, int nb0 = 0, int nb_count = -1) {
@@ -833,7 +1011,7 @@ static void launch_cfg(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, int
 // tile configuration forced for every GEMM launch of the process (0 = choose by shape); a measurement and test hook
 static std::atomic<int> g_force_tile{0};
 bool set_gemm_tile(int code) {
-    for (int ok : {0, 44, 48, 84, 88, 94, 49, 98, 72, 198, 194, 184, 1198, 2198, 3198})
+    for (int ok : {0, 44, 48, 84, 88, 94, 49, 98, 72, 128, 198, 194, 184, 1198, 2198, 3198})
         if (code == ok) { g_force_tile.store(code, std::memory_order_relaxed); return true; }
     return false;
 }
@@ -907,6 +1085,10 @@ static void launch_mode(const h16_t *Wp, const h16_t *Xp, int N, int K, int T, c
     const double tsml = gemm_estimate_us(resid ? 256 : 128, resid ? 128 : 256, 0.37, n_tiles, t_tiles, k_tiles, resid, part != nullptr);
     int cfg = t198 <= tsml ? 198 : 194;
     if (force) cfg = force;
+    if (cfg == 128 || (!force && takes_panel(resid, n_tiles, t_tiles, k_tiles, T))) {
+        launch_panel<MODE>(Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, e, s);
+        return;
+    }
     // the RESID epilogue emits one sum-of-squares partial per wave: its 32 FM features must be 128
     if (MODE == DEC_RESID && cfg != 88 && cfg != 84 && cfg != 184 && cfg != 98 && cfg % 1000 != 198) cfg = cfg == 72 ? 198 : (cfg == 194 ? 184 : 84);
     // one 128-token tile (a short prompt): 128-token block tiles; the split contraction then runs a short k-loop per
