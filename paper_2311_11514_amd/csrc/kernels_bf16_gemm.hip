@@ -952,9 +952,14 @@ __global__ __launch_bounds__(512) void gemm_panel_kernel(const h16_t *__restrict
 // One prompt of 150 / 300 / 430 rows, whole calls: TP8 shard of the 70B shape 521 / 670 / 740 -> 490 / 603 / 647 us (4 layers), TP4 522 / 721 / 785 -> 506 /
 // 682 / 729 (3 layers), 1024-wide fp16 at 200 / 600 / 2000 rows 333 / 391 / 605 -> 275 / 324 / 528.
 // More than one round: only by accident (11264, k = 64 at 600 rows 48 -> 38, but at 430 / 800 33 / 51 -> 37 / 56).
+// Up to 128 rows the skinny kernel is the alternative, with a finishing pass of its own; it needs 32 k-tiles.  Below, 128 x 128 tiles of 4 waves
+// were: 512, k = 16 at 33 .. 128 rows 16.7 -> 8.6 .. 9.3 (768: 10.9 -> 9.9).  From there on wide matrices: 5632, k = 32 at 33 / 64 / 128 rows 12.6 / 12.6 / 14.5 ->
+// 12.1 / 11.7 / 12.0, 11264, k = 64 18.0 / 18.5 / 22.8 -> 17.8 / 18.0 / 18.0, 22528, k = 128 42.0 / 43.5 / 53.6 -> 41.0 / 42.0 / 48.2, but 1024, k = 32 12.0 -> 11.5, 3072,
+// k = 64 at 64 / 128 13.7 / 15.5 -> 18.2 / 18.7, 14336, k = 256 at 117 56 -> 77.
 static bool takes_panel(bool resid, int n_tiles, int t_tiles, int k_tiles, int T) {
     const int tiles = ((n_tiles + 7) / 8) * ((t_tiles + 7) / 8);
-    if (t_tiles <= 8 || tiles > 256) return false;
+    if (tiles > 256) return false;
+    if (t_tiles <= 8) return k_tiles < 32 || (!resid && t_tiles > 2 && 3 * tiles >= 4 * k_tiles);
     if (tiles < 24) return k_tiles <= 48;
     if (tiles <= 64) return k_tiles <= 64;
     if (tiles <= 128) return k_tiles <= 32 + tiles / 2;

@@ -20,6 +20,8 @@ CASES = [
     ("bf16", 256, 4, 4, 288, 1, 0, [100] * 88, True),
     ("f16", 1024, 16, 4, 1376, 1, 0, [140, 260], False),
     ("bf16", 1024, 8, 8, 1056, 1, 0, [90] * 45, False),
+    ("bf16", 512, 8, 2, 1408, 1, 0, [3], False),
+    ("f16", 1024, 8, 4, 2816, 1, 0, [40, 56], False),
 ]
 
 
