@@ -958,8 +958,9 @@ __global__ __launch_bounds__(512) void gemm_panel_kernel(const h16_t *__restrict
 // k = 64 at 64 / 128 13.7 / 15.5 -> 18.2 / 18.7, 14336, k = 256 at 117 56 -> 77.
 static bool takes_panel(bool resid, int n_tiles, int t_tiles, int k_tiles, int T) {
     const int tiles = ((n_tiles + 7) / 8) * ((t_tiles + 7) / 8);
+    if (t_tiles <= 8 && k_tiles < 32) return true;
     if (tiles > 256) return false;
-    if (t_tiles <= 8) return k_tiles < 32 || (!resid && t_tiles > 2 && 3 * tiles >= 4 * k_tiles);
+    if (t_tiles <= 8) return !resid && t_tiles > 2 && 3 * tiles >= 4 * k_tiles;
     if (tiles < 24) return k_tiles <= 48;
     if (tiles <= 64) return k_tiles <= 64;
     if (tiles <= 128) return k_tiles <= 32 + tiles / 2;
@@ -1096,11 +1097,7 @@ static void launch_mode(const h16_t *Wp, const h16_t *Xp, int N, int K, int T, c
     }
     // the RESID epilogue emits one sum-of-squares partial per wave: its 32 FM features must be 128
     if (MODE == DEC_RESID && cfg != 88 && cfg != 84 && cfg != 184 && cfg != 98 && cfg % 1000 != 198) cfg = cfg == 72 ? 198 : (cfg == 194 ? 184 : 84);
-    // one 128-token tile (a short prompt): 128-token block tiles; the split contraction then runs a short k-loop per
-    // block with the weights coming from HBM, so the 256 x 128 tile of RESID keeps six stages in flight instead of four
-    const bool short_prompt = !force && t_tiles <= 8;
-    if (short_prompt && launch_skinny<MODE>(Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, e, part, part_floats, s)) return;
-    if (short_prompt) cfg = MODE == DEC_RESID ? 846 : 44;
+    if (!force && t_tiles <= 8 && launch_skinny<MODE>(Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, e, part, part_floats, s)) return;
 #define HX_G(FM, FT, WM, WT, S) launch_cfg<FM, FT, WM, WT, S, MODE>(Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, e, part, part_floats, s)
     if (cfg == 88) HX_G(4, 4, 2, 2, 4);
     else if (cfg == 98) HX_G(4, 2, 2, 4, 4);
@@ -1130,7 +1127,6 @@ static void launch_mode(const h16_t *Wp, const h16_t *Xp, int N, int K, int T, c
     else if (cfg == 49) { if constexpr (MODE != DEC_RESID) HX_G(2, 2, 4, 2, 4); }
     else if (cfg == 84) HX_G(4, 2, 2, 2, 4);
     else if (cfg == 72) { if constexpr (MODE != DEC_RESID) HX_G(7, 2, 2, 2, 4); }
-    else if (cfg == 846) { if constexpr (MODE == DEC_RESID) HX_G(4, 2, 2, 2, 6); }
     else if (cfg == 48) {
         if constexpr (MODE != DEC_RESID) HX_G(2, 4, 2, 2, 4);
     } else {
