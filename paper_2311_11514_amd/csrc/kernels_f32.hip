@@ -302,8 +302,13 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(F32Proj p, F32Walk k, flo
     // All of this is uniform: said to the compiler, which divides in vector registers, so that the loop counts in scalar ones.
     int whole = 0;
     while (whole < k.rounds && w + whole * k.workers < k.tiles) ++whole;
-    const int u0 = __builtin_amdgcn_readfirstlane(f32_share(k, w)), u1 = __builtin_amdgcn_readfirstlane(f32_share(k, w + 1));
-    const int t0 = __builtin_amdgcn_readfirstlane(u0 / k.ksteps), cut = min(u1, (t0 + 1) * k.ksteps);
+    int u0 = 0, u1 = 0, t0 = 0;
+    if (k.count > 0) {                                // (three divisions a launch of whole tiles has no use for)
+        u0 = __builtin_amdgcn_readfirstlane(f32_share(k, w));
+        u1 = __builtin_amdgcn_readfirstlane(f32_share(k, w + 1));
+        t0 = __builtin_amdgcn_readfirstlane(u0 / k.ksteps);
+    }
+    const int cut = min(u1, (t0 + 1) * k.ksteps);
     const int ranges = __builtin_amdgcn_readfirstlane((u1 > u0 ? 1 : 0) + (u1 > cut ? 1 : 0));
     const int n_pieces = ranges + whole, steps = whole * k.ksteps + u1 - u0;
     if (steps == 0) return;                           // the whole block leaves
@@ -534,23 +539,24 @@ void f32_proj_mode(const F32Proj &p, float *n_buf, float *part, size_t part_floa
     // Whole tiles only: the fullest CU has ceil(tiles / 256) of them, a k-step is 0.95 us.  Dealing out the k-steps of the last, incomplete
     // round evens that out and costs the partial sums' way through memory (written and read, about 4 TB/s) and a second launch, for which
     // 3 us are charged: with 6 / 9 / 12 two layers take, 512 wide at 130 rows 161 -> 173 / 185 / 204 us, at 1000 rows 289 -> 309 / 310 / 310,
-    // 1024 wide at 572 rows 364 -> 364 / 379 / 404, 2048 wide at 100 rows 312 -> 312 / 312 / 337, wider and longer ones the same.
+    // 1024 wide at 572 rows 364 -> 364 / 379 / 404, 2048 wide at 100 rows 312 -> 312 / 312 / 337, wider and longer ones the same.  It has to
+    // gain 1.5 us by this account: contractions of 8 k-steps stay whole.
     const int full = k.tiles / F32_CUS, rest = k.tiles % F32_CUS;
     const double step = 0.95;
     k.rounds = full + (rest > 0);
     k.first = k.count = 0;
-    k.workers = F32_CUS;
+    k.workers = full > 0 ? F32_CUS : (k.tiles + 7) / 8 * 8;
     k.dealers = 1;
     double best = step * k.rounds * k.ksteps;
-    const int most = std::min(F32_CUS, (int)((long)rest * k.ksteps / 4) / 8 * 8);       // blocks that share the rest: at least 4 k-steps each
-    if (rest > 0 && part != nullptr && most >= std::max(8, rest) && (long)rest * k.ksteps < (1l << 23)) {      // (no share longer than a tile)
+    const int most = std::min(F32_CUS, (int)((long)rest * k.ksteps / 4));       // blocks that share the rest: at least 4 k-steps each
+    if (rest > 0 && part != nullptr && most >= std::max(2, rest) && (long)rest * k.ksteps < (1l << 23)) {      // (no share longer than a tile)
         const size_t slots = 2 * (size_t)most;
         const double us = step * (full * k.ksteps + ((double)rest * k.ksteps + most - 1) / most) + 3.0 + (most + rest) * (double)F32_SLOT * 8.0 / 4e6;
-        if (us < best && slots * F32_SLOT <= part_floats) {
+        if (us + 1.5 < best && slots * F32_SLOT <= part_floats) {
             k.rounds = full;
             k.first = full * F32_CUS;
             k.count = rest;
-            k.workers = full > 0 ? F32_CUS : most;
+            k.workers = full > 0 ? F32_CUS : (most + 7) / 8 * 8;
             k.dealers = most;
         }
     }
