@@ -243,7 +243,7 @@ __device__ __forceinline__ void f32_finish4(const F32Proj &p, int t, int n, floa
 //     and the step's one barrier sits in its middle, so that the next step's first operands are fetched before this one ends;
 //   * every CU has the same number of k-steps: the blocks are persistent.  Each takes an equal share of the k-steps of the tiles
 //     that whole rounds of 256 leave over -- partial sums, which f32_tile_finish_kernel adds up -- and then its share of whole tiles.  792 tiles as blocks of their own gave the fullest CU four tiles where 3.1 is the average.
-// The stages run on over tile boundaries.  Measured, two layers of a 2048-wide stage at 572 rows (three prompts), whole call 1154 -> 948 us; 33 .. 3000 rows of 512- to 4096-wide stages 0 .. 23 % less, 10 % on average;
+// The stages run on over tile boundaries.  Measured, two layers of a 2048-wide stage at 572 rows (three prompts), whole call 1154 -> 948 us; 36 random layers of 256 to 4096 columns at 35 .. 1500 rows 1 .. 18 % less, 10 % on average;
 // cycles of the matrix cores / of the launch: QKV (2048 x 3072, whole tiles) 0.96 on the CUs that have one, W1/W3 (2048 x 11264) 0.87, W2 (5632 x
 // 2048, all dealt out, so that blocks on a die are at different k and share little in its L2) 0.86.  Six stages, or a barrier every
 // other step, change nothing.
