@@ -241,26 +241,30 @@ __device__ __forceinline__ void f32_finish4(const F32Proj &p, int t, int n, floa
 //     registers, memory latency showed in every step);
 //   * LDS latency and barriers stay behind MFMAs: the operands of 8 rows are fetched while the 8 rows before them are multiplied,
 //     and the step's one barrier sits in its middle, so that the next step's first operands are fetched before this one ends;
-//   * every CU has the same number of k-steps: the blocks are persistent.  Each takes an equal share of the k-steps of the tiles
-//     that whole rounds of 256 leave over -- partial sums, which f32_tile_finish_kernel adds up -- and then its share of whole tiles.  792 tiles as blocks of their own gave the fullest CU four tiles where 3.1 is the average.
-// The stages run on over tile boundaries.  Measured, two layers of a 2048-wide stage at 572 rows (three prompts), whole call 1154 -> 948 us; 36 random layers of 256 to 4096 columns at 35 .. 1500 rows 1 .. 18 % less, 10 % on average;
-// cycles of the matrix cores / of the launch: QKV (2048 x 3072, whole tiles) 0.96 on the CUs that have one, W1/W3 (2048 x 11264) 0.87, W2 (5632 x
-// 2048, all dealt out, so that blocks on a die are at different k and share little in its L2) 0.86.  Six stages, or a barrier every
-// other step, change nothing.
+//   * every CU has about the same number of k-steps: the blocks are persistent.  The columns of tiles that fill whole rounds of
+//     256 are walked as whole tiles; of the columns that are left, every token block's k-steps are dealt out evenly to as many
+//     blocks -- partial sums, which f32_tile_finish_kernel adds up.  792 tiles as blocks of their own gave the fullest CU
+//     four tiles where 3.1 is the average.
+// All rows of a launch see a column's contraction cut at the same places, so that equal prompts and sequences have equal results
+// wherever in the batch they sit.
+// The stages run on over tile boundaries.  Measured, two layers of a 2048-wide stage at 572 rows (three prompts), whole call
+// 1154 -> 948 us; 36 random layers of 256 to 4096 columns at 35 .. 1500 rows 1 .. 18 % less, 10 % on average.  Six stages, or a
+// barrier every other step, change nothing.
 // -------------------------------------------------------------------------------------------------
 constexpr int F32_BT = 64, F32_BN = 128, F32_BK = 32, F32_ST = 4, F32_CUS = 256;
 constexpr int F32_SLOT = F32_BT * F32_BN;                 // floats of one tile's partial sums
 
-// What the blocks of a launch walk, see above.  Tiles are numbered token block fastest.
+// What the blocks of a launch walk, see above.  Tiles are numbered token block fastest: tile = column * gy + token block.
 struct F32Walk {
-    int gy, tiles, ksteps;
-    int rounds;                // tiles that block w takes whole: w, w + workers, ... (rounds of them, as far as there are tiles)
-    int first, count;          // tiles whose k-steps are dealt out: first .. first + count - 1
-    int workers, dealers;      // blocks of the launch; the first of them that get a share of the dealt-out k-steps, each at least one of them
+    int gy, ksteps;
+    int whole, rounds;         // tiles 0 .. whole - 1 are whole ones; block w takes w, w + workers, ... (at most `rounds` of them)
+    int cols, sharers;         // the columns behind them are dealt out: each token block's to `sharers` blocks, cols <= sharers
+    int workers;               // blocks of the launch
 };
-// first dealt-out k-step of block w (256 x k-steps fits 31 bits: f32_proj_mode)
-__device__ inline int f32_share(const F32Walk &k, int w) {
-    return (int)((unsigned)min(w, k.dealers) * (unsigned)(k.count * k.ksteps) / (unsigned)k.dealers);
+// First k-step, counted over the dealt-out columns, of a token block's sharer i.  It does not depend on the token block, so that a
+// column's contraction is cut at the same places for every row.  (sharers x cols x ksteps fits 31 bits: f32_proj_mode)
+__device__ inline int f32_share(const F32Walk &k, int i) {
+    return (int)((unsigned)min(i, k.sharers) * (unsigned)(k.cols * k.ksteps) / (unsigned)k.sharers);
 }
 
 typedef __attribute__((address_space(3))) void *f32_lds_ptr;
@@ -301,22 +305,24 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(F32Proj p, F32Walk k, flo
     // This block's pieces: up to two ranges of k-steps of dealt-out tiles, then whole tiles (the last ones end everywhere at once).
     // All of this is uniform: said to the compiler, which divides in vector registers, so that the loop counts in scalar ones.
     int whole = 0;
-    while (whole < k.rounds && w + whole * k.workers < k.tiles) ++whole;
-    int u0 = 0, u1 = 0, t0 = 0;
-    if (k.count > 0) {                                // (three divisions a launch of whole tiles has no use for)
-        u0 = __builtin_amdgcn_readfirstlane(f32_share(k, w));
-        u1 = __builtin_amdgcn_readfirstlane(f32_share(k, w + 1));
-        t0 = __builtin_amdgcn_readfirstlane(u0 / k.ksteps);
+    while (whole < k.rounds && w + whole * k.workers < k.whole) ++whole;
+    int u0 = 0, u1 = 0, c0 = 0, first = 0;            // shared k-steps u0 .. u1 - 1, from column c0 on; its tile
+    if (w < k.sharers * k.gy) {                       // (divisions a launch of whole tiles has no use for)
+        const int i = __builtin_amdgcn_readfirstlane(w / k.gy);
+        u0 = __builtin_amdgcn_readfirstlane(f32_share(k, i));
+        u1 = __builtin_amdgcn_readfirstlane(f32_share(k, i + 1));
+        c0 = __builtin_amdgcn_readfirstlane(u0 / k.ksteps);
+        first = k.whole + c0 * k.gy + w - i * k.gy;
     }
-    const int cut = min(u1, (t0 + 1) * k.ksteps);
+    const int cut = min(u1, (c0 + 1) * k.ksteps);
     const int ranges = __builtin_amdgcn_readfirstlane((u1 > u0 ? 1 : 0) + (u1 > cut ? 1 : 0));
     const int n_pieces = ranges + whole, steps = whole * k.ksteps + u1 - u0;
     if (steps == 0) return;                           // the whole block leaves
     struct Piece { int tile, lo, hi; };
     auto piece = [&](int i) {
         if (i >= ranges) return Piece{w + (i - ranges) * k.workers, 0, k.ksteps};
-        if (i == 0) return Piece{k.first + t0, u0 - t0 * k.ksteps, cut - t0 * k.ksteps};
-        return Piece{k.first + t0 + 1, 0, u1 - cut};
+        if (i == 0) return Piece{first, u0 - c0 * k.ksteps, cut - c0 * k.ksteps};
+        return Piece{first + k.gy, 0, u1 - cut};
     };
     const int bnw = GLU ? F32_BN / 2 : F32_BN;
 
@@ -459,36 +465,36 @@ __global__ __launch_bounds__(256) void f32_tile_finish_kernel(F32Proj p, F32Walk
     constexpr bool GLU = MODE == F32_SWIGLU;
     constexpr int Q = GLU ? 2 : 4;                              // waves per 32 x 32
     const int lane = threadIdx.x & 63, idx = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t = idx / (8 * Q), wave = idx / Q % 8, q = idx % Q;
-    // workers whose shares meet k-steps t * ksteps .. (t + 1) * ksteps - 1
-    const int s0 = t * k.ksteps, s1 = s0 + k.ksteps;
-    int w0 = t * k.dealers / k.count;
-    while (w0 > 0 && f32_share(k, w0) > s0) --w0;
-    while (f32_share(k, w0 + 1) <= s0) ++w0;
-    int w1 = w0;                                                // the last of them
-    while (f32_share(k, w1 + 1) < s1) ++w1;
-    if (f32_share(k, w0) <= s0 && w1 == w0) return;             // one worker had all of it and has finished it
-    const int tile = k.first + t;
-    const int row = tile % k.gy * F32_BT + 32 * (wave & 1) + (lane & 31);
-    const int n = tile / k.gy * (GLU ? F32_BN / 2 : F32_BN) + (GLU ? 16 : 32) * (wave >> 1) + 8 * q + 4 * (lane >> 5);
-    // only the first worker's piece can be its second one
-    const float *src = part + (size_t)(2 * w0 + (f32_share(k, w0) < s0 && f32_share(k, w0) / k.ksteps < t)) * F32_SLOT + wave * 1024 + q * 256 + lane * 4;
-    const float *next = part + (size_t)(2 * w0 + 2) * F32_SLOT + wave * 1024 + q * 256 + lane * 4;
+    const int t = idx / (8 * Q), wave = idx / Q % 8, q = idx % Q, col = t / k.gy, bt = t - col * k.gy;
+    // the token block's sharers whose shares meet k-steps col * ksteps .. (col + 1) * ksteps - 1
+    const int s0 = col * k.ksteps, s1 = s0 + k.ksteps;
+    int i0 = col * k.sharers / k.cols;
+    while (i0 > 0 && f32_share(k, i0) > s0) --i0;
+    while (f32_share(k, i0 + 1) <= s0) ++i0;
+    int i1 = i0;                                                // the last of them
+    while (f32_share(k, i1 + 1) < s1) ++i1;
+    if (f32_share(k, i0) <= s0 && i1 == i0) return;             // one block had all of it and has finished it
+    const int row = bt * F32_BT + 32 * (wave & 1) + (lane & 31);
+    const int n = (k.whole / k.gy + col) * (GLU ? F32_BN / 2 : F32_BN) + (GLU ? 16 : 32) * (wave >> 1) + 8 * q + 4 * (lane >> 5);
+    // sharer i is block i * gy + bt; only the first one's piece can be its second one
+    const size_t at0 = (size_t)2 * (i0 * k.gy + bt) * F32_SLOT + wave * 1024 + q * 256 + lane * 4, step = (size_t)2 * k.gy * F32_SLOT;
+    const float *src = part + at0 + (f32_share(k, i0) / k.ksteps < col ? F32_SLOT : 0);
+    const float *next = part + at0 + step;
     floatx4 a = {0.f, 0.f, 0.f, 0.f}, b = a, h = a;
     const bool inside = row < p.T && n < p.cols;
     if (MODE == F32_RESID && inside) h = *reinterpret_cast<const floatx4 *>(p.resid + (size_t)row * p.cols + n);
-    for (int w = w0; w <= w1; w += 8) {
+    for (int i = i0; i <= i1; i += 8) {
         floatx4 va[8], vb[GLU ? 8 : 1];
 #pragma unroll
         for (int z = 0; z < 8; ++z) {
-            const int wz = min(w + z, w1);
-            const float *at = wz == w0 ? src : next + (size_t)(wz - w0 - 1) * 2 * F32_SLOT;
+            const int iz = min(i + z, i1);
+            const float *at = iz == i0 ? src : next + (size_t)(iz - i0 - 1) * step;
             va[z] = *reinterpret_cast<const floatx4 *>(at);
             if constexpr (GLU) vb[z] = *reinterpret_cast<const floatx4 *>(at + 512);
         }
 #pragma unroll
         for (int z = 0; z < 8; ++z)
-            if (w + z <= w1) {
+            if (i + z <= i1) {
                 a += va[z];
                 if constexpr (GLU) b += vb[z];
             }
@@ -534,34 +540,33 @@ void f32_proj_mode(const F32Proj &p, float *n_buf, float *part, size_t part_floa
     const int bn = MODE == F32_SWIGLU ? F32_BN / 2 : F32_BN;
     F32Walk k;
     k.gy = (p.T + F32_BT - 1) / F32_BT;
-    k.tiles = (p.cols + bn - 1) / bn * k.gy;
     k.ksteps = p.Kp / F32_BK;
-    // Whole tiles only: the fullest CU has ceil(tiles / 256) of them, a k-step is 0.95 us.  Dealing out the k-steps of the last, incomplete
-    // round evens that out and costs the partial sums' way through memory (written and read, about 4 TB/s) and a second launch, for which
-    // 3 us are charged: with 6 / 9 / 12 two layers take, 512 wide at 130 rows 161 -> 173 / 185 / 204 us, at 1000 rows 289 -> 309 / 310 / 310,
-    // 1024 wide at 572 rows 364 -> 364 / 379 / 404, 2048 wide at 100 rows 312 -> 312 / 312 / 337, wider and longer ones the same.  It has to
-    // gain 1.5 us by this account: contractions of 8 k-steps stay whole.
-    const int full = k.tiles / F32_CUS, rest = k.tiles % F32_CUS;
+    // Whole tiles only: the fullest CU has ceil(tiles / 256) of them, a k-step is 0.95 us.  Dealing out the k-steps of the columns that
+    // whole rounds leave over evens that out and costs the partial sums' way through memory (written and read, about 4 TB/s) and a
+    // second launch, for which 3 us are charged: with 6 / 9 / 12 two layers take, 512 wide at 130 rows 161 -> 173 / 185 / 204 us, at
+    // 1000 rows 289 -> 309 / 310 / 310, 1024 wide at 572 rows 364 -> 364 / 379 / 404, 2048 wide at 100 rows 312 -> 312 / 312 / 337,
+    // wider and longer ones the same.  It has to gain 1.5 us by this account: contractions of 8 k-steps stay whole.
+    const int cols = (p.cols + bn - 1) / bn, tiles = cols * k.gy, full = tiles / F32_CUS;
     const double step = 0.95;
-    k.rounds = full + (rest > 0);
-    k.first = k.count = 0;
-    k.workers = full > 0 ? F32_CUS : (k.tiles + 7) / 8 * 8;
-    k.dealers = 1;
-    double best = step * k.rounds * k.ksteps;
-    const int most = std::min(F32_CUS, (int)((long)rest * k.ksteps / 4));       // blocks that share the rest: at least 4 k-steps each
-    if (rest > 0 && part != nullptr && most >= std::max(2, rest) && (long)rest * k.ksteps < (1l << 23)) {      // (no share longer than a tile)
-        const size_t slots = 2 * (size_t)most;
-        const double us = step * (full * k.ksteps + ((double)rest * k.ksteps + most - 1) / most) + 3.0 + (most + rest) * (double)F32_SLOT * 8.0 / 4e6;
-        if (us + 1.5 < best && slots * F32_SLOT <= part_floats) {
+    k.whole = tiles;
+    k.rounds = (tiles + F32_CUS - 1) / F32_CUS;
+    k.workers = std::min(F32_CUS, (tiles + 7) / 8 * 8);
+    k.cols = k.sharers = 0;
+    const int left = cols - (int)((long)F32_CUS * full / k.gy);
+    const int most = (int)std::min<long>(F32_CUS / k.gy, (long)left * k.ksteps / 4);      // blocks that share a token block's: at least 4 k-steps each
+    if (left > 0 && part != nullptr && most >= std::max(2, left) && (long)left * k.ksteps < (1l << 23)) {      // (no share longer than a tile)
+        const size_t slots = 2 * (size_t)most * k.gy;
+        const double us = step * (full * k.ksteps + ((double)left * k.ksteps + most - 1) / most) + 3.0 + (most + left) * k.gy * (double)F32_SLOT * 8.0 / 4e6;
+        if (us + 1.5 < step * k.rounds * k.ksteps && slots * F32_SLOT <= part_floats) {
+            k.whole = (cols - left) * k.gy;
             k.rounds = full;
-            k.first = full * F32_CUS;
-            k.count = rest;
-            k.workers = full > 0 ? F32_CUS : (most + 7) / 8 * 8;
-            k.dealers = most;
+            k.workers = full > 0 ? F32_CUS : (most * k.gy + 7) / 8 * 8;
+            k.cols = left;
+            k.sharers = most;
         }
     }
     hipLaunchKernelGGL((f32_tile_kernel<MODE>), dim3(k.workers), dim3(512), 0, s, t, k, part);
-    if (k.count > 0) hipLaunchKernelGGL((f32_tile_finish_kernel<MODE>), dim3((MODE == F32_SWIGLU ? 4 : 8) * k.count), dim3(256), 0, s, t, k, part);
+    if (k.cols > 0) hipLaunchKernelGGL((f32_tile_finish_kernel<MODE>), dim3((MODE == F32_SWIGLU ? 4 : 8) * k.cols * k.gy), dim3(256), 0, s, t, k, part);
 }
 }  // namespace
 

@@ -75,6 +75,23 @@ def test_f32_tiles_dealt_out(case):
     test_f32_prefill_then_decode(case)
 
 
+# equal prompts whose rows sit in different token blocks: tiles cut along the contraction, whole ones and both in one launch
+# (88 columns x 9 token blocks in W1/W3; 24 and 16 columns x 17 in QKV and W_O), one-row prompts, decode steps of many sequences
+@pytest.mark.parametrize("H,hq,hkv,F,rows,batch", [(512, 8, 2, 1408, 50, 3), (2048, 16, 4, 5632, 190, 3), (2048, 16, 4, 256, 350, 3), (1024, 8, 8, 2816, 1, 100)])
+def test_f32_equal_sequences_have_equal_bits(H, hq, hkv, F, rows, batch):
+    cfg = StageConfig("f32same", "f32", H, hq, hkv, F, 2, 1, (0,), batch=batch, seed=704)
+    st = make_gpu_stage(cfg, 0, [generate.layer_weights(cfg, layer) for layer in range(2)])
+    kv = st.kv_cache_create(batch, rows + 2)
+    p, h = gpu_prefill(st, kv, cfg, generate.hidden_rows(cfg, rows).repeat(batch, 1), [rows] * batch)
+    for out in (p, h, *gpu_decode(st, kv, cfg, 0, generate.hidden_rows(cfg, 1, stream_id=1).repeat(batch, 1))):
+        out = np.asarray(out).reshape(batch, -1, H)
+        assert (out == out[:1]).all()
+    for layer in range(2):
+        first = kv.read(layer, 0, 0, rows + 1)
+        for s in range(1, batch):
+            assert all(torch.equal(a, b) for a, b in zip(kv.read(layer, s, 0, rows + 1), first))
+
+
 @pytest.mark.parametrize("rows", [24, 70])
 def test_f32_non_finite_rows_stay_with_their_successors(rows):
     """A row that is not finite reaches the rows behind it through the cache, and none before it."""
