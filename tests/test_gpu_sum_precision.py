@@ -1,0 +1,52 @@
+"""The fp32 sums of a projection against 64 bits, on operands that are known exactly: run_sublayer's W2 with a gate of 32, where
+silu(32) = 32 in fp32, and an up projection of rows of +-1 with integers of 7 or 10 bits, exact in any order.  n additions one behind the
+other, each off by at most u = 2^-24 of the sum so far, which grows with the root of their number: u sqrt(n / 2) of the result where the
+errors are independent.  A matrix instruction of 16-bit operands adds 32 products with about one such rounding.  The gates are
+these; a chain twice as long misses them."""
+import math
+
+import pytest
+import torch
+
+import paper_2311_11514_amd as hx
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24
+TYPE = {"bf16": torch.bfloat16, "f16": torch.float16}
+# dtype, hidden, ffn, rows: the 128 x 128 tiles, a quarter of the contraction per chain
+CASES = [
+    ("f16", 1024, 1024, 430),
+    ("bf16", 2048, 2048, 330),
+    ("f16", 1024, 2816, 600),
+    ("bf16", 512, 7168, 200),
+]
+
+
+@pytest.mark.parametrize("dtype,H,F,T", CASES, ids=[f"{c[0]}_H{c[1]}F{c[2]}T{c[3]}" for c in CASES])
+def test_projection_sums(dtype, H, F, T):
+    td = TYPE[dtype]
+    g = torch.Generator().manual_seed(H + F + T)
+    x = torch.randint(0, 2, (T, H), generator=g).double() * 2 - 1
+    x[:, 0] = 1
+    w1 = torch.zeros(H, F)
+    w1[0] = 32
+    top = 128 if dtype == "bf16" else 1024
+    w3 = torch.randint(1 - top, top, (H, F), generator=g).double() / (16 * top)
+    w2 = (torch.randn(F, H, generator=g) * 0.02).to(td)
+    st = hx.Stage(H, H // 128, H // 128, F, 1, 1, 0, dtype, 1e-12)
+    one, zero = torch.ones(H).to(td).cuda(), torch.zeros(H, H).to(td).cuda()
+    st.load_layer(0, one, zero, zero, zero, zero, one, w1.to(td).cuda(), w3.to(td).cuda(), w2.cuda())
+    kv = st.kv_cache_create(1, T)
+    out = torch.empty(T, H, device="cuda")
+    hx.set_gemm_tile(128)
+    try:
+        st.run_sublayer(kv, 0, 1, x.float().cuda(), [T], 1, out)
+        torch.cuda.synchronize()
+    finally:
+        hx.set_gemm_tile(0)
+    exact = (32 * (x @ w3)).to(td).double() @ w2.double()
+    err = float((out.cpu().double() - exact).norm() / exact.norm())
+    gate = U * math.sqrt(F / 32 / 4 / 2)
+    print(f"{err:.3e} (gate {gate:.3e})", flush=True)
+    assert err < gate
