@@ -252,6 +252,10 @@ __device__ __forceinline__ void f32_finish4(const F32Proj &p, int t, int n, floa
 // barrier every other step, change nothing.
 // -------------------------------------------------------------------------------------------------
 constexpr int F32_BT = 64, F32_BN = 128, F32_BK = 32, F32_ST = 4, F32_CUS = 256;
+// An accumulator's sum joins the tile's after so many k-steps (256 instructions one behind the other): without it whole tiles and long
+// shares had sums up to 1.2 times as far from 64 bits as a contraction split for the whole launch (2048 x 5632 at 572 / 1033 rows
+// 6.0e-7 / 7.8e-7 -> 6.4e-7 / 9.2e-7, with it 3.9e-7 at either); the time is the same.
+constexpr int F32_RUN = 32;
 constexpr int F32_SLOT = F32_BT * F32_BN;                 // floats of one tile's partial sums
 
 // What the blocks of a launch walk, see above.  Tiles are numbered token block fastest: tile = column * gy + token block.
@@ -391,11 +395,13 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(F32Proj p, F32Walk k, flo
         for (int x = 0; x < 4; ++x) mfma(s, x);
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto clear = [&]() {
+    floatx16 sum;                                     // what leaves acc after F32_RUN k-steps, or at a piece's end
+    auto gather = [&]() {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+        for (int r = 0; r < 16; ++r) {
+            sum[r] += acc[0][r] + acc[1][r];
+            acc[0][r] = acc[1][r] = 0.f;
+        }
     };
     load_tile();
 #pragma unroll
@@ -404,13 +410,14 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(F32Proj p, F32Walk k, flo
         for (int x = 0; x < 3; ++x) issue(i * STAGE, x);
         advance();
     }
-    clear();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sum[r] = acc[0][r] = acc[1][r] = 0.f;
     F32_WAIT_VM((F32_ST - 2) * 3);
     asm volatile("s_barrier" ::: "memory");
     fetch(0, 0);
     int ci = 0, buf = 0, lbuf = (F32_ST - 1) * STAGE;
     Piece now = piece(0);
-    int left = now.hi - now.lo;
+    int left = now.hi - now.lo, run = min(left, F32_RUN);          // k-steps to the end of the piece, and until acc is gathered
     // The order below is held by scheduling barriers.  Nothing but the two waits stands between the barrier and the next MFMA: what the step
     // computes for its loads is done ahead of it, the loads go between the MFMAs behind it.
     for (int u = 0; u < steps; ++u) {
@@ -438,21 +445,24 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(F32Proj p, F32Walk k, flo
         advance();
         lbuf = buf;
         buf = nbuf;
-        if (--left == 0) {
-            floatx16 c;
+        if (--run == 0) {
+            gather();
+            left -= F32_RUN;
+            if (left <= 0) {
+                if (now.hi - now.lo == k.ksteps) {
+                    f32_tile_store<MODE>(p, now.tile / k.gy * bnw, now.tile % k.gy * F32_BT, wave, lane, sum);
+                } else {
+                    float *dst = part + (size_t)(2 * w + ci) * F32_SLOT + wave * 1024 + lane * 4;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) c[r] = acc[0][r] + acc[1][r];
-            if (now.hi - now.lo == k.ksteps) {
-                f32_tile_store<MODE>(p, now.tile / k.gy * bnw, now.tile % k.gy * F32_BT, wave, lane, c);
-            } else {
-                float *dst = part + (size_t)(2 * w + ci) * F32_SLOT + wave * 1024 + lane * 4;
+                    for (int q = 0; q < 4; ++q) *reinterpret_cast<floatx4 *>(dst + q * 256) = floatx4{sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
+                }
 #pragma unroll
-                for (int q = 0; q < 4; ++q) *reinterpret_cast<floatx4 *>(dst + q * 256) = floatx4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+                for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+                // (loads and stores complete in the order of their issue: with results still in flight the waits above only wait for more)
+                now = piece(++ci);
+                left = now.hi - now.lo;
             }
-            clear();
-            // (loads and stores complete in the order of their issue: with results still in flight the waits above only wait for more)
-            now = piece(++ci);
-            left = now.hi - now.lo;
+            run = min(left, F32_RUN);
         }
     }
     F32_WAIT_VM(0);

@@ -1,8 +1,9 @@
 """The fp32 sums of a projection against 64 bits, on operands that are known exactly: run_sublayer's W2 with a gate of 32, where
 silu(32) = 32 in fp32, and an up projection of rows of +-1 with integers of 7 or 10 bits, exact in any order.  n additions one behind the
 other, each off by at most u = 2^-24 of the sum so far, which grows with the root of their number: u sqrt(n / 2) of the result where the
-errors are independent.  A matrix instruction of 16-bit operands adds 32 products with about one such rounding.  The gates are
-these; a chain twice as long misses them."""
+errors are independent.  A matrix instruction of 16-bit operands adds 32 products with about one such rounding; one of fp32
+operands adds 2 products with two, to nearest (half of u, root mean square, with room).  The gates are these; a chain twice as long
+misses them."""
 import math
 
 import pytest
@@ -13,13 +14,17 @@ import paper_2311_11514_amd as hx
 pytestmark = pytest.mark.gpu
 
 U = 2.0 ** -24
-TYPE = {"bf16": torch.bfloat16, "f16": torch.float16}
-# dtype, hidden, ffn, rows: the 128 x 128 tiles, a quarter of the contraction per chain
+TYPE = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
+# dtype, hidden, ffn, rows; 16 bits: the 128 x 128 tiles, a quarter of the contraction per chain; fp32: chains of at most 256
+# instructions, whole tiles, dealt-out ones and both in one launch
 CASES = [
     ("f16", 1024, 1024, 430),
     ("bf16", 2048, 2048, 330),
     ("f16", 1024, 2816, 600),
     ("bf16", 512, 7168, 200),
+    ("f32", 512, 1408, 1000),
+    ("f32", 2048, 5632, 572),
+    ("f32", 2048, 5632, 1033),
 ]
 
 
@@ -39,7 +44,7 @@ def test_projection_sums(dtype, H, F, T):
     st.load_layer(0, one, zero, zero, zero, zero, one, w1.to(td).cuda(), w3.to(td).cuda(), w2.cuda())
     kv = st.kv_cache_create(1, T)
     out = torch.empty(T, H, device="cuda")
-    hx.set_gemm_tile(128)
+    hx.set_gemm_tile(0 if dtype == "f32" else 128)
     try:
         st.run_sublayer(kv, 0, 1, x.float().cuda(), [T], 1, out)
         torch.cuda.synchronize()
@@ -47,6 +52,6 @@ def test_projection_sums(dtype, H, F, T):
         hx.set_gemm_tile(0)
     exact = (32 * (x @ w3)).to(td).double() @ w2.double()
     err = float((out.cpu().double() - exact).norm() / exact.norm())
-    gate = U * math.sqrt(F / 32 / 4 / 2)
+    gate = 0.5 * U * math.sqrt(2 * 256 / 2) if dtype == "f32" else U * math.sqrt(F / 32 / 4 / 2)
     print(f"{err:.3e} (gate {gate:.3e})", flush=True)
     assert err < gate
