@@ -859,7 +859,7 @@ __global__ __launch_bounds__(512) void gemm_panel_kernel(const h16_t *__restrict
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc0[i][j] = acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int p = 0; p < S; ++p)
 #pragma unroll
@@ -880,14 +880,21 @@ __global__ __launch_bounds__(512) void gemm_panel_kernel(const h16_t *__restrict
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // Each half of the stages is summed up by itself, so that a chain of additions is a quarter of the contraction: no longer than the
-    // splits' this kernel replaces.  One chain per wave group had the fp32 sums up to 1.37 times as far from 64 bits as those (2048 x 2048 at 600
-    // rows 1.53e-7 -> 2.08e-7, now 1.53e-7); it costs 64 registers and at most 1 % of the kernel.
+    // From 48 k-tiles on each half of the stages is summed up by itself, so that a chain of additions is a quarter of the contraction, no
+    // longer than the splits' that this kernel replaces (16 k-tiles and more).  With one chain per wave group the fp32 sums were up to
+    // 1.37 times as far from 64 bits as those (2048 x 2048 at 600 rows 1.53e-7 -> 2.08e-7, now 1.53e-7).  It costs 64 registers and 0.2 us.
     const int full = k_tiles >> 1;                   // stages with two k-steps
+    const bool quarters = k_tiles >= 48;
     int u = 0;
-    for (; u + 4 <= full - u; u += 2) {
-        step(u, f0, f1, true, acc0);
-        step(u + 1, f1, f0, true, acc0);
+    if (quarters) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc0[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (; u + 4 <= full - u; u += 2) {
+            step(u, f0, f1, true, acc0);
+            step(u + 1, f1, f0, true, acc0);
+        }
     }
     for (; u + 2 <= full; u += 2) {
         step(u, f0, f1, true, acc);
@@ -899,10 +906,12 @@ __global__ __launch_bounds__(512) void gemm_panel_kernel(const h16_t *__restrict
     } else if (u < stages) {
         step(u, f0, f1, grp == 0, acc);
     }
+    if (quarters) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += acc0[i][j];
+            for (int j = 0; j < 4; ++j) acc[i][j] += acc0[i][j];
+    }
     HX_WAIT_VM(0);
     HX_LDS_BARRIER();
 

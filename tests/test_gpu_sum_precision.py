@@ -15,10 +15,11 @@ pytestmark = pytest.mark.gpu
 
 U = 2.0 ** -24
 TYPE = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
-# dtype, hidden, ffn, rows; 16 bits: the 128 x 128 tiles, a quarter of the contraction per chain; fp32: chains of at most 256
+# dtype, hidden, ffn, rows; 16 bits: the 128 x 128 tiles, a quarter of the contraction per chain (half of it below 48 k-tiles); fp32: chains of at most 256
 # instructions, whole tiles, dealt-out ones and both in one launch
 CASES = [
-    ("f16", 1024, 1024, 430),
+    ("bf16", 1024, 1504, 130),
+    ("f16", 1024, 1536, 430),
     ("bf16", 2048, 2048, 330),
     ("f16", 1024, 2816, 600),
     ("bf16", 512, 7168, 200),
@@ -52,6 +53,6 @@ def test_projection_sums(dtype, H, F, T):
         hx.set_gemm_tile(0)
     exact = (32 * (x @ w3)).to(td).double() @ w2.double()
     err = float((out.cpu().double() - exact).norm() / exact.norm())
-    gate = 0.5 * U * math.sqrt(2 * 256 / 2) if dtype == "f32" else U * math.sqrt(F / 32 / 4 / 2)
+    gate = 0.5 * U * math.sqrt(2 * 256 / 2) if dtype == "f32" else U * math.sqrt(F / 32 / (2 if F < 48 * 32 else 4) / 2)
     print(f"{err:.3e} (gate {gate:.3e})", flush=True)
     assert err < gate
