@@ -957,37 +957,45 @@ __global__ __launch_bounds__(512) void gemm_panel_kernel(const h16_t *__restrict
     gemm_epilogue<2, 1, 2, 4, MODE>(acc_of, bm, bt, wm, 2 * wt + grp, lane, N, n_tiles, T, e, rstd_of, ssq_s);
 }
 
-// Which launches: one round of 128 x 128 tiles on the 256 CUs, and a contraction that is short for the number of tiles f (of 256) -- a split
-// one pays 10 .. 25 us for its partial sums and the second launch, whatever its length, and walks it faster.  us per projection, split or larger
-// tiles -> this kernel, at k k-tiles:
-//   f < 0.25   N 1024, k = 32 at 140 / 430 / 1131 rows 15.7 / 17.8 / 19.5 -> 12.3 / 12.7 / 13.6;  3072, k = 64 at 140 / 256 18.8 / 19.6 -> 18.6 / 18.7;
-//              but 1024, k = 88 at 256 / 800 18.5 / 20.8 -> 20.6 / 21.6, 2560, k = 256 at 256 29 -> 70
-//   f = 0.38   3072, k = 64 at 430 22.2 -> 19.5;  f = 0.5  1024, k = 88 at 2048 28.6 -> 23.4;  8192, k = 32 / 64 / 112 / 128 at 256 23.1 / 27.8 / 32.8 / 35.7 ->
-//              16.9 / 24.5 / 37.2 / 40.8
-//   f = 0.62   4096, k = 128 at 600 38.0 -> 37.8;  5120, k = 256 at 430 50.6 -> 63.4
-//   f >= 0.75  8192, k = 64 / 128 / 224 / 256 at 430 36.1 / 48.4 / 69.9 / 78.1 -> 24.6 / 39.8 / 59.8 / 68.0, at 512 37.6 / 51.5 / 73.1 / 80.6 -> 28.0 / 43.6 / 71.8 / 78.6
-//              (the residual projections; 448 loses, 110 -> 118);  6144, k = 128 at 600 59.0 -> 41.6;  3072, k = 64 at 1131 30.5 -> 21.4
-//              without the residual the large tiles are as good once they are well filled: k = 256 at 140 / 330 / 430 rows 65.1 / 79.2 / 65.8 -> 62.4 / 70.0 /
-//              60.8, but at 200 / 256 / 512 68.6 / 73.8 / 67.4 -> 71.3 / 78.6 / 73.4, and at f = 0.78 70.6 -> 74.7
-// One prompt of 150 / 300 / 430 rows, whole calls: TP8 shard of the 70B shape 521 / 670 / 740 -> 490 / 603 / 647 us (4 layers), TP4 522 / 721 / 785 -> 506 /
-// 682 / 729 (3 layers), 1024-wide fp16 at 200 / 600 / 2000 rows 333 / 391 / 605 -> 275 / 324 / 528; 44 random layers
-// (768 .. 8192 wide, 1 .. 8 ranks, 140 .. 1700 rows) 9 % less on average, the worst 0.8 % more.
-// More than one round: only by accident (11264, k = 64 at 600 rows 48 -> 38, but at 430 / 800 33 / 51 -> 37 / 56).
-// Up to 128 rows the skinny kernel is the alternative, with a finishing pass of its own; it needs 32 k-tiles.  Below, 128 x 128 tiles of 4 waves
-// were: 512, k = 16 at 33 .. 128 rows 16.7 -> 8.6 .. 9.3 (768: 10.9 -> 9.9).  From there on wide matrices: 5632, k = 32 at 33 / 64 / 128 rows 12.6 / 12.6 / 14.5 ->
-// 12.1 / 11.7 / 12.0, 11264, k = 64 18.0 / 18.5 / 22.8 -> 17.8 / 18.0 / 18.0, 22528, k = 128 42.0 / 43.5 / 53.6 -> 41.0 / 42.0 / 48.2, but 1024, k = 32 12.0 -> 11.5, 3072,
-// k = 64 at 64 / 128 13.7 / 15.5 -> 18.2 / 18.7, 14336, k = 256 at 117 56 -> 77.
+// Which launches: one round of 128 x 128 tiles on the 256 CUs, and a contraction of k k-tiles that is short for the number of tiles.
+// The alternative has tiles of twice or four times the size, with the contraction split over the CUs that leaves idle: it pays for
+// its partial sums and a second launch whatever the contraction's length, and walks it faster.  It also pays for token rows up
+// to a multiple of 256 (residual projections: 128), this kernel for those up to a multiple of 16.
+// The lines follow what whole calls of 16 widths at 60 row counts take with this kernel and with the other, one projection changed
+// at a time and the rest left to this rule (us per projection, this kernel - the other; both in turn in one process.  A kernel trace
+// will not do: it puts 2 us and more between the two launches of a split contraction, and favours this kernel by that):
+//   tiles   k     rows: difference
+//    44-64  48    400 / 600 rows of 1536 -3 / -2;  but k = 64: 200 / 384 rows of 2048 +1.9 / +3.1
+//    96     64    272 / 330 / 384 rows -1.5 / -0.9 / +0.4;  but k = 96: 200 / 470 rows +4.1 / +4.6
+//   112     88    1792 rows (14 token blocks that share the weights) -3.9;  but 128, k = 112: 256 rows (2 of them) +6.8
+//   144     96    272 / 330 / 384 rows -1.5 / -0.9 / +3.3
+//   160    108    400 / 464 / 470 / 512 rows -3.3 / -1.2 / +0.2 / +1.9;  but k = 128: 600 / 640 rows +2.0 / +3.9
+//   192    256    330 / 464 / 470 / 512 rows -8.4 / -1.8 / +0.2 / +5.8;  k = 176: 1500 rows -2.5;  but k = 256: 1024 rows +4.7
+//   256    224    400 / 470 / 512 rows -9.5 / -1.3 / 0;  but k = 256: 512 rows +7.5, k = 448: 400 rows +7
+// "padded": at least a twentieth of the token blocks' rows do not exist.  600 rows of 640 win, 384 of 384 and 512 of 512 lose.
+// Without the residual the other's tiles are 256 tokens wide, and beyond 128 k-tiles it depends on how full the last of them is:
+// 224 tiles, k = 256 at 174 / 184 / 200 rows over a multiple of 256 -1.7 / +0.4 / +1.0, 240 tiles at 192 / 208 / 256 -6.9 / -1.2 / +0.1,
+// 216, k = 160 at 184 / 208 / 256 -1.6 / +0.6 / +1.6.
+// Up to 128 rows the alternative is the skinny kernel with a finishing pass of its own; it needs 32 k-tiles.  Below, this kernel is
+// 2 to 7 us shorter than 128 x 128 tiles of four waves at every size.  From there on there have to be enough blocks -- W1/W3 of 88
+// tiles, k = 64 at 33 / 64 / 96 / 128 rows -2.0 / -2.0 / -4.6 / -6.9, 216, k = 160 -1.1 / -0.3 / -3.2 / -3.5, but 44, k = 32 +0.9 / +0.6 / 0 / -1.4,
+// 128, k = 96 +0.5 / +1.9 / +0.8 / +1.7 -- or the prompt has to be nearly 128 rows (64, k = 48 +0.3 / +0.7 / -0.7 / -2.9) and the skinny kernel
+// must not fill the chip, as it does at 128, k = 96.  profiles/prefill_tile_choice.txt has every figure.
 static bool takes_panel(bool resid, int n_tiles, int t_tiles, int k_tiles, int T) {
-    const int tiles = ((n_tiles + 7) / 8) * ((t_tiles + 7) / 8);
-    if (t_tiles <= 8 && k_tiles < 32) return true;
+    const int token_blocks = (t_tiles + 7) / 8, tiles = ((n_tiles + 7) / 8) * token_blocks;
+    if (t_tiles <= 8) {
+        if (k_tiles < 32) return true;
+        if (resid || t_tiles <= 2 || tiles > 256) return false;
+        const int skinny = tiles * std::min({8, 512 / tiles, k_tiles / 16}) / 2;          // its blocks of eight waves (launch_skinny)
+        if (t_tiles > 6 && skinny <= 224) return 3 * tiles >= 4 * k_tiles;
+        return tiles >= 64 && k_tiles <= 160 && 20 * tiles >= 27 * k_tiles;
+    }
     if (tiles > 256) return false;
-    if (t_tiles <= 8) return !resid && t_tiles > 2 && 3 * tiles >= 4 * k_tiles;
-    if (tiles < 24) return k_tiles <= 48;
-    if (tiles <= 64) return k_tiles <= 64;
-    if (tiles <= 128) return k_tiles <= 32 + tiles / 2;
-    if (tiles < 180) return k_tiles <= 96 + (tiles - 128);
-    if (resid || k_tiles <= 128) return k_tiles <= 256;
-    return tiles >= 216 && k_tiles <= 256 && (T - 1) % 256 < 190;
+    const bool padded = 20 * t_tiles <= 19 * 8 * token_blocks;
+    if (tiles <= 128) return k_tiles <= std::max(48, token_blocks >= 9 ? 32 + tiles / 2 : padded ? 28 + tiles / 2 : tiles / 2);
+    if (tiles < 180) return k_tiles <= (padded || tiles >= 168 ? tiles - 36 : tiles - 80);
+    if (resid) return k_tiles <= (padded ? 256 : tiles - 16);
+    return k_tiles <= 128 || (tiles >= 216 && k_tiles <= 256 && (T - 1) % 256 < (k_tiles <= 192 || tiles >= 232 ? 210 : 176));
 }
 
 template <int MODE>
