@@ -123,14 +123,14 @@ def test_tiny_f32_group_mode_greedy_tokens():
                                       (MINI64, [1, 128, 129, 256, 5, 127, 130, 64, 33, 257, 2]),
                                       (MINI2K, [300, 212]), (MINI2K, [520, 500]), (MINI5K, [128]), (MINI5K, [61, 40]), (MINIODD, [128]), (MINIODD, [77])])
 def test_bf16_small_prefill_then_decode(cfg, lens):
-    """Short prompts: few token tiles, so the projections with at least 32 k-tiles split their contraction over
+    """Short prompts: few token tiles, so most projections with at least 32 k-tiles split their contraction over
     several blocks and finish in a second pass: up to 128 rows through the skinny kernel (weights in a register ring),
-    beyond through the LDS-staged kernel; MINI64 (16 k-tiles) does neither.  MINIRAG has a ragged last feature block
-    and an odd number of k-tiles; 128 and 129 + 3 rows sit on either side of the one-token-tile limit.  The batch of
-    eleven prompts around the 128-row block size gives the prefill attention a work list of 16 (sequence, block) pairs
-    in an order that differs from the batch order (longest walks first, dealt over the XCDs).  512 and 1020 rows on
-    MINI2K: split launches of 12 to 88 tiles, whose second pass finishes a tile with four blocks (up to 64 tiles) or
-    two (W1/W3 at 1020 rows), each with its share of the tile's waves.  MINI5K: the skinny kernel's 8-wave form (two
+    beyond through the LDS-staged kernel where the contraction is too long for 128 x 128 tiles that walk all of it (QKV
+    and W2 of MINI2K, in 4 or 5 splits of 24 to 64 tiles; the others, and all of MINI64 and of MINIRAG beyond 128 rows, take
+    those tiles).  MINIRAG has a ragged last feature block and an odd number of k-tiles; 128 and 129 + 3 rows sit on either
+    side of the one-token-tile limit.  The batch of eleven prompts around the 128-row block size gives the prefill attention a
+    work list of 16 (sequence, block) pairs in an order that differs from the batch order (longest walks first, dealt over
+    the XCDs).  MINI5K: the skinny kernel's 8-wave form (two
     groups of waves on two halves of a block's contraction, summed through LDS) in every epilogue, full and ragged tile;
     MINIODD: halves of unequal length."""
     w = _weights(cfg)
@@ -183,6 +183,39 @@ def test_bf16_prefill_every_gemm_tile_configuration(tile):
     assert row_rel_err(p, p_ref) < TOL["bf16"]
     with pytest.raises(hx.HexgenError):
         hx.set_gemm_tile(17)
+
+
+MINI2K_F16 = StageConfig("mini2k16", "f16", 2048, 16, 4, 5632, 2, 2, (1,), batch=4, seed=18)
+
+
+@pytest.mark.parametrize("cfg,lens", [(MINIRAG, [129, 3]), (MINI2K, [300, 212]), (MINI2K, [520, 500]), (MINI2K_F16, [200, 79])])
+def test_prefill_split_contraction(cfg, lens):
+    """The LDS-staged kernel with a split contraction and its finishing pass in every epilogue, forced for all projections (tiles of
+    128 x 256, 256 x 128 and 256 x 256; a contraction of 32 k-tiles or more is split where they leave half of the chip idle):
+    MINIRAG's W1/W3 (180 feature tiles) ends in a ragged feature block in two splits, whose padding waves must not store
+    into the next split's sums, and its W2 splits 45 k-tiles; 300 + 212 and 520 + 500 rows of MINI2K have full and ragged token blocks
+    in 2 to 5 splits."""
+    import paper_2311_11514_amd as hx
+    w = _weights(cfg)
+    rank = cfg.tp_ranks[0]
+    X = generate.hidden_rows(cfg, sum(lens), stream_id=9)
+    ora = make_oracle(cfg, rank, w)
+    oc = ora.new_cache(len(lens))
+    p_ref, h_ref = ora.prefill(oc, X, lens)
+    st = make_gpu_stage(cfg, rank, w)
+    for tile in (194, 184, 198):
+        kv = st.kv_cache_create(len(lens), max(lens))
+        hx.set_gemm_tile(tile)
+        try:
+            p, h = gpu_prefill(st, kv, cfg, X, lens)
+        finally:
+            hx.set_gemm_tile(0)
+        assert row_rel_err(h, h_ref) < TOL[cfg.dtype] and row_rel_err(p, p_ref) < TOL[cfg.dtype], tile
+        for layer in range(cfg.n_layers):
+            for s, n in enumerate(lens):
+                for got, ref in zip(kv.read(layer, s, 0, n), (oc.k[layer][s], oc.v[layer][s])):
+                    d = cfg.head_dim
+                    assert row_rel_err(got.numpy().reshape(-1, d), ref.reshape(-1, d)) < TOL[cfg.dtype], tile
 
 
 # a launch of a few more than a multiple of 256 large GEMM tiles: the feature blocks that fill whole rounds of the chip go
