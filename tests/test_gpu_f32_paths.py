@@ -60,13 +60,15 @@ def test_f32_prefill_then_decode(case):
 
 # the tiled products' ways of dealing tiles out to the CUs: a launch of fewer than 256 tiles cut along the contraction, of whole
 # tiles, of two full rounds and a few tiles whose k-steps go round (258 x 2 in W1/W3, the last one
-# 52 columns wide), contractions of two and four k-steps
+# 52 columns wide), contractions of two and four k-steps; 17 token blocks, of which 15 columns of tiles make a round and one column of
+# W_O (the residual) and nine of QKV are dealt out behind it
 DEALT = [
     (1024, 8, 2, 1500, 1, 0, [200, 33]),
     (64, 1, 1, 4096, 1, 0, [40, 60]),
     (128, 2, 1, 130, 1, 0, [1000, 88]),
     (512, 4, 2, 16500, 1, 0, [100]),
     (1024, 8, 2, 16700, 1, 0, [80]),
+    (2048, 16, 4, 96, 1, 0, [1033]),
 ]
 
 
