@@ -31,6 +31,32 @@ typedef __bf16 hx_elem;
 #endif
 typedef __attribute__((__vector_size__(8 * sizeof(hx_elem)))) hx_elem h16x8;
 
+// ---- direct-to-LDS loads and their waits --------------------------------------------------------------------------
+// s_waitcnt that only constrains vmcnt (gfx9 encoding: vmcnt[3:0] | expcnt<<4 | lgkmcnt<<8 | vmcnt[5:4]<<14)
+#define HX_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
+// s_waitcnt lgkmcnt(0) alone (vmcnt and expcnt left at "no wait")
+#define HX_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14))
+// Workgroup barrier WITHOUT the device-memory release a __syncthreads() carries: that release would make
+// the compiler drain every outstanding direct-to-LDS load (vmcnt(0)) at each k-step and undo the
+// pipelining.  LDS reads of the previous step have been consumed by MFMAs before this point; the loads
+// of the step about to be read are covered by the explicit vmcnt wait issued just before.
+#define HX_LDS_BARRIER()                        \
+    do {                                        \
+        HX_WAIT_LGKM0();                        \
+        asm volatile("s_barrier" ::: "memory"); \
+    } while (0)
+__device__ __forceinline__ unsigned hx_lds_addr(const void *p) {
+    return (unsigned)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void *)p);
+}
+// 16 bytes per lane from src + off to lds + 16 * lane (lds, src: the same in every lane).  The compiler does not see these loads in its
+// own vmcnt bookkeeping; every wait on them is explicit (HX_WAIT_VM).  M0 is written here and cannot be named as clobbered: it is a
+// reserved register (the compiler rejects it in a clobber list as undefined behaviour) that the compiler never
+// allocates and only sets itself immediately in front of an instruction of its own that reads it; the kernels that use this
+// contain no such instruction (no LDS-direct builtin, no movrel, no message), so nothing relies on its value.
+__device__ __forceinline__ void hx_load_lds16(unsigned lds, unsigned off, const void *src) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(src) : "memory");
+}
+
 // Decode activations are hi + lo pairs (split_h16), laid out by the number of rows T of the call:
 //   T <= 2: compact token-major, per token and k-tile one 128-byte line holding the 32 hi values then the 32 lo values; a
 //           projection touches one cache line per (token, k-tile) where a 16-token tile would cost it eight;

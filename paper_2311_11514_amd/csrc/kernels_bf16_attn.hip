@@ -557,9 +557,6 @@ void launch_attn_decode_rows(const h16_t *q, h16_t *kc, h16_t *vc, KvGeom kg, in
 // The K and V tiles of a step (16 KB at d = 128) are shared by the block's waves through LDS (direct-to-LDS loads,
 // three stages); two blocks fit a CU, so one wave's softmax arithmetic hides behind the other's MFMAs.
 // -------------------------------------------------------------------------------------------------
-#define HX_AS1(p) ((const __attribute__((address_space(1))) void *)(p))
-#define HX_AS3(p) ((__attribute__((address_space(3))) void *)(p))
-#define HX_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 
 template <int D, int NWV>
@@ -628,11 +625,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_prefill_kernel(const h16_t *
         for (int x = 0; x < LPT; ++x) {
             const int tile = wave + NWV * x;
             const h16x8 *src = tile < 2 * KT ? ks + (size_t)(2 * t * KT + tile) * 64 : vs + (size_t)(t * DT + tile - 2 * KT) * 64;
-            const unsigned lds_addr = (unsigned)reinterpret_cast<uintptr_t>(HX_AS3(&smem[t % S][tile][0]));
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         :
-                         : "s"(lds_addr), "v"(lane_bytes), "s"(src)
-                         : "memory");
+            hx_load_lds16(hx_lds_addr(&smem[t % S][tile][0]), lane_bytes, src);
         }
     };
     // the query block has landed before the first hidden load is issued: the compiler, which does not see those
@@ -643,8 +636,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_prefill_kernel(const h16_t *
     for (int t = 0; t < nt; ++t) {
         if (t + 1 < nt) HX_WAIT_VM(LPT);      // step t has landed; the loads of step t + 1 stay in flight
         else HX_WAIT_VM(0);
-        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));       // this wave's LDS reads are complete
-        asm volatile("s_barrier" ::: "memory");
+        HX_LDS_BARRIER();
         if (t + 2 < nt) issue(t + 2);         // into the buffer of step t - 1, which every wave has left
         if (t >= nt_w) continue;              // this wave's rows end before the tile (it still feeds the others)
         const h16x8(*st)[64] = smem[t % S];

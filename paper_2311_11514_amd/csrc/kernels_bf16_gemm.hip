@@ -19,22 +19,6 @@
 #include "kernels.h"
 #include "kvlayout.h"
 
-#define HX_AS1(p) ((const __attribute__((address_space(1))) void *)(p))
-#define HX_AS3(p) ((__attribute__((address_space(3))) void *)(p))
-// s_waitcnt that only constrains vmcnt (gfx9 encoding: vmcnt[3:0] | expcnt<<4 | lgkmcnt<<8 | vmcnt[5:4]<<14)
-#define HX_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
-// s_waitcnt lgkmcnt(0) alone (vmcnt and expcnt left at "no wait")
-#define HX_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14))
-// Workgroup barrier WITHOUT the device-memory release a __syncthreads() carries: that release would make
-// the compiler drain every outstanding direct-to-LDS load (vmcnt(0)) at each k-step and undo the
-// pipelining.  LDS reads of the previous step have been consumed by MFMAs before this point; the loads
-// of the step about to be read are covered by the explicit vmcnt wait issued just before.
-#define HX_LDS_BARRIER()                        \
-    do {                                        \
-        HX_WAIT_LGKM0();                        \
-        asm volatile("s_barrier" ::: "memory"); \
-    } while (0)
-
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 
 namespace HX_NS {
@@ -392,24 +376,16 @@ __global__ __launch_bounds__(64 * WM * WT) void gemm_mfma_kernel(const h16_t *__
     // k-steps past the end are clamped to the last one (they land in a buffer nobody reads any more), so that
     // every k-step issues exactly LPT loads and the loop body stays one basic block.  The load is written in
     // its scalar-base form (tile address in scalar registers, the lane's 16-byte slot as the 32-bit vector
-    // offset, LDS destination in M0), which the compiler does not select for this instruction by itself: it
-    // would spend a 64-bit vector add per load inside the MFMA stream.  The compiler does not see these
-    // loads in its own vmcnt bookkeeping; every wait on them is explicit (HX_WAIT_VM), and vmcnt is drained
-    // before the epilogue issues ordinary loads.  M0 is written here and cannot be named as clobbered: it is a
-    // reserved register (the compiler rejects it in a clobber list as undefined behaviour) that the compiler never
-    // allocates and only sets itself immediately in front of an instruction of its own that reads it; this kernel
-    // contains no such instruction (no LDS-direct builtin, no movrel, no message), so nothing relies on its value.
+    // offset, LDS destination in M0: hx_load_lds16), which the compiler does not select for this instruction by itself: it
+    // would spend a 64-bit vector add per load inside the MFMA stream.  vmcnt is drained before the epilogue issues
+    // ordinary loads.
     const unsigned lane_bytes = (unsigned)lane * 16u;
     auto issue_one = [&](int kt, int x) {
         const int kc = ABL == 2 ? 0 : min(kt, k_len - 1);
         h16x8 *st = smem + (size_t)(kt % S) * STAGE;
         const h16x8 *src = x < LA ? asrc[x] + kc * astep : bsrc[x - LA] + (size_t)kc * 64;
         h16x8 *dst = x < LA ? st + (wave + NW * x) * 64 : st + (TA + wave + NW * (x - LA)) * 64;
-        const unsigned lds_addr = (unsigned)reinterpret_cast<uintptr_t>(HX_AS3(dst));
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     :
-                     : "s"(lds_addr), "v"(lane_bytes), "s"(src)
-                     : "memory");
+        hx_load_lds16(hx_lds_addr(dst), lane_bytes, src);
     };
     // 32x32x16 operand for k-half kh of a pair of 16-row tiles: lane l takes row l % 32, k-group 2 kh + l / 32
     const int frag = ((lane & 31) >> 4) * 64 + (lane & 15) + 16 * (lane >> 5);
@@ -842,12 +818,12 @@ __global__ __launch_bounds__(512) void gemm_panel_kernel(const h16_t *__restrict
     const h16x8 *bsrc = reinterpret_cast<const h16x8 *>(Xp) + (size_t)min(bt * 8 + wave, t_tiles - 1) * k_tiles * 64;
     const size_t astep = (size_t)n_tiles * 64;
     const unsigned lane_bytes = (unsigned)lane * 16u;
-    const unsigned lds0 = (unsigned)reinterpret_cast<uintptr_t>(HX_AS3(smem)) + wave * 1024u;
+    const unsigned lds0 = hx_lds_addr(smem) + wave * 1024u;
     auto issue = [&](int stage, int x) {            // x: 0, 1 weights, 2, 3 activations of the even and the odd k-step
         const int kt = min(2 * stage + (x & 1), k_tiles - 1);
         const h16x8 *src = x < 2 ? asrc + kt * astep : bsrc + (size_t)kt * 64;
         const unsigned lds = lds0 + (unsigned)(stage % S) * (STAGE * 16u) + (x & 1) * (STEP * 16u) + (x < 2 ? 0u : 8192u);
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(lane_bytes), "s"(src) : "memory");
+        hx_load_lds16(lds, lane_bytes, src);
     };
     struct Ops { h16x8 a[4], b[4]; } f0, f1;
     auto fetch = [&](Ops &o, int stage, int x) {    // operand x: four activation tiles, then four weight tiles

@@ -271,10 +271,6 @@ __device__ inline int f32_share(const F32Walk &k, int i) {
     return (int)((unsigned)min(i, k.sharers) * (unsigned)(k.cols * k.ksteps) / (unsigned)k.sharers);
 }
 
-typedef __attribute__((address_space(3))) void *f32_lds_ptr;
-#define F32_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
-#define F32_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14))
-
 // A wave's 32 x 32 result: lane l holds row l % 32 and, in register 4 q + r, column 8 q + 4 (l / 32) + r of the wave's columns (SwiGLU:
 // quads 0, 1 are 16 gate columns, quads 2, 3 the up columns that belong to them)
 template <int MODE>
@@ -351,11 +347,11 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(F32Proj p, F32Walk k, flo
         wsrc = p.w + (size_t)(q.lo * F32_BK + 2 * wave) * p.N;
     };
     // the x-th of the three loads of a k-step into stage buffer `buf` (floats from the start of LDS)
-    const unsigned lds0 = (unsigned)reinterpret_cast<uintptr_t>((f32_lds_ptr)smem) + wave * 1024u;
+    const unsigned lds0 = hx_lds_addr(smem) + wave * 1024u;
     auto issue = [&](int buf, int x) {
         const unsigned lds = lds0 + 4u * buf + (x == 0 ? 0u : x == 1 ? 8192u : 4u * SW);
         const float *src = x == 0 ? wsrc : x == 1 ? wsrc + whalf : xsrc;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(x < 2 ? woff : xoff), "s"(src) : "memory");
+        hx_load_lds16(lds, x < 2 ? woff : xoff, src);
     };
     size_t wadv = wstep;
     int xadv = F32_BK;
@@ -412,7 +408,7 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(F32Proj p, F32Walk k, flo
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) sum[r] = acc[0][r] = acc[1][r] = 0.f;
-    F32_WAIT_VM((F32_ST - 2) * 3);
+    HX_WAIT_VM((F32_ST - 2) * 3);
     asm volatile("s_barrier" ::: "memory");
     fetch(0, 0);
     int ci = 0, buf = 0, lbuf = (F32_ST - 1) * STAGE;
@@ -428,9 +424,8 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(F32Proj p, F32Walk k, flo
         fetch(buf, 2);
         __builtin_amdgcn_sched_barrier(0);
         multiply(1);
-        F32_WAIT_VM((F32_ST - 3) * 3);          // this wave's loads of step u + 1 have landed ...
-        F32_WAIT_LGKM0();
-        asm volatile("s_barrier" ::: "memory");       // ... and everybody's; nobody reads step u - 1 any more
+        HX_WAIT_VM((F32_ST - 3) * 3);          // this wave's loads of step u + 1 have landed ...
+        HX_LDS_BARRIER();                       // ... and everybody's; nobody reads step u - 1 any more
         fetch(buf, 3);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -465,7 +460,7 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(F32Proj p, F32Walk k, flo
             run = min(left, F32_RUN);
         }
     }
-    F32_WAIT_VM(0);
+    HX_WAIT_VM(0);
 }
 
 // The dealt-out tiles: adds a tile's pieces up in the order of the contraction.  One wave per 32 x 8 results (SwiGLU: 32 x 8 gate and
