@@ -150,8 +150,10 @@ struct F32Proj {
     float *resid_out, *out_resid;
     int32_t *lens;             // not NULL (T <= 32 only): lens[0 .. T) += 1 once every earlier launch is through
 };
-// n_buf [T][K] (normalised rows) and part (partial sums of a split contraction, may be NULL) are needed for T > 32 only
-void f32_launch_proj(int mode, const F32Proj &p, float *n_buf, float *part, size_t part_floats, hipStream_t s);
+// n_buf [T][K] (normalised rows) and part (partial sums, kF32PartFloats or NULL: no tile is cut) are needed for T > 32 only.
+// Each of 256 blocks has at most two pieces of a 64 x 128 tile to leave there, whatever the shape: 16 MB
+constexpr size_t kF32PartFloats = (size_t)2 * 256 * 64 * 128;
+void f32_launch_proj(int mode, const F32Proj &p, float *n_buf, float *part, hipStream_t s);
 void f32_launch_rope_append(const float *qkv, int T, int hq_l, int hkv_l, int d, int smax, RowMap rm,
                             const float *cos_tab, const float *sin_tab, float *q_out, float *kc, float *vc,
                             hipStream_t s);

@@ -257,6 +257,7 @@ constexpr int F32_BT = 64, F32_BN = 128, F32_BK = 32, F32_ST = 4, F32_CUS = 256;
 // 6.0e-7 / 7.8e-7 -> 6.4e-7 / 9.2e-7, with it 3.9e-7 at either); the time is the same.
 constexpr int F32_RUN = 32;
 constexpr int F32_SLOT = F32_BT * F32_BN;                 // floats of one tile's partial sums
+static_assert(kF32PartFloats == (size_t)2 * F32_CUS * F32_SLOT, "two pieces per block");
 
 // What the blocks of a launch walk, see above.  Tiles are numbered token block fastest: tile = column * gy + token block.
 struct F32Walk {
@@ -524,7 +525,7 @@ void f32_stream_flags(const F32Proj &p, hipStream_t s) {
 }
 
 template <int MODE>
-void f32_proj_mode(const F32Proj &p, float *n_buf, float *part, size_t part_floats, hipStream_t s) {
+void f32_proj_mode(const F32Proj &p, float *n_buf, float *part, hipStream_t s) {
     if (p.T <= 32) {
         constexpr int NM = MODE == F32_SWIGLU ? 2 : 1;
         const bool wide = p.cols / 32 >= 128;
@@ -560,9 +561,8 @@ void f32_proj_mode(const F32Proj &p, float *n_buf, float *part, size_t part_floa
     const int left = cols - (int)((long)F32_CUS * full / k.gy);
     const int most = (int)std::min<long>(F32_CUS / k.gy, (long)left * k.ksteps / 4);      // blocks that share a token block's: at least 4 k-steps each
     if (left > 0 && part != nullptr && most >= std::max(2, left) && (long)left * k.ksteps < (1l << 23)) {      // (no share longer than a tile)
-        const size_t slots = 2 * (size_t)most * k.gy;
         const double us = step * (full * k.ksteps + ((double)left * k.ksteps + most - 1) / most) + 3.0 + (most + left) * k.gy * (double)F32_SLOT * 8.0 / 4e6;
-        if (us + 1.5 < step * k.rounds * k.ksteps && slots * F32_SLOT <= part_floats) {
+        if (us + 1.5 < step * k.rounds * k.ksteps) {
             k.whole = (cols - left) * k.gy;
             k.rounds = full;
             k.workers = full > 0 ? F32_CUS : (most * k.gy + 7) / 8 * 8;
@@ -575,12 +575,12 @@ void f32_proj_mode(const F32Proj &p, float *n_buf, float *part, size_t part_floa
 }
 }  // namespace
 
-void f32_launch_proj(int mode, const F32Proj &p, float *n_buf, float *part, size_t part_floats, hipStream_t s) {
+void f32_launch_proj(int mode, const F32Proj &p, float *n_buf, float *part, hipStream_t s) {
     if (p.T <= 0 || p.cols <= 0) return;
     switch (mode) {
-        case F32_PLAIN: f32_proj_mode<F32_PLAIN>(p, n_buf, part, part_floats, s); break;
-        case F32_RESID: f32_proj_mode<F32_RESID>(p, n_buf, part, part_floats, s); break;
-        case F32_SWIGLU: f32_proj_mode<F32_SWIGLU>(p, n_buf, part, part_floats, s); break;
+        case F32_PLAIN: f32_proj_mode<F32_PLAIN>(p, n_buf, part, s); break;
+        case F32_RESID: f32_proj_mode<F32_RESID>(p, n_buf, part, s); break;
+        case F32_SWIGLU: f32_proj_mode<F32_SWIGLU>(p, n_buf, part, s); break;
     }
 }
 

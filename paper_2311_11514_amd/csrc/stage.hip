@@ -75,8 +75,8 @@ struct Workspace {
     h16_t *n = nullptr, *o = nullptr, *u = nullptr, *q = nullptr;
     float *dec_part = nullptr;       // split partial sums of the batched decode projections
     size_t dec_part_floats = 0;
-    float *gemm_part = nullptr;      // fp32 partial tiles of a split prefill contraction (short prompts)
-    size_t gemm_part_floats = 0;
+    float *gemm_part = nullptr;      // fp32 partial tiles of a split prefill contraction
+    size_t gemm_part_floats = 0;     // (16-bit stages; an fp32 stage has kF32PartFloats)
     h16_t *xa_n = nullptr, *xa_o = nullptr, *xa_u = nullptr;   // decode operands, hi / lo (dec_act_offset)
     h16_t *q_lo = nullptr;
     float *att_o = nullptr, *att_ml = nullptr;
@@ -203,8 +203,7 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
         HX_TRY(dmalloc(&w.u32, T * st->F_p));
         if (rows > kF32StreamRows) {
             HX_TRY(dmalloc(&w.n32, T * st->H));
-            w.gemm_part_floats = (size_t)8 << 20;       // 32 MB: 8 splits of 512 rows x 2048 columns
-            HX_TRY(dmalloc(&w.gemm_part, w.gemm_part_floats));
+            HX_TRY(dmalloc(&w.gemm_part, kF32PartFloats));
         }
     }
     // row_seq, row_pos, cu_rows, pos0, new lengths, attention work list (at most rows / 128 + batch pairs)
@@ -577,7 +576,7 @@ F32Proj f32_proj(const hexgen_stage *st, const float *x, const float *g, const v
     return p;
 }
 void proj_f32(hexgen_stage *st, int mode, const F32Proj &p, hipStream_t s) {
-    f32_launch_proj(mode, p, st->ws.n32, st->ws.gemm_part, st->ws.gemm_part_floats, s);
+    f32_launch_proj(mode, p, st->ws.n32, st->ws.gemm_part, s);
 }
 // RMSNorm, QKV, rotary embedding, cache append and attention; leaves o in the workspace
 void attn_f32(hexgen_stage *st, hexgen_kv_cache *kv, int layer, const Rows &r, const float *h, hipStream_t s) {
@@ -1412,7 +1411,7 @@ hexgen_status_t hexgen_head_greedy(hexgen_head_t *hd, const void *hidden_a, cons
             p.T = n; p.K = H; p.Kp = round_up(H, 32); p.N = hd->Vpad; p.cols = hd->Vpad;
             p.eps = hd->eps;
             p.out = hd->logits;
-            f32_launch_proj(F32_PLAIN, p, nullptr, nullptr, 0, s);
+            f32_launch_proj(F32_PLAIN, p, nullptr, nullptr, s);
             launch_row_argmax(hd->logits, hd->Vpad, hd->Vl, n, hd->r * hd->Vl, token_out + r0, logit_out ? logit_out + r0 : nullptr, s);
         }
     }
