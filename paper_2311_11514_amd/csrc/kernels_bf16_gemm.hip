@@ -125,7 +125,8 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
         }
         if (!e.last_layer) {
             // sum of squares of each token over the 128 features of one partial: the two lane halves hold disjoint rows
-            static_assert(MODE != DEC_RESID || 32 * FM == GEMM_SSQ_COLS || 32 * FM * WM == GEMM_SSQ_COLS, "one partial per wave, or per block, and token");
+            static_assert(MODE != DEC_RESID || 32 * FM == GEMM_SSQ_COLS || 32 * FM * WM == GEMM_SSQ_COLS,
+                          "one partial per wave, or per block, and token");
             if constexpr (32 * FM == GEMM_SSQ_COLS) {
                 const int grp = (bm * TA + wm * FM * 2) * 16 / GEMM_SSQ_COLS;
 #pragma unroll
@@ -583,7 +584,8 @@ __global__ __launch_bounds__(256) void gemm_finish_kernel(const float *__restric
 #pragma unroll 8
         for (int gI = tid >> 5; gI < groups; gI += 8) ss += e.ssq_in[(size_t)gI * T + token];
     }
-    ResidPre pre;          // residual and gain are here with the first sums (W2 at 117 rows of a TP4 70B shard 6.8 -> 6.0 us, at 90 rows 5.8 -> 5.2)
+    // residual and gain are here with the first sums (kernel trace, W2 of a TP4 70B shard: 117 rows 6.8 -> 6.0 us, 90 rows 5.8 -> 5.2)
+    ResidPre pre;
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
@@ -623,7 +625,8 @@ __global__ __launch_bounds__(256) void gemm_finish_kernel(const float *__restric
         }
         __syncthreads();
     }
-    gemm_epilogue<1, 1, 4, 1, MODE>([&](int, int) { return acc; }, fb0 + fb, bt, wave, 0, lane, N, n_tiles, T, e, [&](int tl) { return rstd_s[tl]; }, ssq_lds, MODE == DEC_RESID ? &pre : nullptr);
+    gemm_epilogue<1, 1, 4, 1, MODE>([&](int, int) { return acc; }, fb0 + fb, bt, wave, 0, lane, N, n_tiles, T, e, [&](int tl) { return rstd_s[tl]; },
+                                    ssq_lds, MODE == DEC_RESID ? &pre : nullptr);
 }
 
 // the finishing launch of a split contraction over feature blocks (of 32) nb32_first .. + nb32_count - 1
@@ -774,12 +777,13 @@ __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__re
 }
 
 // -------------------------------------------------------------------------------------------------
-// 128 features x 128 tokens per block, for launches of more than 128 rows that larger tiles would leave with few blocks and a split
-// contraction (takes_panel): no partial sums, no finishing pass.  Eight waves of 64 x 64, four on the even and four on the odd k-steps, which
-// takes a third off what 64 x 32 wave tiles read from LDS; their sums meet through LDS at the end.  A stage holds two k-steps (32 KB, four
-// stages).  A wave's operands of the next stage are read under the MFMAs of this one, so that at its one barrier a stage's buffer is already
-// in registers everywhere and free to be loaded again.  Bound by LDS (48 KB read and written per k-step, 384 cycles against 256 of
-// MFMAs) and by cache misses: a k-step takes 0.14 .. 0.2 us on cached operands, 0.16 .. 0.25 in earnest.
+// 128 features x 128 tokens per block and the whole contraction in it, no partial sums and no finishing pass: for launches that larger
+// tiles would leave with few blocks and a split contraction, for short contractions and for short prompts on wide matrices (takes_panel).
+// Eight waves of 64 x 64, four on the even and four on the odd k-steps, which takes a third off what 64 x 32 wave tiles read from LDS;
+// their sums meet through LDS at the end.  A stage holds two k-steps (32 KB, four stages).  A wave's operands of the next stage are read
+// under the MFMAs of this one, so that at its one barrier a stage's buffer is already in registers everywhere and free to be loaded again.
+// A k-step is 256 cycles of MFMAs and 256 of LDS reads (32 KB), with 16 KB written to LDS by the loads beside them; it takes 0.14 .. 0.2 us
+// (340 .. 480 cycles at 2.4 GHz) on cached operands and 0.16 .. 0.25 in earnest: cache misses cost the difference.
 // -------------------------------------------------------------------------------------------------
 template <int MODE>
 __global__ __launch_bounds__(512) void gemm_panel_kernel(const h16_t *__restrict__ Wp, const h16_t *__restrict__ Xp, int N, int k_tiles,
@@ -1004,9 +1008,9 @@ static void launch_cfg(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, int
                                   (int)dyn);
         raised = true;
     }
-    // A short prompt gives few tiles, each walking the whole contraction while most of the chip idles and the weights
-    // arrive at a fraction of the HBM rate: the contraction is then split over blockIdx.y (at most 8 ways, at least
-    // 16 k-steps each, partials within the scratch) until the chip holds as many blocks as it can.
+    // Few tiles, each walking the whole contraction, leave most of the chip idle, and the weights arrive at a fraction of the HBM rate:
+    // the contraction is then split over blockIdx.y (at most 8 ways, at least 16 k-steps each, partials within the scratch)
+    // until the chip holds as many blocks as it can.  By default these are launches of more than 128 rows that takes_panel leaves.
     int splits = 1;
     const PartGeom pg = part_geom(n_tiles, t_tiles, nb0 * FM * WM, n_blocks * FM * WM);
     const int resident = dyn <= 72 * 1024 ? 512 : 256;       // blocks the chip holds at once (LDS: two per CU or one)

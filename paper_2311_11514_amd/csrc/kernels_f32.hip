@@ -248,8 +248,8 @@ __device__ __forceinline__ void f32_finish4(const F32Proj &p, int t, int n, floa
 // All rows of a launch see a column's contraction cut at the same places, so that equal prompts and sequences have equal results
 // wherever in the batch they sit.
 // The stages run on over tile boundaries.  Measured, two layers of a 2048-wide stage at 572 rows (three prompts), whole call
-// 1154 -> 948 us; 36 random layers of 256 to 4096 columns at 35 .. 1500 rows 1 .. 18 % less, 10 % on average.  Six stages, or a
-// barrier every other step, change nothing.
+// 1154 -> 948 us (under the profiler W1/W3 223 us, 118 TFLOP/s of the 154 a large library product reaches); 36 random layers of 256 to
+// 4096 columns at 35 .. 1500 rows 1 .. 18 % less, 10 % on average.  Six stages, or a barrier every other step, change nothing.
 // -------------------------------------------------------------------------------------------------
 constexpr int F32_BT = 64, F32_BN = 128, F32_BK = 32, F32_ST = 4, F32_CUS = 256;
 // An accumulator's sum joins the tile's after so many k-steps (256 instructions one behind the other): without it whole tiles and long
@@ -282,7 +282,8 @@ __device__ __forceinline__ void f32_tile_store(const F32Proj &p, int bn, int bt,
     floatx4 h[Q];
     if (MODE == F32_RESID) {
 #pragma unroll
-        for (int q = 0; q < Q; ++q) h[q] = *reinterpret_cast<const floatx4 *>(p.resid + (size_t)t * p.cols + min(bn + 32 * wn + 8 * q + 4 * hl, p.cols - 4));
+        for (int q = 0; q < Q; ++q)
+            h[q] = *reinterpret_cast<const floatx4 *>(p.resid + (size_t)t * p.cols + min(bn + 32 * wn + 8 * q + 4 * hl, p.cols - 4));
     }
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -450,7 +451,8 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(F32Proj p, F32Walk k, flo
                 } else {
                     float *dst = part + (size_t)(2 * w + ci) * F32_SLOT + wave * 1024 + lane * 4;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) *reinterpret_cast<floatx4 *>(dst + q * 256) = floatx4{sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<floatx4 *>(dst + q * 256) = floatx4{sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
                 }
 #pragma unroll
                 for (int r = 0; r < 16; ++r) sum[r] = 0.f;
@@ -549,9 +551,9 @@ void f32_proj_mode(const F32Proj &p, float *n_buf, float *part, hipStream_t s) {
     k.ksteps = p.Kp / F32_BK;
     // Whole tiles only: the fullest CU has ceil(tiles / 256) of them, a k-step is 0.95 us.  Dealing out the k-steps of the columns that
     // whole rounds leave over evens that out and costs the partial sums' way through memory (written and read, about 4 TB/s) and a
-    // second launch, for which 3 us are charged: with 6 / 9 / 12 two layers take, 512 wide at 130 rows 161 -> 173 / 185 / 204 us, at
-    // 1000 rows 289 -> 309 / 310 / 310, 1024 wide at 572 rows 364 -> 364 / 379 / 404, 2048 wide at 100 rows 312 -> 312 / 312 / 337,
-    // wider and longer ones the same.  It has to gain 1.5 us by this account: contractions of 8 k-steps stay whole.
+    // second launch, for which 3 us are charged: with 6, 9 or 12 two layers of 512 columns at 130 rows take 7, 15 and 27 % longer, at
+    // 1000 rows 7 %, 1024 columns at 572 rows 0, 4 and 11 %, 2048 at 100 rows 0, 0 and 8 %, wider and longer ones the same.  It has to gain
+    // 1.5 us by this account: contractions of 8 k-steps stay whole.
     const int cols = (p.cols + bn - 1) / bn, tiles = cols * k.gy, full = tiles / F32_CUS;
     const double step = 0.95;
     k.whole = tiles;
@@ -559,9 +561,11 @@ void f32_proj_mode(const F32Proj &p, float *n_buf, float *part, hipStream_t s) {
     k.workers = std::min(F32_CUS, (tiles + 7) / 8 * 8);
     k.cols = k.sharers = 0;
     const int left = cols - (int)((long)F32_CUS * full / k.gy);
-    const int most = (int)std::min<long>(F32_CUS / k.gy, (long)left * k.ksteps / 4);      // blocks that share a token block's: at least 4 k-steps each
-    if (left > 0 && part != nullptr && most >= std::max(2, left) && (long)left * k.ksteps < (1l << 23)) {      // (no share longer than a tile)
-        const double us = step * (full * k.ksteps + ((double)left * k.ksteps + most - 1) / most) + 3.0 + (most + left) * k.gy * (double)F32_SLOT * 8.0 / 4e6;
+    // blocks that share a token block's: at least 4 k-steps each, and no share is longer than a tile
+    const int most = (int)std::min<long>(F32_CUS / k.gy, (long)left * k.ksteps / 4);
+    if (left > 0 && part != nullptr && most >= std::max(2, left) && (long)left * k.ksteps < (1l << 23)) {
+        const double part_us = (most + left) * k.gy * (double)F32_SLOT * 8.0 / 4e6;
+        const double us = step * (full * k.ksteps + ((double)left * k.ksteps + most - 1) / most) + 3.0 + part_us;
         if (us + 1.5 < step * k.rounds * k.ksteps) {
             k.whole = (cols - left) * k.gy;
             k.rounds = full;
@@ -571,7 +575,8 @@ void f32_proj_mode(const F32Proj &p, float *n_buf, float *part, hipStream_t s) {
         }
     }
     hipLaunchKernelGGL((f32_tile_kernel<MODE>), dim3(k.workers), dim3(512), 0, s, t, k, part);
-    if (k.cols > 0) hipLaunchKernelGGL((f32_tile_finish_kernel<MODE>), dim3((MODE == F32_SWIGLU ? 4 : 8) * k.cols * k.gy), dim3(256), 0, s, t, k, part);
+    const int finish = (MODE == F32_SWIGLU ? 4 : 8) * k.cols * k.gy;
+    if (finish > 0) hipLaunchKernelGGL((f32_tile_finish_kernel<MODE>), dim3(finish), dim3(256), 0, s, t, k, part);
 }
 }  // namespace
 
