@@ -952,6 +952,7 @@ __global__ __launch_bounds__(512) void gemm_panel_kernel(const h16_t *__restrict
 //   160    108    400 / 464 / 470 / 512 rows -3.3 / -1.2 / +0.2 / +1.9;  but k = 128: 600 / 640 rows +2.0 / +3.9
 //   192    256    330 / 464 / 470 / 512 rows -8.4 / -1.8 / +0.2 / +5.8;  k = 176: 1500 rows -2.5;  but k = 256: 1024 rows +4.7
 //   256    224    400 / 470 / 512 rows -9.5 / -1.3 / 0;  but k = 256: 512 rows +7.5, k = 448: 400 rows +7
+// Every line also leaves out what would add up longer chains (48 and more k-tiles: quarters) than the split contraction does.
 // "padded": at least a twentieth of the token blocks' rows do not exist.  600 rows of 640 win, 384 of 384 and 512 of 512 lose.
 // Without the residual the other's tiles are 256 tokens wide, and beyond 128 k-tiles it depends on how full the last of them is:
 // 224 tiles, k = 256 at 174 / 184 / 200 rows over a multiple of 256 -1.7 / +0.4 / +1.0, 240 tiles at 192 / 208 / 256 -6.9 / -1.2 / +0.1,
@@ -972,7 +973,7 @@ static bool takes_panel(bool resid, int n_tiles, int t_tiles, int k_tiles, int T
     }
     if (tiles > 256) return false;
     const bool padded = 20 * t_tiles <= 19 * 8 * token_blocks;
-    if (tiles <= 128) return k_tiles <= std::max(48, token_blocks >= 9 ? 32 + tiles / 2 : padded ? 28 + tiles / 2 : tiles / 2);
+    if (tiles <= 128) return k_tiles <= std::max(48, token_blocks >= 9 ? 4 + 3 * tiles / 4 : padded ? 28 + tiles / 2 : tiles / 2);
     if (tiles < 180) return k_tiles <= (padded || tiles >= 168 ? tiles - 36 : tiles - 80);
     if (resid) return k_tiles <= (padded ? 256 : tiles - 16);
     return k_tiles <= 128 || (tiles >= 216 && k_tiles <= 256 && (T - 1) % 256 < (k_tiles <= 192 || tiles >= 232 ? 210 : 176));
