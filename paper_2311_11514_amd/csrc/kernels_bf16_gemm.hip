@@ -43,11 +43,11 @@ __device__ __forceinline__ void resid_request(ResidPre &p, int token, int n0, in
         if (!e.last_layer) p.g[q] = *reinterpret_cast<const floatx4 *>(e.g_next + n);
     }
 }
-template <int FM, int FT, int WM, int WT, int MODE, typename AccF, typename RstdF>
-__device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int wm, int wt, int lane, int N,
+template <int FM, int FT, int WM, int NTOK, int MODE, typename AccF, typename RstdF>
+__device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int wm, int tl0, int lane, int N,
                                               int n_tiles, int T, const GemmEpi &e, RstdF rstd_of,
                                               float *ssq_lds = nullptr, const ResidPre *pre = nullptr) {
-    constexpr int TA = 2 * FM * WM, TB = 2 * FT * WT, NTOK = TB * 16;
+    constexpr int TA = 2 * FM * WM;
     const int hl = lane >> 5;
     if (MODE == DEC_RESID) {
         // Residual read-modify-write.  Walks the wave tile one 32-feature block (i) at a time and fetches the
@@ -59,17 +59,20 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
 #pragma unroll
         for (int j = 0; j < FT; ++j) {
             ssq[j] = 0.f;
-            token[j] = (bt * TB + (wt * FT + j) * 2) * 16 + (lane & 31);
+            token[j] = bt * NTOK + tl0 + 32 * j + (lane & 31);
         }
-        floatx4 hv[2][FT][4];
-        auto load_h = [&](floatx4(&dst)[FT][4], int i) {
+        // a step of the walk: JC of the wave's FT token blocks (all of them, or one where they are many: registers)
+        constexpr int JC = FT > 2 ? 1 : FT, STEPS = FM * FT / JC;
+        floatx4 hv[2][JC][4];
+        auto load_h = [&](floatx4(&dst)[JC][4], int step) {
+            const int i = step / (FT / JC), j0 = step % (FT / JC) * JC;
 #pragma unroll
-            for (int j = 0; j < FT; ++j)
+            for (int j = 0; j < JC; ++j)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int n = (bm * TA + (wm * FM + i) * 2) * 16 + 8 * q + 4 * hl;
-                    dst[j][q] = (token[j] < T && n < N)
-                                    ? *reinterpret_cast<const floatx4 *>(e.h + h_tile_offset(token[j], n, N))
+                    dst[j][q] = (token[j0 + j] < T && n < N)
+                                    ? *reinterpret_cast<const floatx4 *>(e.h + h_tile_offset(token[j0 + j], n, N))
                                     : floatx4{0.f, 0.f, 0.f, 0.f};
                 }
         };
@@ -79,25 +82,29 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
 #pragma unroll
             for (int q = 0; q < 4; ++q) hv[0][0][q] = pre->h[q];
         }
+        floatx4 gv[4];
 #pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            floatx4 gv[4];
+        for (int step = 0; step < STEPS; ++step) {
+            const int i = step / (FT / JC), j0 = step % (FT / JC) * JC;
+            if (j0 == 0) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = (bm * TA + (wm * FM + i) * 2) * 16 + 8 * q + 4 * hl;
-                if (pre != nullptr) gv[q] = pre->g[q];
-                else gv[q] = (n < N && !e.last_layer) ? *reinterpret_cast<const floatx4 *>(e.g_next + n)
-                                                 : floatx4{0.f, 0.f, 0.f, 0.f};
+                for (int q = 0; q < 4; ++q) {
+                    const int n = (bm * TA + (wm * FM + i) * 2) * 16 + 8 * q + 4 * hl;
+                    if (pre != nullptr) gv[q] = pre->g[q];
+                    else gv[q] = (n < N && !e.last_layer) ? *reinterpret_cast<const floatx4 *>(e.g_next + n)
+                                                     : floatx4{0.f, 0.f, 0.f, 0.f};
+                }
             }
-            if (i + 1 < FM) load_h(hv[(i + 1) & 1], i + 1);
+            if (step + 1 < STEPS) load_h(hv[(step + 1) & 1], step + 1);
 #pragma unroll
-            for (int j = 0; j < FT; ++j) {
+            for (int jj = 0; jj < JC; ++jj) {
+                const int j = j0 + jj;
                 const floatx16 c = acc_of(i, j);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int n = (bm * TA + (wm * FM + i) * 2) * 16 + 8 * q + 4 * hl;
                     if (token[j] >= T || n >= N) continue;
-                    const floatx4 h4 = hv[i & 1][j][q];
+                    const floatx4 h4 = hv[step & 1][jj][q];
                     const floatx4 v = {c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
                     if (e.last_layer) {
                         uint2 po;
@@ -125,8 +132,8 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
         }
         if (!e.last_layer) {
             // sum of squares of each token over the 128 features of one partial: the two lane halves hold disjoint rows
-            static_assert(MODE != DEC_RESID || 32 * FM == GEMM_SSQ_COLS || 32 * FM * WM == GEMM_SSQ_COLS,
-                          "one partial per wave, or per block, and token");
+            constexpr int WP = GEMM_SSQ_COLS / (32 * FM);           // waves that share a partial
+            static_assert(MODE != DEC_RESID || (WP * 32 * FM == GEMM_SSQ_COLS && WM % WP == 0), "whole waves per partial, whole partials per block");
             if constexpr (32 * FM == GEMM_SSQ_COLS) {
                 const int grp = (bm * TA + wm * FM * 2) * 16 / GEMM_SSQ_COLS;
 #pragma unroll
@@ -135,20 +142,21 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
                     if (hl == 0 && token[j] < T) e.ssq_out[(size_t)grp * T + token[j]] = tot;
                 }
             } else {
-                // the block's WM waves each hold a quarter of the partial's features: summed through LDS in wave order
+                // WP neighbouring waves hold a partial's features between them: summed through LDS in wave order
 #pragma unroll
                 for (int j = 0; j < FT; ++j) {
                     const float tot = ssq[j] + __shfl_xor(ssq[j], 32, 64);
-                    if (hl == 0) ssq_lds[wm * NTOK + (wt * FT + j) * 32 + (lane & 31)] = tot;
+                    if (hl == 0) ssq_lds[wm * NTOK + tl0 + 32 * j + (lane & 31)] = tot;
                 }
                 __syncthreads();
-                if (wm == 0) {
+                if (wm % WP == 0) {
+                    const int grp = (bm * WM + wm) / WP;
 #pragma unroll
                     for (int j = 0; j < FT; ++j) {
                         float tot = 0.f;
 #pragma unroll
-                        for (int w = 0; w < WM; ++w) tot += ssq_lds[w * NTOK + (wt * FT + j) * 32 + (lane & 31)];
-                        if (hl == 0 && token[j] < T) e.ssq_out[(size_t)bm * T + token[j]] = tot;
+                        for (int w = 0; w < WP; ++w) tot += ssq_lds[(wm + w) * NTOK + tl0 + 32 * j + (lane & 31)];
+                        if (hl == 0 && token[j] < T && grp * GEMM_SSQ_COLS < N) e.ssq_out[(size_t)grp * T + token[j]] = tot;
                     }
                 }
             }
@@ -157,7 +165,7 @@ __device__ __forceinline__ void gemm_epilogue(AccF acc_of, int bm, int bt, int w
     }
 #pragma unroll
     for (int j = 0; j < FT; ++j) {
-        const int tl = (wt * FT + j) * 32 + (lane & 31);       // token column inside the block tile
+        const int tl = tl0 + 32 * j + (lane & 31);             // token column inside the block tile
         const int token = bt * NTOK + tl;
         const bool tv = token < T;
         const float r = e.ssq_in != nullptr ? rstd_of(tl) : 1.0f;
@@ -475,7 +483,7 @@ __global__ __launch_bounds__(64 * WM * WT) void gemm_mfma_kernel(const h16_t *__
                 for (int j = 0; j < FT; ++j) store_part(i, j, acc_of(i, j));
             return;
         }
-        gemm_epilogue<FM, FT, WM, WT, MODE>(acc_of, bm, bt, wm, wt, lane, N, n_tiles, T, e, rstd_of);
+        gemm_epilogue<FM, FT, WM, NTOK, MODE>(acc_of, bm, bt, wm, wt * FT * 32, lane, N, n_tiles, T, e, rstd_of);
         return;
     }
     constexpr int H1 = (LPT + 1) / 2, H2 = LPT / 2;  // loads issued behind / in front of the barrier
@@ -557,7 +565,132 @@ __global__ __launch_bounds__(64 * WM * WT) void gemm_mfma_kernel(const h16_t *__
             for (int j = 0; j < FT; ++j) store_part(i, j, acc[i][j]);
         return;
     }
-    gemm_epilogue<FM, FT, WM, WT, MODE>([&](int i, int j) { return acc[i][j]; }, bm, bt, wm, wt, lane, N, n_tiles, T, e, rstd_of);
+    gemm_epilogue<FM, FT, WM, NTOK, MODE>([&](int i, int j) { return acc[i][j]; }, bm, bt, wm, wt * FT * 32, lane, N, n_tiles, T, e, rstd_of);
+}
+
+// -------------------------------------------------------------------------------------------------
+// 256 features x 32 (TA32 + TB32) tokens per block: the two-phase loop above with wave tiles of 64 features x 32 TA32 tokens (waves 0 .. 3)
+// and x 32 TB32 tokens (waves 4 .. 7).  The two waves of a SIMD are one of either kind and take turns on the matrix core, so the kinds need
+// not be equal: 7 x 32 tokens are 4 + 3, and a k-step is 512 + 384 cycles of MFMAs.  One prompt of 430 rows pays for 448 in it instead of
+// 512.  Bound like the 256-wide tiles by the power limit when the chip is full (that prompt's W1/W3 on a TP2 shard, 224 tiles either
+// way: 1.65 GHz, 416 -> 403 us per layer) and by LDS traffic, 11 or 10 reads of 1 KB per wave and k-step instead of 12.  Waves 0 .. 3 load the weights, waves
+// 4 .. 7 the activations.  Every result is one chain over the block's k-steps, as in those tiles: the same bits before the epilogue.
+// -------------------------------------------------------------------------------------------------
+template <int TA32, int TB32, int MODE>
+__global__ __launch_bounds__(512) void gemm_cols_kernel(const h16_t *__restrict__ Wp, const h16_t *__restrict__ Xp, int N, int k_tiles,
+                                                        int n_tiles, int t_tiles, int T, int n_blocks, int t_blocks, GemmEpi e,
+                                                        float *__restrict__ part) {
+    constexpr int S = 4, WA = 16, TT = 2 * (TA32 + TB32), STAGE = (WA + TT) * 64, NTOK = 16 * TT;
+    extern __shared__ h16x8 smem[];                 // [S][WA + TT][64], then 1024 floats
+    float *ssq_s = reinterpret_cast<float *>(smem + (size_t)S * STAGE);
+    const int total = n_blocks * t_blocks;
+    int id = blockIdx.x;
+    const int per_xcd = (total + 7) / 8;
+    id = (id & 7) * per_xcd + (id >> 3);
+    if (id >= total) return;                     // only when total is not a multiple of 8
+    int bm, bt;
+    gemm_tile_of_id(id, n_blocks, t_blocks, 4, min(8, t_blocks), bm, bt);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int k0 = (int)((long)blockIdx.y * k_tiles / gridDim.y);
+    const int k_len = (int)((long)(blockIdx.y + 1) * k_tiles / gridDim.y) - k0;
+    auto sum_squares = [&]() {
+        if (MODE == DEC_RESID || e.ssq_in == nullptr || part != nullptr) return;
+        const int groups = e.norm_dim / GEMM_SSQ_COLS, tok = tid & 255, token = min(bt * NTOK + tok, T - 1);
+        float ss = 0.f;
+#pragma unroll 32
+        for (int gI = tid >> 8; gI < groups; gI += 2) ss += e.ssq_in[(size_t)gI * T + token];
+        ssq_s[tid] = ss;
+    };
+    auto rstd_of = [&](int tl) { return 1.0f / sqrtf((ssq_s[tl] + ssq_s[256 + tl]) / (float)e.norm_dim + e.eps); };
+    const PartGeom pg = part_geom(n_tiles, t_tiles, 0, n_blocks * 8);
+
+    auto group = [&](auto grp_c) {
+        constexpr int GRP = decltype(grp_c)::value, FT = GRP == 0 ? TA32 : TB32;
+        // waves 0 .. 3 copy the weight tiles of a k-step, waves 4 .. 7 the activation tiles (the last ones may be copied twice); tiles
+        // outside the matrix are clamped to its last ones, k-steps past the end to the last one
+        constexpr int LPT = GRP == 0 ? WA / 4 : (TT + 3) / 4;
+        const int wm = wave & 3;
+        const h16x8 *src[LPT];
+        unsigned dst[LPT];
+#pragma unroll
+        for (int x = 0; x < LPT; ++x) {
+            const int i = wm + 4 * x, j = min(i, TT - 1);
+            src[x] = GRP == 0 ? reinterpret_cast<const h16x8 *>(Wp) + ((size_t)k0 * n_tiles + min(bm * WA + i, n_tiles - 1)) * 64
+                              : reinterpret_cast<const h16x8 *>(Xp) + ((size_t)min(bt * TT + j, t_tiles - 1) * k_tiles + k0) * 64;
+            dst[x] = hx_lds_addr(smem + (GRP == 0 ? i : WA + j) * 64);
+        }
+        const size_t step = GRP == 0 ? (size_t)n_tiles * 64 : 64;
+        const unsigned lane_bytes = (unsigned)lane * 16u;
+        auto issue = [&](int kt) {
+            const int kc = min(kt, k_len - 1);
+            const unsigned st = (unsigned)(kt % S) * (STAGE * 16u);
+#pragma unroll
+            for (int x = 0; x < LPT; ++x) hx_load_lds16(dst[x] + st, lane_bytes, src[x] + kc * step);
+        };
+#pragma unroll
+        for (int p2 = 0; p2 < S - 1; ++p2) issue(p2);
+        sum_squares();
+        HX_WAIT_VM((S - 2) * LPT);
+        HX_LDS_BARRIER();
+        if (GRP == 1) asm volatile("s_barrier" ::: "memory");       // half a step behind waves 0 .. 3 from here on
+        floatx4 a16[4][2 * FT];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2 * FT; ++j) a16[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        h16x8 pa[4], pb[2 * FT];
+        for (int kt = 0; kt < k_len; ++kt) {
+            const h16x8 *sa = smem + (size_t)(kt % S) * STAGE + wm * 4 * 64 + lane;
+            const h16x8 *sb = smem + (size_t)(kt % S) * STAGE + (WA + GRP * 2 * TA32) * 64 + lane;
+#pragma unroll
+            for (int x = 0; x < 2 * FT; ++x) pb[x] = sb[x * 64];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) pa[x] = sa[x * 64];
+            issue(kt + S - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            HX_WAIT_VM((S - 2) * LPT);
+            HX_LDS_BARRIER();
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2 * FT; ++j) a16[i][j] = hx_mfma16(pa[i], pb[j], a16[i][j]);
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_barrier" ::: "memory");
+        }
+        if (GRP == 0) asm volatile("s_barrier" ::: "memory");       // the barrier waves 4 .. 7 passed ahead of their loop
+        HX_WAIT_VM(0);
+        auto acc_of = [&](int i, int j) {           // into the register layout of a 32 x 32 result, as in gemm_mfma_kernel
+            floatx16 c;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int from = 16 * (2 * (q & 1) + (lane >> 5)) + (lane & 15);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float v0 = __shfl(a16[2 * i + (q >> 1)][2 * j][r], from, 64);
+                    const float v1 = __shfl(a16[2 * i + (q >> 1)][2 * j + 1][r], from, 64);
+                    c[4 * q + r] = (lane & 16) ? v1 : v0;
+                }
+            }
+            return c;
+        };
+        if (part != nullptr) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < FT; ++j) {
+                    const int nb = bm * 8 + wm * 2 + i, tb = bt * (TA32 + TB32) + GRP * TA32 + j;
+                    const floatx16 c = acc_of(i, j);
+                    if (nb < pg.nb && tb < pg.tb) part_store(part + part_offset(pg, blockIdx.y, nb, tb), c, lane);
+                }
+            return;
+        }
+        gemm_epilogue<2, FT, 4, NTOK, MODE>(acc_of, bm, bt, wm, GRP * TA32 * 32, lane, N, n_tiles, T, e, rstd_of, ssq_s);
+    };
+    if (wave < 4) group(std::integral_constant<int, 0>{});
+    else group(std::integral_constant<int, 1>{});
 }
 
 // Second pass of a split contraction.  A block of 4 waves finishes 128 features x 32 tokens, a wave one 32 x 32 result tile:
@@ -625,7 +758,7 @@ __global__ __launch_bounds__(256) void gemm_finish_kernel(const float *__restric
         }
         __syncthreads();
     }
-    gemm_epilogue<1, 1, 4, 1, MODE>([&](int, int) { return acc; }, fb0 + fb, bt, wave, 0, lane, N, n_tiles, T, e, [&](int tl) { return rstd_s[tl]; },
+    gemm_epilogue<1, 1, 4, 32, MODE>([&](int, int) { return acc; }, fb0 + fb, bt, wave, 0, lane, N, n_tiles, T, e, [&](int tl) { return rstd_s[tl]; },
                                     ssq_lds, MODE == DEC_RESID ? &pre : nullptr);
 }
 
@@ -934,7 +1067,7 @@ __global__ __launch_bounds__(512) void gemm_panel_kernel(const h16_t *__restrict
         }
         return c;
     };
-    gemm_epilogue<2, 1, 2, 4, MODE>(acc_of, bm, bt, wm, 2 * wt + grp, lane, N, n_tiles, T, e, rstd_of, ssq_s);
+    gemm_epilogue<2, 1, 2, NTOK, MODE>(acc_of, bm, bt, wm, (2 * wt + grp) * 32, lane, N, n_tiles, T, e, rstd_of, ssq_s);
 }
 
 // Which launches: one round of 128 x 128 tiles on the 256 CUs, and a contraction of k k-tiles that is short for the number of tiles.
@@ -992,6 +1125,16 @@ static void launch_panel(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, i
     hipLaunchKernelGGL(kern, dim3((nb * tb + 7) / 8 * 8), dim3(512), dyn, s, Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, nb, tb, e);
 }
 
+// Few tiles, each walking the whole contraction, leave most of the chip idle, and the weights arrive at a fraction of the HBM rate:
+// the contraction is then split over blockIdx.y (at most 8 ways, at least 16 k-steps each, partials within the scratch) until the chip
+// holds as many blocks as it can (`resident`).
+static int tile_splits(long total, int resident, int k_tiles, const PartGeom &pg, const float *part, size_t part_floats) {
+    if (part == nullptr || 2 * total > resident || k_tiles < 32) return 1;
+    int splits = (int)std::max<long>(1, std::min<long>({8, resident / total, k_tiles / 16}));
+    while (splits > 1 && part_offset(pg, splits, 0, 0) > part_floats) --splits;
+    return splits;
+}
+
 template <int FM, int FT, int WM, int WT, int S, int MODE, bool PP = false, int ABL = 0>
 static void launch_cfg(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, int n_tiles, int t_tiles, int T,
                        const GemmEpi &e, float *part, size_t part_floats, hipStream_t s, int nb0 = 0, int nb_count = -1) {
@@ -1009,25 +1152,44 @@ static void launch_cfg(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, int
                                   (int)dyn);
         raised = true;
     }
-    // Few tiles, each walking the whole contraction, leave most of the chip idle, and the weights arrive at a fraction of the HBM rate:
-    // the contraction is then split over blockIdx.y (at most 8 ways, at least 16 k-steps each, partials within the scratch)
-    // until the chip holds as many blocks as it can.  By default these are launches of more than 128 rows that takes_panel leaves.
-    int splits = 1;
+    // (by default these are launches of more than 128 rows that takes_panel leaves)
     const PartGeom pg = part_geom(n_tiles, t_tiles, nb0 * FM * WM, n_blocks * FM * WM);
     const int resident = dyn <= 72 * 1024 ? 512 : 256;       // blocks the chip holds at once (LDS: two per CU or one)
-    if (part != nullptr && 2 * total <= resident && k_tiles >= 32) {
-        splits = std::max(1, std::min({8, resident / total, k_tiles / 16}));
-        while (splits > 1 && part_offset(pg, splits, 0, 0) > part_floats) --splits;
-    }
+    const int splits = tile_splits(total, resident, k_tiles, pg, part, part_floats);
     hipLaunchKernelGGL(kern, dim3(grid, splits), dim3(64 * WM * WT), dyn, s, Wp, Xp, N, k_tiles, n_tiles, t_tiles, T,
                        n_blocks, t_blocks, e, splits > 1 ? part : nullptr, pm_h, std::min(pt_w, t_blocks), nb0);
     if (splits > 1) launch_finish<MODE>(part, splits, N, n_tiles, t_tiles, T, nb0 * FM * WM, n_blocks * FM * WM, e, s);
 }
 
+// splits of a launch of 256 features x tt16 token tiles; at most one block per CU of a die (tiles are dealt to the dies in turn)
+static int cols_splits(int tt16, int n_tiles, int t_tiles, int k_tiles, const float *part, size_t part_floats) {
+    const int n_blocks = (n_tiles + 15) / 16, total = n_blocks * ((t_tiles + tt16 - 1) / tt16);
+    const int splits = tile_splits(total, 256, k_tiles, part_geom(n_tiles, t_tiles, 0, n_blocks * 8), part, part_floats);
+    return std::min(splits, std::max(1, 32 / ((total + 7) / 8)));
+}
+
+template <int TA32, int TB32, int MODE>
+static void launch_cols(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, int n_tiles, int t_tiles, int T, const GemmEpi &e, float *part,
+                        size_t part_floats, hipStream_t s) {
+    constexpr int TT = 2 * (TA32 + TB32);
+    const int n_blocks = (n_tiles + 15) / 16, t_blocks = (t_tiles + TT - 1) / TT, total = n_blocks * t_blocks;
+    const size_t dyn = (size_t)4 * (16 + TT) * 1024 + 1024 * sizeof(float);
+    auto kern = gemm_cols_kernel<TA32, TB32, MODE>;
+    static bool raised = false;
+    if (!raised) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+        raised = true;
+    }
+    const int splits = cols_splits(TT, n_tiles, t_tiles, k_tiles, part, part_floats);
+    hipLaunchKernelGGL(kern, dim3((total + 7) / 8 * 8, splits), dim3(512), dyn, s, Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, n_blocks, t_blocks, e,
+                       splits > 1 ? part : nullptr);
+    if (splits > 1) launch_finish<MODE>(part, splits, N, n_tiles, t_tiles, T, 0, n_blocks * 8, e, s);
+}
+
 // tile configuration forced for every GEMM launch of the process (0 = choose by shape); a measurement and test hook
 static std::atomic<int> g_force_tile{0};
 bool set_gemm_tile(int code) {
-    for (int ok : {0, 44, 48, 84, 88, 94, 49, 98, 72, 128, 198, 194, 184, 1198, 2198, 3198})
+    for (int ok : {0, 160, 192, 224, 44, 48, 84, 88, 94, 49, 98, 72, 128, 198, 194, 184, 1198, 2198, 3198})
         if (code == ok) { g_force_tile.store(code, std::memory_order_relaxed); return true; }
     return false;
 }
@@ -1053,6 +1215,22 @@ static double gemm_estimate_us(int tm, int tt, double step_us, int n_tiles, int 
         us += part_mb / 5.0 + 8.0 + part_mb / 2.5 + (resid ? 15.0 : 0.0);
     }
     return us;
+}
+
+// Time of one projection with tm x tt tiles in `splits`, for the choice between tiles of 160, 192 and 224 tokens and the ones of 256 (or
+// 128) that the estimate above has picked.  Fitted to whole calls of one prompt of 140 .. 5000 rows on layers of the 70B shape (one to
+// eight ranks) and of 1024 .. 5120 columns, each projection's tiles changed alone (5300 differences).  A k-step of a 256 x 256 block
+// takes 0.65 us when every CU has one and 0.40 when few have, most of it in proportion to the tile: beyond that the power limit sets the
+// clock.  Blocks are dealt to the eight dies in turn and 32 CUs each: 84 tiles in three splits are 33 blocks on seven of them, two rounds.
+static double tile_us(int mode, int tm, int tt, int splits, int n_tiles, int t_tiles, int k_tiles) {
+    const int total = (int)((long)((n_tiles * 16 + tm - 1) / tm) * ((t_tiles * 16 + tt - 1) / tt));
+    const long blocks = (long)((total + 7) / 8) * 8 * splits, full = blocks / 256, rem = blocks % 256;
+    const double area = tm * tt / 65536.0, ks = (double)k_tiles / splits;
+    double us = full * (ks * (0.155 + 0.49 * area) + 5.7);
+    if (rem > 0) us += ks * (0.155 + area * (0.24 + 0.25 * rem / 256.0)) + 5.7;
+    // what the epilogue adds: the residual stream's values, scattered cache rows
+    if (splits == 1) return us + (mode == DEC_RESID ? 3.4 * area * (full + (rem > 0)) : mode == DEC_QKV ? 10.0 * blocks / 256.0 : 0.0);
+    return us + splits * (double)n_tiles * t_tiles * 1024.0 / 1e6 * 0.40;          // MB of partial sums, written and read
 }
 
 // one 128-token tile, at least 32 k-tiles: skinny kernel + finishing pass; returns false when it does not apply
@@ -1087,6 +1265,31 @@ static bool launch_skinny(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, 
     return true;
 }
 
+// Tiles of 256 features x 160, 192 or 224 tokens (gemm_cols_kernel) in place of `cfg`, 198 (nA > 0: in two launches) or 194?  Rows are
+// then paid for up to fewer than 256, and the number of tiles fits the CUs more often.  Whole calls of one prompt: TP1 shard of the 70B
+// shape (one layer) at 285 / 437 / 604 rows 714 / 757 / 1102 -> 606 / 732 / 1004 us, TP2 (two) at 328 / 430 / 600 792 / 855 / 1239 -> 710 / 812 /
+// 1194, TP4 (three) at 274 / 570 / 737 667 / 1046 / 1135 -> 643 / 931 / 1054, 3072-wide (three) at 312 / 449 / 1087 569 / 579 / 1026 -> 496 / 546 / 944.
+// At 470 .. 512, 900 .. 1024 and 2048 rows 256 is the better tile (TP2's W1/W3 at 470 rows +112 us in tiles of 224, +85 in 192) and stays.
+//   * At least 4 us and 2 % by the estimate, whose error is of that size; up to 256 rows nothing is that much better.
+//   * No chain of additions gets longer: at least as many splits as the launch had (two launches: its second one).
+template <int MODE>
+static int token_tile(int cfg, int nA, int n_tiles, int t_tiles, int k_tiles, const float *part, size_t part_floats) {
+    constexpr bool resid = MODE == DEC_RESID;
+    const int tm = cfg == 198 || resid ? 256 : 128, tt = cfg == 198 || !resid ? 256 : 128;
+    const int n = n_tiles - 16 * nA, blocks = (n * 16 + tm - 1) / tm;
+    const int now = tile_splits((long)blocks * ((t_tiles * 16 + tt - 1) / tt), 256, k_tiles, part_geom(n, t_tiles, 0, blocks * (tm / 32)), part, part_floats);
+    double best = tile_us(MODE, tm, tt, now, n, t_tiles, k_tiles);
+    if (nA > 0) best += tile_us(MODE, tm, tt, 1, 16 * nA, t_tiles, k_tiles);
+    best = 0.98 * best - 4.0;
+    for (int t : {160, 192, 224}) {
+        const int sp = cols_splits(t / 16, n_tiles, t_tiles, k_tiles, part, part_floats);
+        if (sp < now) continue;
+        const double us = tile_us(MODE, 256, t, sp, n_tiles, t_tiles, k_tiles);
+        if (us < best) { best = us; cfg = t; }
+    }
+    return cfg;
+}
+
 template <int MODE>
 static void launch_mode(const h16_t *Wp, const h16_t *Xp, int N, int K, int T, const GemmEpi &e, float *part,
                         size_t part_floats, hipStream_t s) {
@@ -1105,6 +1308,22 @@ static void launch_mode(const h16_t *Wp, const h16_t *Xp, int N, int K, int T, c
         launch_panel<MODE>(Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, e, s);
         return;
     }
+    // A launch of `total` 256 x 256 tiles, a few more than a multiple of the 256 that the chip holds, would run its last round nearly
+    // empty (1280 rows x 14336 features: 280 tiles, two rounds for 1.09 rounds of work).  Then the feature blocks whose tiles fill
+    // whole rounds go first (nA of them), and the few that remain follow as a launch of their own, which launch_cfg splits along the
+    // contraction so that it fills the chip as well.
+    const int nb = (n_tiles + 15) / 16, tb = (t_tiles + 15) / 16, total = nb * tb, rem = total % 256;
+    int nA = (total - rem) / tb;
+    if (force || cfg != 198 || total <= 256 || rem == 0 || rem > 128 || part == nullptr || k_tiles < 32 || nA < 1 || nA >= nb ||
+        gemm_estimate_us(256, 256, 0.55, nA * 16, t_tiles, k_tiles, resid, true) +
+                gemm_estimate_us(256, 256, 0.55, (nb - nA) * 16, t_tiles, k_tiles, resid, true) >= t198)
+        nA = 0;
+    if (!force && t_tiles > 16) cfg = token_tile<MODE>(cfg, nA, n_tiles, t_tiles, k_tiles, part, part_floats);
+#define HX_COLS(A, B) launch_cols<A, B, MODE>(Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, e, part, part_floats, s)
+    if (cfg == 224) { HX_COLS(4, 3); return; }
+    if (cfg == 192) { HX_COLS(3, 3); return; }
+    if (cfg == 160) { HX_COLS(3, 2); return; }
+#undef HX_COLS
     // the RESID epilogue emits one sum-of-squares partial per wave: its 32 FM features must be 128
     if (MODE == DEC_RESID && cfg != 88 && cfg != 84 && cfg != 184 && cfg != 98 && cfg % 1000 != 198) cfg = cfg == 72 ? 198 : (cfg == 194 ? 184 : 84);
     if (!force && t_tiles <= 8 && launch_skinny<MODE>(Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, e, part, part_floats, s)) return;
@@ -1112,16 +1331,7 @@ static void launch_mode(const h16_t *Wp, const h16_t *Xp, int N, int K, int T, c
     if (cfg == 88) HX_G(4, 4, 2, 2, 4);
     else if (cfg == 98) HX_G(4, 2, 2, 4, 4);
     else if (cfg == 198) {
-        // The chip holds 256 of these blocks; a launch of a few more than a multiple of 256 would run its last round
-        // nearly empty (1280 rows x 14336 features: 280 tiles, two rounds for 1.09 rounds of work).  Then the feature
-        // blocks whose tiles fill whole rounds go first, and the few that remain follow as a launch of their own, which
-        // launch_cfg splits along the contraction so that it fills the chip as well.
-        const int nb = (n_tiles + 15) / 16, tb = (t_tiles + 15) / 16, total = nb * tb, rem = total % 256;
-        const int nA = (total - rem) / tb;
-        if (!force && total > 256 && rem > 0 && rem <= 128 && part != nullptr && k_tiles >= 32 && nA >= 1 && nA < nb &&
-            gemm_estimate_us(256, 256, 0.55, nA * 16, t_tiles, k_tiles, resid, true) +
-                    gemm_estimate_us(256, 256, 0.55, (nb - nA) * 16, t_tiles, k_tiles, resid, true) <
-                t198) {
+        if (nA > 0) {
             launch_cfg<4, 2, 2, 4, 4, MODE, true>(Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, e, part, part_floats, s, 0, nA);
             launch_cfg<4, 2, 2, 4, 4, MODE, true>(Wp, Xp, N, k_tiles, n_tiles, t_tiles, T, e, part, part_floats, s, nA, nb - nA);
         } else {
