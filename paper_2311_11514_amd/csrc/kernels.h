@@ -119,6 +119,9 @@ struct GemmEpi {
     // SWIGLU
     h16_t *u;                 // fragment tiles [T/16][F_l/32]
     int F_l;
+    // counters of the skinny kernel, one per 128 features, zero between launches: blocks of a split contraction that have arrived, the
+    // last of which finishes the tile.  NULL: a launch of its own does
+    unsigned *arrived;
 };
 // per row of logits [n][ld]: the largest of the first `valid` entries and its index + id0 (lowest index wins ties)
 void launch_row_argmax(const float *logits, int64_t ld, int valid, int n, int id0, int32_t *token_out, float *logit_out,

@@ -266,6 +266,25 @@ __device__ __forceinline__ void part_store(float *dst, const floatx16 &c, int la
         *reinterpret_cast<floatx4 *>(dst + q * 256 + lane * 4) = floatx4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
 }
 
+// The same for a block of the same launch: past the caches of the die (common.h, device-scope accesses)
+__device__ __forceinline__ void part_store_dev(float *dst, const floatx16 &c, int lane) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const floatx4 v = {c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+        asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(dst + q * 256 + lane * 4), "v"(v) : "memory");
+    }
+}
+__device__ __forceinline__ void part_load_dev(const float *src, floatx4 (&v)[4], int lane) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        union { uint64_t u[2]; floatx4 f; } r;
+        const uint64_t *p = reinterpret_cast<const uint64_t *>(src + q * 256 + lane * 4);
+        r.u[0] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        r.u[1] = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v[q] = r.f;
+    }
+}
+
 // Linear tile id -> (feature block bm, token block bt).  Ids are dealt out patch by patch: a patch is pm_h feature
 // blocks x pt_w token blocks (lower / narrower at the edges), patches run along the token blocks first, and inside a
 // patch the feature block varies fastest.  pm_h = 1, pt_w = t_blocks is the plain row-major order.
@@ -786,9 +805,19 @@ static void launch_finish(const float *part, int splits, int N, int n_tiles, int
 // in step with the other (one barrier serves both) and the second group's results added to the first's through LDS
 // before anything is stored: as many waves and k-steps per wave as two blocks of 4 on two splits, half the partial sums.
 // -------------------------------------------------------------------------------------------------
-template <int KG, int NT>
-__global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__restrict__ Wp, const h16_t *__restrict__ Xp,
-                                                              int k_tiles, int n_tiles, int t_tiles, float *__restrict__ part, int T_rows) {
+// OWN (W1/W3): no finishing launch.  With one split a block holds the whole contraction.  With two, the block that arrives last adds the
+// other's partial sums to its own and finishes the tile: nobody waits for anybody, the sums go past the dies' caches and are added in
+// split order, so the results are the finishing kernel's whoever was last.
+struct SkinnyOwn {
+    const float *ssq_in;       // as in GemmEpi
+    int norm_dim, T, F_l;
+    float eps;
+    h16_t *u;
+    unsigned *arrived;         // per block of features
+};
+template <int KG, int NT, bool OWN>
+__global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__restrict__ Wp, const h16_t *__restrict__ Xp, int k_tiles,
+                                                              int n_tiles, int t_tiles, float *part, int T_rows, SkinnyOwn e) {
     constexpr int RING = NT <= 2 ? 8 : 6, XT = 2 * NT, XW = (XT + 3) / 4;      // 16-token tiles of the block, and per wave
     constexpr int XBUF = 2 * XT * 64, RED = 4 * NT * 16 * 64 / 4;       // LDS in h16x8: staging per group; sums of a group
     __shared__ h16x8 smem[KG == 2 && RED > KG * XBUF ? RED : KG * XBUF];
@@ -872,41 +901,111 @@ __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__re
             step(i, kt);
         }
     }
+    // From here on a wave has 32 features and the token blocks j0 .. j0 + FTW - 1 (those from NT on do not exist): all of them, or with two
+    // groups one half each, whose sums over both groups meet through the staging buffers -- group 0 + group 1, in that order, every time.
+    constexpr int FTW = KG == 2 ? (NT + 1) / 2 : NT;
+    const int j0 = kg * FTW;
+    floatx16 sum[FTW];
     if constexpr (KG == 2) {
-        // group 1 hands its results to group 0 through the staging buffers; group 0 + group 1, in that order, every time
         float *red = reinterpret_cast<float *>(smem);
         __syncthreads();
-        if (kg == 1) {
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) red[((w4 * NT + j) * 16 + r) * 64 + lane] = acc[j][r];
-        }
-        __syncthreads();
-        if (kg != 0) return;
 #pragma unroll
         for (int j = 0; j < NT; ++j)
+            if ((j < FTW) == (kg == 1)) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][r] += red[((w4 * NT + j) * 16 + r) * 64 + lane];
+                for (int r = 0; r < 16; ++r) red[((w4 * NT + j) * 16 + r) * 64 + lane] = acc[j][r];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < FTW; ++j) {
+            const bool there = j0 + j < NT;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float mine = kg == 0 ? acc[j][r] : FTW + j < NT ? acc[FTW + j < NT ? FTW + j : 0][r] : 0.f;
+                sum[j][r] = there ? mine + red[((w4 * NT + j0 + j) * 16 + r) * 64 + lane] : 0.f;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < FTW; ++j) sum[j] = acc[j];
     }
     const PartGeom pg = part_geom(n_tiles, t_tiles, 0, gridDim.x * 4);
-    if (T_rows > 0) {                    // row-major sums [split][row][feature] for a consumer that works on whole rows
-        const int n0 = (id * 4 + w4) * 32 + 4 * (lane >> 5), N = n_tiles * 16;
+    const int nb = id * 4 + w4, split = blockIdx.y, splits = gridDim.y;
+    if constexpr (!OWN) {
+        if (T_rows > 0) {                    // row-major sums [split][row][feature] for a consumer that works on whole rows
+            const int n0 = nb * 32 + 4 * (lane >> 5), N = n_tiles * 16;
 #pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const int row = 32 * j + (lane & 31);
-            if (row >= T_rows) continue;
-            float *dst = part + ((size_t)blockIdx.y * T_rows + row) * N;
+            for (int j = 0; j < FTW; ++j) {
+                const int row = 32 * (j0 + j) + (lane & 31);
+                if (row >= T_rows) continue;
+                float *dst = part + ((size_t)split * T_rows + row) * N;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (n0 + 8 * q < N)
-                    *reinterpret_cast<floatx4 *>(dst + n0 + 8 * q) = floatx4{acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+                for (int q = 0; q < 4; ++q)
+                    if (n0 + 8 * q < N)
+                        *reinterpret_cast<floatx4 *>(dst + n0 + 8 * q) = floatx4{sum[j][4 * q], sum[j][4 * q + 1], sum[j][4 * q + 2], sum[j][4 * q + 3]};
+            }
+            return;
         }
-        return;
-    }
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
-        if (id * 4 + w4 < pg.nb && j < pg.tb) part_store(part + part_offset(pg, blockIdx.y, id * 4 + w4, j), acc[j], lane);
+        for (int j = 0; j < FTW; ++j)
+            if (nb < pg.nb && j0 + j < pg.tb) part_store(part + part_offset(pg, split, nb, j0 + j), sum[j], lane);
+    } else {
+        constexpr int NTP = 32 * KG * FTW, SH = 256 * KG / NTP;        // token columns of the block's waves
+        __shared__ float s_ss[8][NTP];
+        __shared__ int s_last;
+        if (splits > 1) {
+#pragma unroll
+            for (int j = 0; j < FTW; ++j)
+                if (nb < pg.nb && j0 + j < pg.tb) part_store_dev(part + part_offset(pg, split, nb, j0 + j), sum[j], lane);
+        }
+        if (e.ssq_in != nullptr) {          // the rows' sums of squares, in the finishing kernel's eight shares, while the stores are on their way
+            const int groups = e.norm_dim / GEMM_SSQ_COLS, tok = tid % NTP, token = min(tok, e.T - 1);
+            for (int sh = tid / NTP; sh < 8 && tid < SH * NTP; sh += SH) {
+                float ss = 0.f;
+#pragma unroll 8
+                for (int gI = sh; gI < groups; gI += 8) ss += e.ssq_in[(size_t)gI * e.T + token];
+                s_ss[sh][tok] = ss;
+            }
+        }
+        if (splits > 1) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's stores have reached memory ...
+            __syncthreads();                                      // ... and every other wave's of the block,
+            if (tid == 0) {                                       // before the block counts itself
+                const unsigned before = __hip_atomic_fetch_add(&e.arrived[id], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_last = before + 1 == (unsigned)splits;
+                if (s_last) __hip_atomic_store(&e.arrived[id], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);     // for the next launch
+            }
+            __syncthreads();
+            if (!s_last) return;
+#pragma unroll
+            for (int j = 0; j < FTW; ++j) {
+                if (nb >= pg.nb || j0 + j >= pg.tb) continue;
+                floatx4 v[4];
+                floatx16 tot;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) tot[r] = 0.f;
+                for (int z = 0; z < splits; ++z) {                // in split order
+                    if (z != split) part_load_dev(part + part_offset(pg, z, nb, j0 + j), v, lane);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) tot[r] += z == split ? sum[j][r] : v[r >> 2][r & 3];
+                }
+                sum[j] = tot;
+            }
+        } else {
+            __syncthreads();
+        }
+        auto rstd_of = [&](int tl) {
+            float ss = s_ss[0][tl];
+#pragma unroll
+            for (int w = 1; w < 8; ++w) ss += s_ss[w][tl];
+            return 1.0f / sqrtf(ss / (float)e.norm_dim + e.eps);
+        };
+        GemmEpi g;
+        g.ssq_in = e.ssq_in;
+        g.u = e.u;
+        g.F_l = e.F_l;
+        gemm_epilogue<1, FTW, 4, NTP, DEC_SWIGLU>([&](int, int j) { return sum[j]; }, id, 0, w4, 32 * j0, lane, n_tiles * 16, n_tiles, e.T, g, rstd_of);
+    }
 }
 
 // -------------------------------------------------------------------------------------------------
@@ -1251,15 +1350,30 @@ static bool launch_skinny(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, 
     // QKV 20 x 8 -> x 4: 25.6 -> 32.4), and 8-wave blocks at an unchanged number of splits gain nothing there either.
     const bool pair = splits % 2 == 0 && n_blocks * (splits / 2) >= 160;
     if (pair) splits /= 2;
+    // W1/W3 finishes its own tiles up to two splits: a finishing launch is 8 to 10 us of a call.  Whole calls: TP1 (one split) 90 / 33 rows 398 / 351
+    // -> 377 / 339 us, 50 decoding sequences 1402 -> 1332; TP2 (one) 60 rows 410 -> 399; TP4 (two) 40 / 60 / 90 / 117 rows 372 / 383 / 430 / 461 -> 364 /
+    // 374 / 418 / 453, 40 / 60 / 90 / 120 sequences 2769 / 2840 / 3405 / 3461 -> 2704 / 2775 / 3341 / 3406.  With four splits (W_O, W2) and eight (QKV) the last
+    // blocks, a quarter and less of the CUs, take 2.5 and 10 us longer than the launch.
+    const bool own = MODE == DEC_SWIGLU && splits <= 2 && tail == nullptr && (splits == 1 || e.arrived != nullptr);
+    const SkinnyOwn oe{e.ssq_in, e.norm_dim, T, e.F_l, e.eps, e.u, e.arrived};
     auto run = [&](auto kern, int kg) {
-        hipLaunchKernelGGL(kern, dim3(n_blocks, splits), dim3(256 * kg), 0, s, Wp, Xp, k_tiles, n_tiles, t_tiles, part, tail != nullptr ? T : 0);
+        hipLaunchKernelGGL(kern, dim3(n_blocks, splits), dim3(256 * kg), 0, s, Wp, Xp, k_tiles, n_tiles, t_tiles, part, tail != nullptr ? T : 0, oe);
     };
+#define HX_SK(KG, NT)                                                                   \
+    do {                                                                                \
+        if constexpr (MODE == DEC_SWIGLU) {                                             \
+            if (own) { run(gemm_skinny_kernel<KG, NT, true>, KG); break; }              \
+        }                                                                               \
+        run(gemm_skinny_kernel<KG, NT, false>, KG);                                     \
+    } while (0)
     switch ((t_tiles + 1) / 2) {
-        case 1: if (pair) run(gemm_skinny_kernel<2, 1>, 2); else run(gemm_skinny_kernel<1, 1>, 1); break;
-        case 2: if (pair) run(gemm_skinny_kernel<2, 2>, 2); else run(gemm_skinny_kernel<1, 2>, 1); break;
-        case 3: if (pair) run(gemm_skinny_kernel<2, 3>, 2); else run(gemm_skinny_kernel<1, 3>, 1); break;
-        default: if (pair) run(gemm_skinny_kernel<2, 4>, 2); else run(gemm_skinny_kernel<1, 4>, 1); break;
+        case 1: if (pair) HX_SK(2, 1); else HX_SK(1, 1); break;
+        case 2: if (pair) HX_SK(2, 2); else HX_SK(1, 2); break;
+        case 3: if (pair) HX_SK(2, 3); else HX_SK(1, 3); break;
+        default: if (pair) HX_SK(2, 4); else HX_SK(1, 4); break;
     }
+#undef HX_SK
+    if (own) return true;
     if (tail != nullptr) *tail = QkvTail{part, splits, T, N, nullptr, e.cos_tab, e.sin_tab, e.ssq_in, e.norm_dim, e.eps};
     else launch_finish<MODE>(part, splits, N, n_tiles, t_tiles, T, 0, n_blocks * 4, e, s);
     return true;

@@ -77,6 +77,7 @@ struct Workspace {
     size_t dec_part_floats = 0;
     float *gemm_part = nullptr;      // fp32 partial tiles of a split prefill contraction
     size_t gemm_part_floats = 0;     // (16-bit stages; an fp32 stage has kF32PartFloats)
+    unsigned *gemm_arrived = nullptr;         // per 128 features of a projection: blocks of its split contraction that have arrived; zero between launches
     h16_t *xa_n = nullptr, *xa_o = nullptr, *xa_u = nullptr;   // decode operands, hi / lo (dec_act_offset)
     h16_t *q_lo = nullptr;
     float *att_o = nullptr, *att_ml = nullptr;
@@ -138,7 +139,7 @@ bool known_dtype(hexgen_dtype_t dt) { return dt == HEXGEN_F32 || is_h16(dt); }
 #define HX_K(dt, fn, ...) ((dt) == HEXGEN_F16 ? f16::fn(__VA_ARGS__) : bf16::fn(__VA_ARGS__))
 
 void free_ws(Workspace &w) {
-    void *ptrs[] = {w.dec_part, w.gemm_part, w.h, w.n, w.o, w.u, w.q, w.xa_n, w.xa_o, w.xa_u, w.q_lo, w.ssq, w.ssq_pf, w.att_o, w.att_ml, w.att_arrived, w.qkv32, w.n32, w.q32, w.o32, w.u32,
+    void *ptrs[] = {w.dec_part, w.gemm_part, w.gemm_arrived, w.h, w.n, w.o, w.u, w.q, w.xa_n, w.xa_o, w.xa_u, w.q_lo, w.ssq, w.ssq_pf, w.att_o, w.att_ml, w.att_arrived, w.qkv32, w.n32, w.q32, w.o32, w.u32,
                     w.rowmap};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -184,6 +185,8 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
         }
         w.gemm_part_floats = (size_t)16 << 20;      // 64 MB: 8 splits of the widest short-prompt launch
         HX_TRY(dmalloc(&w.gemm_part, w.gemm_part_floats));
+        HX_TRY(dmalloc(&w.gemm_arrived, (nmax + 127) / 128));
+        HX_HIP(hipMemset(w.gemm_arrived, 0, (nmax + 127) / 128 * sizeof(unsigned)));
         HX_TRY(dmalloc(&w.att_o, drows * st->hq_l * kAttnMaxSplit * st->d));
         HX_TRY(dmalloc(&w.att_ml, drows * st->hq_l * kAttnMaxSplit * 2));
         HX_TRY(dmalloc(&w.att_arrived, drows * st->hkv_l));
@@ -335,6 +338,7 @@ GemmEpi gemm_epi_base(hexgen_stage *st, int mode) {
     e.mode = mode;
     e.norm_dim = st->H;
     e.eps = st->eps;
+    e.arrived = st->ws.gemm_arrived;
     return e;
 }
 
