@@ -408,13 +408,18 @@ __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__
 constexpr int sk_chunk(int np) { return np <= 4 ? 8 : 4; }
 
 // NP: operand tiles per k-tile (dec_act_tiles), 1 .. 8 for 3 .. 64 rows
-template <int NP>
+// MODE (DEC_SWIGLU, DEC_BEST; UT feature tiles per unit): one split, the block finishes its own units -- the waves of a unit of two tiles meet through
+// LDS -- and no partial sums or finishing launch are needed; else -1: partial sums, and the rows' rstd on the side.
+template <int NP, int MODE, int UT>
 __global__ __launch_bounds__(512) void decode_splitk_kernel(const h16_t *__restrict__ Wp, const h16_t *__restrict__ Xa,
                                                            int n_tiles, int k_tiles, int T,
-                                                           float *__restrict__ part, const float *__restrict__ ssq_in,
-                                                           int ssq_units, int norm_dim, float eps,
-                                                           float *__restrict__ rstd_out) {
-    constexpr int NB = NP == 1 ? 1 : NP / 2, CH = sk_chunk(NP);
+                                                           float *__restrict__ part, float *__restrict__ rstd_out, DecodeEpi e) {
+    constexpr int NB = NP == 1 ? 1 : NP / 2, CH = sk_chunk(NP), RW = NP;       // RW rows per wave for rstd
+    constexpr bool OWN = MODE >= 0;
+    __shared__ float s_rstd[OWN ? 64 : 1];
+    const float *ssq_in = e.ssq_in;
+    const int ssq_units = e.ssq_units, norm_dim = e.norm_dim;
+    const float eps = e.eps;
     constexpr int XT = CH * NP / 8;                    // operand tiles of a chunk each wave copies
     extern __shared__ h16x8 sk_lds[];                  // [2][CH][NP][64]
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
@@ -453,8 +458,14 @@ __global__ __launch_bounds__(512) void decode_splitk_kernel(const h16_t *__restr
     // sums of squares are requested now and added up after the main loop, when they have long arrived).
     const int n_blocks = gridDim.x * gridDim.y, bid = blockIdx.y * gridDim.x + blockIdx.x;
     const int rstd_row = bid + wave * n_blocks;
-    const bool rstd_mine = rstd_out != nullptr && rstd_row < T;
-    float sv[RSTD_REGS];
+    const bool rstd_mine = !OWN && rstd_out != nullptr && rstd_row < T;
+    float sv[RSTD_REGS], so[OWN ? RW : 1][RSTD_REGS];
+    if constexpr (OWN) {          // every row's, by every block: requested ahead of the weights (rows past the last re-read it)
+        if (ssq_in != nullptr) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r) rstd_request(e, min(wave + 8 * r, T - 1), lane, so[r]);
+        }
+    }
     if (rstd_mine && ssq_in != nullptr) {
 #pragma unroll
         for (int q = 0; q < RSTD_REGS; ++q) sv[q] = ssq_in[(size_t)rstd_row * ssq_units + min(lane + 64 * q, ssq_units - 1)];
@@ -467,6 +478,15 @@ __global__ __launch_bounds__(512) void decode_splitk_kernel(const h16_t *__restr
     h16x8 xr[XT], wc[CH], wn[CH];
     load_x(0, xr);
     load_w(0, wc);
+    if constexpr (OWN) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const int t = wave + 8 * r;
+            if (t >= T) continue;
+            if (ssq_in != nullptr) rstd_finish(e, t, lane, so[r], s_rstd);
+            else if (lane == 0) s_rstd[t] = 1.0f;
+        }
+    }
     store_x(0, xr);
     load_x(1, xr);
     for (int c = 0; c < n_chunks; ++c) {
@@ -504,7 +524,7 @@ __global__ __launch_bounds__(512) void decode_splitk_kernel(const h16_t *__restr
         }
         if (lane == 0) rstd_out[rstd_row] = r;
     }
-    if (rstd_out != nullptr)           // a launch of fewer than T / 8 blocks: the rows not dealt out above
+    if (!OWN && rstd_out != nullptr)   // a launch of fewer than T / 8 blocks: the rows not dealt out above
         for (int row = rstd_row + 8 * n_blocks; row < T; row += 8 * n_blocks) {
             float r = 1.0f;
             if (ssq_in != nullptr) {
@@ -515,12 +535,39 @@ __global__ __launch_bounds__(512) void decode_splitk_kernel(const h16_t *__restr
             }
             if (lane == 0) rstd_out[row] = r;
         }
-    if (!tile_ok) return;
+    if (!OWN && !tile_ok) return;
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] += acl[b];
     if (NP == 1) {          // token columns 8 .. 15 hold the lo parts of tokens 0 .. 7
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[0][r] += __shfl_xor(acc[0][r], 8, 64);
+    }
+    if constexpr (OWN) {
+        const EpiPre pre{};
+        if constexpr (UT == 1) {
+            if (!tile_ok) return;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const floatx4 v[1] = {acc[b]};
+                decode_epilogue<MODE, 1>(v, tile, b, lane, N, T, e, s_rstd, pre);
+            }
+        } else {             // a unit's even wave finishes its even token tiles, the odd one the others
+            floatx4 *ex = reinterpret_cast<floatx4 *>(sk_lds);
+            __syncthreads();                 // nobody reads the operand any more
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                if ((b ^ wave) & 1) ex[(wave * NB + b) * 64 + lane] = acc[b];
+            __syncthreads();
+            if (!tile_ok) return;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                if ((b ^ wave) & 1) continue;
+                const floatx4 other = ex[((wave ^ 1) * NB + b) * 64 + lane];
+                const floatx4 v[2] = {wave & 1 ? other : acc[b], wave & 1 ? acc[b] : other};
+                decode_epilogue<MODE, 2>(v, tile >> 1, b, lane, N, T, e, s_rstd, pre);
+            }
+        }
+        return;
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -607,12 +654,17 @@ void launch_mode(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, co
 }  // namespace
 
 namespace {
-template <int NP>
+template <int NP, int MODE, int UT>
 void launch_splitk_main(dim3 grid, const h16_t *Wp, const h16_t *Xa, int n_tiles, int k_tiles, int T, float *part, const DecodeEpi &e,
                         float *rstd, hipStream_t s) {
     const size_t lds = (size_t)2 * sk_chunk(NP) * NP * 64 * sizeof(h16x8);
-    hipLaunchKernelGGL(decode_splitk_kernel<NP>, grid, dim3(512), lds, s, Wp, Xa, n_tiles, k_tiles, T, part, e.ssq_in, e.ssq_units,
-                       e.norm_dim, e.eps, rstd);
+    if constexpr (MODE == DEC_BEST || (MODE == DEC_SWIGLU && NP <= 4)) {           // (more than 32 rows: the head)
+        if (grid.y == 1) {
+            hipLaunchKernelGGL((decode_splitk_kernel<NP, MODE, UT>), grid, dim3(512), lds, s, Wp, Xa, n_tiles, k_tiles, T, nullptr, nullptr, e);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((decode_splitk_kernel<NP, -1, 1>), grid, dim3(512), lds, s, Wp, Xa, n_tiles, k_tiles, T, part, rstd, e);
 }
 
 template <int MODE, int UT>
@@ -638,13 +690,17 @@ void launch_splitk(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, 
     }
     const dim3 grid(groups, splits);
     switch (np) {
-        case 1: launch_splitk_main<1>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
-        case 2: launch_splitk_main<2>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
-        case 4: launch_splitk_main<4>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
-        case 6: launch_splitk_main<6>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
-        default: launch_splitk_main<8>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
+        case 1: launch_splitk_main<1, MODE, UT>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
+        case 2: launch_splitk_main<2, MODE, UT>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
+        case 4: launch_splitk_main<4, MODE, UT>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
+        case 6: launch_splitk_main<6, MODE, UT>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
+        default: launch_splitk_main<8, MODE, UT>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
     }
     if (mid) (void)hipEventRecord(mid, s);
+    // One split: the kernel has finished its units (W1/W3 of the full-width 70B layer, 448 groups, at 4 / 16 / 32 rows: whole calls of four steps 1218 /
+    // 1255 / 1547 -> 1208 / 1244 / 1513 us; the 4096 x 50304 head at 24 rows 93.0 -> 88.2).  A second split saves less than its launch costs only
+    // where one leaves CUs empty: forced to one, the 250 groups of the 8192 x 32000 head at 48 rows take 124.6 us instead of 111.
+    if ((MODE == DEC_BEST || (MODE == DEC_SWIGLU && np <= 4)) && splits == 1) return;
     if constexpr (MODE == DEC_QKV) {          // the decode attention finishes the projection
         *tail = QkvTail{scratch, splits, T, N, rstd, e.cos_tab, e.sin_tab};
     } else {
