@@ -166,6 +166,11 @@ void f32_launch_attn_prefill(const float *q, float *kc, float *vc, int hq_l, int
 // one new row per sequence at pos[seq]: rotary embedding and cache append of the raw projection qkv, then the attention
 void f32_launch_attn_decode(const float *qkv, float *kc, float *vc, int b, int hq_l, int hkv_l, int d, int smax, const int32_t *pos,
                             const float *cos_tab, const float *sin_tab, float *o, hipStream_t s);
+// The same and the W_O projection behind it (p: F32_RESID with resid_out, p.x not read) in one launch, where f32_attn_wo_fits: T rows of `cols`
+// columns, the longest context `positions`, the new one included
+bool f32_attn_wo_fits(int T, int hq_l, int hkv_l, int d, int cols, int positions);
+void f32_launch_attn_wo(const float *qkv, float *kc, float *vc, int hq_l, int hkv_l, int d, int smax, const int32_t *pos, const float *cos_tab,
+                        const float *sin_tab, const F32Proj &p, hipStream_t s);
 void f32_launch_kv_copy(float *kc, float *vc, float *k, float *v, int hkv_l, int d, int smax, int seq,
                         int pos0, int n, int to_cache, hipStream_t s);
 

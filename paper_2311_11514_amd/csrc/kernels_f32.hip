@@ -805,6 +805,198 @@ void f32_launch_attn_decode(const float *qkv, float *kc, float *vc, int b, int h
     else hipLaunchKernelGGL((f32_attn_kernel<64, 8, true>), grid, dim3(512), 0, s, qkv, kc, vc, hq_l, hkv_l, smax, pos, nullptr, nullptr, cos_tab, sin_tab, o);
 }
 
+// -------------------------------------------------------------------------------------------------
+// A decode step's attention and W_O in one launch, for few sequences with short contexts on a narrow stage: every block computes
+// the attention of all (sequence, kv head) pairs for itself -- at most eight, one to eight waves each -- and goes on with 16 columns of W_O, whose
+// weights it has requested before.  Bound by latency: the launch it saves and the trip of o through memory are longer than
+// reading a few KB of keys and values 32 times from L2 (f32_attn_wo_fits; the tiny stage's eight steps with its head 618 -> 552 us).  The pairs' new keys and values are taken from LDS by every block, block 0
+// appends them to the cache.  W_O adds up in f32_stream_kernel's order.
+// -------------------------------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(512) void f32_attn_wo_kernel(const float *__restrict__ qkv, float *kc, float *vc, int hq_l, int hkv_l, int smax,
+                                                         const int32_t *__restrict__ pos0, const float *__restrict__ cos_tab,
+                                                         const float *__restrict__ sin_tab, F32Proj p) {
+    constexpr int W = 8, KT = D / 16, VH = D / 64, HALF = D / 2, QS = D + 4, U = 4;
+    extern __shared__ __align__(16) float lds[];
+    __shared__ float s_m[W][16], s_l[W][16];
+    __shared__ floatx4 red[W][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    const int G = hq_l / hkv_l, pairs = p.T * hkv_l, qw = hq_l * D;
+    float *s_o = lds, *s_new = lds + W * 16 * D;          // [W][16][D]; [pairs][G + 2][QS]: rotated heads, new key and value; then o [T][qw]
+    const int n0 = blockIdx.x * 16, col = n0 + i, chunks = p.Kp >> 4;
+    float wv[U][4];
+    auto request = [&](int u, int c) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) wv[u][x] = p.w[(size_t)(16 * c + 4 * g + x) * p.N + col];
+    };
+    floatx4 res = {0.f, 0.f, 0.f, 0.f};
+    if (wave == 0) res = *reinterpret_cast<const floatx4 *>(p.resid + (size_t)min(i, p.T - 1) * p.N + n0 + 4 * g);
+    for (int idx = threadIdx.x; idx < pairs * (G + 2) * HALF; idx += 64 * W) {
+        const int row = idx / HALF, e = idx - row * HALF, pair = row / (G + 2), hh = row - pair * (G + 2), seq = pair / hkv_l, c = pair - seq * hkv_l;
+        const float *src = qkv + ((size_t)seq * (hq_l + 2 * hkv_l) + (hh < G ? c * G + hh : (hh == G ? hq_l + c : hq_l + hkv_l + c))) * D;
+        const int pos = pos0[seq];
+        float lo = src[e], hi = src[e + HALF];
+        if (hh <= G) {
+            const float cs = cos_tab[(size_t)pos * HALF + e], sn = sin_tab[(size_t)pos * HALF + e];
+            const float rlo = lo * cs - hi * sn, rhi = hi * cs + lo * sn;
+            lo = rlo; hi = rhi;
+        }
+        s_new[row * QS + e] = lo;
+        s_new[row * QS + e + HALF] = hi;
+        if (hh >= G && blockIdx.x == 0) {
+            float *dst = (hh == G ? kc : vc) + (((size_t)seq * hkv_l + c) * smax + pos) * D;
+            dst[e] = lo;
+            dst[e + HALF] = hi;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) request(u, min(wave + u * W, chunks - 1));
+    HX_LDS_BARRIER();                                      // (the weights stay in flight)
+    const int parts = W / pairs, pair = wave / parts, part = wave - pair * parts;
+    if (pair < pairs) {
+        const int seq = pair / hkv_l, c = pair - seq * hkv_l, pos = pos0[seq], there = max(pos - 1, 0);
+        const float *K = kc + ((size_t)seq * hkv_l + c) * smax * D, *V = vc + ((size_t)seq * hkv_l + c) * smax * D;
+        const float *q = s_new + (pair * (G + 2) + min(i, G - 1)) * QS, *nk = s_new + (pair * (G + 2) + G) * QS, *nv = nk + QS;
+        floatx4 qf[KT];
+#pragma unroll
+        for (int k = 0; k < KT; ++k) qf[k] = *reinterpret_cast<const floatx4 *>(q + 16 * k + 4 * g);
+        const float scale = 1.0f / sqrtf((float)D);
+        floatx4 oacc[VH][4];
+#pragma unroll
+        for (int h = 0; h < VH; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) oacc[h][e] = floatx4{0.f, 0.f, 0.f, 0.f};
+        float m = -INFINITY, lsum = 0.f;
+        for (int t = part; t <= pos >> 4; t += parts) {
+            floatx4 kf[KT], vf[4][VH];
+#pragma unroll
+            for (int k = 0; k < KT; ++k) kf[k] = *reinterpret_cast<const floatx4 *>(K + (size_t)min(16 * t + i, there) * D + 16 * k + 4 * g);
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int h = 0; h < VH; ++h)
+                    vf[x][h] = *reinterpret_cast<const floatx4 *>(V + (size_t)min(16 * t + 4 * g + x, there) * D + 64 * h + 4 * i);
+            if (16 * t + 15 >= pos) {                      // the new row, which block 0 is writing; values behind it are 0, as their weights will be
+#pragma unroll
+                for (int k = 0; k < KT; ++k)
+                    if (16 * t + i >= pos) kf[k] = *reinterpret_cast<const floatx4 *>(nk + 16 * k + 4 * g);
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+#pragma unroll
+                    for (int h = 0; h < VH; ++h)
+                        if (16 * t + 4 * g + x >= pos)
+                            vf[x][h] = 16 * t + 4 * g + x == pos ? *reinterpret_cast<const floatx4 *>(nv + 64 * h + 4 * i) : floatx4{0.f, 0.f, 0.f, 0.f};
+            }
+            floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < KT; ++k)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) s = f32_mfma16(kf[k][x], qf[k][x], s);
+            float mx = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[r] = 16 * t + 4 * g + r <= pos ? s[r] * scale : -INFINITY;
+                mx = fmaxf(mx, s[r]);
+            }
+            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            const float m_new = fmaxf(m, mx);
+            const float base = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = expf(m - base);
+            m = m_new;
+            float ps = 0.f, pr[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                pr[r] = expf(s[r] - base);
+                ps += pr[r];
+            }
+            lsum = lsum * alpha + ps;
+#pragma unroll
+            for (int h = 0; h < VH; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) oacc[h][e] *= alpha;
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int h = 0; h < VH; ++h)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) oacc[h][e] = f32_mfma16(vf[x][h][e], pr[x], oacc[h][e]);
+        }
+        lsum += __shfl_xor(lsum, 16, 64);
+        lsum += __shfl_xor(lsum, 32, 64);
+        if (g == 0) { s_m[wave][i] = m; s_l[wave][i] = lsum; }
+#pragma unroll
+        for (int h = 0; h < VH; ++h)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                *reinterpret_cast<floatx4 *>(s_o + (wave * 16 + i) * D + 64 * h + 16 * g + 4 * r) = floatx4{oacc[h][0][r], oacc[h][1][r], oacc[h][2][r], oacc[h][3][r]};
+    }
+    HX_LDS_BARRIER();
+    for (int idx = threadIdx.x * 4; idx < p.T * qw; idx += 64 * W * 4) {
+        const int seq = idx / qw, head = (idx - seq * qw) / D, dd = idx % D, c = head / G, j = head - c * G, w0 = (seq * hkv_l + c) * parts;
+        float M = -INFINITY;
+        for (int w = w0; w < w0 + parts; ++w) M = fmaxf(M, s_m[w][j]);
+        float L = 0.f;
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int w = w0; w < w0 + parts; ++w) {
+            if (s_l[w][j] == 0.f) continue;
+            const float wt = expf(s_m[w][j] - M);
+            L += s_l[w][j] * wt;
+            acc += *reinterpret_cast<const floatx4 *>(s_o + (w * 16 + j) * D + dd) * wt;
+        }
+        *reinterpret_cast<floatx4 *>(s_new + idx) = acc / L;
+    }
+    HX_LDS_BARRIER();
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int c0 = wave; c0 < chunks; c0 += U * W)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + u * W;
+            if (c < chunks) {
+                const floatx4 x = *reinterpret_cast<const floatx4 *>(s_new + min(i, p.T - 1) * qw + 16 * c + 4 * g);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc = f32_mfma16(wv[u][q], x[q], acc);
+                request(u, min(c + U * W, chunks - 1));
+            }
+        }
+    red[wave][lane] = acc;
+    __syncthreads();
+    if (wave != 0) return;
+    floatx4 v = red[0][lane];
+#pragma unroll
+    for (int w = 1; w < W; ++w) v += red[w][lane];
+    if (i < p.T) *reinterpret_cast<floatx4 *>(p.resid_out + (size_t)i * p.cols + n0 + 4 * g) = res + v;
+}
+static size_t f32_attn_wo_lds(int T, int hq_l, int hkv_l, int d) {
+    return (size_t)(8 * 16 * d + T * (hq_l + 2 * hkv_l) * (d + 4)) * sizeof(float);
+}
+// Few pairs (what every block stages), and about two tiles of 16 positions per wave at head dim 64, one at 128: a further one is 2 us of
+// latency, which is what the fused launch saves.  Two layers and eight steps, us, apart -> fused:
+//   head dim 64   4 pairs at 8 / 20 / 50 / 64 positions 396 / 398 / 400 / 401 -> 368 / 382 / 398 / 426, from 33 on (a prompt of 32, with the head) 618 ->
+//                 552, 1024 columns at 20 / 50 628 / 637 -> 617 / 642; 3 pairs at 20 / 50 372 / 374 -> 358 / 378; 2 pairs at 60 / 110 / 250 461 / 469 / 501 ->
+//                 448 / 453 / 519; 1 pair at 60 / 240 / 500 375 / 405 / 454 -> 354 / 386 / 439; 8 pairs at 20 458 -> 464
+//   head dim 128  1 pair at 60 / 110 397 / 410 -> 373 / 392; 2 pairs at 30 / 56 651 / 658 -> 647 / 662, two sequences of one at 20 656 -> 673
+// 2048 columns at 20 positions 1332 -> 1327.
+bool f32_attn_wo_fits(int T, int hq_l, int hkv_l, int d, int cols, int positions) {
+    const int pairs = T * hkv_l;
+    if (pairs > 4 || hq_l / hkv_l > 16 || cols > 1024 || f32_attn_wo_lds(T, hq_l, hkv_l, d) > 128 * 1024) return false;
+    if (d != 64) return pairs == 1 && positions <= 128;
+    return positions <= (pairs <= 2 ? 256 / pairs : 48);
+}
+void f32_launch_attn_wo(const float *qkv, float *kc, float *vc, int hq_l, int hkv_l, int d, int smax, const int32_t *pos, const float *cos_tab,
+                        const float *sin_tab, const F32Proj &p, hipStream_t s) {
+    const dim3 grid(p.cols / 16);
+    const size_t lds = f32_attn_wo_lds(p.T, hq_l, hkv_l, d);
+    static bool raised = false;
+    if (!raised) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(f32_attn_wo_kernel<64>), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(f32_attn_wo_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+        raised = true;
+    }
+    if (d == 128) hipLaunchKernelGGL(f32_attn_wo_kernel<128>, grid, dim3(512), lds, s, qkv, kc, vc, hq_l, hkv_l, smax, pos, cos_tab, sin_tab, p);
+    else hipLaunchKernelGGL(f32_attn_wo_kernel<64>, grid, dim3(512), lds, s, qkv, kc, vc, hq_l, hkv_l, smax, pos, cos_tab, sin_tab, p);
+}
+
 // staging [n][hkv_l][d] <-> cache rows pos0.. of sequence seq
 __global__ void f32_kv_copy_kernel(float *kc, float *vc, float *k, float *v, int hkv_l, int d, int smax, int seq,
                                    int pos0, int n, int to_cache) {
