@@ -196,8 +196,8 @@ class Bench:
 
 def hbm_roofline(cfg, b, k):
     achieved = k["bytes_per_launch"] / (k["avg_launch_us"] * 1e-6) / 1e9
-    name = ("decode_splitk_kernel<4> (W1/W3 projection, 17..32 rows; its finishing kernel with the SwiGLU epilogue "
-            "follows)" if b > 16 else
+    name = ("decode_splitk_kernel<4, ...> (W1/W3 projection, 17..32 rows; with the SwiGLU epilogue where its contraction is "
+            "not split, else a finishing kernel with it follows)" if b > 16 else
             "decode_proj_kernel or decode_splitk_kernel, by size (W1/W3 projection, 3..16 rows)" if b > 2 else
             "decode_proj_kernel (W1/W3 projection + SwiGLU epilogue, one or two rows)")
     traffic, src = measured_traffic(cfg.name)
