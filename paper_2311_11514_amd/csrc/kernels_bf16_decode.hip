@@ -798,14 +798,24 @@ bool unit_pairs(int mode, int N, int k_tiles, int T) {
 //     short.  Whole call at 32 rows, split -> single: 512 x 32000 22.7 -> 28.1 us, 1024 x 32000 27.7 -> 31.8, 1024 x 50304 34.4 -> 34.7.
 //   * The QKV projection has no finishing launch to save (the attention sums its partials):
 //           8 rows:  42 -0.9 (TP4), 50 -0.6, 84 +3.5 (TP2)    16 rows: 25 -1.0, 84 +1.5
-//     56 MiB, and at least 128 blocks (TP8 has 80: +0.9 .. +4.7).
+//     56 MiB, and at least 128 blocks (TP8 of the 70B shape has 80: +0.9 .. +4.7) or a contraction so short that one block walks it in the
+//     time the partial sums take: without them the attention's blocks begin with the context at once.  Whole layers of four widths' shards,
+//     split -> single, n = 48 .. 96 units, k k-tiles, at 3 / 7 / 12 / 20 / 32 rows:
+//           n = 48, k =  16 26.2 -> 23.9 / 27.2 -> 25.0 / 27.9 -> 26.2 / 31.8 -> 30.8 / 32.6 -> 32.6 us
+//           n = 96, k =  32 29.9 -> 27.6 / 30.0 -> 27.7 / 32.3 -> 30.4 / 37.3 -> 36.7 / 39.1 -> 39.1  (n = 80 at 32 rows 38.7 -> 39.5)
+//           n = 96, k =  64 32.4 -> 30.7 / 32.5 -> 30.5 / 35.1 -> 33.7 / 41.2 -> 41.5 / 42.9 -> 44.1
+//           n = 96, k = 128 40.7 -> 39.9 / 41.3 -> 39.7 / 44.8 -> 44.6 / 52.6 -> 55.1 / 56.2 -> 60.2  (n = 48 at 12 rows 38.7 -> 39.1)
+//           n = 80, k = 256 55.3 -> 56.5 / 56.2 -> 57.3 / 61.5 -> 65.6
+//     So up to 128, 64 and 16 k-tiles at one, two and four operand tiles.  A chain of additions is as long either way: k / 8 tiles and eight
+//     waves' sums in the one, eight tiles of a chunk and k / 8 splits in the other.
 bool decode_single_kernel(int mode, int N, int k_tiles, int T) {
     if (T <= 2) return true;
     if (T > 32) return false;
     if (k_tiles < 8) return true;              // not one chunk of the split kernel
     const int tiles = mode == DEC_SWIGLU ? 2 : 1, units = N / 16 / tiles, pair = unit_pairs(mode, N, k_tiles, T) ? 2 : 1, np = dec_act_tiles(T);
     const size_t operand = (size_t)(units / pair) * k_tiles * np << 10;
-    if (mode == DEC_QKV) return units >= 128 && operand * pair <= (size_t)56 << 20;
+    if (mode == DEC_QKV)
+        return units < 128 ? k_tiles <= (np == 1 ? 128 : np == 2 ? 64 : 16) : operand * pair <= (size_t)56 << 20;
     if (mode == DEC_RESID && units > 256 && units <= 1024 && units != 512) return pair == 2;
     if (mode == DEC_RESID && pair == 2) return true;
     if (units < 192) return k_tiles * (tiles + np) <= (np < 4 ? 384 + 3 * units : mode == DEC_SWIGLU ? 300 + 3 * units : 320 + 2 * units);
