@@ -246,11 +246,13 @@ __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__
     const int unit = blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
 
-    floatx4 acc[UT][NB];
+    // QKV: the lo products have sums of their own, as in the split form (half as many roundings per sum)
+    constexpr int LO = MODE == DEC_QKV && NP >= 2 ? 1 : 0;
+    floatx4 acc[1 + LO][UT][NB];
 #pragma unroll
     for (int u = 0; u < UT; ++u)
 #pragma unroll
-        for (int b = 0; b < NB; ++b) acc[u][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < NB; ++b) acc[0][u][b] = acc[LO][u][b] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     const h16x8 *wp[UT];
 #pragma unroll
@@ -330,8 +332,8 @@ __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__
         for (int u = 0; u < UT; ++u)
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                if (NX > 1) acc[u][b] = hx_mfma16(a[i][u], x[NX > 1 ? 2 * b + 1 : 0], acc[u][b]);
-                acc[u][b] = hx_mfma16(a[i][u], x[2 * b], acc[u][b]);
+                if (NX > 1) acc[LO][u][b] = hx_mfma16(a[i][u], x[NX > 1 ? 2 * b + 1 : 0], acc[LO][u][b]);
+                acc[0][u][b] = hx_mfma16(a[i][u], x[2 * b], acc[0][u][b]);
             }
     };
     // steady state: slot i is consumed and at once refilled with the tile one ring round ahead, so UNROLL - 1
@@ -372,7 +374,7 @@ __global__ __launch_bounds__(WAVES * 64) void decode_proj_kernel(const h16_t *__
 #pragma unroll
     for (int u = 0; u < UT; ++u)
 #pragma unroll
-        for (int b = 0; b < NB; ++b) red[wave][u * NB + b][lane] = acc[u][b];
+        for (int b = 0; b < NB; ++b) red[wave][u * NB + b][lane] = LO ? acc[0][u][b] + acc[LO][u][b] : acc[0][u][b];
     __syncthreads();
     if (!finisher) return;
 
@@ -800,14 +802,18 @@ bool unit_pairs(int mode, int N, int k_tiles, int T) {
 //           8 rows:  42 -0.9 (TP4), 50 -0.6, 84 +3.5 (TP2)    16 rows: 25 -1.0, 84 +1.5
 //     56 MiB, and at least 128 blocks (TP8 of the 70B shape has 80: +0.9 .. +4.7) or a contraction so short that one block walks it in the
 //     time the partial sums take: without them the attention's blocks begin with the context at once.  Whole layers of four widths' shards,
-//     split -> single, n = 48 .. 96 units, k k-tiles, at 3 / 7 / 12 / 20 / 32 rows:
-//           n = 48, k =  16 26.2 -> 23.9 / 27.2 -> 25.0 / 27.9 -> 26.2 / 31.8 -> 30.8 / 32.6 -> 32.6 us
-//           n = 96, k =  32 29.9 -> 27.6 / 30.0 -> 27.7 / 32.3 -> 30.4 / 37.3 -> 36.7 / 39.1 -> 39.1  (n = 80 at 32 rows 38.7 -> 39.5)
-//           n = 96, k =  64 32.4 -> 30.7 / 32.5 -> 30.5 / 35.1 -> 33.7 / 41.2 -> 41.5 / 42.9 -> 44.1
-//           n = 96, k = 128 40.7 -> 39.9 / 41.3 -> 39.7 / 44.8 -> 44.6 / 52.6 -> 55.1 / 56.2 -> 60.2  (n = 48 at 12 rows 38.7 -> 39.1)
+//     split -> single, n units, k k-tiles, at 3 / 7 / 12 / 20 / 32 rows:
+//           n = 12, k =  16 24.8 -> 23.1 / 25.4 -> 23.4 / 25.5 -> 23.6 / 29.6 -> 28.7 / 30.3 -> 29.7 us
+//           n = 24, k =  64 28.7 -> 26.8 / 28.8 -> 27.0 / 30.2 -> 28.7 / 33.7 -> 34.1 / 35.2 -> 36.7
+//           n = 40, k = 128 35.1 -> 34.6 / 35.7 -> 34.9 / 37.3 -> 38.1 / 44.5 -> 47.7 / 46.4 -> 51.9
+//           n = 48, k =  16 27.5 -> 25.4 / 27.8 -> 25.6 / 29.2 -> 27.4 / 32.7 -> 31.9 / 33.9 -> 33.8
+//           n = 96, k =  32 30.4 -> 27.6 / 30.6 -> 28.3 / 32.2 -> 30.7 / 38.1 -> 37.2 / 39.3 -> 39.6
+//           n = 96, k =  64 32.8 -> 31.0 / 33.4 -> 31.2 / 35.3 -> 34.0 / 41.3 -> 41.6 / 43.2 -> 44.2
+//           n = 96, k = 128 41.1 -> 40.0 / 41.5 -> 40.1 / 44.9 -> 44.6 / 52.5 -> 55.1 / 56.0 -> 60.0  (n = 48 at 12 rows 38.8 -> 39.2)
 //           n = 80, k = 256 55.3 -> 56.5 / 56.2 -> 57.3 / 61.5 -> 65.6
-//     So up to 128, 64 and 16 k-tiles at one, two and four operand tiles.  A chain of additions is as long either way: k / 8 tiles and eight
-//     waves' sums in the one, eight tiles of a chunk and k / 8 splits in the other.
+//     So up to 128, 64 and 16 k-tiles at one, two and four operand tiles, whatever the number of units (12 to 96 measured).  The sums are
+//     as good either way: chains of k / 8 tiles and eight waves' sums in the one, of a chunk's eight tiles and k / 8 splits in the
+//     other, the lo products with sums of their own in both.
 bool decode_single_kernel(int mode, int N, int k_tiles, int T) {
     if (T <= 2) return true;
     if (T > 32) return false;

@@ -56,3 +56,33 @@ def test_projection_sums(dtype, H, F, T):
     gate = 0.5 * U * math.sqrt(2 * 256 / 2) if dtype == "f32" else U * math.sqrt(F / 32 / (2 if F < 48 * 32 else 4) / 2)
     print(f"{err:.3e} (gate {gate:.3e})", flush=True)
     assert err < gate
+
+
+# dtype, hidden, heads, kv heads, rows: one, two and four operand tiles; QKV of 48, 96 and 192 units, all in one kernel
+QKV_CASES = [("f16", 1024, 16, 4, 7), ("f16", 1024, 16, 4, 12), ("bf16", 1024, 16, 4, 16), ("f16", 512, 8, 2, 17), ("bf16", 512, 8, 2, 32), ("bf16", 2048, 32, 8, 9)]
+
+
+@pytest.mark.parametrize("dtype,H,hq,hkv,T", QKV_CASES, ids=[f"{c[0]}_H{c[1]}T{c[4]}" for c in QKV_CASES])
+def test_decode_qkv_sums_lo_products_apart(dtype, H, hq, hkv, T):
+    """The hi products of k-tiles 0 and 8, one wave's first two, are +31 B + S and -31 B - S, exact in fp32; the lo product of tile 8 is less than half
+    a unit of 31 B in the last place.  It is all that is left of V, and nothing is left of it where it is added to the hi products' sum."""
+    td = TYPE[dtype]
+    B, S, lo = (2.0 ** 15, 64.0, 2.0 ** -12) if dtype == "f16" else (2.0 ** 20, 64.0, 2.0 ** -9)
+    wv = torch.zeros(H, hkv * 64)
+    for tile, sign in ((0, 1), (8, -1)):
+        wv[32 * tile:32 * tile + 31] = sign * B
+        wv[32 * tile + 31] = sign * S
+    x = torch.ones(T, H)
+    x[:, 32 * 8 + 31] += lo * torch.tensor([1.0, -1.0]).repeat(16)[:T]
+    st = hx.Stage(H, hq, hkv, 64, 1, 1, 0, dtype, 1e-5)
+    one, zero = torch.ones(H), torch.zeros
+    st.load_layer(0, *[w.to(td).cuda() for w in (one, zero(H, H), zero(H, hkv * 64), wv, zero(H, H), one, zero(H, 64), zero(H, 64), zero(64, H))])
+    kv = st.kv_cache_create(T, 32)
+    st.run_sublayer(kv, 0, 0, x.cuda(), None, T, torch.empty(T, H, device="cuda"))
+    torch.cuda.synchronize()
+    x = x.double()
+    exact = (x @ wv.double()) / torch.sqrt((x * x).mean(1, keepdim=True) + 1e-5)
+    got = torch.stack([kv.read(0, i, 0, 1)[1].reshape(-1).double() for i in range(T)])
+    err = float(((got - exact) / exact).abs().max())
+    print(f"{err:.3e}", flush=True)
+    assert err < (2.0 ** -10 if dtype == "f16" else 2.0 ** -7)
