@@ -801,7 +801,7 @@ bool unit_pairs(int mode, int N, int k_tiles, int T) {
 //   * The QKV projection has no finishing launch to save (the attention sums its partials):
 //           8 rows:  42 -0.9 (TP4), 50 -0.6, 84 +3.5 (TP2)    16 rows: 25 -1.0, 84 +1.5
 //     56 MiB, and at least 128 blocks (TP8 of the 70B shape has 80: +0.9 .. +4.7) or a contraction so short that one block walks it in the
-//     time the partial sums take: without them the attention's blocks begin with the context at once.  Whole layers of four widths' shards,
+//     time the partial sums take: without them the attention's blocks begin with the context at once.  Whole layers of shards,
 //     split -> single, n units, k k-tiles, at 3 / 7 / 12 / 20 / 32 rows:
 //           n = 12, k =  16 24.8 -> 23.1 / 25.4 -> 23.4 / 25.5 -> 23.6 / 29.6 -> 28.7 / 30.3 -> 29.7 us
 //           n = 24, k =  64 28.7 -> 26.8 / 28.8 -> 27.0 / 30.2 -> 28.7 / 33.7 -> 34.1 / 35.2 -> 36.7

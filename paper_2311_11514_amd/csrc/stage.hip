@@ -73,8 +73,7 @@ struct Workspace {
     float *h = nullptr;        // residual stream [T][H] fp32
     // bf16 path
     h16_t *n = nullptr, *o = nullptr, *u = nullptr, *q = nullptr;
-    float *dec_part = nullptr;       // split partial sums of the batched decode projections
-    size_t dec_part_floats = 0;
+    float *dec_part = nullptr;       // split partial sums of the batched decode projections, dec_part_floats of the rows
     float *gemm_part = nullptr;      // fp32 partial tiles of a split prefill contraction
     size_t gemm_part_floats = 0;     // (16-bit stages; an fp32 stage has kF32PartFloats)
     unsigned *gemm_arrived = nullptr;         // per 128 features of a projection: blocks of its split contraction that have arrived; zero between launches
@@ -110,6 +109,7 @@ struct hexgen_stage {
     std::vector<void *> taps;
     Workspace ws;
     Workspace *cur = nullptr;        // the workspace the decode flow runs on: &ws, or a view of the static scratch array
+    size_t dec_part_row = 0;         // 16 bits: most floats per row of the split decode projections' partial sums (dec_part_floats)
     int last_decode_rows = 0;        // rows of the last decode call that ran on the weight-streaming kernels
     int ws_batch_cap = 0;
     int64_t weight_bytes = 0;
@@ -137,6 +137,17 @@ bool is_h16(hexgen_dtype_t dt) { return dt == HEXGEN_BF16 || dt == HEXGEN_F16; }
 bool known_dtype(hexgen_dtype_t dt) { return dt == HEXGEN_F32 || is_h16(dt); }
 // The 16-bit kernels exist once per element type (namespaces bf16 and f16): pick by the stage's type.
 #define HX_K(dt, fn, ...) ((dt) == HEXGEN_F16 ? f16::fn(__VA_ARGS__) : bf16::fn(__VA_ARGS__))
+
+// Floats for the partial sums of the split decode projections of `rows` rows.  How often a contraction is split depends on it (see
+// launch_splitk), so it is a matter of the shape and the rows alone, and not of what the workspace has grown to: a step gives the
+// same bits whatever ran before it, in either decode call.  Per row two matrices of the widest projection and 512 x 128 features; fewer
+// than 32 rows may take what 32 do, up to the full-width 70B layer's share each (dec_part_row): four and eight splits of narrower matrices' W1/W3
+// (8192 x 22016 at 4 / 12 / 24 rows, one split -> four, a layer 252 / 259 / 283 -> 243 / 253 / 279 us; 4096 x 11008 at 12 rows, two -> eight, 97 -> 95), but
+// one of the full-width layer's (at 4 / 12 rows, eight -> one 294 / 318 -> 289 / 290).
+size_t dec_part_own(const hexgen_stage *st) { return (size_t)512 * 128 + 2 * (size_t)std::max(std::max(st->nqkv, st->H), 2 * st->F_l); }
+size_t dec_part_floats(const hexgen_stage *st, int rows) {
+    return std::min((size_t)kDecodeMaxRows * dec_part_own(st), (size_t)rows * st->dec_part_row);
+}
 
 void free_ws(Workspace &w) {
     void *ptrs[] = {w.dec_part, w.gemm_part, w.gemm_arrived, w.h, w.n, w.o, w.u, w.q, w.xa_n, w.xa_o, w.xa_u, w.q_lo, w.ssq, w.ssq_pf, w.att_o, w.att_ml, w.att_arrived, w.qkv32, w.n32, w.q32, w.o32, w.u32,
@@ -179,10 +190,7 @@ hexgen_status_t ensure_workspace(hexgen_stage *st, int rows, int batch) {
         HX_TRY(dmalloc(&w.xa_o, dec_act_elems((int)drows, st->qw)));
         HX_TRY(dmalloc(&w.xa_u, dec_act_elems((int)drows, st->F_l)));
         HX_TRY(dmalloc(&w.q_lo, drows * st->qw));
-        if (drows > 2) {      // splits x features stays near 512 x 128 (see launch_splitk), plus one unsplit matrix
-            w.dec_part_floats = drows * ((size_t)512 * 128 + 2 * nmax);
-            HX_TRY(dmalloc(&w.dec_part, w.dec_part_floats));
-        }
+        if (drows > 2) HX_TRY(dmalloc(&w.dec_part, dec_part_floats(st, (int)drows)));
         w.gemm_part_floats = (size_t)16 << 20;      // 64 MB: 8 splits of the widest short-prompt launch
         HX_TRY(dmalloc(&w.gemm_part, w.gemm_part_floats));
         HX_TRY(dmalloc(&w.gemm_arrived, (nmax + 127) / 128));
@@ -482,7 +490,8 @@ void decode_proj(hexgen_stage *st, const Rows &r, const void *Wp, const h16_t *X
             mid = nullptr;
         }
     }
-    HX_K(st->dtype, launch_decode_proj, static_cast<const h16_t *>(Wp), Xa, N, K, r.T, e, st->cur->dec_part, st->cur->dec_part_floats, s, mid);
+    HX_K(st->dtype, launch_decode_proj, static_cast<const h16_t *>(Wp), Xa, N, K, r.T, e, st->cur->dec_part,
+         dec_part_floats(st, r.T), s, mid);
     if (mid) st->prof.ev[PROF_W13_MAIN].push_back(mid);
     st->prof.mark(slot, s);
 }
@@ -504,7 +513,7 @@ void attn_decode_h16(hexgen_stage *st, hexgen_kv_cache *kv, int layer, const Row
     QkvTail tail{};
     st->prof.mark(PROF_QKV, s);
     HX_K(st->dtype, launch_decode_qkv, static_cast<const h16_t *>(ly.wqkv), w.xa_n, st->nqkv, st->H, r.T, e, st->cur->dec_part,
-         st->cur->dec_part_floats, &tail, s);
+         dec_part_floats(st, r.T), &tail, s);
     st->prof.mark(PROF_QKV, s);
     st->prof.mark(PROF_ATTN, s);
     HX_K(st->dtype, launch_attn_decode, w.q, w.q_lo, kc, vc, kg, st->hq_l, w.row_pos, r.batch, pick_attn_split(st, kv, r.batch), w.att_o,
@@ -704,7 +713,6 @@ size_t carve_decode_workspace(const hexgen_stage *st, int rows, unsigned char *b
         return p;
     };
     const size_t T = (size_t)rows;
-    const size_t nmax = (size_t)std::max(std::max(st->nqkv, st->H), 2 * st->F_l);
     Workspace v;
     v.cap_rows = rows;
     v.h = static_cast<float *>(take(T * st->H * sizeof(float)));
@@ -713,10 +721,7 @@ size_t carve_decode_workspace(const hexgen_stage *st, int rows, unsigned char *b
     v.xa_u = static_cast<h16_t *>(take(dec_act_elems(rows, st->F_l) * sizeof(h16_t)));
     v.q = static_cast<h16_t *>(take(T * st->qw * sizeof(h16_t)));
     v.q_lo = static_cast<h16_t *>(take(T * st->qw * sizeof(h16_t)));
-    if (rows > 2) {
-        v.dec_part_floats = T * ((size_t)512 * 128 + 2 * nmax);
-        v.dec_part = static_cast<float *>(take(v.dec_part_floats * sizeof(float)));
-    }
+    if (rows > 2) v.dec_part = static_cast<float *>(take(dec_part_floats(st, rows) * sizeof(float)));
     v.att_o = static_cast<float *>(take(T * st->hq_l * kAttnMaxSplit * st->d * sizeof(float)));
     v.att_ml = static_cast<float *>(take(T * st->hq_l * kAttnMaxSplit * 2 * sizeof(float)));
     v.att_arrived = static_cast<unsigned int *>(take(T * st->hkv_l * sizeof(unsigned int)));
@@ -769,6 +774,11 @@ hexgen_status_t hexgen_stage_create(int hidden, int n_heads, int n_kv_heads, int
     st->dtype = dtype;
     st->F_p = dtype == HEXGEN_F32 ? round_up(F_l, 32) : F_l;
     st->cur = &st->ws;
+    if (is_h16(dtype)) {
+        st->dec_part_row = std::max(dec_part_own(st), (size_t)512 * 128 + 2 * 57344 + DEC_SCRATCH_RSTD);
+        // 32 rows do not fit the static array: fewer rows, which may, take no more than their own
+        if (carve_decode_workspace(st, kDecodeMaxRows, nullptr, nullptr) > kStaticScratchBytes) st->dec_part_row = dec_part_own(st);
+    }
     try {       // no exception may cross the C boundary
         st->layers.resize(n_layers);
         st->taps.assign(n_layers, nullptr);

@@ -1,0 +1,37 @@
+"""A decode step gives the same bits whatever ran on the stage before it, and through either decode call: how often a contraction is split (W1/W3 of
+this width: eight times at 9 to 19 rows) does not depend on how far the workspace has grown."""
+import pytest
+import torch
+
+import paper_2311_11514_amd as hx
+
+pytestmark = pytest.mark.gpu
+
+H, F = 4096, 11008
+
+
+@pytest.mark.parametrize("dtype,rows", [("bf16", 9), ("f16", 17), ("bf16", 4)])
+def test_before_and_after_a_longer_call(dtype, rows):
+    print(dtype, rows, flush=True)
+    td = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    w = [torch.randn(*s, generator=g, device="cuda").mul_(0.02).to(td) for s in ((H, H), (H, H // 4), (H, H // 4), (H, H), (H, F), (H, F), (F, H))]
+    one = torch.ones(H, device="cuda", dtype=td)
+    st = hx.Stage(H, 32, 8, F, 1, 1, 0, dtype)
+    st.load_layer(0, one, *w[:4], one, *w[4:])
+    x, prompt = (torch.randn(n, H, generator=g, device="cuda").to(td) for n in (rows, 64))
+
+    def step(call):
+        kv = st.kv_cache_create(rows, 16)
+        kv.set_lengths([3] * rows)
+        p, r = torch.empty_like(x), torch.empty_like(x)
+        call(kv, 0, x, p, r)
+        torch.cuda.synchronize()
+        return p, r
+
+    first = step(st.decode)
+    static = step(st.decode_static)
+    st.prefill(st.kv_cache_create(1, 64), prompt, [64], torch.empty_like(prompt), torch.empty_like(prompt))
+    after = step(st.decode)
+    for other in (static, after):
+        assert torch.equal(first[0], other[0]) and torch.equal(first[1], other[1])
