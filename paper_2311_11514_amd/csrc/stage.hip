@@ -591,30 +591,39 @@ F32Proj f32_proj(const hexgen_stage *st, const float *x, const float *g, const v
 void proj_f32(hexgen_stage *st, int mode, const F32Proj &p, hipStream_t s) {
     f32_launch_proj(mode, p, st->ws.n32, st->ws.gemm_part, s);
 }
-// RMSNorm, QKV, rotary embedding, cache append and attention; leaves o in the workspace, or (wo not NULL, true returned) goes on with W_O
-bool attn_f32(hexgen_stage *st, hexgen_kv_cache *kv, int layer, const Rows &r, const float *h, hipStream_t s, const F32Proj *wo = nullptr) {
+// Does a step take attention and W_O in one launch?  By the longest context; a step that is being recorded may be replayed at any length of its
+// cache, which the host does not see, and goes by the cache's capacity.
+bool takes_attn_wo(const hexgen_stage *st, const hexgen_kv_cache *kv, const Rows &r, hipStream_t s) {
+    if (!r.decode) return false;
+    int positions = 0;
+    for (int i = 0; i < r.batch; ++i) positions = std::max(positions, kv->lens[i] + 1);
+    if (!f32_attn_wo_fits(r.T, st->hq_l, st->hkv_l, st->d, st->H, positions)) return false;
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &c) != hipSuccess) {       // the null stream beside a recording
+        (void)hipGetLastError();
+        c = hipStreamCaptureStatusActive;
+    }
+    return c == hipStreamCaptureStatusNone || f32_attn_wo_fits(r.T, st->hq_l, st->hkv_l, st->d, st->H, kv->max_seq);
+}
+// RMSNorm, QKV, rotary embedding, cache append and attention; leaves o in the workspace, or (wo not NULL: takes_attn_wo) goes on with W_O
+void attn_f32(hexgen_stage *st, hexgen_kv_cache *kv, int layer, const Rows &r, const float *h, hipStream_t s, const F32Proj *wo = nullptr) {
     Workspace &w = st->ws;
     const Layer &ly = st->layers[layer];
     float *kc = static_cast<float *>(kv->k) + (size_t)layer * kv->layer_stride;
     float *vc = static_cast<float *>(kv->v) + (size_t)layer * kv->layer_stride;
     proj_f32(st, F32_PLAIN, f32_proj(st, h, ly.g_attn, ly.wqkv, r.T, st->H, st->nqkv, st->nqkv, w.qkv32), s);
-    if (wo != nullptr && r.decode) {
-        int positions = 0;
-        for (int i = 0; i < r.batch; ++i) positions = std::max(positions, kv->lens[i] + 1);
-        if (f32_attn_wo_fits(r.T, st->hq_l, st->hkv_l, st->d, wo->cols, positions)) {
-            f32_launch_attn_wo(w.qkv32, kc, vc, st->hq_l, st->hkv_l, st->d, kv->smax, kv->d_lens, kv->cos_tab, kv->sin_tab, *wo, s);
-            return true;
-        }
+    if (wo != nullptr) {
+        f32_launch_attn_wo(w.qkv32, kc, vc, st->hq_l, st->hkv_l, st->d, kv->smax, kv->d_lens, kv->cos_tab, kv->sin_tab, *wo, s);
+        return;
     }
     if (r.max_new == 1) {          // row = sequence
         f32_launch_attn_decode(w.qkv32, kc, vc, r.batch, st->hq_l, st->hkv_l, st->d, kv->smax, r.decode ? kv->d_lens : w.pos0, kv->cos_tab,
                                kv->sin_tab, w.o32, s);
-        return false;
+        return;
     }
     f32_launch_rope_append(w.qkv32, r.T, st->hq_l, st->hkv_l, st->d, kv->smax, r.rm, kv->cos_tab, kv->sin_tab, w.q32, kc,
                            vc, s);
     f32_launch_attn_prefill(w.q32, kc, vc, st->hq_l, st->hkv_l, st->d, kv->smax, w.pos0, w.cu_rows, w.items, r.n_items, w.o32, s);
-    return false;
 }
 // RMSNorm, W1/W3 and SwiGLU; leaves u in the workspace
 void ffn_f32(hexgen_stage *st, int layer, const Rows &r, const float *h, hipStream_t s) {
@@ -625,13 +634,15 @@ hexgen_status_t forward_f32(hexgen_stage *st, hexgen_kv_cache *kv, const Rows &r
                             void *out_partial, void *out_resid, int32_t *advance_lens, hipStream_t s) {
     Workspace &w = st->ws;
     const float *h = static_cast<const float *>(hidden_in);      // the residual stream: the caller's rows, then w.h
+    const bool attn_wo = takes_attn_wo(st, kv, r, s);
     for (int l = 0; l < st->L; ++l) {
         const Layer &ly = st->layers[l];
         if (st->taps[l]) HX_HIP(hipMemcpyAsync(st->taps[l], h, sizeof(float) * (size_t)r.T * st->H, hipMemcpyDeviceToDevice, s));
         F32Proj p = f32_proj(st, w.o32, nullptr, ly.wo, r.T, st->qw, st->H, st->H, nullptr);
         p.resid = h;
         p.resid_out = w.h;
-        if (!attn_f32(st, kv, l, r, h, s, &p)) proj_f32(st, F32_RESID, p, s);
+        attn_f32(st, kv, l, r, h, s, attn_wo ? &p : nullptr);
+        if (!attn_wo) proj_f32(st, F32_RESID, p, s);
         h = w.h;
         ffn_f32(st, l, r, h, s);
         p = f32_proj(st, w.u32, nullptr, ly.w2, r.T, st->F_p, st->H, st->H, nullptr);
@@ -1198,7 +1209,7 @@ hexgen_status_t hexgen_stage_run_sublayer(hexgen_stage_t *st, hexgen_kv_cache_t 
         }
     } else {
         const Layer &ly = st->layers[layer];
-        if (which == 0) (void)attn_f32(st, kv, layer, r, h, s);
+        if (which == 0) attn_f32(st, kv, layer, r, h, s);
         else ffn_f32(st, layer, r, h, s);
         if (which == 0) proj_f32(st, F32_PLAIN, f32_proj(st, st->ws.o32, nullptr, ly.wo, r.T, st->qw, st->H, st->H, p), s);
         else proj_f32(st, F32_PLAIN, f32_proj(st, st->ws.u32, nullptr, ly.w2, r.T, st->F_p, st->H, st->H, p), s);

@@ -3,9 +3,13 @@ of the 16-position tiles and of the line where the step goes back to two launche
 a pair (three pairs), one wave to eight per pair, either head width, 1 to 16 query heads per kv head, ragged contexts.  The cached rows
 and the other sequences' must come out right as well; a value that is not finite in the new row reaches its own element alone, as
 with separate launches.  fp32 sums of up to 1024 terms: 1e-6 .. 1e-5 in practice; the gate is the suite's 1e-4."""
+import ctypes as C
+
 import numpy as np
 import pytest
+import torch
 
+from paper_2311_11514_amd.binding import lib
 from tests.helpers import TOL, check, gpu_decode, make_gpu_stage, make_oracle
 from workloads import StageConfig, generate
 
@@ -60,3 +64,38 @@ def test_new_row_that_is_not_finite():
     kv.set_lengths([4, 9])
     _, h = gpu_decode(st, kv, cfg, 0, generate.hidden_rows(cfg, 2, stream_id=1).abs() + 0.1)
     assert np.isinf(h).all()
+
+
+def test_recorded_step_goes_by_the_capacity():
+    """A replayed step meets contexts that the host has not seen: recorded for a cache whose rows all lie within the one launch's range it has one node
+    less per layer than for a long cache, whatever the contexts at the recording.  Its replays agree with eager steps."""
+    cfg = StageConfig("awograph", "f32", 256, 4, 1, 96, 2, 1, (0,), batch=1, seed=78)
+    st = make_gpu_stage(cfg, 0, [generate.layer_weights(cfg, l) for l in range(2)])
+    x = generate.hidden_rows(cfg, 1, stream_id=1).cuda()
+    p, r, pe, re = (torch.empty_like(x) for _ in range(4))
+    nodes = []
+    for capacity in (200, 2000):
+        kv, eager = st.kv_cache_create(1, capacity), st.kv_cache_create(1, capacity)
+        for c in (kv, eager):
+            for l in range(2):
+                c.fill(l, 0, *generate.synthetic_kv(cfg, l, 0, 20))
+            c.set_lengths([20])
+        st.decode(eager, 0, x, pe, re)                  # (sizes the workspace)
+        torch.cuda.synchronize()
+        g, s = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            g.capture_begin()
+            st.decode(kv, 0, x, p, r, stream=s)
+            g.capture_end()
+        n = C.c_size_t()
+        assert lib.hipGraphGetNodes(C.c_void_p(g.raw_cuda_graph()), None, C.byref(n)) == 0
+        nodes.append(n.value)
+        g.instantiate()
+        for k in range(3):
+            if k:
+                st.decode(eager, k, x, pe, re)
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.allclose(p, pe, rtol=1e-4, atol=1e-5) and torch.allclose(r, re, rtol=1e-4, atol=1e-5)
+    print(nodes, flush=True)
+    assert nodes[1] == nodes[0] + 2
