@@ -16,7 +16,9 @@
  *   - the library owns its copy of the weights (repacked), the KV cache and its workspace;
  *   - kernels are enqueued on `stream` (a hipStream_t passed as void*, NULL = default stream)
  *     and the call returns without synchronising, except where stated;
- *   - calls on one stage / cache are not thread-safe;
+ *   - calls on one stage / cache are not thread-safe, nor may two of them overlap in time on the device: they share the stage's
+ *     workspace, so calls on different streams have to be put in order (events) by the caller (a prefill waits for the
+ *     device by itself);
  *   - weights use the paper's x . W convention (Section 2): W is [in, out], row-major.
  *   - `dtype` fixes the storage type of weights, stage inputs / outputs and the KV cache.
  *     The residual stream, every accumulator, the softmax and the norm statistics are fp32.

@@ -119,8 +119,8 @@ struct GemmEpi {
     // SWIGLU
     h16_t *u;                 // fragment tiles [T/16][F_l/32]
     int F_l;
-    // counters of the skinny kernel, one per 128 features, zero between launches: blocks of a split contraction that have arrived, the
-    // last of which finishes the tile.  NULL: a launch of its own does
+    // counters of the skinny kernel, one per 128 features, even between launches: blocks of a contraction in two splits that have arrived,
+    // the second of which finishes the tile.  NULL: a launch of its own does
     unsigned *arrived;
 };
 // per row of logits [n][ld]: the largest of the first `valid` entries and its index + id0 (lowest index wins ties)

@@ -807,13 +807,14 @@ static void launch_finish(const float *part, int splits, int N, int n_tiles, int
 // -------------------------------------------------------------------------------------------------
 // OWN (W1/W3): no finishing launch.  With one split a block holds the whole contraction.  With two, the block that arrives last adds the
 // other's partial sums to its own and finishes the tile: nobody waits for anybody, the sums go past the dies' caches and are added in
-// split order, so the results are the finishing kernel's whoever was last.
+// split order, so the results are the finishing kernel's whoever was last.  The arrivals are only ever counted up, two a launch, and an
+// odd one is the last: even launches that overlap, which a caller must not have, leave nothing behind for the next.
 struct SkinnyOwn {
     const float *ssq_in;       // as in GemmEpi
     int norm_dim, T, F_l;
     float eps;
     h16_t *u;
-    unsigned *arrived;         // per block of features
+    unsigned *arrived;         // two splits: per block of features, even between launches
 };
 template <int KG, int NT, bool OWN>
 __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__restrict__ Wp, const h16_t *__restrict__ Xp, int k_tiles,
@@ -971,9 +972,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_skinny_kernel(const h16_t *__re
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's stores have reached memory ...
             __syncthreads();                                      // ... and every other wave's of the block,
             if (tid == 0) {                                       // before the block counts itself
-                const unsigned before = __hip_atomic_fetch_add(&e.arrived[id], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                s_last = before + 1 == (unsigned)splits;
-                if (s_last) __hip_atomic_store(&e.arrived[id], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);     // for the next launch
+                s_last = __hip_atomic_fetch_add(&e.arrived[id], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u;
             }
             __syncthreads();
             if (!s_last) return;

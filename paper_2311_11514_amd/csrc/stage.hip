@@ -76,7 +76,7 @@ struct Workspace {
     float *dec_part = nullptr;       // split partial sums of the batched decode projections, dec_part_floats of the rows
     float *gemm_part = nullptr;      // fp32 partial tiles of a split prefill contraction
     size_t gemm_part_floats = 0;     // (16-bit stages; an fp32 stage has kF32PartFloats)
-    unsigned *gemm_arrived = nullptr;         // per 128 features of a projection: blocks of its split contraction that have arrived; zero between launches
+    unsigned *gemm_arrived = nullptr;         // per 128 features of W1/W3: arrivals at its two splits, even between launches
     h16_t *xa_n = nullptr, *xa_o = nullptr, *xa_u = nullptr;   // decode operands, hi / lo (dec_act_offset)
     h16_t *q_lo = nullptr;
     float *att_o = nullptr, *att_ml = nullptr;

@@ -4,6 +4,7 @@ blocks, of which one group of waves has fewer; a matrix that ends inside a block
 arrival counters are zero again, and which block was last does not show.  The gate is the suite's per type (rounding of
 16-bit operands)."""
 import pytest
+import torch
 
 from tests.helpers import TOL, check, gpu_prefill, make_gpu_stage, make_oracle
 from workloads import StageConfig, generate
@@ -39,3 +40,28 @@ def test_w13_finishes_its_own_tiles(case):
     for _ in range(6):
         p2, h2 = gpu_prefill(st, kv, cfg, X, lens)
         assert (p2 == p).all() and (h2 == h).all()
+
+
+def test_overlapping_launches_leave_nothing_behind():
+    """Two splits count their arrivals in counters that outlive the call.  The same FFN sub-layer many times on two streams at once (equal inputs, so that whatever
+    the calls share holds the same values), which a caller must not do: calls after them are not affected."""
+    cfg = StageConfig("w13over", "bf16", 1024, 8, 2, 5536, 1, 1, (0,), batch=1, seed=611)
+    st = make_gpu_stage(cfg, 0, [generate.layer_weights(cfg, 0)])
+    kv = st.kv_cache_create(1, 64)
+    xs = [generate.hidden_rows(cfg, 40, stream_id=i).cuda() for i in range(2)]
+
+    def alone(x):
+        out = torch.empty_like(x)
+        st.run_sublayer(kv, 0, 1, x, [40], 1, out)
+        torch.cuda.synchronize()
+        return out
+
+    want = [alone(x) for x in xs]
+    streams, outs = [torch.cuda.Stream(), torch.cuda.Stream()], [torch.empty_like(xs[1]) for _ in range(2)]
+    for _ in range(100):
+        for s, out in zip(streams, outs):
+            st.run_sublayer(kv, 0, 1, xs[1], [40], 1, out, stream=s)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for x, ref in zip(xs, want):
+            assert torch.equal(alone(x), ref)
