@@ -662,7 +662,13 @@ void launch_splitk_main(dim3 grid, const h16_t *Wp, const h16_t *Xa, int n_tiles
     const size_t lds = (size_t)2 * sk_chunk(NP) * NP * 64 * sizeof(h16x8);
     if constexpr (MODE == DEC_BEST || (MODE == DEC_SWIGLU && NP <= 4)) {           // (more than 32 rows: the head)
         if (grid.y == 1) {
-            hipLaunchKernelGGL((decode_splitk_kernel<NP, MODE, UT>), grid, dim3(512), lds, s, Wp, Xa, n_tiles, k_tiles, T, nullptr, nullptr, e);
+            auto kern = decode_splitk_kernel<NP, MODE, UT>;
+            static bool raised = false;       // static + dynamic LDS exceed the default 64 KB per block at four and eight operand tiles
+            if (!raised) {
+                (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                raised = true;
+            }
+            hipLaunchKernelGGL(kern, grid, dim3(512), lds, s, Wp, Xa, n_tiles, k_tiles, T, nullptr, nullptr, e);
             return;
         }
     }
