@@ -72,6 +72,12 @@ hexgen_status_t hexgen_set_gemm_tile(int code);
  * choice by batch and context lengths; 0 restores the default.  HEXGEN_ERR_INVALID_ARG outside 0..8. */
 hexgen_status_t hexgen_set_attn_split(int nsplit);
 
+/* How a decode step of `rows` rows (1..32; a pass of the head: 1..64) runs a projection (0 QKV, 1 W_O, 2 W1/W3, 3 W2) of a 16-bit stage, or the
+ * head: 0 = one kernel of complete dot products, n >= 1 = the contraction in n splits (W1/W3 and the head: 1 finishes its own
+ * results).  -1 for anything else.  Host arithmetic on the shape; for tests that are meant for one of the forms. */
+int hexgen_stage_decode_splits(const hexgen_stage_t *st, int projection, int rows);
+int hexgen_head_splits(const hexgen_head_t *hd, int rows);
+
 #ifdef __cplusplus
 }
 #endif

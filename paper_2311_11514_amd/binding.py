@@ -51,6 +51,8 @@ SIGNATURES = {
     "hexgen_mfma_probe": (_i, [_i, _vp, _i, _i, _vp]),
     "hexgen_set_gemm_tile": (_i, [_i]),
     "hexgen_set_attn_split": (_i, [_i]),
+    "hexgen_stage_decode_splits": (_i, [_vp, _i, _i]),
+    "hexgen_head_splits": (_i, [_vp, _i]),
     "hexgen_embed_rows": (_i, [_vp, _i, _i, _i, _vp, _i, _vp, _vp]),
     "hexgen_head_create": (_i, [_i, _i, _i, _i, _i, C.c_float, C.POINTER(_vp)]),
     "hexgen_head_load": (_i, [_vp, _vp, _vp]),
@@ -218,6 +220,10 @@ class Stage:
                "hexgen_stage_time_w13_decode")
         return ms.value, n.value
 
+    def decode_splits(self, projection: int, rows: int) -> int:
+        """How a decode step of that many rows runs projection 0 QKV, 1 W_O, 2 W1/W3, 3 W2: 0 in one kernel, else the splits of its contraction."""
+        return int(lib.hexgen_stage_decode_splits(self.handle, projection, rows))
+
     def weight_bytes(self) -> int:
         return int(lib.hexgen_stage_weight_bytes(self.handle))
 
@@ -297,6 +303,10 @@ class Head:
         g, w = g_final.to(td).contiguous(), w_lm.to(td).contiguous()
         assert tuple(w.shape) == (self.hidden, self.vocab) and g.numel() == self.hidden
         _check(lib.hexgen_head_load(self.handle, _ptr(g), _ptr(w)), "hexgen_head_load")
+
+    def splits(self, rows: int) -> int:
+        """How a pass over that many rows runs the projection: 0 in one kernel, else the splits of its contraction."""
+        return int(lib.hexgen_head_splits(self.handle, rows))
 
     def greedy(self, hidden_a: torch.Tensor, hidden_b: Optional[torch.Tensor] = None, stream=None):
         """Returns (token ids int32 [n], logits float32 [n]) of this rank's candidates, on the device."""

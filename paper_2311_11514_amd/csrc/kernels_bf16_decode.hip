@@ -675,27 +675,30 @@ void launch_splitk_main(dim3 grid, const h16_t *Wp, const h16_t *Xa, int n_tiles
     hipLaunchKernelGGL((decode_splitk_kernel<NP, -1, 1>), grid, dim3(512), lds, s, Wp, Xa, n_tiles, k_tiles, T, part, rstd, e);
 }
 
-template <int MODE, int UT>
-void launch_splitk(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, const DecodeEpi &e, float *scratch,
-                   size_t scratch_floats, hipStream_t s, hipEvent_t mid, QkvTail *tail = nullptr) {
-    const int n_tiles = N / 16, groups = (n_tiles + 7) / 8, np = dec_act_tiles(T);
-    // Two blocks fit a CU (registers, 64 KB of LDS), 512 on the chip.  The number of splits (at most 8, or 16 for a matrix of
-    // fewer than 64 feature groups: the finishing kernel walks them one after the other; partials within the scratch)
-    // minimises rounds of blocks x chunks per block, in units of one chunk per block (512 blocks x 64 KB: about 5.6 us), plus the
-    // partial sums' way through memory and back (about 5 TB/s: a wide matrix with a short contraction is not split into
-    // eight to save half a round); on a tie the fewer splits win.
-    const int chunks = (k_tiles + sk_chunk(np) - 1) / sk_chunk(np);
-    const size_t part_floats = scratch_floats - DEC_SCRATCH_RSTD;      // the tail of the scratch carries the rows' rstd
-    float *rstd = scratch + part_floats;
+// Number of splits of the split form.  Two blocks fit a CU (registers, 64 KB of LDS), 512 on the chip.  The number (at most 8, or 16 for a matrix of
+// fewer than 64 feature groups: the finishing kernel walks them one after the other; partials within the scratch)
+// minimises rounds of blocks x chunks per block, in units of one chunk per block (512 blocks x 64 KB: about 5.6 us), plus the
+// partial sums' way through memory and back (about 5 TB/s: a wide matrix with a short contraction is not split into
+// eight to save half a round); on a tie the fewer splits win.
+int splitk_splits(int N, int k_tiles, int T, size_t scratch_floats) {
+    const int groups = (N / 16 + 7) / 8, np = dec_act_tiles(T), chunks = (k_tiles + sk_chunk(np) - 1) / sk_chunk(np);
+    const int cap = groups * 8 < 512 ? 16 : 8;      // a narrow matrix (TP8 QKV: 10 groups) fills more of the chip with 16
     int splits = 1;
     long best = -1;
-    const int cap = groups * 8 < 512 ? 16 : 8;      // a narrow matrix (TP8 QKV: 10 groups) fills more of the chip with 16
     for (int c = 1; c <= std::min(cap, chunks); ++c) {
-        if (c > 1 && (size_t)c * T * N > part_floats) break;
+        if (c > 1 && (size_t)c * T * N > scratch_floats - DEC_SCRATCH_RSTD) break;
         const long traffic = c > 1 ? (long)((double)c * T * N * 8.0 / 5e6 / 5.6 * 16.0) : 0;
         const long cost = (long)((groups * c + 511) / 512) * ((chunks + c - 1) / c) * 16 + c + traffic;
         if (best < 0 || cost < best) { best = cost; splits = c; }
     }
+    return splits;
+}
+
+template <int MODE, int UT>
+void launch_splitk(const h16_t *Wp, const h16_t *Xa, int N, int k_tiles, int T, const DecodeEpi &e, float *scratch,
+                   size_t scratch_floats, int splits, hipStream_t s, hipEvent_t mid, QkvTail *tail = nullptr) {
+    const int n_tiles = N / 16, groups = (n_tiles + 7) / 8, np = dec_act_tiles(T);
+    float *rstd = scratch + scratch_floats - DEC_SCRATCH_RSTD;      // the tail of the scratch carries the rows' rstd
     const dim3 grid(groups, splits);
     switch (np) {
         case 1: launch_splitk_main<1, MODE, UT>(grid, Wp, Xa, n_tiles, k_tiles, T, scratch, e, rstd, s); break;
@@ -840,20 +843,26 @@ bool decode_single_kernel(int mode, int N, int k_tiles, int T) {
 
 int decode_best_units(int N) { return best_pairs(N) ? N / 32 : N / 16; }
 
+int decode_splits(int mode, int N, int K, int T, size_t scratch_floats) {
+    if (decode_single_kernel(mode, N, K / 32, T) || scratch_floats < (size_t)T * N + DEC_SCRATCH_RSTD) return 0;
+    return splitk_splits(N, K / 32, T, scratch_floats);
+}
+
 void launch_decode_proj(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, const DecodeEpi &e, float *scratch,
                         size_t scratch_floats, hipStream_t s, hipEvent_t mid) {
-    const int k_tiles = K / 32;
-    const bool single = decode_single_kernel(e.mode, N, k_tiles, T);
-    if (!single && e.mode != DEC_QKV && scratch != nullptr && scratch_floats >= (size_t)T * N + DEC_SCRATCH_RSTD) {
+    const int k_tiles = K / 32, splits = scratch != nullptr && e.mode != DEC_QKV ? decode_splits(e.mode, N, K, T, scratch_floats) : 0;
+    if (splits > 0) {
+#define HX_SPLITK(MODE, UT) launch_splitk<MODE, UT>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, splits, s, mid)
         switch (e.mode) {
-            case DEC_RAW: launch_splitk<DEC_RAW, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
-            case DEC_RESID: launch_splitk<DEC_RESID, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
-            case DEC_SWIGLU: launch_splitk<DEC_SWIGLU, 2>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid); break;
+            case DEC_RAW: HX_SPLITK(DEC_RAW, 1); break;
+            case DEC_RESID: HX_SPLITK(DEC_RESID, 1); break;
+            case DEC_SWIGLU: HX_SPLITK(DEC_SWIGLU, 2); break;
             case DEC_BEST:
-                if (best_pairs(N)) launch_splitk<DEC_BEST, 2>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid);
-                else launch_splitk<DEC_BEST, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, mid);
+                if (best_pairs(N)) HX_SPLITK(DEC_BEST, 2);
+                else HX_SPLITK(DEC_BEST, 1);
                 break;
         }
+#undef HX_SPLITK
         return;
     }
     const bool pair = unit_pairs(e.mode, N, k_tiles, T);
@@ -877,9 +886,9 @@ void launch_decode_qkv(const h16_t *Wp, const h16_t *Xa, int N, int K, int T, co
                        size_t scratch_floats, QkvTail *tail, hipStream_t s) {
     *tail = QkvTail{nullptr, 0, T, N, nullptr, e.cos_tab, e.sin_tab};
     const int k_tiles = K / 32;
-    if (e.mode == DEC_QKV && !decode_single_kernel(e.mode, N, k_tiles, T) && scratch != nullptr &&
-        scratch_floats >= (size_t)T * N + DEC_SCRATCH_RSTD)
-        launch_splitk<DEC_QKV, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, s, nullptr, tail);
+    const int splits = e.mode == DEC_QKV && scratch != nullptr ? decode_splits(e.mode, N, K, T, scratch_floats) : 0;
+    if (splits > 0)
+        launch_splitk<DEC_QKV, 1>(Wp, Xa, N, k_tiles, T, e, scratch, scratch_floats, splits, s, nullptr, tail);
     else
         launch_decode_proj(Wp, Xa, N, K, T, e, scratch, scratch_floats, s, nullptr);
 }

@@ -1283,6 +1283,12 @@ hexgen_status_t hexgen_stage_time_w13_decode(hexgen_stage_t *st, int reps, doubl
     return HEXGEN_OK;
 }
 
+int hexgen_stage_decode_splits(const hexgen_stage_t *st, int projection, int rows) {
+    if (!st || !is_h16(st->dtype) || projection < 0 || projection > 3 || rows < 1 || rows > kDecodeMaxRows) return -1;
+    const int mode[4] = {DEC_QKV, DEC_RESID, DEC_SWIGLU, DEC_RESID}, N[4] = {st->nqkv, st->H, 2 * st->F_l, st->H}, K[4] = {st->H, st->qw, st->H, st->F_l};
+    return bf16::decode_splits(mode[projection], N[projection], K[projection], rows, rows > 2 ? dec_part_floats(st, rows) : 0);      // the same for fp16
+}
+
 hexgen_status_t hexgen_stream_copy(void *dst, const void *src, int64_t bytes, int blocks, void *stream) {
     if (!dst || !src || bytes < 0 || bytes % 16 || blocks <= 0) return HEXGEN_ERR_INVALID_ARG;
     launch_stream_copy(src, dst, bytes, blocks, static_cast<hipStream_t>(stream));
@@ -1450,6 +1456,11 @@ hexgen_status_t hexgen_head_greedy(hexgen_head_t *hd, const void *hidden_a, cons
     }
     HX_HIP(hipGetLastError());
     return HEXGEN_OK;
+}
+
+int hexgen_head_splits(const hexgen_head_t *hd, int rows) {
+    if (!hd || !is_h16(hd->dtype) || rows < 1 || rows > kHeadRows) return -1;
+    return bf16::decode_splits(DEC_BEST, hd->Vpad, hd->H, rows, hd->scratch_floats);
 }
 
 hexgen_status_t hexgen_embed_rows(const void *table, hexgen_dtype_t dtype, int hidden, int vocab, const int32_t *tokens,

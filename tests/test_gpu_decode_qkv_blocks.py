@@ -24,6 +24,7 @@ def test_decode_step(dtype, hidden, heads, kv_heads, tp, rows):
         w = [generate.layer_weights(cfg, 0)]
         _sides[cfg.name] = make_oracle(cfg, 0, w), make_gpu_stage(cfg, 0, w)
     ora, st = _sides[cfg.name]
+    assert (st.decode_splits(0, rows) == 0) == (hidden // 32 <= (128 if rows <= 8 else 64 if rows <= 16 else 16))
     lens = [1 + (i * 7) % 5 for i in range(rows)]
     lens[1], lens[2] = 40, 300
     X = generate.hidden_rows(cfg, sum(lens))

@@ -18,6 +18,7 @@ def test_before_and_after_a_longer_call(dtype, rows):
     w = [torch.randn(*s, generator=g, device="cuda").mul_(0.02).to(td) for s in ((H, H), (H, H // 4), (H, H // 4), (H, H), (H, F), (H, F), (F, H))]
     one = torch.ones(H, device="cuda", dtype=td)
     st = hx.Stage(H, 32, 8, F, 1, 1, 0, dtype)
+    assert st.decode_splits(2, rows) == (8 if rows > 8 else 0)
     st.load_layer(0, one, *w[:4], one, *w[4:])
     x, prompt = (torch.randn(n, H, generator=g, device="cuda").to(td) for n in (rows, 64))
 

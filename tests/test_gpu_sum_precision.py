@@ -75,6 +75,7 @@ def test_decode_qkv_sums_lo_products_apart(dtype, H, hq, hkv, T):
     x = torch.ones(T, H)
     x[:, 32 * 8 + 31] += lo * torch.tensor([1.0, -1.0]).repeat(16)[:T]
     st = hx.Stage(H, hq, hkv, 64, 1, 1, 0, dtype, 1e-5)
+    assert st.decode_splits(0, T) == 0
     one, zero = torch.ones(H), torch.zeros
     st.load_layer(0, *[w.to(td).cuda() for w in (one, zero(H, H), zero(H, hkv * 64), wv, zero(H, H), one, zero(H, 64), zero(H, 64), zero(64, H))])
     kv = st.kv_cache_create(T, 32)
