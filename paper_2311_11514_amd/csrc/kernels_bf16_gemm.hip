@@ -1350,9 +1350,9 @@ static bool launch_skinny(const h16_t *Wp, const h16_t *Xp, int N, int k_tiles, 
     const bool pair = splits % 2 == 0 && n_blocks * (splits / 2) >= 160;
     if (pair) splits /= 2;
     // W1/W3 finishes its own tiles up to two splits: a finishing launch is 8 to 10 us of a call.  Whole calls: TP1 (one split) 90 / 33 rows 398 / 351
-    // -> 377 / 339 us, 50 decoding sequences 1402 -> 1332; TP2 (one) 60 rows 410 -> 399; TP4 (two) 40 / 60 / 90 / 117 rows 372 / 383 / 430 / 461 -> 364 /
-    // 374 / 418 / 453, 40 / 60 / 90 / 120 sequences 2769 / 2840 / 3405 / 3461 -> 2704 / 2775 / 3341 / 3406.  With four splits (W_O, W2) and eight (QKV) the last
-    // blocks, a quarter and less of the CUs, take 2.5 and 10 us longer than the launch.
+    // -> 377 / 339 us, 50 decoding sequences 1402 -> 1332; TP2 (one) 60 rows 410 -> 399; TP4 (two; of three layers and of eight steps, least of three processes
+    // each) 40 / 60 / 90 / 117 rows 372 / 384 / 424 / 450 -> 363 / 373 / 416 / 445, 40 / 60 / 120 sequences 2710 / 2826 / 3428 -> 2631 / 2749 / 3385, 90 ragged ones
+    // 3354 -> 3281.  With four splits (W_O, W2) and eight (QKV) the last blocks, a quarter and less of the CUs, take 2.5 and 10 us longer than the launch.
     const bool own = MODE == DEC_SWIGLU && splits <= 2 && tail == nullptr && (splits == 1 || e.arrived != nullptr);
     const SkinnyOwn oe{e.ssq_in, e.norm_dim, T, e.F_l, e.eps, e.u, e.arrived};
     auto run = [&](auto kern, int kg) {

@@ -807,10 +807,11 @@ void f32_launch_attn_decode(const float *qkv, float *kc, float *vc, int b, int h
 
 // -------------------------------------------------------------------------------------------------
 // A decode step's attention and W_O in one launch, for few sequences with short contexts on a narrow stage: every block computes
-// the attention of all (sequence, kv head) pairs for itself -- at most eight, one to eight waves each -- and goes on with 16 columns of W_O, whose
+// the attention of all (sequence, kv head) pairs for itself -- at most four, two to eight waves each -- and goes on with 16 columns of W_O, whose
 // weights it has requested before.  Bound by latency: the launch it saves and the trip of o through memory are longer than
-// reading a few KB of keys and values 32 times from L2 (f32_attn_wo_fits; the tiny stage's eight steps with its head 618 -> 552 us).  The pairs' new keys and values are taken from LDS by every block, block 0
-// appends them to the cache.  W_O adds up in f32_stream_kernel's order.
+// reading a few KB of keys and values 32 times from L2 (f32_attn_wo_fits; the tiny stage's 32-row prompt and eight steps with its head 600 ->
+// 566 us, medians of eight processes).  The pairs' new keys and values are taken from LDS by every block, block 0 appends them to the cache.  W_O
+// adds up in f32_stream_kernel's order.
 // -------------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(512) void f32_attn_wo_kernel(const float *__restrict__ qkv, float *kc, float *vc, int hq_l, int hkv_l, int smax,
@@ -972,8 +973,8 @@ static size_t f32_attn_wo_lds(int T, int hq_l, int hkv_l, int d) {
 }
 // Few pairs (what every block stages), and about two tiles of 16 positions per wave at head dim 64, one at 128: a further one is 2 us of
 // latency, which is what the fused launch saves.  Two layers and eight steps, us, apart -> fused:
-//   head dim 64   4 pairs at 8 / 20 / 50 / 64 positions 396 / 398 / 400 / 401 -> 368 / 382 / 398 / 426, from 33 on (a prompt of 32, with the head) 618 ->
-//                 552, 1024 columns at 20 / 50 628 / 637 -> 617 / 642; 3 pairs at 20 / 50 372 / 374 -> 358 / 378; 2 pairs at 60 / 110 / 250 461 / 469 / 501 ->
+//   head dim 64   4 pairs at 8 / 20 / 50 / 64 positions 396 / 398 / 400 / 401 -> 368 / 382 / 398 / 426, from 33 on (a prompt of 32, with the head) 600 ->
+//                 566, 1024 columns at 20 / 50 628 / 637 -> 617 / 642; 3 pairs at 20 / 50 372 / 374 -> 358 / 378; 2 pairs at 60 / 110 / 250 461 / 469 / 501 ->
 //                 448 / 453 / 519; 1 pair at 60 / 240 / 500 375 / 405 / 454 -> 354 / 386 / 439; 8 pairs at 20 458 -> 464
 //   head dim 128  1 pair at 60 / 110 397 / 410 -> 373 / 392; 2 pairs at 30 / 56 651 / 658 -> 647 / 662, two sequences of one at 20 656 -> 673
 // 2048 columns at 20 positions 1332 -> 1327.

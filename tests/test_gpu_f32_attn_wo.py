@@ -1,6 +1,6 @@
 """fp32 decode steps whose attention and W_O are one launch (few sequences with short contexts on a narrow stage), at contexts on both sides
 of the 16-position tiles and of the line where the step goes back to two launches: none, one and several tiles per wave, waves without
-a pair (three pairs), one wave to eight per pair, either head width, 1 to 16 query heads per kv head, ragged contexts.  The cached rows
+a pair (three pairs), two waves to eight per pair, either head width, 1 to 16 query heads per kv head, ragged contexts.  The cached rows
 and the other sequences' must come out right as well; a value that is not finite in the new row reaches its own element alone, as
 with separate launches.  fp32 sums of up to 1024 terms: 1e-6 .. 1e-5 in practice; the gate is the suite's 1e-4."""
 import ctypes as C
