@@ -48,11 +48,11 @@ def test_overlapping_launches_leave_nothing_behind():
     cfg = StageConfig("w13over", "bf16", 1024, 8, 2, 5536, 1, 1, (0,), batch=1, seed=611)
     st = make_gpu_stage(cfg, 0, [generate.layer_weights(cfg, 0)])
     kv = st.kv_cache_create(1, 64)
-    xs = [generate.hidden_rows(cfg, 40, stream_id=i).cuda() for i in range(2)]
+    xs = [generate.hidden_rows(cfg, 19, stream_id=i).cuda() for i in range(2)]          # (128 x 128 tiles take more rows of this width)
 
     def alone(x):
         out = torch.empty_like(x)
-        st.run_sublayer(kv, 0, 1, x, [40], 1, out)
+        st.run_sublayer(kv, 0, 1, x, [19], 1, out)
         torch.cuda.synchronize()
         return out
 
@@ -60,7 +60,7 @@ def test_overlapping_launches_leave_nothing_behind():
     streams, outs = [torch.cuda.Stream(), torch.cuda.Stream()], [torch.empty_like(xs[1]) for _ in range(2)]
     for _ in range(100):
         for s, out in zip(streams, outs):
-            st.run_sublayer(kv, 0, 1, xs[1], [40], 1, out, stream=s)
+            st.run_sublayer(kv, 0, 1, xs[1], [19], 1, out, stream=s)
     torch.cuda.synchronize()
     for _ in range(3):
         for x, ref in zip(xs, want):
